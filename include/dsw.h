@@ -332,11 +332,11 @@ int dsw_adjoint_trajectory(dsw_grid *grid, const dsw_fields *ckpts, int32_t nste
  *                         workgroup per line, that many rows per thread,
  *                         separators by cyclic reduction in LDS; 0 = one
  *                         thread per line.  Lines the partitioned solver
- *                         cannot take (more than 256 chunks, or a cyclic line
- *                         whose chunk count is not a power of two) fall back
- *                         to one thread per line.  The transposed phi
- *                         solves of the adjoint take two rows per thread
- *                         wherever the line allows it.
+ *                         cannot take (more than 256 chunks; a cyclic line
+ *                         takes a power-of-two count of chunks, some of them
+ *                         a row shorter) fall back to one thread per line.
+ *                         The transposed phi solves of the adjoint take two
+ *                         rows per thread wherever the line allows it.
  *   rows_per_thread_r/_theta
  *                         r / theta sweeps: 4 = partitioned solver (each
  *                         workgroup on a few neighbouring lines split into

@@ -642,7 +642,7 @@ extern "C" int dsw_split_step_pert(dsw_grid *G, const dsw_fields *Un, dsw_fields
   std::vector<Pass> plan;
   plan_step(G, own_work(G), F(Un), F(Unp1), tau, K, [&](const Pass &p) { plan.push_back(p); });
   for (const Pass &p : plan)  // the kernel kinds with a perturbation-form variant
-    if (p.kind == PK_SW0 || p.kind == PK_SW1 || p.kind == PK_SW2_LINE)
+    if (p.kind == PK_SW0 || p.kind == PK_SW1 || (p.tk == 3 && (p.kind == PK_SW2_LINE || !phi_part_equal(g, G->cfg.phi_pm))))
       return fail(DSW_EINVAL, "perturbation step: the grid's lines need the thread-per-line solver, "
                               "which has no perturbation form");
   hipStream_t st = (hipStream_t)stream;
@@ -764,7 +764,7 @@ extern "C" int dsw_split_step_forced(dsw_grid *G, const dsw_fields *Un, dsw_fiel
   if (bnd && (!bnd->ur || !bnd->ut || !bnd->uf)) return fail(DSW_EINVAL, "bnd needs ur, ut and uf");
   const Geo &g = G->geo;
   int pm = G->cfg.phi_pm;
-  if (!(pm > 0 && phi_part_supported(g, pm))) pm = phi_part_supported(g, 4) ? 4 : (phi_part_supported(g, 2) ? 2 : 0);
+  if (!(pm > 0 && phi_part_equal(g, pm))) pm = phi_part_equal(g, 4) ? 4 : (phi_part_equal(g, 2) ? 2 : 0);
   if (!pm) return fail(DSW_EINVAL, "forced step: the phi lines do not fit the partitioned solver");
   if (families(g, 0).nb >= TWIST_LINES || families(g, 1).nb >= TWIST_LINES)
     return fail(DSW_EINVAL, "forced step: too many r or theta lines");

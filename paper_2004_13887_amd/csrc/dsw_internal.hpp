@@ -295,8 +295,10 @@ void launch_courant(const Geo &g, const Mat &m, const Fields &U, double tau, uns
 void launch_residual(const Geo &g, const Mat &m, const Fields &Un, const Fields &Uk, double tau,
                      const Fields &R, const Fields &Ub, int *status, hipStream_t st);
 
-// partitioned phi solver: whether a grid's phi lines fit it
+// partitioned phi solver: whether a grid's phi lines fit it, and whether they
+// also split into equal chunks (what the forced and the perturbation step take)
 bool phi_part_supported(const Geo &g, int pm);
+bool phi_part_equal(const Geo &g, int pm);
 
 // doubles of scratch needed by the sweeps of a grid
 void sweep_scratch_size(const Geo &g, long *blk, long *sca);

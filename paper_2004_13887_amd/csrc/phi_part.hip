@@ -3,7 +3,7 @@
 //
 // One workgroup per line slot (i, j).  It solves the 3x3-block line in
 // (p, T, u_phi) and the two scalar lines (u_r on r-face i, u_theta on
-// theta-face j) that share that slot.  Thread t owns rows [4t, 4t + 4):
+// theta-face j) that share that slot.  Thread t owns a chunk of up to 4 rows:
 //   1. it assembles its rows (consecutive threads read consecutive phi cells:
 //      contiguous loads) and eliminates its interior rows with the block
 //      Thomas recurrence, carrying the dependence on the previous chunk's last
@@ -22,8 +22,33 @@ namespace dsw {
 
 constexpr int PT_MAX = 256;  // chunks per line (lines up to PM * 256 cells)
 
+// Chunks of a line of n rows, at most pm rows each.  A cyclic line takes the
+// next power of two (the cyclic reduction closes on itself only then), its
+// rows spread over the chunks as evenly as they go (never fewer than one: the
+// power of two is at most n); any other line takes full chunks and a last
+// one with the rest.  A 360-cell circle is 128 chunks of 2 or 3 rows; solved
+// by one thread per line, as every circle without a power-of-two count of
+// full chunks once was, the phi pass of a 360 x 180 x 40 sphere took 3.29 ms.
+__host__ __device__ inline int phi_chunks(int n, int cyc, int pm) {
+  const int full = (n + pm - 1) / pm;
+  if (!cyc) return full;
+  int T = 1;
+  while (T < full) T *= 2;
+  return T;
+}
+
+// rows [a0, a0 + len) of chunk t (len 0 past the last chunk)
 template <int PM>
-__host__ __device__ inline int part_chunks(int n) { return (n + PM - 1) / PM; }
+__device__ __forceinline__ void phi_chunk(int n, int cyc, int T, int t, int &a0, int &len) {
+  if (cyc) {
+    const int lg = 31 - __builtin_clz((unsigned)T), base = n >> lg, rem = n & (T - 1);
+    a0 = t * base + min(t, rem);
+    len = t < T ? base + (t < rem ? 1 : 0) : 0;
+  } else {
+    a0 = t * PM;
+    len = t < T ? min(PM, n - a0) : 0;
+  }
+}
 
 // ---------------------------------------------------------- 3x3 helpers --
 __device__ __forceinline__ void mm3s(const double *A, const double *B, double *C, double s) {
@@ -170,11 +195,11 @@ __device__ __forceinline__ void pcr_scalar2(int t, int T, int cyc, double *A, do
 template <int PM, bool TR, class US>
 __device__ __forceinline__ void part_block_line(const Geo &g, const Mat &m, const US &u, const Fields &rhs,
                                 const Out &o, int i, int j, double hs, double *lds, int *status) {
-  const int N = g.np, T = part_chunks<PM>(N), cyc = g.periodic;
+  const int N = g.np, cyc = g.periodic, T = phi_chunks(N, cyc, PM);
   const int t = threadIdx.x;
   const bool act = t < T;
-  const int a0 = t * PM;
-  const int len = act ? min(PM, N - a0) : 0;
+  int a0, len;
+  phi_chunk<PM>(N, cyc, T, t, a0, len);
   double Cm[PM - 1][9], Em[PM - 1][9], Ym[PM - 1][3];
   // structural non-zeros of the row blocks (transposed rows: L = U^T, U = L^T)
   constexpr unsigned mL = TR ? nz_tr(NZ_U) : NZ_L, mU = TR ? nz_tr(NZ_L) : NZ_U;
@@ -259,7 +284,7 @@ __device__ __forceinline__ void part_block_line(const Geo &g, const Mat &m, cons
   if (act) {
     int nt_ = t + 1;
     bool has_next = nt_ < T;
-    if (cyc) { nt_ %= T; has_next = true; }
+    if (cyc) { nt_ &= T - 1; has_next = true; }
     const int nlen = has_next ? (int)sL[nt_] : 0;
     // last interior row of this chunk
     double Gl[3] = {0, 0, 0}, Vl[9], Wl[9];
@@ -354,11 +379,11 @@ __device__ __forceinline__ void part_block_line(const Geo &g, const Mat &m, cons
 template <int PM, int FAM, bool TR, class US>
 __device__ __forceinline__ void part_scalar_line(const Geo &g, const Mat &m, const US &u, const Fields &rhs,
                                  const Out &o, int a, int b, double hs, double *lds, int *status) {
-  const int N = g.np, T = part_chunks<PM>(N), cyc = g.periodic;
+  const int N = g.np, cyc = g.periodic, T = phi_chunks(N, cyc, PM);
   const int t = threadIdx.x;
   const bool act = t < T;
-  const int a0 = t * PM;
-  const int len = act ? min(PM, N - a0) : 0;
+  int a0, len;
+  phi_chunk<PM>(N, cyc, T, t, a0, len);
   const int ofid = FAM == 0 ? F_UR : F_UT;
   double Cm[PM - 1], Em[PM - 1], Ym[PM - 1];
   SRow R;
@@ -407,7 +432,7 @@ __device__ __forceinline__ void part_scalar_line(const Geo &g, const Mat &m, con
   if (act) {
     int nt_ = t + 1;
     bool has_next = nt_ < T;
-    if (cyc) { nt_ %= T; has_next = true; }
+    if (cyc) { nt_ &= T - 1; has_next = true; }
     const int nlen = has_next ? (int)sL[nt_] : 0;
     double Gl = 0.0, Vl = 0.0, Wl = 0.0;
 #pragma unroll
@@ -458,11 +483,11 @@ template <int PM, class US>
 __device__ __forceinline__ void part_scalar_lines2(const Geo &g, const Mat &m, const US &u, const Fields &rhs,
                                                    const Out &o, int i, int j, double hs, double *lds,
                                                    int *status) {
-  const int N = g.np, T = part_chunks<PM>(N), cyc = g.periodic;
+  const int N = g.np, cyc = g.periodic, T = phi_chunks(N, cyc, PM);
   const int t = threadIdx.x;
   const bool act = t < T;
-  const int a0 = t * PM;
-  const int len = act ? min(PM, N - a0) : 0;
+  int a0, len;
+  phi_chunk<PM>(N, cyc, T, t, a0, len);
   double Cm[2][PM - 1], Em[2][PM - 1], Ym[2][PM - 1];
   SRow S[2] = {{0, 1, 0, 0}, {0, 1, 0, 0}};
   {
@@ -499,7 +524,7 @@ __device__ __forceinline__ void part_scalar_lines2(const Geo &g, const Mat &m, c
   if (act) {
     int nt_ = t + 1;
     bool has_next = nt_ < T;
-    if (cyc) { nt_ %= T; has_next = true; }
+    if (cyc) { nt_ &= T - 1; has_next = true; }
 #pragma unroll
     for (int f = 0; f < 2; f++) {
       const double *sG = lds + 4 * T * f, *sV = sG + T, *sW = sG + 2 * T, *sL = sG + 3 * T;
@@ -707,22 +732,21 @@ void launch_phi_T(int pm, const PassArgs &a, unsigned blocks, unsigned threads, 
 
 bool phi_part_supported(const Geo &g, int pm) {
   if (pm != 2 && pm != 4) return false;
-  const int T = (g.np + pm - 1) / pm;
-  if (T > PT_MAX) return false;
-  if (g.periodic) { // cyclic reduction needs a power-of-two number of equal chunks
-    if (g.np % pm != 0) return false;
-    if (T & (T - 1)) return false;
-  }
-  return true;
+  return phi_chunks(g.np, g.periodic, pm) <= PT_MAX;
+}
+
+bool phi_part_equal(const Geo &g, int pm) {
+  if (!phi_part_supported(g, pm)) return false;
+  return !g.periodic || g.np == pm * phi_chunks(g.np, 1, pm);
 }
 
 unsigned phi_part_threads(const Geo &g, int pm) {
-  const int T = (g.np + pm - 1) / pm;
+  const int T = phi_chunks(g.np, g.periodic, pm);
   return (unsigned)(((T + 63) / 64) * 64);
 }
 
 size_t phi_part_lds(const Geo &g, int pm) {
-  const int T = (g.np + pm - 1) / pm;
+  const int T = phi_chunks(g.np, g.periodic, pm);
   return sizeof(double) * 24 * (size_t)T;
 }
 
