@@ -321,7 +321,7 @@ extern "C" int dsw_residual(dsw_grid *G, const dsw_fields *Un, const dsw_fields 
       (rc = check_fields(Ubar, "Ubar")))
     return rc;
   if (!(tau > 0.0)) return fail(DSW_EINVAL, "tau must be > 0");
-  launch_residual(G->geo, G->m, F(Un), F(Uk), tau, F(R), F(Ubar), G->status, (hipStream_t)stream);
+  launch_residual(G->geo, G->m, F(Un), F(Uk), tau, F(R), F(Ubar), G->count, G->status, (hipStream_t)stream);
   return check_launch("residual kernel");
 }
 

@@ -291,9 +291,10 @@ void launch_phi_pert(int pm, const PassArgs &a, unsigned blocks, unsigned thread
 void launch_courant(const Geo &g, const Mat &m, const Fields &U, double tau, unsigned long long *out,
                     hipStream_t st);
 
-// public residual: forms the midpoint on the fly from Un and Uk and writes it
+// public residual: forms the midpoint from Un and Uk and writes it (cnt: the
+// lengths of the five arrays)
 void launch_residual(const Geo &g, const Mat &m, const Fields &Un, const Fields &Uk, double tau,
-                     const Fields &R, const Fields &Ub, int *status, hipStream_t st);
+                     const Fields &R, const Fields &Ub, const long *cnt, int *status, hipStream_t st);
 
 // partitioned phi solver: whether a grid's phi lines fit it, and whether they
 // also split into equal chunks (what the forced and the perturbation step take)

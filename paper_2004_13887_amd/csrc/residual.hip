@@ -21,11 +21,14 @@
 // One thread per point of the extended index space (nr+1) x (nt+1) x npf; a
 // thread owns the centre (i,j,k) and the three faces with the same indices.
 // Two variants:
-//   * the C-ABI call forms the midpoint on the fly from Un and Uk and writes it;
 //   * inside a split step the midpoint is already resident (written by the
 //     previous iteration's last sweep, or U^n itself at the first iteration),
-//     so every neighbour read is a single load.
+//     so every neighbour read is a single load; the C-ABI call writes the
+//     midpoint first and then runs the same launches;
+//   * on a small grid the C-ABI call forms the midpoint on the fly from Un and
+//     Uk and writes it, in one launch.
 #include <algorithm>
+#include <cstring>
 #include <type_traits>
 
 #include "dsw_common.hpp"
@@ -243,13 +246,6 @@ __device__ __forceinline__ void residual_point(const Geo &g, const Mat &m, const
   if (!isfinite(chk)) status[ST_DIVERGED] = 1; // plain vector store
 }
 
-// public form: midpoint formed from Un and Uk and written out; 3-D grid
-__global__ void __launch_bounds__(256) k_residual_mid(Geo g, Mat m, SrcMid s, Diff dU, double tau,
-                                                      Fields R, Fields Ub, int *status) {
-  residual_point<SrcMid, true>(g, m, s, dU, tau, R, Ub, status, blockIdx.z, blockIdx.y,
-                               blockIdx.x * blockDim.x + threadIdx.x);
-}
-
 // split-step form: the midpoint is resident; flat grid of workgroups over
 // (phi block, theta index, r index).  B: a batch of grids, each workgroup
 // reads its grid's arguments from the batch table; else one grid by value.
@@ -280,6 +276,23 @@ __host__ __device__ inline unsigned res_general_blocks(const Geo &g, int bs) {
   return (unsigned)res_nk(g, bs) * pairs;
 }
 
+// the pair of workgroup pair number rest of the general launch
+__device__ __forceinline__ void res_pair(const Geo &g, unsigned rest, bool shell, int &i, int &j) {
+  const unsigned na = 3u * (unsigned)(g.nt + 1);
+  if (!shell) {
+    j = (int)(rest % (unsigned)(g.nt + 1));
+    i = (int)(rest / (unsigned)(g.nt + 1));
+  } else if (rest < na) {
+    const unsigned ia = rest / (unsigned)(g.nt + 1);
+    j = (int)(rest % (unsigned)(g.nt + 1));
+    i = ia == 0 ? 0 : (ia == 1 ? g.nr - 1 : g.nr);
+  } else {
+    const unsigned r2 = rest - na, jb = r2 % 3u;
+    i = 1 + (int)(r2 / 3u);
+    j = jb == 0 ? 0 : (jb == 1 ? g.nt - 1 : g.nt);
+  }
+}
+
 // W: a forced pass (wall velocities and source term); PT: the
 // perturbation-pressure form
 template <bool W = false, bool PT = false>
@@ -289,23 +302,7 @@ __device__ __forceinline__ void residual_body(const PassArgs &a, unsigned w) {
   const unsigned nkb = (unsigned)res_nk(g, bs);
   const unsigned kb = w % nkb, rest = w / nkb;
   int i, j;
-  if (res_interior_blocks(g, bs) > 0) {  // the shell (the interior launch does the rest)
-    const unsigned na = 3u * (unsigned)(g.nt + 1);
-    if (rest < na) {
-      const unsigned ia = rest / (unsigned)(g.nt + 1);
-      j = (int)(rest % (unsigned)(g.nt + 1));
-      i = ia == 0 ? 0 : (ia == 1 ? g.nr - 1 : g.nr);
-    } else {
-      const unsigned r2 = rest - na;
-      if (r2 >= 3u * (unsigned)(g.nr - 2)) return;
-      const unsigned jb = r2 % 3u;
-      i = 1 + (int)(r2 / 3u);
-      j = jb == 0 ? 0 : (jb == 1 ? g.nt - 1 : g.nt);
-    }
-  } else {
-    j = (int)(rest % (g.nt + 1));
-    i = (int)(rest / (g.nt + 1));
-  }
+  res_pair(g, rest, res_interior_blocks(g, bs) > 0, i, j);  // the shell where the interior launch does the rest
   decltype(auto) s = SrcSel<W, PT>::get(a);
   residual_point<std::decay_t<decltype(s)>, false>(g, a.m, s, a.d, a.tau, a.R, Fields{}, a.status, i, j,
                                                    (int)(kb * blockDim.x + threadIdx.x));
@@ -446,6 +443,40 @@ __global__ void __launch_bounds__(256) k_residual_in(PassArgs a, Batch bt) {
   }
 }
 
+// public form on a small grid: the midpoint formed on the fly from Un and Uk
+// and written out, every point in one launch
+__global__ void __launch_bounds__(256) k_residual_mid(Geo g, Mat m, SrcMid s, Diff dU, double tau,
+                                                      Fields R, Fields Ub, int *status) {
+  residual_point<SrcMid, true>(g, m, s, dU, tau, R, Ub, status, blockIdx.z, blockIdx.y,
+                               blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+// Ub = (Un + Uk) / 2 over the five arrays: two values per thread, one 16-byte
+// load from each where the arrays allow it (callers' arrays may start at any
+// multiple of 8 bytes)
+struct MidArrays {
+  const double *n[5], *k[5];
+  double *u[5];
+  long pairs[6], cnt[5];  // prefix sums of the pairs, array lengths
+};
+__global__ void __launch_bounds__(256) k_midpoint(MidArrays a) {
+  long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= a.pairs[5]) return;
+  int f = 0;
+  while (t >= a.pairs[f + 1]) f++;
+  const long x = 2 * (t - a.pairs[f]);
+  const double *n = a.n[f] + x, *k = a.k[f] + x;
+  double *u = a.u[f] + x;
+  const bool two = x + 1 < a.cnt[f];
+  if (two && (((uintptr_t)a.n[f] | (uintptr_t)a.k[f] | (uintptr_t)a.u[f]) & 15u) == 0) {
+    const double2 vn = *(const double2 *)n, vk = *(const double2 *)k;
+    *(double2 *)u = double2{0.5 * (vk.x + vn.x), 0.5 * (vk.y + vn.y)};
+  } else {
+    u[0] = 0.5 * (k[0] + n[0]);
+    if (two) u[1] = 0.5 * (k[1] + n[1]);
+  }
+}
+
 unsigned residual_interior_blocks(const Geo &g, int bs) { return res_interior_blocks(g, bs); }
 unsigned residual_general_blocks(const Geo &g, int bs) { return res_general_blocks(g, bs); }
 
@@ -453,18 +484,56 @@ static void set5(const double **dst, const Fields &f) {
   dst[F_P] = f.p; dst[F_UR] = f.ur; dst[F_UT] = f.ut; dst[F_UF] = f.uf; dst[F_T] = f.T;
 }
 
+// From this many interior workgroups (of 64 points) on, the public residual
+// writes the midpoint first and reads it back.  Forming it at every neighbour
+// read instead doubles the loads of the interior kernel, which then needs
+// more than 256 registers (one wave per SIMD; 2.06 ms on the 512 x 256 x 128
+// sphere).  Measured, one launch for every point against midpoint + interior +
+// shell: 512 x 256 x 128 sphere 2.82 -> 1.36 ms, 1024 x 512 x 64 sector 5.83 ->
+// 2.93 ms, 256 x 128 x 64 sector 0.364 -> 0.198 ms; on 32 x 32 x 16 the one
+// launch wins (15 against 23 us).
+constexpr unsigned RES_MID_SPLIT = 3000;
+
 void launch_residual(const Geo &g, const Mat &m, const Fields &Un, const Fields &Uk, double tau,
-                     const Fields &R, const Fields &Ub, int *status, hipStream_t st) {
-  SrcMid s;
-  set5(s.n, Un);
-  set5(s.k, Uk);
-  Diff d;
-  set5(d.n, Un);
-  set5(d.k, Uk);
-  d.same = 0;
-  dim3 block(64, 1, 1);
-  dim3 grid((g.npf + 63) / 64, g.nt + 1, g.nr + 1);
-  hipLaunchKernelGGL(k_residual_mid, grid, block, 0, st, g, m, s, d, tau, R, Ub, status);
+                     const Fields &R, const Fields &Ub, const long *cnt, int *status, hipStream_t st) {
+  const unsigned th = 64;
+  if (res_interior_blocks(g, (int)th) < RES_MID_SPLIT) {
+    SrcMid s;
+    set5(s.n, Un);
+    set5(s.k, Uk);
+    Diff d;
+    set5(d.n, Un);
+    set5(d.k, Uk);
+    d.same = 0;
+    const dim3 grid((unsigned)res_nk(g, (int)th), g.nt + 1, g.nr + 1);
+    hipLaunchKernelGGL(k_residual_mid, grid, dim3(th), 0, st, g, m, s, d, tau, R, Ub, status);
+    return;
+  }
+  MidArrays w;
+  set5(w.n, Un);
+  set5(w.k, Uk);
+  const double *u[5];
+  set5(u, Ub);
+  w.pairs[0] = 0;
+  for (int f = 0; f < 5; f++) {
+    w.u[f] = const_cast<double *>(u[f]);
+    w.cnt[f] = cnt[f];
+    w.pairs[f + 1] = w.pairs[f] + (cnt[f] + 1) / 2;
+  }
+  hipLaunchKernelGGL(k_midpoint, dim3((unsigned)((w.pairs[5] + 255) / 256)), dim3(256), 0, st, w);
+  PassArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.g = g;
+  a.m = m;
+  set5(a.u.a, Ub);
+  set5(a.d.n, Un);
+  set5(a.d.k, Uk);
+  a.tau = tau;
+  a.R = R;
+  a.status = status;
+  const Batch none{nullptr, nullptr, 0};
+  launch_residual_in_pass(g.periodic != 0, a, none, residual_interior_blocks(g, (int)th), th, st);
+  launch_residual_pass(a, none, residual_general_blocks(g, (int)th), th, st);
 }
 
 void launch_residual_pass(const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads,
