@@ -347,18 +347,17 @@ int dsw_adjoint_trajectory(dsw_grid *grid, const dsw_fields *ckpts, int32_t nste
  *                         intermediates in a scratch array (the scalar
  *                         lines of lines with 64, 128 or 256 rows run
  *                         apart, by the partitioned solver); -1 = by line
- *                         length: partitioned where a line has at most 128
- *                         rows (32 chunks), else two-ended (in an ensemble,
+ *                         length: partitioned where a line has at most 256
+ *                         rows (64 chunks), else two-ended (in an ensemble,
  *                         member by member).  Lines of more than
  *                         4 x sweep_block rows take the two-ended solver.
  *                         The transposed r solves of the adjoint take the
- *                         same solver; the transposed theta solves always
- *                         the two-ended one.  Measured: partitioned r
- *                         0.16 ms, theta 0.19 ms against 0.20 / 0.31 ms
- *                         two-ended on the 256 x 128 x 64 sector; on the
- *                         512 x 256 x 128 sphere r 1.37 / 1.37 ms (2.4x
- *                         fewer HBM bytes partitioned) and theta 1.71 /
- *                         1.43 ms.
+ *                         same solver on lines of at most 128 rows; the
+ *                         transposed theta solves always the two-ended one.
+ *                         Measured: partitioned r 0.11 ms, theta 0.13 ms
+ *                         against 0.20 / 0.30 ms two-ended on the
+ *                         256 x 128 x 64 sector; on the 512 x 256 x 128
+ *                         sphere r 0.98 / 1.37 ms and theta 1.01 / 1.37 ms.
  * Default {64, 256, 256, 4, -1, -1}.  dsw_set_config returns DSW_EINVAL for
  * other values.  dsw_ensemble_tune times candidate shapes per pass and keeps
  * each pass's best; its result is also kept for the process per set of member

@@ -172,8 +172,10 @@ extern "C" int dsw_init_grid(const dsw_grid_desc *desc, const dsw_material *mat,
   const int nr = desc->n_r, nt = desc->n_theta, np = desc->n_phi;
   // metric tables (host, then device)
   const size_t nt1 = (size_t)nt + 1, nr1 = (size_t)nr + 1;
-  std::vector<double> h(2 * (nr + nr1) + 4 * (nt + nt1) + (nt + 2));
-  double *rc = h.data(), *rf = rc + nr, *sc = rf + nr1, *cc = sc + nt, *sf = cc + nt, *cf = sf + nt1;
+  const size_t o_rc = 8 * ((size_t)nr + nt);  // the row tables first: 64-byte rows
+  std::vector<double> h(o_rc + 2 * (nr + nr1) + 4 * (nt + nt1) + (nt + 2));
+  double *mr = h.data(), *mt = mr + 8 * (size_t)nr;
+  double *rc = h.data() + o_rc, *rf = rc + nr, *sc = rf + nr1, *cc = sc + nt, *sf = cc + nt, *cf = sf + nt1;
   double *irc = cf + nt1, *irf = irc + nr, *isc = irf + nr1, *ctc = isc + nt, *isf = ctc + nt,
          *ctf = isf + nt1, *scx = ctf + nt1;
   const double dr = (desc->r2 - desc->r1) / nr, dt = (desc->theta2 - desc->theta1) / nt,
@@ -201,6 +203,34 @@ extern "C" int dsw_init_grid(const dsw_grid_desc *desc, const dsw_material *mat,
     isf[f] = sf[f] != 0.0 ? 1.0 / sf[f] : 0.0;
     ctf[f] = sf[f] != 0.0 ? cf[f] / sf[f] : 0.0;
   }
+  const double idr = 1.0 / dr, idt = 1.0 / dt;
+  for (int i = 0; i < nr; i++) {
+    double *q = mr + 8 * (size_t)i;
+    q[0] = rf[i + 1] * rf[i + 1] * (irc[i] * irc[i] * idr);
+    q[1] = -rf[i] * rf[i] * (irc[i] * irc[i] * idr);
+    if (i + 1 < nr) {
+      const double d2 = idr * idr, irF2 = irf[i + 1] * irf[i + 1], rF2 = rf[i + 1] * rf[i + 1];
+      const double ra2 = rc[i] * rc[i], rb2 = rc[i + 1] * rc[i + 1];
+      const double ira2 = irc[i] * irc[i], irb2 = irc[i + 1] * irc[i + 1];
+      q[2] = -rb2 * irF2 * d2 - (1.0 / 3.0) * rf[i + 2] * rf[i + 2] * irb2 * d2;
+      q[3] = (rb2 + ra2) * irF2 * d2 + (1.0 / 3.0) * rF2 * (irb2 + ira2) * d2;
+      q[4] = -ra2 * irF2 * d2 - (1.0 / 3.0) * rf[i] * rf[i] * ira2 * d2;
+    }
+    q[5] = irc[i];
+  }
+  for (int j = 0; j < nt; j++) {
+    double *q = mt + 8 * (size_t)j;
+    q[0] = sf[j + 1] * (isc[j] * idt);
+    q[1] = -sf[j] * (isc[j] * idt);
+    if (j + 1 < nt) {
+      const double d2 = idt * idt, isF = isf[j + 1];
+      q[2] = (-sc[j + 1] * isF - (1.0 / 3.0) * sf[j + 2] * isc[j + 1]) * d2;
+      q[3] = ((sc[j + 1] + sc[j]) * isF + (1.0 / 3.0) * sf[j + 1] * (isc[j + 1] + isc[j])) * d2;
+      q[4] = (-sc[j] * isF - (1.0 / 3.0) * sf[j] * isc[j]) * d2;
+    }
+    q[5] = ctc[j];
+    q[6] = isc[j];
+  }
   if (hipMalloc(&G->tables, h.size() * sizeof(double)) != hipSuccess) {
     delete G;
     return fail(DSW_ENOMEM, "metric tables");
@@ -212,7 +242,9 @@ extern "C" int dsw_init_grid(const dsw_grid_desc *desc, const dsw_material *mat,
   g.pole_lo = pole_lo; g.pole_hi = pole_hi;
   g.dr = dr; g.dt = dt; g.dp = dp;
   g.idr = 1.0 / dr; g.idt = 1.0 / dt; g.idp = 1.0 / dp;
-  double *t = G->tables;
+  g.mr = G->tables;
+  g.mt = G->tables + 8 * (size_t)nr;
+  double *t = G->tables + o_rc;
   const long o_rf = nr, o_sc = o_rf + nr1, o_cc = o_sc + nt, o_sf = o_cc + nt, o_cf = o_sf + nt1,
              o_irc = o_cf + nt1, o_irf = o_irc + nr, o_isc = o_irf + nr1, o_ctc = o_isc + nt,
              o_isf = o_ctc + nt, o_ctf = o_isf + nt1, o_scx = o_ctf + nt1;
@@ -950,7 +982,7 @@ static void launch_T(const dsw_grid *G, int d, const Pass &p, hipStream_t st) {
     const int pm = phi_part_supported(G->geo, 2) ? 2 : G->cfg.phi_pm;
     launch_phi_T(pm, p.a, (unsigned)G->geo.nr * (unsigned)G->geo.nt, phi_part_threads(G->geo, pm),
                  phi_part_lds(G->geo, pm), st);
-  } else if (d == 0 && p.kind == PK_SW0P) {
+  } else if (d == 0 && p.kind == PK_SW0P && families(G->geo, 0).n <= 128) {
     // the transposed theta lines keep the two-ended solver: their row window
     // costs the partitioned kernel its second wave per SIMD (theta 0.59 ms
     // against 0.37 ms on the 256 x 128 x 64 sector; r 0.20 against 0.33 ms)

@@ -5,7 +5,7 @@
 // A workgroup takes L neighbouring lines of one family (consecutive phi
 // index: the lanes that read one row of their lines read contiguous memory)
 // and splits every line into T chunks of PM rows; thread t = c * L + l holds
-// chunk c of line l.  As in the phi solver:
+// chunk c of line l (the first chunk is the short one).  As in the phi solver:
 //   1. each thread assembles its rows and eliminates the interior ones with
 //      the block Thomas recurrence, carrying the dependence on the last row
 //      of the chunk before ("spike"), then sweeps back so that every interior
@@ -16,7 +16,20 @@
 //   3. the interior rows are filled in from the separators and stored.
 // Every intermediate stays in registers and LDS: no scratch array, so the
 // pass moves one read of its inputs and one write of its result.
-#include "rows.hpp"
+//
+// The plain and the perturbation-pressure sweeps take the *_fast bodies: every
+// input of a chunk loaded before its first row is eliminated, 32-bit byte
+// offsets from uniform bases, metric factors from per-row tables, no row under
+// a branch.  The bodies that assemble a row at a time under a branch on the
+// chunk's length (the forced and the transposed sweeps keep them) spent half
+// of their instructions on addresses, ghost cases and register moves, and one
+// memory latency per row.  Line solves, before -> after: 512 x 256 x 128
+// sphere r 1.34 -> 0.98, theta 1.80 -> 1.01 ms; 256 x 128 x 64 sector r 0.145
+// -> 0.109, theta 0.183 -> 0.130 ms; 32 x 32 x 16 theta 19.6 -> 13.8 us.  The
+// block lines stay at two waves per SIMD (256 registers: 63 doubles of
+// intermediates and the reduction's 30) and are bound by their FP64 work and
+// the reduction's barriers; the scalar lines by their reads.
+#include "rows_fast.hpp"
 
 namespace dsw {
 
@@ -285,6 +298,371 @@ __device__ __forceinline__ void rt_block_lines(const Geo &g, const Mat &m, const
   block_store<D>(g, o, pa, pb, a0 + len - 1, xs);
 }
 
+// ------------------------------------------- block lines, plain and pert --
+// The block lines [line0, line0 + L) of sweep D with every input of a chunk's
+// rows loaded before the first row is eliminated (rows_fast.hpp); mode 0.
+// PT: perturbation-pressure form.  Byte offsets in 32 bits (off32_ok).
+template <int D, int PM, bool PT>
+__device__ __forceinline__ void rt_block_fast(const PassArgs &a, unsigned line0, double *lds) {
+  const Geo &g = a.g;
+  const Mat &m = a.m;
+  const double hs = a.tau;
+  const int n = D == 0 ? g.nr : g.nt, T = (n + PM - 1) / PM, L = (int)blockDim.x / T, pad = T * PM - n;
+  const unsigned nb = (unsigned)(D == 0 ? g.nt : g.nr) * (unsigned)g.np;
+  const int t = threadIdx.x, c = (int)((unsigned)t / (unsigned)L), l = t - c * L;
+  const bool act = c < T && line0 + l < nb;
+  const unsigned line = min(line0 + (unsigned)l, nb - 1);
+  const int cc = min(c, T - 1), s0 = cc * PM - pad;  // row of q = 0; negative: fillers
+  const int pa = (int)(line / (unsigned)g.np), k = (int)line - pa * g.np;
+  if (act && c == 0) {
+    const bool edge = pa == 0 || pa == (D == 0 ? g.nt : g.nr) - 1 || (!g.periodic && (k == 0 || k == g.np - 1));
+    if (edge) zero_bnd<D>(g, a.o.x, pa, k);
+    else if (D == 0) a.o.x.ur[idx_r(g, 0, pa, k)] = 0.0;
+    else a.o.x.ut[idx_t(g, pa, 0, k)] = 0.0;
+  }
+  // byte offsets of row 0 and row strides; the phi face after the cell
+  const unsigned sC = 8u * (unsigned)(D == 0 ? g.nt * g.np : g.np);
+  const unsigned sT = 8u * (unsigned)(D == 0 ? (g.nt + 1) * g.np : g.np);
+  const unsigned sF = 8u * (unsigned)(D == 0 ? g.nt * g.npf : g.npf);
+  const unsigned oC = 8u * (unsigned)(D == 0 ? pa * g.np + k : pa * g.nt * g.np + k);
+  const unsigned oT = 8u * (unsigned)(D == 0 ? pa * g.np + k : pa * (g.nt + 1) * g.np + k);
+  const unsigned oF = 8u * (unsigned)(D == 0 ? pa * g.npf + k : pa * g.nt * g.npf + k);
+  const int dF = 8 * (g.periodic && k == g.np - 1 ? 1 - g.np : 1);
+  const double *u_r = a.u.a[F_UR], *u_t = a.u.a[F_UT], *u_f = a.u.a[F_UF];
+  const double *mt = D == 0 ? g.mr : g.mt;
+  // per row what its coefficients need, P and T one cell further: held from
+  // here to the row's elimination
+  double gG[PM], gGG[PM], gTR[PM], P[PM + 1], Te[PM + 1], b0[PM], b1[PM], b2[PM];
+  double uw[PM + 1];  // the line's own velocity on the faces before row 0 .. after row PM - 1
+  {
+    // offsets of row q (fillers read row 0)
+    auto row = [&](int q) { return (unsigned)max(s0 + q, 0); };
+    const double irk = D == 0 ? 0.0 : g.irc[pa];
+    const double ctk = D == 0 ? g.ctc[pa] : 0.0, isk = D == 0 ? g.isc[pa] : 0.0;
+    if constexpr (D == 0) {
+#pragma unroll
+      for (int q = 0; q <= PM; q++) uw[q] = ldo(u_r, oC + row(q) * sC);
+    } else {
+#pragma unroll
+      for (int q = 0; q <= PM; q++) uw[q] = ldo(u_t, oT + row(q) * sT);
+    }
+    const unsigned up = 8u * (unsigned)(g.nt * g.np);  // one r plane of u_r
+    double va[PM + 2];  // D 1: the centre-averaged u_r of rows -1 .. PM
+    double tim[PM + 1], tip[PM + 1];  // D 1: u_theta on the planes i - 1, i + 1
+    if constexpr (D == 1) {
+      const double sgl = g.pole_lo ? 1.0 : -1.0, sgh = g.pole_hi ? 1.0 : -1.0;
+#pragma unroll
+      for (int q = -1; q <= PM; q++) {
+        const int s = s0 + q;
+        const unsigned o = oC + (unsigned)min(max(s, 0), n - 1) * sC;
+        const double v = 0.5 * (ldo(u_r, o) + ldo(u_r, o + up));
+        va[q + 1] = s < 0 ? sgl * v : (s >= n ? sgh * v : v);
+      }
+      const unsigned pT = 8u * (unsigned)((g.nt + 1) * g.np);
+      const bool lo = pa == 0, hi = pa == g.nr - 1;
+      const unsigned om = lo ? oT : oT - pT, op = hi ? oT : oT + pT;
+#pragma unroll
+      for (int q = 0; q <= PM; q++) {
+        const unsigned ro = row(q) * sT;
+        const double x = ldo(u_t, om + ro), y = ldo(u_t, op + ro);
+        tim[q] = lo ? -x : x;
+        tip[q] = hi ? -y : y;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < PM; q++) {
+      const unsigned s = row(q), o = oC + s * sC;
+      const unsigned of = oF + s * sF;
+      const double f0 = ldo(u_f, of), f1 = ldo(u_f, of + (unsigned)dF);
+      P[q] = ldo(a.u.a[F_P], o);
+      Te[q] = ldo(a.u.a[F_T], o);
+      b0[q] = ldo(a.rhs.p, o);
+      b1[q] = ldo(a.rhs.T, o);
+      b2[q] = D == 0 ? ldo(a.rhs.ur, o + sC) : ldo(a.rhs.ut, oT + s * sT + sT);
+      if constexpr (D == 0) {
+        const unsigned ot = oT + s * sT;
+        const double t0 = ldo(u_t, ot), t1 = ldo(u_t, ot + 8u * (unsigned)g.np), ir = ldo(mt, 64u * s + 40u);
+        const double ur = 0.5 * (uw[q] + uw[q + 1]), ut = 0.5 * (t0 + t1);
+        const double gg = ((t1 - t0) * g.idt + 2.0 * ur + (f1 - f0) * (isk * g.idp) + ut * ctk) * ir;  // Gtt + Gff
+        gG[q] = 0.0;  // from uw
+        gTR[q] = gg;  // less G
+        gGG[q] = gg * ir;
+        if constexpr (PT) P[q] += a.pref[s];
+      } else {
+        const double ct = ldo(mt, 64u * s + 40u), is = ldo(mt, 64u * s + 48u);
+        const double ur = va[q + 1], ut = 0.5 * (uw[q] + uw[q + 1]);
+        // u_r differences across the plane: one more load of each face
+        const double grr = (ldo(u_r, o + up) - ldo(u_r, o)) * g.idr;
+        const double G = ((uw[q + 1] - uw[q]) * g.idt + ur) * irk;
+        const double gff = ((f1 - f0) * (is * g.idp) + ur + ut * ct) * irk;
+        const double srt = 0.5 * ((tip[q] + tip[q + 1]) - (tim[q] + tim[q + 1])) * (0.5 * g.idr) +
+                           (va[q + 2] - va[q]) * (0.5 * irk * g.idt) - ut * irk;
+        gG[q] = G;
+        gTR[q] = grr + gff;
+        gGG[q] = (gff * ct - 0.5 * srt) * irk;
+        if constexpr (PT) P[q] += a.pref[pa];
+      }
+      P[q] += m.pinf;
+    }
+    {
+      const unsigned s = (unsigned)min(s0 + PM, n - 1), o = oC + s * sC;
+      P[PM] = ldo(a.u.a[F_P], o);
+      Te[PM] = ldo(a.u.a[F_T], o);
+      if constexpr (PT) P[PM] += a.pref[D == 0 ? (int)s : pa];
+      P[PM] += m.pinf;
+    }
+  }
+  const double irl = D == 0 ? 1.0 : g.irc[pa];
+  const double h = D == 0 ? g.idr : irl * g.idt;
+  auto assemble = [&](int q, FRow &R) {
+    const int s = s0 + q;
+    const unsigned o = 64u * (unsigned)max(s, 0);
+    RowMetric x;
+    const double2 d = ldo2(mt, o), w = ldo2(mt, o + 16);
+    x.h = h;
+    x.dp = d.x * irl;
+    x.dm = d.y * irl;
+    x.lp = x.dp * h;
+    x.lm = -x.dm * h;
+    const double w2 = irl * irl;
+    x.wp = w.x * w2;
+    x.w0 = w.y * w2;
+    x.wm = ldo(mt, o + 32) * w2;
+    RowIn in;
+    in.vel = 0.5 * (uw[q] + uw[q + 1]);
+    in.un = uw[q + 1];
+    in.G = D == 0 ? (uw[q + 1] - uw[q]) * g.idr : gG[q];
+    in.tr = in.G + gTR[q];
+    in.gg = gGG[q];
+    in.P = P[q];
+    in.T = Te[q];
+    in.irho = 2.0 * m.Rg * Te[q] * Te[q + 1] * rcp_nr(P[q] * Te[q + 1] + P[q + 1] * Te[q]);
+    in.b0 = b0[q];
+    in.b1 = b1[q];
+    in.b2 = b2[q];
+    frow(m, hs, in, x, s == 0, q == PM - 1 && cc == T - 1, q == PM - 2 && cc == T - 1, s >= 0, R);
+  };
+  Chunk<PM> ch;
+#pragma unroll
+  for (int q = 0; q < PM - 1; q++) {
+    FRow R;
+    assemble(q, R);
+    ch.eliminate(q, R);
+  }
+  FRow S;
+  assemble(PM - 1, S);
+  ch.back();
+  double *rec = lds + (size_t)t * SEP_REC;
+  if (c < T) {
+#pragma unroll
+    for (int z = 0; z < 3; z++) rec[z] = ch.Y[0][z];
+#pragma unroll
+    for (int z = 0; z < 9; z++) { rec[3 + z] = ch.E[0][z]; rec[12 + z] = ch.C[0][z]; }
+  }
+  __syncthreads();
+  double A[9], B[9], Cc[9], r[3];
+  {
+    const double *nx = lds + (size_t)(cc < T - 1 ? t + L : min(t, T * L - 1)) * SEP_REC;
+    double P[SEP_REC];
+#pragma unroll
+    for (int z = 0; z < 21; z++) P[z] = nx[z];
+    ch.reduce(S, P, P + 3, P + 12, A, B, Cc, r);
+  }
+  bool sing = ch.sing;
+  for (int hh = 1; hh < T; hh *= 2) {
+    __syncthreads();
+    if (c < T) sing |= sep_publish(A, B, Cc, r, rec);
+    __syncthreads();
+    const int lo = max(cc - hh, 0) * L + l, hi = min(cc + hh, T - 1) * L + l;
+    sep_fold(A, B, Cc, r, lds + (size_t)lo * SEP_REC, lds + (size_t)hi * SEP_REC);
+  }
+  double Bi[9], xs[3], xl[3];
+  sing |= inv3q(B, Bi);
+  mv3(Bi, r, xs);
+  if (act && sing) a.status[ST_SINGULAR] = 1;
+  __syncthreads();
+  if (c < T) {
+#pragma unroll
+    for (int z = 0; z < 3; z++) rec[z] = xs[z];
+  }
+  __syncthreads();
+  if (!act) return;
+  {
+    const double *pl = lds + (size_t)(c > 0 ? t - L : t) * SEP_REC;
+#pragma unroll
+    for (int z = 0; z < 3; z++) xl[z] = c > 0 ? pl[z] : 0.0;
+  }
+#pragma unroll
+  for (int q = 0; q < PM; q++) {
+    const int s = s0 + q;
+    if (s < 0) continue;
+    double v[3];
+    if (q < PM - 1) ch.fill(q, xl, xs, v);
+    else { v[0] = xs[0]; v[1] = xs[1]; v[2] = xs[2]; }
+    const unsigned o = oC + (unsigned)s * sC;
+    sto(a.o.x.p, o, v[0]);
+    sto(a.o.x.T, o, v[1]);
+    if (D == 0) sto(a.o.x.ur, o + sC, v[2]);
+    else sto(a.o.x.ut, oT + (unsigned)s * sT + sT, v[2]);
+  }
+}
+
+// ------------------------------------------ scalar lines, plain and pert --
+// The lines [line0, line0 + L) of both scalar families in one form: the row
+// of a line reads the two cells on either side of its face (their mean
+// density) and the sum of the sweep direction's velocity over the same two
+// columns on the row's two faces, so the families differ in byte offsets
+// only.  Inputs of all rows of a chunk are loaded first, chunks are aligned to
+// their ends (fillers: a = -1, b = 1, c = 0, r = 0), as on the block lines.
+// LDS 4 doubles per thread; mode 0.
+template <int D, int PM, bool PT>
+__device__ __forceinline__ void rt_scalar_fast(const PassArgs &a, int fam, unsigned line0, double *lds) {
+  const Geo &g = a.g;
+  const Mat &m = a.m;
+  const double hs = a.tau;
+  const int n = D == 0 ? g.nr : g.nt, T = (n + PM - 1) / PM, L = (int)blockDim.x / T, pad = T * PM - n;
+  const unsigned nkf = (unsigned)(g.periodic ? g.np : g.np - 1), wid = fam == 0 ? (unsigned)g.np : nkf;
+  const unsigned nl = (unsigned)(D == 0 ? g.nt : g.nr) * wid - (fam == 0 ? wid : 0u);
+  const int t = threadIdx.x, c = (int)((unsigned)t / (unsigned)L), l = t - c * L;
+  const bool act = c < T && line0 + l < nl;
+  const unsigned line = min(line0 + (unsigned)l, nl - 1), q0 = line / wid;
+  const int cc = min(c, T - 1), s0 = cc * PM - pad;
+  const int k = (int)(line - q0 * wid) + (fam == 0 || g.periodic ? 0 : 1), pa = (int)q0 + (fam == 0 ? 1 : 0);
+  // cells A and B (before and after the face), velocity columns A and B, output
+  const unsigned N = (unsigned)g.np;
+  unsigned oA, oB, vA, vB, oX;
+  const unsigned sC = 8u * (D == 0 ? (unsigned)g.nt * N : N);
+  const unsigned sV = 8u * (D == 0 ? (unsigned)g.nt * N : N);
+  unsigned sX;
+  double *X;
+  const double *Rh;
+  if (fam == 0) {
+    if (D == 0) {  // u_theta on theta face pa: cells (., pa - 1, k), (., pa, k)
+      oB = 8u * ((unsigned)pa * N + k);
+      oA = oB - 8u * N;
+      vA = oA; vB = oB; oX = oB;
+      sX = 8u * (unsigned)(g.nt + 1) * N;
+      X = a.o.x.ut; Rh = a.rhs.ut;
+    } else {  // u_r on r face pa: cells (pa - 1, ., k), (pa, ., k)
+      oB = 8u * ((unsigned)(pa * g.nt) * N + k);
+      oA = oB - 8u * (unsigned)g.nt * N;
+      vB = 8u * ((unsigned)(pa * (g.nt + 1)) * N + k);
+      vA = vB - 8u * (unsigned)(g.nt + 1) * N;
+      oX = oB;
+      sX = sC;
+      X = a.o.x.ur; Rh = a.rhs.ur;
+    }
+  } else {  // u_phi on phi face k: cells (., k - 1), (., k)
+    const int k1 = g.periodic && k == 0 ? g.np - 1 : k - 1;
+    const unsigned ro = D == 0 ? (unsigned)pa * N : (unsigned)(pa * g.nt) * N;
+    oA = 8u * (ro + k1); oB = 8u * (ro + k);
+    const unsigned vo = D == 0 ? ro : (unsigned)(pa * (g.nt + 1)) * N;
+    vA = 8u * (vo + k1); vB = 8u * (vo + k);
+    oX = 8u * ((D == 0 ? (unsigned)pa * g.npf : (unsigned)(pa * g.nt) * g.npf) + k);
+    sX = 8u * (D == 0 ? (unsigned)g.nt * g.npf : (unsigned)g.npf);
+    X = a.o.x.uf; Rh = a.rhs.uf;
+  }
+  const double *V = a.u.a[D == 0 ? F_UR : F_UT], *mt = D == 0 ? g.mr : g.mt;
+  const double irr = D == 0 ? 1.0 : (fam == 0 ? g.irf[pa] : g.irc[pa]);
+  const double hh = D == 0 ? g.idr : irr * g.idt, hv = 0.125 * hs * hh, hn = hs * m.mu * 2.0 * m.Rg * hh * irr;
+  double sglo = -1.0, sghi = -1.0;
+  if (D == 1 && fam == 0) { sglo = g.pole_lo ? 1.0 : -1.0; sghi = g.pole_hi ? 1.0 : -1.0; }
+  double ra[PM], rb[PM], rc[PM], rr[PM];
+  {
+    double vs[PM + 1];
+#pragma unroll
+    for (int q = 0; q <= PM; q++) {
+      const unsigned o = (unsigned)max(s0 + q, 0) * sV;
+      vs[q] = ldo(V, vA + o) + ldo(V, vB + o);
+    }
+#pragma unroll
+    for (int q = 0; q < PM; q++) {
+      const int s = s0 + q;
+      const unsigned sc = (unsigned)max(s, 0), o = sc * sC;
+      double Pa = ldo(a.u.a[F_P], oA + o), Pb = ldo(a.u.a[F_P], oB + o);
+      const double Ta = ldo(a.u.a[F_T], oA + o), Tb = ldo(a.u.a[F_T], oB + o);
+      if constexpr (PT) {
+        const int ib = D == 0 ? (int)sc : pa;
+        Pa += a.pref[D == 1 && fam == 0 ? ib - 1 : ib];
+        Pb += a.pref[ib];
+      }
+      Pa += m.pinf;
+      Pb += m.pinf;
+      const double2 d = ldo2(mt, 64u * sc);
+      const double nu = hn * Ta * Tb * rcp_nr(Pa * Tb + Pb * Ta);  // tau/2 mu / rho times h
+      const double ua = hv * (vs[q] + vs[q + 1]), qp = nu * d.x, qm = nu * d.y;
+      double ca = qm - ua, cb = qp - qm, cn = ua - qp, r = ldo(Rh, oX + sc * sX);
+      if (s == 0) { cb += sglo * ca; ca = 0.0; }
+      if (q == PM - 1 && cc == T - 1) { cb += sghi * cn; cn = 0.0; }
+      cb += 1.0;
+      const bool real = s >= 0;
+      ra[q] = real ? ca : -1.0;
+      rb[q] = real ? cb : 1.0;
+      rc[q] = real ? cn : 0.0;
+      rr[q] = real ? r : 0.0;
+    }
+  }
+  // eliminate: x_q = Y_q - C_q x_{q+1} - E_q x_left, then to (g, V, W)
+  bool sing = false;
+#pragma unroll
+  for (int q = 0; q < PM - 1; q++) {
+    double dp = rb[q], y = rr[q], lx = ra[q];
+    if (q > 0) {
+      dp = fma_(-ra[q], rc[q - 1], dp);
+      y = fma_(-ra[q], rr[q - 1], y);
+      lx = -ra[q] * ra[q - 1];
+    }
+    sing |= !(dp != 0.0);
+    const double id = rcp_nr(dp);
+    rc[q] *= id;
+    rr[q] = y * id;
+    ra[q] = lx * id;
+  }
+  ra[PM - 2] = -ra[PM - 2];
+  rc[PM - 2] = -rc[PM - 2];
+#pragma unroll
+  for (int q = PM - 3; q >= 0; q--) {
+    rr[q] = fma_(-rc[q], rr[q + 1], rr[q]);
+    ra[q] = fma_(-rc[q], ra[q + 1], -ra[q]);
+    rc[q] = -rc[q] * rc[q + 1];
+  }
+  double *rec = lds + 4 * (size_t)t;
+  if (c < T) { rec[0] = rr[0]; rec[1] = ra[0]; rec[2] = rc[0]; }
+  __syncthreads();
+  const double *nx = lds + 4 * (size_t)(cc < T - 1 ? t + L : min(t, T * L - 1));
+  double A = ra[PM - 1] * ra[PM - 2];
+  double B = fma_(rc[PM - 1], nx[1], fma_(ra[PM - 1], rc[PM - 2], rb[PM - 1]));
+  double C = rc[PM - 1] * nx[2];
+  double r = fma_(-rc[PM - 1], nx[0], fma_(-ra[PM - 1], rr[PM - 2], rr[PM - 1]));
+  for (int h = 1; h < T; h *= 2) {
+    const double ib = rcp_nr(B);
+    sing |= !(B != 0.0);
+    __syncthreads();
+    if (c < T) { rec[0] = A * ib; rec[1] = C * ib; rec[2] = r * ib; }
+    __syncthreads();
+    const double *lo = lds + 4 * (size_t)(max(cc - h, 0) * L + l), *hi = lds + 4 * (size_t)(min(cc + h, T - 1) * L + l);
+    B = fma_(-C, hi[0], fma_(-A, lo[1], B));
+    r = fma_(-C, hi[2], fma_(-A, lo[2], r));
+    A = -A * lo[0];
+    C = -C * hi[1];
+  }
+  sing |= !(B != 0.0);
+  const double xs = r * rcp_nr(B);
+  if (act && sing) a.status[ST_SINGULAR] = 1;
+  __syncthreads();
+  if (c < T) rec[0] = xs;
+  __syncthreads();
+  if (!act) return;
+  const double xl = c > 0 ? lds[4 * (size_t)(t - L)] : 0.0;
+#pragma unroll
+  for (int q = 0; q < PM; q++) {
+    const int s = s0 + q;
+    if (s < 0) continue;
+    const double v = q < PM - 1 ? fma_(rc[q], xs, fma_(ra[q], xl, rr[q])) : xs;
+    sto(X, oX + (unsigned)s * sX, v);
+  }
+}
+
 // ----------------------------------------------------------- scalar lines --
 // Lines [line0, line0 + L) of scalar family FAM of sweep D; LDS 4 doubles
 // per thread.
@@ -417,7 +795,8 @@ __device__ __forceinline__ void rt_body(const PassArgs &a, unsigned w, double *l
   if (w < nbw) {
     if constexpr (PART != 1) {
       const unsigned L = bs / (unsigned)rt_chunks<PM>(families(g, D).n);
-      rt_block_lines<D, PM, TR>(g, a.m, u, a.rhs, a.o, (long)w * L, a.tau, lds, a.status);
+      if constexpr (!W && !TR) rt_block_fast<D, PM, PT>(a, w * L, lds);
+      else rt_block_lines<D, PM, TR>(g, a.m, u, a.rhs, a.o, (long)w * L, a.tau, lds, a.status);
     }
     return;
   }
@@ -425,7 +804,8 @@ __device__ __forceinline__ void rt_body(const PassArgs &a, unsigned w, double *l
     const unsigned w2 = w - nbw;
     const unsigned L = bs / (unsigned)rt_chunks<RT_PMS>(families(g, D).n);
     const unsigned nwa = rt_scalar_wgs_a(g, D, bs);
-    if (w2 < nwa) rt_scalar_lines<D, 0, RT_PMS, TR>(g, a.m, u, a.rhs, a.o, (long)w2 * L, a.tau, lds, a.status);
+    if constexpr (!W && !TR) rt_scalar_fast<D, RT_PMS, PT>(a, w2 < nwa ? 0 : 1, (w2 < nwa ? w2 : w2 - nwa) * L, lds);
+    else if (w2 < nwa) rt_scalar_lines<D, 0, RT_PMS, TR>(g, a.m, u, a.rhs, a.o, (long)w2 * L, a.tau, lds, a.status);
     else rt_scalar_lines<D, 1, RT_PMS, TR>(g, a.m, u, a.rhs, a.o, (long)(w2 - nwa) * L, a.tau, lds, a.status);
   }
 }
@@ -434,7 +814,7 @@ __device__ __forceinline__ void rt_body(const PassArgs &a, unsigned w, double *l
 // neighbouring lines of neighbouring workgroups (which share cache lines and
 // neighbour cells) meet in one L2.
 template <int D, int PM, int PART, bool B>
-__global__ void __launch_bounds__(256) k_rt_part(PassArgs a, Batch bt) {
+__global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_part(PassArgs a, Batch bt) {
   extern __shared__ double lds[];
   if constexpr (B) {
     const int mb = batch_member(bt, blockIdx.x);
@@ -452,7 +832,7 @@ __global__ void __launch_bounds__(256) k_rt_partF(PassArgs a) {
 
 // perturbation-pressure form, one grid
 template <int D, int PM, int PART>
-__global__ void __launch_bounds__(256) k_rt_partP(PassArgs a) {
+__global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_partP(PassArgs a) {
   extern __shared__ double lds[];
   rt_body<D, PM, PART, false, false, true>(a, xcd_contiguous(blockIdx.x, gridDim.x), lds);
 }
@@ -473,7 +853,7 @@ constexpr unsigned RT_SPLIT_WGS = 1024;
 
 bool rt_part_supported(const Geo &g, int d, unsigned bs, int pm) {
   const Families F = families(g, d);
-  return d < 2 && pm == 4 && bs <= 256 && rt_block_chunks(F.n, pm) <= (int)bs &&
+  return d < 2 && pm == 4 && bs <= 256 && off32_ok(g) && rt_block_chunks(F.n, pm) <= (int)bs &&
          rt_chunks<RT_PMS>(F.n) <= (int)bs;
 }
 
@@ -554,7 +934,7 @@ void launch_rt_T(int d, const PassArgs &a, unsigned threads, hipStream_t st) {
 // on 64 uneven sectors (lines of 64 to 256 rows) the ragged chunks and idle
 // lanes made the two passes slower than the one two-ended launch.
 bool rt_scalar_supported(const Geo &g, int d, unsigned bs) {
-  if (d > 1 || bs > 256) return false;
+  if (d > 1 || bs > 256 || !off32_ok(g)) return false;
   const int n = families(g, d).n, T = rt_chunks<RT_PMS>(n);
   return n % RT_PMS == 0 && T <= (int)bs && bs % (unsigned)T == 0 && rt_scalar_wgs(g, d, bs) > 0;
 }
@@ -593,13 +973,13 @@ void launch_rt_scalar_pass(int d, const PassArgs &a, const Batch &b, unsigned bl
 }
 
 // the solver a grid takes by default: partitioned where a block line
-// splits into at most 32 chunks (L >= 8 neighbouring lines per 256-thread
-// workgroup), else two-ended.  Measured: partitioned r 0.16 / theta 0.19 ms
-// against 0.20 / 0.31 ms two-ended on the 256 x 128 x 64 sector (64 and 128
-// rows); theta on the 512 x 256 x 128 sphere (256 rows, 64 chunks) 1.74
-// against 1.63 ms.
+// splits into at most 64 chunks (L >= 4 neighbouring lines per 256-thread
+// workgroup), else two-ended.  Measured, partitioned against two-ended, line
+// solves: theta on the 512 x 256 x 128 sphere (256 rows) 1.01 / 1.37 ms, theta
+// and r on 200 x 200 x 200 cells 0.56 / 0.81 and 0.67 / 0.74 ms, theta on the
+// 1024 x 512 x 64 sector (512 rows, 128 chunks) 3.2 / 3.0 ms.
 int rt_default_pm(const Geo &g, int d) {
-  return rt_part_supported(g, d, 256, 4) && rt_block_chunks(families(g, d).n, 4) <= 32 ? 4 : 0;
+  return rt_part_supported(g, d, 256, 4) && rt_block_chunks(families(g, d).n, 4) <= 64 ? 4 : 0;
 }
 
 template <int D, int PM>
