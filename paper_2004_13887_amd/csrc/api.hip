@@ -507,9 +507,9 @@ static unsigned kind_threads(int kind, const Geo &g, const Cfg &c) {
   case PK_SW1B:
   case PK_SW1S:
   case PK_SW1P: return (unsigned)c.sweep_bs[1];
-  case PK_SW2_PART:
+  case PK_SW2_PART: return phi_part_threads(g, c.phi_pm);
   case PK_SW2_CP:
-  case PK_SW2_CN: return phi_part_threads(g, c.phi_pm);
+  case PK_SW2_CN: return phi_fast_threads(g, c.phi_pm);
   default: return 128u; // boundary copy, thread-per-line phi
   }
 }
@@ -533,6 +533,8 @@ static unsigned kind_blocks(int kind, const Geo &g, const Cfg &c, unsigned threa
   case PK_SW0P: return rt_part_blocks(g, 0, threads, 4);
   case PK_SW1P: return rt_part_blocks(g, 1, threads, 4);
   case PK_SW2_LINE: return cdiv(sweep_lines(g, 2), threads);
+  case PK_SW2_CP:
+  case PK_SW2_CN: return phi_fast_blocks(g, c.phi_pm, threads);
   default: return (unsigned)g.nr * (unsigned)g.nt; // PK_SW2_PART
   }
 }
@@ -540,7 +542,8 @@ static unsigned kind_blocks(int kind, const Geo &g, const Cfg &c, unsigned threa
 static size_t kind_lds(int kind, const Geo &g, const Cfg &c) {
   if (kind == PK_SW0P || kind == PK_SW1P) return rt_part_lds(kind_threads(kind, g, c));
   if (kind == PK_SW0S || kind == PK_SW1S) return rt_scalar_lds(kind_threads(kind, g, c));
-  return (kind == PK_SW2_PART || kind == PK_SW2_CP || kind == PK_SW2_CN) ? phi_part_lds(g, c.phi_pm) : 0;
+  if (kind == PK_SW2_CP || kind == PK_SW2_CN) return phi_fast_lds(kind_threads(kind, g, c));
+  return kind == PK_SW2_PART ? phi_part_lds(g, c.phi_pm) : 0;
 }
 
 static void launch_kind(int kind, const Cfg &c, const PassArgs &a, const Batch &b, unsigned blocks,
@@ -695,6 +698,11 @@ extern "C" int dsw_split_step_pert(dsw_grid *G, const dsw_fields *Un, dsw_fields
       case PK_SW0B: launch_sweep2_pert(0, a, sweep2_blocks(g, 0, th), th, st); break;
       case PK_SW1T:
       case PK_SW1B: launch_sweep2_pert(1, a, sweep2_blocks(g, 1, th), th, st); break;
+      case PK_SW2_CP:
+      case PK_SW2_CN:
+        launch_phi_pert_c(G->cfg.phi_pm, p.kind == PK_SW2_CP, a, kind_blocks(p.kind, g, G->cfg, th), th,
+                          kind_lds(p.kind, g, G->cfg), st);
+        break;
       default:  // PK_SW2_PART
         launch_phi_pert(G->cfg.phi_pm, a, kind_blocks(p.kind, g, G->cfg, th), th, kind_lds(p.kind, g, G->cfg), st);
       }

@@ -181,9 +181,8 @@ enum PassKind { PK_BND = 0, PK_RES = 1, PK_SW0 = 2, PK_SW1 = 3, PK_SW2_LINE = 4,
                 PK_RES_IN = 6, PK_SW0T = 7, PK_SW1T = 8, PK_RES_INP = 9, PK_SW0P = 10, PK_SW1P = 11,
                 PK_SW0B = 12, PK_SW1B = 13, PK_SW0S = 14, PK_SW1S = 15, PK_NONE = 16,
                 PK_SW2_CP = 17, PK_SW2_CN = 18 };
-// PK_SW2_CP / PK_SW2_CN: the partitioned phi pass of a grid with an interior
-// (periodic / bounded phi); in a batch, each member's ring slots and then its
-// interior slots (the interior ones through the interior source).
+// PK_SW2_CP / PK_SW2_CN: the partitioned phi pass with 32-bit byte offsets
+// (periodic / bounded phi); PK_SW2_PART: the same on grids beyond them.
 
 // forced split step (source term, wall velocities, Dirichlet data at the new
 // time level): one grid, the general residual over every point, the
@@ -304,17 +303,23 @@ bool phi_part_equal(const Geo &g, int pm);
 // doubles of scratch needed by the sweeps of a grid
 void sweep_scratch_size(const Geo &g, long *blk, long *sca);
 
-// the kind of the phi pass of a grid under a configuration
-// whether a grid's phi pass can take its interior slots through the
-// interior source (it has an interior, and 32-bit indices reach)
-bool phi_interior_split(const Geo &g);
-// a batch of grids that all have an interior (P: periodic phi): each
-// member's boundary ring, then its interior slots
+// whether the byte offsets of a grid's arrays fit 32 bits
+__host__ __device__ inline bool off32_ok(const Geo &g) {
+  return (long)(g.nr + 1) * (g.nt + 1) * (g.np + 1) < (1L << 29);
+}
+// the phi pass of such a grid, or of a batch of them: shape, workgroups
+// (block lines, then as many for the scalar lines), launch
+unsigned phi_fast_threads(const Geo &g, int pm);
+unsigned phi_fast_blocks(const Geo &g, int pm, unsigned threads);
+size_t phi_fast_lds(unsigned threads);
 void launch_phi_pass_c(int pm, bool periodic, const PassArgs &a, const Batch &b, unsigned blocks,
                        unsigned threads, size_t lds, hipStream_t st);
+void launch_phi_pert_c(int pm, bool periodic, const PassArgs &a, unsigned blocks, unsigned threads, size_t lds,
+                       hipStream_t st);
+// the kind of the phi pass of a grid under a configuration
 inline int phi_kind(const Geo &g, const Cfg &c) {
   if (!(c.phi_pm > 0 && phi_part_supported(g, c.phi_pm))) return PK_SW2_LINE;
-  if (phi_interior_split(g)) return g.periodic ? PK_SW2_CP : PK_SW2_CN;
+  if (off32_ok(g)) return g.periodic ? PK_SW2_CP : PK_SW2_CN;
   return PK_SW2_PART;
 }
 

@@ -14,9 +14,21 @@
 //      reduction, log2(#chunks) steps;
 //   3. interior rows are filled in from the separators.
 // All intermediates stay in registers and LDS: no scratch traffic.
+//
+// The plain and the perturbation-pressure sweeps take the *_fast bodies: a
+// workgroup on as many neighbouring slots as its lanes hold, every input of a
+// chunk loaded before its first row is eliminated, ghosts by clamped 32-bit
+// offsets and signs instead of branches (so no slot needs a launch or a
+// source of its own).  Line solves, one row at a time against this: 512 x 256
+// x 128 sphere 1.24 -> 0.98 ms, 200 x 200 x 200 cells 0.66 -> 0.51, 150 x 101
+// x 37 84 -> 55 us, 32 x 32 x 16 28 -> 14 us.  The block lines are bound by
+// their FP64 work at two waves per SIMD (a third of it the cyclic reduction)
+// and its barriers, the scalar lines by their reads; the scalar reductions
+// keep each quantity contiguous over the lanes (a record per lane, as the
+// block reductions have, put 16 lanes on one bank: 0.55 against 0.45 ms).
 #include <algorithm>
 
-#include "rows.hpp"
+#include "rows_fast.hpp"
 
 namespace dsw {
 
@@ -578,6 +590,499 @@ __device__ __forceinline__ void part_scalar_lines2(const Geo &g, const Mat &m, c
   __syncthreads();
 }
 
+// ---------------------------------------- plain and perturbation sweeps --
+// A workgroup takes L = blockDim / T neighbouring slots; thread t = l T + c
+// holds chunk c of slot l's lines.  Ghosts across r and theta are a clamped
+// index and a sign per lane, across phi the wrap (CYC) or the same.
+
+// the rows of a lane's chunk: row q is cell s0 + q; rows before the chunk's
+// first one (real) are fillers
+struct PhiChunk {
+  int T, L, l, c, s0, pad;  // pad: fillers of this chunk
+  bool act;
+  unsigned line;
+};
+
+template <int PM, bool CYC>
+__device__ __forceinline__ PhiChunk phi_lane(const Geo &g, unsigned w) {
+  PhiChunk p;
+  p.T = phi_chunks(g.np, CYC, PM);
+  p.L = (int)blockDim.x / p.T;
+  const int t = threadIdx.x;
+  p.l = (int)((unsigned)t / (unsigned)p.T);
+  p.c = t - p.l * p.T;
+  const unsigned n = (unsigned)g.nr * (unsigned)g.nt;
+  p.act = p.l < p.L && w * p.L + p.l < n;
+  p.line = min(w * (unsigned)p.L + (unsigned)min(p.l, p.L - 1), n - 1);
+  if (CYC) {  // rows spread evenly over the chunks
+    const int lg = 31 - __builtin_clz((unsigned)p.T), base = g.np >> lg, rem = g.np & (p.T - 1);
+    const int len = base + (p.c < rem ? 1 : 0);
+    p.pad = PM - len;
+    p.s0 = p.c * base + min(p.c, rem) - p.pad;
+  } else {  // the first chunk is the short one
+    p.s0 = p.c * PM - (p.T * PM - g.np);
+    p.pad = max(-p.s0, 0);
+  }
+  return p;
+}
+
+// byte offset of cell (or face) s along phi: wrapped, or the nearest cell
+template <bool CYC>
+__device__ __forceinline__ unsigned phi_pos(const Geo &g, int s) {
+  if (CYC) s = s < 0 ? s + g.np : (s >= g.np ? s - g.np : s);
+  else s = min(max(s, 0), g.np - 1);
+  return 8u * (unsigned)s;
+}
+
+// The block line of every slot of the workgroup.  LDS SEP_REC doubles per
+// thread.
+template <int PM, bool CYC, bool PT>
+__device__ __forceinline__ void phi_block_fast(const PassArgs &a, unsigned w, double *lds) {
+  const Geo &g = a.g;
+  const Mat &m = a.m;
+  const double hs = a.tau;
+  const PhiChunk pc = phi_lane<PM, CYC>(g, w);
+  const int T = pc.T, t = threadIdx.x, c = pc.c, s0 = pc.s0, np = g.np;
+  const unsigned N8 = 8u * (unsigned)np, F8 = 8u * (unsigned)g.npf;
+  const int i = (int)(pc.line / (unsigned)g.nt), j = (int)pc.line - i * g.nt;
+  const double ir = g.irc[i], is = g.isc[j], ct = g.ctc[j], irs = ir * is;
+  const double h = irs * g.idp;  // 1 / spacing; dp = h, dm = -h
+  // per row: v = u_r + cot u_theta at rows -1 .. PM, e = Grr + Gtt; per face:
+  // own velocity uw, wf the r and theta differences of u_phi
+  double v[PM + 2], e[PM], uw[PM + 1], wf[PM + 1], P[PM + 1], Te[PM + 1], b0[PM], b1[PM], b2[PM];
+  {
+    unsigned pos[PM + 2];  // cells s0 - 1 .. s0 + PM
+#pragma unroll
+    for (int q = 0; q < PM + 2; q++) pos[q] = phi_pos<CYC>(g, s0 + q - 1);
+    unsigned fpos[PM + 1];  // faces s0 .. s0 + PM (a bounded line has face np)
+#pragma unroll
+    for (int q = 0; q <= PM; q++) fpos[q] = CYC ? pos[q + 1] : 8u * (unsigned)max(s0 + q, 0);
+    const double *u_r = a.u.a[F_UR], *u_t = a.u.a[F_UT], *u_f = a.u.a[F_UF];
+    const unsigned oC = pc.line * N8, pl = (unsigned)g.nt * N8;
+    const unsigned oT = (unsigned)(i * (g.nt + 1) + j) * N8, oF = pc.line * F8, pF = (unsigned)g.nt * F8;
+    // u_phi on the four neighbouring lines: a wall or pole negates it
+    const double sim = i == 0 ? -1.0 : 1.0, sip = i == g.nr - 1 ? -1.0 : 1.0;
+    const double sjm = j == 0 ? -1.0 : 1.0, sjp = j == g.nt - 1 ? -1.0 : 1.0;
+    const unsigned oim = i == 0 ? oF : oF - pF, oip = i == g.nr - 1 ? oF : oF + pF;
+    const unsigned ojm = j == 0 ? oF : oF - F8, ojp = j == g.nt - 1 ? oF : oF + F8;
+    const double kr = 0.5 * g.idr, kt = 0.5 * ir * g.idt * ct;
+    const double kip = kr * sip, kim = kr * sim, kjp = kt * sjp, kjm = kt * sjm;
+#pragma unroll
+    for (int q = 0; q <= PM; q++) uw[q] = ldo(u_f, oF + fpos[q]);
+#pragma unroll
+    for (int q = 0; q <= PM; q++) wf[q] = kip * ldo(u_f, oip + fpos[q]);
+#pragma unroll
+    for (int q = 0; q <= PM; q++) wf[q] = fma_(-kim, ldo(u_f, oim + fpos[q]), wf[q]);
+#pragma unroll
+    for (int q = 0; q <= PM; q++) wf[q] = fma_(kjp, ldo(u_f, ojp + fpos[q]), wf[q]);
+#pragma unroll
+    for (int q = 0; q <= PM; q++) wf[q] = fma_(-kjm, ldo(u_f, ojm + fpos[q]), wf[q]);
+#pragma unroll
+    for (int q = 0; q < PM + 2; q++) {
+      const double r0 = ldo(u_r, oC + pos[q]), r1 = ldo(u_r, oC + pl + pos[q]);
+      const double t0 = ldo(u_t, oT + pos[q]), t1 = ldo(u_t, oT + N8 + pos[q]);
+      const double ur = 0.5 * (r0 + r1), ut = 0.5 * (t0 + t1);
+      v[q] = fma_(ut, ct, ur);
+      if (!CYC && (s0 + q - 1 < 0 || s0 + q - 1 >= np)) v[q] = -v[q];  // no slip
+      if (q >= 1 && q <= PM) e[q - 1] = (r1 - r0) * g.idr + fma_(t1 - t0, g.idt, ur) * ir;
+    }
+#pragma unroll
+    for (int q = 0; q <= PM; q++) P[q] = ldo(a.u.a[F_P], oC + pos[q + 1]);
+#pragma unroll
+    for (int q = 0; q <= PM; q++) Te[q] = ldo(a.u.a[F_T], oC + pos[q + 1]);
+#pragma unroll
+    for (int q = 0; q < PM; q++) b0[q] = ldo(a.rhs.p, oC + pos[q + 1]);
+#pragma unroll
+    for (int q = 0; q < PM; q++) b1[q] = ldo(a.rhs.T, oC + pos[q + 1]);
+#pragma unroll
+    for (int q = 0; q < PM; q++) b2[q] = ldo(a.rhs.uf, oF + fpos[q + 1]);
+    double add = m.pinf;
+    if constexpr (PT) {
+      const double pr = a.pref[i];
+#pragma unroll
+      for (int q = 0; q <= PM; q++) P[q] += pr;
+    }
+#pragma unroll
+    for (int q = 0; q <= PM; q++) P[q] += add;
+  }
+  RowMetric x;
+  x.h = h;
+  x.dp = h;
+  x.dm = -h;
+  x.lp = x.lm = h * h;
+  x.wp = x.wm = (-4.0 / 3.0) * (h * h);
+  x.w0 = (8.0 / 3.0) * (h * h);
+  auto assemble = [&](int q, FRow &R) {
+    RowIn in;
+    in.vel = 0.5 * (uw[q] + uw[q + 1]);
+    in.un = uw[q + 1];
+    in.G = fma_(uw[q + 1] - uw[q], h, v[q + 1] * ir);
+    in.tr = e[q] + in.G;
+    in.gg = (-0.5 * ir) * (0.5 * (wf[q] + wf[q + 1]) + (v[q + 2] - v[q]) * (0.5 * h) - in.vel * (ir * (1.0 + ct * ct)));
+    in.P = P[q];
+    in.T = Te[q];
+    in.irho = 2.0 * m.Rg * Te[q] * Te[q + 1] * rcp_nr(P[q] * Te[q + 1] + P[q + 1] * Te[q]);
+    in.b0 = b0[q];
+    in.b1 = b1[q];
+    in.b2 = b2[q];
+    frow(m, hs, in, x, !CYC && s0 + q == 0, !CYC && q == PM - 1 && c == T - 1, !CYC && q == PM - 2 && c == T - 1,
+         q >= pc.pad, R);
+  };
+  Chunk<PM> ch;
+#pragma unroll
+  for (int q = 0; q < PM - 1; q++) {
+    FRow R;
+    assemble(q, R);
+    ch.eliminate(q, R);
+  }
+  FRow S;
+  assemble(PM - 1, S);
+  ch.back();
+  // the first row of the chunk, for the chunk before it (a circle's first
+  // chunk follows its last one, and uneven chunks start after their fillers)
+  double *rec = lds + (size_t)t * SEP_REC;
+  if (pc.l < pc.L) {
+    double f[21];
+#pragma unroll
+    for (int z = 0; z < 3; z++) f[z] = ch.Y[0][z];
+#pragma unroll
+    for (int z = 0; z < 9; z++) { f[3 + z] = ch.E[0][z]; f[12 + z] = ch.C[0][z]; }
+    if (CYC && T * PM != np) {
+#pragma unroll
+      for (int q = 1; q < PM - 1; q++)
+        if (pc.pad == q) {
+#pragma unroll
+          for (int z = 0; z < 3; z++) f[z] = ch.Y[q][z];
+#pragma unroll
+          for (int z = 0; z < 9; z++) { f[3 + z] = ch.E[q][z]; f[12 + z] = ch.C[q][z]; }
+        }
+      if (pc.pad == PM - 1) {  // the separator itself
+#pragma unroll
+        for (int z = 0; z < 21; z++) f[z] = z == 12 || z == 16 || z == 20 ? 1.0 : 0.0;
+      }
+    }
+#pragma unroll
+    for (int z = 0; z < 20; z += 2) *(double2 *)(rec + z) = double2{f[z], f[z + 1]};
+    rec[20] = f[20];
+  }
+  __syncthreads();
+  const int base = t - c;  // this line's first thread
+  double A[9], B[9], Cc[9], r[3];
+  {
+    const int nx = CYC ? ((c + 1) & (T - 1)) : min(c + 1, T - 1);
+    const double *src = lds + (size_t)(pc.l < pc.L ? base + nx : 0) * SEP_REC;
+    double f[SEP_REC];
+#pragma unroll
+    for (int z = 0; z < 20; z += 2) { const double2 y = *(const double2 *)(src + z); f[z] = y.x; f[z + 1] = y.y; }
+    f[20] = src[20];
+    ch.reduce(S, f, f + 3, f + 12, A, B, Cc, r);
+  }
+  bool sing = ch.sing;
+  for (int hh = 1; hh < T; hh *= 2) {
+    __syncthreads();
+    if (pc.l < pc.L) sing |= sep_publish(A, B, Cc, r, rec);
+    __syncthreads();
+    const int lo = CYC ? ((c - hh) & (T - 1)) : max(c - hh, 0), hi = CYC ? ((c + hh) & (T - 1)) : min(c + hh, T - 1);
+    const int b = pc.l < pc.L ? base : 0;
+    sep_fold(A, B, Cc, r, lds + (size_t)(b + lo) * SEP_REC, lds + (size_t)(b + hi) * SEP_REC);
+  }
+  double xs[3], xl[3];
+  {
+    double Si[9];
+    if (CYC) {  // the couplings left over point at the separator itself
+#pragma unroll
+      for (int z = 0; z < 9; z++) B[z] += A[z] + Cc[z];
+    }
+    sing |= inv3q(B, Si);
+    mv3(Si, r, xs);
+  }
+  if (pc.act && sing) a.status[ST_SINGULAR] = 1;
+  __syncthreads();
+  if (pc.l < pc.L) {
+#pragma unroll
+    for (int z = 0; z < 3; z++) rec[z] = xs[z];
+  }
+  __syncthreads();
+  {
+    const int lt = c > 0 ? t - 1 : (CYC ? base + T - 1 : t);
+    const double *pl = lds + (size_t)(pc.l < pc.L ? lt : 0) * SEP_REC;
+#pragma unroll
+    for (int z = 0; z < 3; z++) xl[z] = CYC || c > 0 ? pl[z] : 0.0;
+  }
+  __syncthreads();
+  // staged in LDS, stored row by row: whole lines per store instruction
+  const int LN = pc.L * np;
+  if (pc.act) {
+    double *sx = lds + pc.l * np + s0;
+#pragma unroll
+    for (int q = 0; q < PM; q++) {
+      if (q < pc.pad) continue;
+      double y[3];
+      if (q < PM - 1) ch.fill(q, xl, xs, y);
+      else { y[0] = xs[0]; y[1] = xs[1]; y[2] = xs[2]; }
+      sx[q] = y[0];
+      sx[LN + q] = y[1];
+      sx[2 * LN + q] = y[2];
+    }
+  }
+  __syncthreads();
+  const unsigned line0 = w * (unsigned)pc.L;
+  const int todo = (int)min((unsigned)pc.L, (unsigned)g.nr * (unsigned)g.nt - line0) * np;
+  const long c0 = (long)line0 * np, f0 = (long)line0 * g.npf;
+  for (int q = t; q < todo; q += blockDim.x) {
+    put(a.o, F_P, c0 + q, lds[q]);
+    put(a.o, F_T, c0 + q, lds[LN + q]);
+    const int lq = pc.L > 1 ? (int)((unsigned)q / (unsigned)np) : 0, k = q - lq * np;
+    put(a.o, F_UF, f0 + lq * g.npf + (CYC ? (k + 1 == np ? 0 : k + 1) : k + 1), lds[2 * LN + q]);
+  }
+}
+
+// Both scalar lines of every slot: u_r on its r face (i >= 1) and u_theta on
+// its theta face (j >= 1).  The two lines share the slot's own cell and u_phi
+// loads and one set of barriers.  LDS 8 doubles per thread.
+template <int PM, bool CYC, bool PT>
+__device__ __forceinline__ void phi_scalar_fast(const PassArgs &a, unsigned w, double *lds) {
+  const Geo &g = a.g;
+  const Mat &m = a.m;
+  const double hs = a.tau;
+  const PhiChunk pc = phi_lane<PM, CYC>(g, w);
+  const int T = pc.T, t = threadIdx.x, c = pc.c, s0 = pc.s0, np = g.np;
+  const unsigned N8 = 8u * (unsigned)np, F8 = 8u * (unsigned)g.npf;
+  const int i = (int)(pc.line / (unsigned)g.nt), j = (int)pc.line - i * g.nt;
+  const int im = max(i - 1, 0), jm = max(j - 1, 0);
+  double ra[2][PM], rb[2][PM], rc[2][PM], rr[2][PM];
+  {
+    unsigned pos[PM], fpos[PM + 1];
+#pragma unroll
+    for (int q = 0; q < PM; q++) pos[q] = phi_pos<CYC>(g, s0 + q);
+#pragma unroll
+    for (int q = 0; q <= PM; q++) fpos[q] = CYC ? phi_pos<true>(g, s0 + q) : 8u * (unsigned)max(s0 + q, 0);
+    const unsigned l0 = pc.line, li = (unsigned)(im * g.nt + j), lj = (unsigned)(i * g.nt + jm);
+    const double *u_f = a.u.a[F_UF], *Pp = a.u.a[F_P], *Tp = a.u.a[F_T];
+    double f[3][PM + 1];
+#pragma unroll
+    for (int q = 0; q <= PM; q++) f[0][q] = ldo(u_f, l0 * F8 + fpos[q]);
+#pragma unroll
+    for (int q = 0; q <= PM; q++) f[1][q] = ldo(u_f, li * F8 + fpos[q]);
+#pragma unroll
+    for (int q = 0; q <= PM; q++) f[2][q] = ldo(u_f, lj * F8 + fpos[q]);
+    double P[3][PM], Te[3][PM];
+#pragma unroll
+    for (int z = 0; z < 3; z++) {
+      const unsigned o = (z == 0 ? l0 : z == 1 ? li : lj) * N8;
+#pragma unroll
+      for (int q = 0; q < PM; q++) P[z][q] = ldo(Pp, o + pos[q]);
+#pragma unroll
+      for (int q = 0; q < PM; q++) Te[z][q] = ldo(Tp, o + pos[q]);
+    }
+    const unsigned oT = (unsigned)(i * (g.nt + 1) + j) * N8;
+#pragma unroll
+    for (int q = 0; q < PM; q++) rr[0][q] = ldo(a.rhs.ur, l0 * N8 + pos[q]);
+#pragma unroll
+    for (int q = 0; q < PM; q++) rr[1][q] = ldo(a.rhs.ut, oT + pos[q]);
+    if constexpr (PT) {
+      const double p0 = a.pref[i], pm = a.pref[im];
+#pragma unroll
+      for (int q = 0; q < PM; q++) { P[0][q] += p0; P[1][q] += pm; P[2][q] += p0; }
+    }
+#pragma unroll
+    for (int z = 0; z < 3; z++)
+#pragma unroll
+      for (int q = 0; q < PM; q++) P[z][q] += m.pinf;
+#pragma unroll
+    for (int z = 0; z < 2; z++) {
+      // u_r: 1 / r of its face; u_theta: 1 / sin of its face (0 at a pole,
+      // whose line is not solved)
+      const double h = (z == 0 ? g.irf[i] * g.isc[j] : g.irc[i] * g.isf[j]) * g.idp;
+      const double hv = 0.125 * hs * h, hn = hs * m.mu * 2.0 * m.Rg * (h * h);
+#pragma unroll
+      for (int q = 0; q < PM; q++) {
+        const double Ta = Te[0][q], Tb = Te[1 + z][q];
+        const double nu = hn * Ta * Tb * rcp_nr(P[0][q] * Tb + P[1 + z][q] * Ta);
+        const double ua = hv * ((f[0][q] + f[0][q + 1]) + (f[1 + z][q] + f[1 + z][q + 1]));
+        double ca = -ua - nu, cb = 2.0 * nu, cn = ua - nu;
+        if (!CYC && s0 + q == 0) { cb -= ca; ca = 0.0; }
+        if (!CYC && q == PM - 1 && c == T - 1) { cb -= cn; cn = 0.0; }
+        const bool real = q >= pc.pad;
+        ra[z][q] = real ? ca : -1.0;
+        rb[z][q] = real ? 1.0 + cb : 1.0;
+        rc[z][q] = real ? cn : 0.0;
+        rr[z][q] = real ? rr[z][q] : 0.0;
+      }
+    }
+  }
+  bool sing[2] = {false, false};
+#pragma unroll
+  for (int z = 0; z < 2; z++) {
+#pragma unroll
+    for (int q = 0; q < PM - 1; q++) {
+      double dp = rb[z][q], y = rr[z][q], lx = ra[z][q];
+      if (q > 0) {
+        dp = fma_(-ra[z][q], rc[z][q - 1], dp);
+        y = fma_(-ra[z][q], rr[z][q - 1], y);
+        lx = -ra[z][q] * ra[z][q - 1];
+      }
+      sing[z] |= !(dp != 0.0);
+      const double id = rcp_nr(dp);
+      rc[z][q] *= id;
+      rr[z][q] = y * id;
+      ra[z][q] = lx * id;
+    }
+    ra[z][PM - 2] = -ra[z][PM - 2];
+    rc[z][PM - 2] = -rc[z][PM - 2];
+#pragma unroll
+    for (int q = PM - 3; q >= 0; q--) {
+      rr[z][q] = fma_(-rc[z][q], rr[z][q + 1], rr[z][q]);
+      ra[z][q] = fma_(-rc[z][q], ra[z][q + 1], -ra[z][q]);
+      rc[z][q] = -rc[z][q] * rc[z][q + 1];
+    }
+  }
+  // exchange and reduction: quantity q of line z at ex[(4 z + q) * blockDim + t],
+  // so that a wave's accesses are contiguous
+  const int nth = (int)blockDim.x;
+  double *ex = lds + t;
+  if (pc.l < pc.L) {
+#pragma unroll
+    for (int z = 0; z < 2; z++) {
+      double gq = rr[z][0], vq = ra[z][0], wq = rc[z][0];
+      if (CYC && T * PM != np) {
+#pragma unroll
+        for (int q = 1; q < PM - 1; q++)
+          if (pc.pad == q) { gq = rr[z][q]; vq = ra[z][q]; wq = rc[z][q]; }
+        if (pc.pad == PM - 1) { gq = 0.0; vq = 0.0; wq = 1.0; }
+      }
+      ex[4 * z * nth] = gq; ex[(4 * z + 1) * nth] = vq; ex[(4 * z + 2) * nth] = wq;
+    }
+  }
+  __syncthreads();
+  const int base = pc.l < pc.L ? t - c : 0;
+  const int nxc = CYC ? ((c + 1) & (T - 1)) : min(c + 1, T - 1);
+  double A[2], B[2], C[2], r[2];
+#pragma unroll
+  for (int z = 0; z < 2; z++) {
+    const double *nx = lds + base + nxc + 4 * z * nth;
+    const double sa = ra[z][PM - 1], sc = rc[z][PM - 1];
+    A[z] = sa * ra[z][PM - 2];
+    B[z] = fma_(sc, nx[nth], fma_(sa, rc[z][PM - 2], rb[z][PM - 1]));
+    C[z] = sc * nx[2 * nth];
+    r[z] = fma_(-sc, nx[0], fma_(-sa, rr[z][PM - 2], rr[z][PM - 1]));
+  }
+  for (int hh = 1; hh < T; hh *= 2) {
+    const int lo = CYC ? ((c - hh) & (T - 1)) : max(c - hh, 0), hi = CYC ? ((c + hh) & (T - 1)) : min(c + hh, T - 1);
+    const double *pl = lds + base + lo, *ph = lds + base + hi;
+    double ib[2];
+#pragma unroll
+    for (int z = 0; z < 2; z++) { ib[z] = rcp_nr(B[z]); sing[z] |= !(B[z] != 0.0); }
+    __syncthreads();
+    if (pc.l < pc.L) {
+#pragma unroll
+      for (int z = 0; z < 2; z++) {
+        ex[4 * z * nth] = A[z] * ib[z];
+        ex[(4 * z + 1) * nth] = C[z] * ib[z];
+        ex[(4 * z + 2) * nth] = r[z] * ib[z];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int z = 0; z < 2; z++) {
+      const double *x = pl + 4 * z * nth, *y = ph + 4 * z * nth;
+      B[z] = fma_(-C[z], y[0], fma_(-A[z], x[nth], B[z]));
+      r[z] = fma_(-C[z], y[2 * nth], fma_(-A[z], x[2 * nth], r[z]));
+      A[z] = -A[z] * x[0];
+      C[z] = -C[z] * y[nth];
+    }
+  }
+  double xs[2], xl[2];
+#pragma unroll
+  for (int z = 0; z < 2; z++) {
+    const double S = CYC ? A[z] + B[z] + C[z] : B[z];
+    sing[z] |= !(S != 0.0);
+    xs[z] = r[z] * rcp_nr(S);
+  }
+  const bool on[2] = {pc.act && i >= 1, pc.act && j >= 1};
+  if ((on[0] && sing[0]) || (on[1] && sing[1])) a.status[ST_SINGULAR] = 1;
+  __syncthreads();
+  if (pc.l < pc.L) { ex[0] = xs[0]; ex[nth] = xs[1]; }
+  __syncthreads();
+  {
+    const int lt = c > 0 ? c - 1 : (CYC ? T - 1 : 0);
+#pragma unroll
+    for (int z = 0; z < 2; z++) xl[z] = CYC || c > 0 ? lds[base + lt + z * nth] : 0.0;
+  }
+  __syncthreads();
+  const int LN = pc.L * np;
+  if (pc.act) {
+    double *sx = lds + pc.l * np + s0;
+#pragma unroll
+    for (int z = 0; z < 2; z++)
+#pragma unroll
+      for (int q = 0; q < PM; q++)
+        if (q >= pc.pad) sx[z * LN + q] = q < PM - 1 ? fma_(rc[z][q], xs[z], fma_(ra[z][q], xl[z], rr[z][q])) : xs[z];
+  }
+  __syncthreads();
+  const unsigned line0 = w * (unsigned)pc.L;
+  const int todo = (int)min((unsigned)pc.L, (unsigned)g.nr * (unsigned)g.nt - line0) * np;
+  for (int q = t; q < todo; q += blockDim.x) {
+    const unsigned lq = pc.L > 1 ? (unsigned)q / (unsigned)np : 0u, ln = line0 + lq, ii = ln / (unsigned)g.nt;
+    const int k = q - (int)lq * np;
+    if (ii >= 1) put(a.o, F_UR, (long)line0 * np + q, lds[q]);
+    if (ln - ii * g.nt >= 1) put(a.o, F_UT, ((long)ln + ii) * np + k, lds[LN + q]);  // i (nt + 1) + j
+  }
+}
+
+// workgroups of a grid's block lines (and as many of its scalar lines)
+__host__ __device__ inline unsigned phi_fast_wgs(const Geo &g, int pm, unsigned bs) {
+  const unsigned L = bs / (unsigned)phi_chunks(g.np, g.periodic, pm);
+  return ((unsigned)g.nr * (unsigned)g.nt + L - 1) / L;
+}
+
+// PART 0: the block lines; 1: the scalar lines; 2: both, the block lines in the
+// first half of the workgroups.  COMB: workgroups numbered as for PART 2
+// whatever the part (a batched launch's member table counts both halves).
+template <int PM, int PART, bool CYC, bool PT, bool COMB>
+__device__ __forceinline__ void phi_fast_body(const PassArgs &a, unsigned w, double *lds) {
+  const Geo &g = a.g;
+  const unsigned nbw = PART == 2 || COMB ? phi_fast_wgs(g, PM, blockDim.x) : 0u;
+  const bool block = PART == 0 ? (!COMB || w < nbw) : (PART == 2 && w < nbw);
+  if constexpr (PART != 1) {
+    if (block) {
+      if (a.o.mode == 0) {  // boundary-normal faces of x that no phi line owns
+        const PhiChunk pc = phi_lane<PM, CYC>(g, w);
+        if (pc.act) {
+          const Fields &x = a.o.x;
+          const int i = (int)(pc.line / (unsigned)g.nt), j = (int)pc.line - i * g.nt;
+          if (i == 0 || j == 0 || i == g.nr - 1 || j == g.nt - 1)
+            for (int k = pc.c; k < g.np; k += pc.T) {
+              if (i == 0) x.ur[idx_r(g, 0, j, k)] = 0.0;
+              if (i == g.nr - 1) x.ur[idx_r(g, g.nr, j, k)] = 0.0;
+              if (j == 0) x.ut[idx_t(g, i, 0, k)] = 0.0;
+              if (j == g.nt - 1) x.ut[idx_t(g, i, g.nt, k)] = 0.0;
+            }
+          if (!CYC && pc.c == 0) x.uf[idx_f(g, i, j, 0)] = 0.0;
+        }
+      }
+      phi_block_fast<PM, CYC, PT>(a, w, lds);
+      return;
+    }
+  }
+  if constexpr (PART != 0) {
+    if (COMB && w < nbw) return;
+    phi_scalar_fast<PM, CYC, PT>(a, PART == 2 || COMB ? w - nbw : w, lds);
+  }
+}
+
+template <int PM, int PART, bool CYC, bool PT>
+__global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_phi_fast(PassArgs a) {
+  extern __shared__ double lds[];
+  phi_fast_body<PM, PART, CYC, PT, false>(a, PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x, lds);
+}
+template <int PM, int PART, bool CYC>
+__global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_phi_fastB(PassArgs a, Batch bt) {
+  extern __shared__ double lds[];
+  const int mb = batch_member(bt, blockIdx.x);
+  phi_fast_body<PM, PART, CYC, false, true>(batch_args(bt, mb), blockIdx.x - bt.woff[mb], lds);
+}
+
 // one workgroup per (i, j): block line (i, j), u_r line on r-face i (i >= 1),
 // u_theta line on theta-face j (j >= 1).  Flat grid of nr * nt workgroups per
 // grid; one grid or a batch of grids.  The workgroup may be wider than the
@@ -669,35 +1174,6 @@ __global__ void __launch_bounds__(256) DSW_OCC(DSW_WAVES_PHI) k_phi_partP(PassAr
   phi_body<PM, false, PART, false, 0, false, true>(a, w, lds);
 }
 
-// one grid, every slot: the boundary ring's slots (MAP 2, the general
-// source) in workgroups [0, ring), then the interior slots (MAP 1, the
-// interior source; P: periodic phi); PT: perturbation-pressure form.  One
-// launch instead of one per slot set: the ring's few hundred workgroups fill
-// the interior launch's tail instead of running as a launch of their own.
-template <int PM, int PART, bool P, bool PT>
-__global__ void __launch_bounds__(256) DSW_OCC(DSW_WAVES_PHI) k_phi_partC(PassArgs a) {
-  extern __shared__ double lds[];
-  const unsigned w = PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
-  const unsigned ring = 2u * (unsigned)a.g.nr + 2u * (unsigned)(a.g.nt - 2);
-  if (w < ring) phi_body<PM, false, PART, false, 2, false, PT>(a, w, lds);
-  else phi_body<PM, false, PART, false, 1, P, PT>(a, w - ring, lds);
-}
-
-// a batch of grids with an interior (P: periodic phi): member m's workgroups
-// take its boundary ring's slots first, then its interior slots, as
-// k_phi_partC does for one grid
-template <int PM, int PART, bool P>
-__global__ void __launch_bounds__(256) DSW_OCC(DSW_WAVES_PHI) k_phi_partCB(PassArgs a, Batch bt) {
-  extern __shared__ double lds[];
-  const unsigned w = PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
-  const int mb = batch_member(bt, w);
-  const PassArgs &am = batch_args(bt, mb);
-  const unsigned wl = w - bt.woff[mb];
-  const unsigned ring = 2u * (unsigned)am.g.nr + 2u * (unsigned)(am.g.nt - 2);
-  if (wl < ring) phi_body<PM, false, PART, false, 2>(am, wl, lds);
-  else phi_body<PM, false, PART, false, 1, P>(am, wl - ring, lds);
-}
-
 // forced split step, one grid: as the plain sweep, all three lines of a slot
 // in one launch, or from PHI_SPLIT_SLOTS slots on the block lines and the
 // scalar lines as two
@@ -755,33 +1231,21 @@ size_t phi_part_lds(const Geo &g, int pm) {
 // 0.31 ms on 8192 slots of 256 cells).
 constexpr unsigned PHI_SPLIT_SLOTS = 16384;
 
-// Whether a split pass of one grid takes the interior slots with the
-// interior source: the slots' 32-bit indices reach, and the grid has an
-// interior.  The interior source drops the ghost code across r and theta
-// boundaries and forms 32-bit indices: measured on the 512 x 256 x 128
-// sphere, the phi pass 1.83 -> 1.78 ms, results bitwise unchanged.
-bool phi_interior_split(const Geo &g) {
-  return g.nr >= 3 && g.nt >= 3 && (long)(g.nr + 1) * (g.nt + 1) * g.npf < 0x7fffffffL;
+// Workgroup width of the fast kernels: the narrowest whose lanes the slots'
+// chunks fill to within 5 % of what any width reaches (narrower workgroups
+// wait less at their barriers; 34 chunks fill 238 of 256 lanes but 34 of 64).
+unsigned phi_fast_threads(const Geo &g, int pm) {
+  const unsigned T = (unsigned)phi_chunks(g.np, g.periodic, pm);
+  auto use = [&](unsigned bs) { return (double)(bs / T * T) / bs; };
+  const double best = std::max(use(64), std::max(use(128), use(256)));
+  for (const unsigned bs : {64u, 128u})
+    if (use(bs) >= 0.95 * best) return bs;
+  return 256;
 }
 
-// one grid, split: the block lines of every slot (ring, then interior), then
-// their scalar lines (at the interior slots both lines of a slot at once: 10
-// doubles of LDS per thread)
-template <int PM, bool PT>
-static void launch_phi_in(const PassArgs &a, unsigned threads, size_t lds, size_t lds_s, hipStream_t st) {
-  const Geo &g = a.g;
-  (void)lds_s;
-  const size_t lds_s2 = sizeof(double) * 10 * (size_t)threads;
-  const dim3 gall((unsigned)(g.nr - 2) * (unsigned)(g.nt - 2) + 2u * (unsigned)g.nr + 2u * (unsigned)(g.nt - 2));
-  const dim3 bl(threads);
-  if (g.periodic) {
-    hipLaunchKernelGGL((k_phi_partC<PM, 0, true, PT>), gall, bl, lds, st, a);
-    hipLaunchKernelGGL((k_phi_partC<PM, 1, true, PT>), gall, bl, lds_s2, st, a);
-  } else {
-    hipLaunchKernelGGL((k_phi_partC<PM, 0, false, PT>), gall, bl, lds, st, a);
-    hipLaunchKernelGGL((k_phi_partC<PM, 1, false, PT>), gall, bl, lds_s2, st, a);
-  }
-}
+unsigned phi_fast_blocks(const Geo &g, int pm, unsigned threads) { return 2 * phi_fast_wgs(g, pm, threads); }
+
+size_t phi_fast_lds(unsigned threads) { return sizeof(double) * SEP_REC * (size_t)threads; }
 
 // the block lines, then the scalar lines (their LDS: the exchange and
 // reduction arrays, 5 doubles per chunk, or the staged line, PM per chunk),
@@ -790,11 +1254,6 @@ void launch_phi_pass(int pm, const PassArgs &a, const Batch &b, unsigned blocks,
                      size_t lds, hipStream_t st) {
   const dim3 gr(blocks), bl(threads);
   const size_t lds_s = sizeof(double) * (size_t)(pm > 5 ? pm : 5) * threads;
-  if (!b.tab && blocks >= PHI_SPLIT_SLOTS && phi_interior_split(a.g)) {
-    if (pm == 2) launch_phi_in<2, false>(a, threads, lds, lds_s, st);
-    else launch_phi_in<4, false>(a, threads, lds, lds_s, st);
-    return;
-  }
   if (blocks < PHI_SPLIT_SLOTS) {
     if (b.tab) {
       if (pm == 2) hipLaunchKernelGGL((k_phi_part<2, true, 2>), gr, bl, lds, st, a, b);
@@ -824,43 +1283,59 @@ void launch_phi_pass(int pm, const PassArgs &a, const Batch &b, unsigned blocks,
   }
 }
 
-template <int PM, bool P>
-static void launch_phi_cb(const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads, size_t lds,
-                          hipStream_t st) {
-  const dim3 gr(blocks), bl(threads);
-  if (blocks < PHI_SPLIT_SLOTS) {
-    hipLaunchKernelGGL((k_phi_partCB<PM, 2, P>), gr, bl, lds, st, a, b);
-    return;
+// From this many workgroups on, the block and the scalar lines run as two
+// launches (the scalar lines need half of the block lines' registers and a
+// third of their LDS); below it one launch runs both side by side.
+constexpr unsigned PHI_FAST_SPLIT = 1024;
+
+template <int PM, bool CYC, bool PT>
+static void launch_phi_fast(const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads, size_t lds,
+                            hipStream_t st) {
+  const size_t lds_s = sizeof(double) * 8 * (size_t)threads;
+  const dim3 gr(blocks), half(blocks / 2), bl(threads);
+  if (b.tab) {
+    if constexpr (!PT) {
+      if (blocks < PHI_FAST_SPLIT) {
+        hipLaunchKernelGGL((k_phi_fastB<PM, 2, CYC>), gr, bl, lds, st, a, b);
+      } else {
+        hipLaunchKernelGGL((k_phi_fastB<PM, 0, CYC>), gr, bl, lds, st, a, b);
+        hipLaunchKernelGGL((k_phi_fastB<PM, 1, CYC>), gr, bl, lds_s, st, a, b);
+      }
+    }
+  } else if (blocks < PHI_FAST_SPLIT) {
+    hipLaunchKernelGGL((k_phi_fast<PM, 2, CYC, PT>), gr, bl, lds, st, a);
+  } else {
+    hipLaunchKernelGGL((k_phi_fast<PM, 0, CYC, PT>), half, bl, lds, st, a);
+    hipLaunchKernelGGL((k_phi_fast<PM, 1, CYC, PT>), half, bl, lds_s, st, a);
   }
-  const size_t lds_s2 = sizeof(double) * 10 * (size_t)threads;  // both scalar lines of a slot at once
-  hipLaunchKernelGGL((k_phi_partCB<PM, 0, P>), gr, bl, lds, st, a, b);
-  hipLaunchKernelGGL((k_phi_partCB<PM, 1, P>), gr, bl, lds_s2, st, a, b);
+}
+
+template <bool PT>
+static void launch_phi_fast_pm(int pm, bool periodic, const PassArgs &a, const Batch &b, unsigned blocks,
+                               unsigned threads, size_t lds, hipStream_t st) {
+  if (pm == 2) {
+    if (periodic) launch_phi_fast<2, true, PT>(a, b, blocks, threads, lds, st);
+    else launch_phi_fast<2, false, PT>(a, b, blocks, threads, lds, st);
+  } else {
+    if (periodic) launch_phi_fast<4, true, PT>(a, b, blocks, threads, lds, st);
+    else launch_phi_fast<4, false, PT>(a, b, blocks, threads, lds, st);
+  }
 }
 
 void launch_phi_pass_c(int pm, bool periodic, const PassArgs &a, const Batch &b, unsigned blocks,
                        unsigned threads, size_t lds, hipStream_t st) {
-  if (!b.tab) {  // one grid: as any partitioned phi pass
-    launch_phi_pass(pm, a, b, blocks, threads, lds, st);
-    return;
-  }
-  if (pm == 2) {
-    if (periodic) launch_phi_cb<2, true>(a, b, blocks, threads, lds, st);
-    else launch_phi_cb<2, false>(a, b, blocks, threads, lds, st);
-  } else {
-    if (periodic) launch_phi_cb<4, true>(a, b, blocks, threads, lds, st);
-    else launch_phi_cb<4, false>(a, b, blocks, threads, lds, st);
-  }
+  launch_phi_fast_pm<false>(pm, periodic, a, b, blocks, threads, lds, st);
+}
+
+void launch_phi_pert_c(int pm, bool periodic, const PassArgs &a, unsigned blocks, unsigned threads, size_t lds,
+                       hipStream_t st) {
+  launch_phi_fast_pm<true>(pm, periodic, a, Batch{nullptr, nullptr, 0}, blocks, threads, lds, st);
 }
 
 void launch_phi_pert(int pm, const PassArgs &a, unsigned blocks, unsigned threads, size_t lds,
                      hipStream_t st) {
   const dim3 gr(blocks), bl(threads);
   const size_t lds_s = sizeof(double) * (size_t)(pm > 5 ? pm : 5) * threads;
-  if (blocks >= PHI_SPLIT_SLOTS && phi_interior_split(a.g)) {
-    if (pm == 2) launch_phi_in<2, true>(a, threads, lds, lds_s, st);
-    else launch_phi_in<4, true>(a, threads, lds, lds_s, st);
-    return;
-  }
   if (blocks < PHI_SPLIT_SLOTS) {
     if (pm == 2) hipLaunchKernelGGL((k_phi_partP<2, 2>), gr, bl, lds, st, a);
     else hipLaunchKernelGGL((k_phi_partP<4, 2>), gr, bl, lds, st, a);

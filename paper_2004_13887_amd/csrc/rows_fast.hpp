@@ -28,11 +28,6 @@ __device__ __forceinline__ void sto(double *base, unsigned off, double v) {
   *(double *)((char *)base + off) = v;
 }
 
-// whether every array's byte offsets fit 32 bits
-__host__ __device__ inline bool off32_ok(const Geo &g) {
-  return (long)(g.nr + 1) * (g.nt + 1) * (g.np + 1) < (1L << 29);
-}
-
 __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 // One block row, scaled by tau/2 with the identity added, structural

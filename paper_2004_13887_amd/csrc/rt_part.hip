@@ -626,34 +626,37 @@ __device__ __forceinline__ void rt_scalar_fast(const PassArgs &a, int fam, unsig
     ra[q] = fma_(-rc[q], ra[q + 1], -ra[q]);
     rc[q] = -rc[q] * rc[q + 1];
   }
-  double *rec = lds + 4 * (size_t)t;
-  if (c < T) { rec[0] = rr[0]; rec[1] = ra[0]; rec[2] = rc[0]; }
+  // exchange and reduction: quantity q at ex[q * blockDim + t], so that a
+  // wave's accesses are contiguous
+  const int nth = (int)blockDim.x;
+  double *ex = lds + t;
+  if (c < T) { ex[0] = rr[0]; ex[nth] = ra[0]; ex[2 * nth] = rc[0]; }
   __syncthreads();
-  const double *nx = lds + 4 * (size_t)(cc < T - 1 ? t + L : min(t, T * L - 1));
+  const double *nx = lds + (cc < T - 1 ? t + L : min(t, T * L - 1));
   double A = ra[PM - 1] * ra[PM - 2];
-  double B = fma_(rc[PM - 1], nx[1], fma_(ra[PM - 1], rc[PM - 2], rb[PM - 1]));
-  double C = rc[PM - 1] * nx[2];
+  double B = fma_(rc[PM - 1], nx[nth], fma_(ra[PM - 1], rc[PM - 2], rb[PM - 1]));
+  double C = rc[PM - 1] * nx[2 * nth];
   double r = fma_(-rc[PM - 1], nx[0], fma_(-ra[PM - 1], rr[PM - 2], rr[PM - 1]));
   for (int h = 1; h < T; h *= 2) {
     const double ib = rcp_nr(B);
     sing |= !(B != 0.0);
     __syncthreads();
-    if (c < T) { rec[0] = A * ib; rec[1] = C * ib; rec[2] = r * ib; }
+    if (c < T) { ex[0] = A * ib; ex[nth] = C * ib; ex[2 * nth] = r * ib; }
     __syncthreads();
-    const double *lo = lds + 4 * (size_t)(max(cc - h, 0) * L + l), *hi = lds + 4 * (size_t)(min(cc + h, T - 1) * L + l);
-    B = fma_(-C, hi[0], fma_(-A, lo[1], B));
-    r = fma_(-C, hi[2], fma_(-A, lo[2], r));
+    const double *lo = lds + max(cc - h, 0) * L + l, *hi = lds + min(cc + h, T - 1) * L + l;
+    B = fma_(-C, hi[0], fma_(-A, lo[nth], B));
+    r = fma_(-C, hi[2 * nth], fma_(-A, lo[2 * nth], r));
     A = -A * lo[0];
-    C = -C * hi[1];
+    C = -C * hi[nth];
   }
   sing |= !(B != 0.0);
   const double xs = r * rcp_nr(B);
   if (act && sing) a.status[ST_SINGULAR] = 1;
   __syncthreads();
-  if (c < T) rec[0] = xs;
+  if (c < T) ex[0] = xs;
   __syncthreads();
   if (!act) return;
-  const double xl = c > 0 ? lds[4 * (size_t)(t - L)] : 0.0;
+  const double xl = c > 0 ? lds[t - L] : 0.0;
 #pragma unroll
   for (int q = 0; q < PM; q++) {
     const int s = s0 + q;
