@@ -871,10 +871,15 @@ extern "C" int dsw_split_step_forced(dsw_grid *G, const dsw_fields *Un, dsw_fiel
       }
       if (d < 2) {
         const unsigned bs = (unsigned)G->cfg.sweep_bs[d];
-        if (rt_kind(g, G->cfg, d) == (d == 0 ? PK_SW0P : PK_SW1P)) launch_rt_forced(d, 4, p.a, bs, st);
-        else launch_sweep2_forced(d, p.a, sweep2_blocks(g, d, bs), bs, st);
+        emit_sweep(G, p, [&](const Pass &q) {
+          if (q.kind == PK_SW0P || q.kind == PK_SW1P) launch_rt_forced(d, 4, q.a, bs, st);
+          else if (q.kind == PK_SW0S || q.kind == PK_SW1S) launch_single(G, q, st);  // no wall data
+          else if (q.kind == PK_SW0B || q.kind == PK_SW1B)
+            launch_sweep2_forced(d, q.a, sweep2_block_blocks(g, d, bs), bs, st);
+          else launch_sweep2_forced(d, q.a, sweep2_blocks(g, d, bs), bs, st);
+        });
       } else {
-        launch_phi_forced(pm, p.a, (unsigned)g.nr * (unsigned)g.nt, phi_part_threads(g, pm), phi_part_lds(g, pm), st);
+        launch_phi_forced(pm, p.a, st);
       }
     }
     if (it == 0) {

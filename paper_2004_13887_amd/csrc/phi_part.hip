@@ -153,56 +153,6 @@ __device__ __forceinline__ void pcr_scalar(int t, int T, int cyc, double &A, dou
   }
 }
 
-// Two independent scalar systems of the same size T, reduced side by side:
-// the steps of pcr_scalar for each, under one set of barriers.  LDS: system
-// f at lds + 4 T f (8 T doubles).
-__device__ __forceinline__ void pcr_scalar2(int t, int T, int cyc, double *A, double *B, double *C, double *r,
-                                            double *lds, double *x, int *status) {
-  const bool act = t < T;
-  for (int h = 1; h < T; h *= 2) {
-    if (act) {
-#pragma unroll
-      for (int f = 0; f < 2; f++) {
-        double *L = lds + 4 * T * f;
-        L[t] = A[f]; L[T + t] = C[f]; L[2 * T + t] = r[f]; L[3 * T + t] = B[f];
-      }
-    }
-    __syncthreads();
-    if (act) {
-      int lo = t - h, hi = t + h;
-      bool has_lo = lo >= 0, has_hi = hi < T;
-      if (cyc) { lo &= T - 1; hi &= T - 1; has_lo = has_hi = true; }  // cyclic: T a power of two
-#pragma unroll
-      for (int f = 0; f < 2; f++) {
-        const double *sA = lds + 4 * T * f, *sC = sA + T, *sR = sA + 2 * T, *sB = sA + 3 * T;
-        double nA = 0.0, nC = 0.0, nB = B[f], nr = r[f];
-        if (has_lo) {
-          const double al = -A[f] * rcp_nr(sB[lo]);
-          nA = al * sA[lo];
-          nB += al * sC[lo];
-          nr += al * sR[lo];
-        }
-        if (has_hi) {
-          const double be = -C[f] * rcp_nr(sB[hi]);
-          nC = be * sC[hi];
-          nB += be * sA[hi];
-          nr += be * sR[hi];
-        }
-        A[f] = nA; B[f] = nB; C[f] = nC; r[f] = nr;
-      }
-    }
-    __syncthreads();
-  }
-  if (act) {
-#pragma unroll
-    for (int f = 0; f < 2; f++) {
-      const double S = A[f] + B[f] + C[f];
-      if (!(S != 0.0)) status[ST_SINGULAR] = 1;
-      x[f] = r[f] * rcp_nr(S);
-    }
-  }
-}
-
 // ------------------------------------------------------------ block line --
 template <int PM, bool TR, class US>
 __device__ __forceinline__ void part_block_line(const Geo &g, const Mat &m, const US &u, const Fields &rhs,
@@ -484,112 +434,6 @@ __device__ __forceinline__ void part_scalar_line(const Geo &g, const Mat &m, con
   __syncthreads();
 }
 
-// Both scalar lines of slot (i, j) at once (u_r on r-face i, u_theta on
-// theta-face j; both must exist, as at the interior slots): the steps of
-// part_scalar_line for each line, with the rows of both lines assembled
-// before either is eliminated and one set of barriers for the two
-// reductions, so that each line's load and barrier latency overlaps the
-// other's.  LDS: 10 doubles per chunk (line f's exchange and reduction at
-// 4 T f, its separators at 8 T + T f; the staged lines at N f).
-template <int PM, class US>
-__device__ __forceinline__ void part_scalar_lines2(const Geo &g, const Mat &m, const US &u, const Fields &rhs,
-                                                   const Out &o, int i, int j, double hs, double *lds,
-                                                   int *status) {
-  const int N = g.np, cyc = g.periodic, T = phi_chunks(N, cyc, PM);
-  const int t = threadIdx.x;
-  const bool act = t < T;
-  int a0, len;
-  phi_chunk<PM>(N, cyc, T, t, a0, len);
-  double Cm[2][PM - 1], Em[2][PM - 1], Ym[2][PM - 1];
-  SRow S[2] = {{0, 1, 0, 0}, {0, 1, 0, 0}};
-  {
-    long xi;
-    double *arr;
-    const auto row0 = [&](int s, SRow &Q) { scalar_row<2, 0>(g, m, u, rhs, i, j, s, N, cyc, hs, Q, xi, arr); };
-    const auto row1 = [&](int s, SRow &Q) { scalar_row<2, 1>(g, m, u, rhs, i, j, s, N, cyc, hs, Q, xi, arr); };
-    const bool s0 = scalar_chunk_fwd<PM>(row0, a0, len, N, Cm[0], Em[0], Ym[0], S[0]);
-    const bool s1 = scalar_chunk_fwd<PM>(row1, a0, len, N, Cm[1], Em[1], Ym[1], S[1]);
-    if (s0 || s1) status[ST_SINGULAR] = 1;
-  }
-#pragma unroll
-  for (int f = 0; f < 2; f++) {
-#pragma unroll
-    for (int q = PM - 2; q >= 0; q--) {
-      if (q == len - 2) { Em[f][q] = -Em[f][q]; Cm[f][q] = -Cm[f][q]; }
-      else if (q < len - 2) {
-        Ym[f][q] -= Cm[f][q] * Ym[f][q + 1];
-        Em[f][q] = -Em[f][q] - Cm[f][q] * Em[f][q + 1];
-        Cm[f][q] = -Cm[f][q] * Cm[f][q + 1];
-      }
-    }
-  }
-  if (act) {
-#pragma unroll
-    for (int f = 0; f < 2; f++) {
-      double *sG = lds + 4 * T * f, *sV = sG + T, *sW = sG + 2 * T, *sL = sG + 3 * T;
-      sL[t] = (double)len;
-      if (len >= 2) { sG[t] = Ym[f][0]; sV[t] = Em[f][0]; sW[t] = Cm[f][0]; }
-    }
-  }
-  __syncthreads();
-  double A[2] = {0.0, 0.0}, B[2] = {1.0, 1.0}, C[2] = {0.0, 0.0}, r[2] = {0.0, 0.0};
-  if (act) {
-    int nt_ = t + 1;
-    bool has_next = nt_ < T;
-    if (cyc) { nt_ &= T - 1; has_next = true; }
-#pragma unroll
-    for (int f = 0; f < 2; f++) {
-      const double *sG = lds + 4 * T * f, *sV = sG + T, *sW = sG + 2 * T, *sL = sG + 3 * T;
-      const int nlen = has_next ? (int)sL[nt_] : 0;
-      double Gl = 0.0, Vl = 0.0, Wl = 0.0;
-#pragma unroll
-      for (int q = 0; q < PM - 1; q++)
-        if (q == len - 2) { Gl = Ym[f][q]; Vl = Em[f][q]; Wl = Cm[f][q]; }
-      B[f] = S[f].b;
-      r[f] = S[f].r;
-      if (len >= 2) { A[f] = S[f].a * Vl; B[f] += S[f].a * Wl; r[f] -= S[f].a * Gl; }
-      else A[f] = S[f].a;
-      if (nlen >= 2) { B[f] += S[f].c * sV[nt_]; C[f] = S[f].c * sW[nt_]; r[f] -= S[f].c * sG[nt_]; }
-      else C[f] = S[f].c;
-    }
-  }
-  __syncthreads();
-  double xs[2] = {0.0, 0.0};
-  pcr_scalar2(t, T, cyc, A, B, C, r, lds, xs, status);
-  if (act) {
-    lds[8 * T + t] = xs[0];
-    lds[9 * T + t] = xs[1];
-  }
-  __syncthreads();
-  double val[2][PM];
-  if (act) {
-#pragma unroll
-    for (int f = 0; f < 2; f++) {
-      double xl = 0.0;
-      if (t > 0 || cyc) xl = lds[(8 + f) * T + (t > 0 ? t - 1 : T - 1)];
-#pragma unroll
-      for (int q = 0; q < PM - 1; q++)
-        if (q < len - 1) val[f][q] = Ym[f][q] + Em[f][q] * xl + Cm[f][q] * xs[f];
-    }
-  }
-  __syncthreads(); // the LDS is free: stage both lines, store them contiguously
-  if (act) {
-#pragma unroll
-    for (int f = 0; f < 2; f++) {
-#pragma unroll
-      for (int q = 0; q < PM - 1; q++)
-        if (q < len - 1) lds[f * N + a0 + q] = val[f][q];
-      lds[f * N + a0 + len - 1] = xs[f];
-    }
-  }
-  __syncthreads();
-  for (int s = t; s < N; s += blockDim.x) {
-    put(o, F_UR, idx_r(g, i, j, s), lds[s]);
-    put(o, F_UT, idx_t(g, i, j, s), lds[N + s]);
-  }
-  __syncthreads();
-}
-
 // ---------------------------------------- plain and perturbation sweeps --
 // A workgroup takes L = blockDim / T neighbouring slots; thread t = l T + c
 // holds chunk c of slot l's lines.  Ghosts across r and theta are a clamped
@@ -634,9 +478,10 @@ __device__ __forceinline__ unsigned phi_pos(const Geo &g, int s) {
   return 8u * (unsigned)s;
 }
 
-// The block line of every slot of the workgroup.  LDS SEP_REC doubles per
-// thread.
-template <int PM, bool CYC, bool PT>
+// The block line of every slot of the workgroup.  W: a forced pass, whose
+// ghosts across a wall are 2 g - u (the scalar lines read none); PT:
+// perturbation-pressure form.  LDS SEP_REC doubles per thread.
+template <int PM, bool CYC, bool W, bool PT>
 __device__ __forceinline__ void phi_block_fast(const PassArgs &a, unsigned w, double *lds) {
   const Geo &g = a.g;
   const Mat &m = a.m;
@@ -677,13 +522,34 @@ __device__ __forceinline__ void phi_block_fast(const PassArgs &a, unsigned w, do
     for (int q = 0; q <= PM; q++) wf[q] = fma_(kjp, ldo(u_f, ojp + fpos[q]), wf[q]);
 #pragma unroll
     for (int q = 0; q <= PM; q++) wf[q] = fma_(-kjm, ldo(u_f, ojm + fpos[q]), wf[q]);
+    if constexpr (W) {
+      const Wall &wl = a.wall;
+      const unsigned fj = (unsigned)j * F8, fi = (unsigned)i * F8;
+      auto add = [&](const double *v, unsigned o, double s) {
+        if (!v) return;
+#pragma unroll
+        for (int q = 0; q <= PM; q++) wf[q] = fma_(s, ldo(v, o + fpos[q]), wf[q]);
+      };
+      if (i == 0) add(wl.uf_r1, fj, -2.0 * kr);
+      if (i == g.nr - 1) add(wl.uf_r2, fj, 2.0 * kr);
+      if (j == 0 && !g.pole_lo) add(wl.uf_t1, fi, -2.0 * kt);
+      if (j == g.nt - 1 && !g.pole_hi) add(wl.uf_t2, fi, 2.0 * kt);
+    }
 #pragma unroll
     for (int q = 0; q < PM + 2; q++) {
       const double r0 = ldo(u_r, oC + pos[q]), r1 = ldo(u_r, oC + pl + pos[q]);
       const double t0 = ldo(u_t, oT + pos[q]), t1 = ldo(u_t, oT + N8 + pos[q]);
       const double ur = 0.5 * (r0 + r1), ut = 0.5 * (t0 + t1);
       v[q] = fma_(ut, ct, ur);
-      if (!CYC && (s0 + q - 1 < 0 || s0 + q - 1 >= np)) v[q] = -v[q];  // no slip
+      if (!CYC && (s0 + q - 1 < 0 || s0 + q - 1 >= np)) {  // no slip
+        v[q] = -v[q];
+        if constexpr (W) {
+          const bool lo = s0 + q - 1 < 0;
+          const double *wr = lo ? a.wall.ur_p1 : a.wall.ur_p2, *wt = lo ? a.wall.ut_p1 : a.wall.ut_p2;
+          const int wi = i * g.nt + j, wj = i * (g.nt + 1) + j;
+          v[q] += wallv(wr, wi) + wallv(wr, wi + g.nt) + ct * (wallv(wt, wj) + wallv(wt, wj + 1));
+        }
+      }
       if (q >= 1 && q <= PM) e[q - 1] = (r1 - r0) * g.idr + fma_(t1 - t0, g.idt, ur) * ir;
     }
 #pragma unroll
@@ -1039,7 +905,7 @@ __host__ __device__ inline unsigned phi_fast_wgs(const Geo &g, int pm, unsigned 
 // PART 0: the block lines; 1: the scalar lines; 2: both, the block lines in the
 // first half of the workgroups.  COMB: workgroups numbered as for PART 2
 // whatever the part (a batched launch's member table counts both halves).
-template <int PM, int PART, bool CYC, bool PT, bool COMB>
+template <int PM, int PART, bool CYC, bool W, bool PT, bool COMB>
 __device__ __forceinline__ void phi_fast_body(const PassArgs &a, unsigned w, double *lds) {
   const Geo &g = a.g;
   const unsigned nbw = PART == 2 || COMB ? phi_fast_wgs(g, PM, blockDim.x) : 0u;
@@ -1061,7 +927,7 @@ __device__ __forceinline__ void phi_fast_body(const PassArgs &a, unsigned w, dou
           if (!CYC && pc.c == 0) x.uf[idx_f(g, i, j, 0)] = 0.0;
         }
       }
-      phi_block_fast<PM, CYC, PT>(a, w, lds);
+      phi_block_fast<PM, CYC, W, PT>(a, w, lds);
       return;
     }
   }
@@ -1071,51 +937,28 @@ __device__ __forceinline__ void phi_fast_body(const PassArgs &a, unsigned w, dou
   }
 }
 
-template <int PM, int PART, bool CYC, bool PT>
+template <int PM, int PART, bool CYC, bool W, bool PT>
 __global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_phi_fast(PassArgs a) {
   extern __shared__ double lds[];
-  phi_fast_body<PM, PART, CYC, PT, false>(a, PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x, lds);
+  phi_fast_body<PM, PART, CYC, W, PT, false>(a, PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x, lds);
 }
 template <int PM, int PART, bool CYC>
 __global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_phi_fastB(PassArgs a, Batch bt) {
   extern __shared__ double lds[];
   const int mb = batch_member(bt, blockIdx.x);
-  phi_fast_body<PM, PART, CYC, false, true>(batch_args(bt, mb), blockIdx.x - bt.woff[mb], lds);
+  phi_fast_body<PM, PART, CYC, false, false, true>(batch_args(bt, mb), blockIdx.x - bt.woff[mb], lds);
 }
 
 // one workgroup per (i, j): block line (i, j), u_r line on r-face i (i >= 1),
 // u_theta line on theta-face j (j >= 1).  Flat grid of nr * nt workgroups per
 // grid; one grid or a batch of grids.  The workgroup may be wider than the
 // chunk count: threads past it only join the barriers.  PART 0: the block
-// line; 1: the two scalar lines; 2: all three.  On large launches the
-// forward sweep runs parts 0 and 1 as two launches: the scalar lines need far
-// fewer registers (about 55 against 256) and on their own run at a much
-// higher occupancy; on small ones the second launch costs more than that
-// gains.
-// MAP: 0 every slot, w = i * nt + j; 1 the interior slots
-// (1 <= i <= nr - 2, 1 <= j <= nt - 2), whose rows read no ghost across an
-// r or theta boundary, with the interior source (32-bit indices, ghosts in
-// phi only; P: periodic phi); 2 the other slots, with the general source.
-template <int PM, bool TR, int PART = 2, bool W = false, int MAP = 0, bool P = false, bool PT = false>
+// line; 1: the two scalar lines (which need far fewer registers).
+// W: forced pass (wall velocities); PT: perturbation-pressure form.
+template <int PM, bool TR, int PART, bool W = false, bool PT = false>
 __device__ __forceinline__ void phi_body(const PassArgs &a, unsigned w, double *lds) {
   const Geo &g = a.g;
-  int i, j;
-  if constexpr (MAP == 1) {
-    j = 1 + (int)(w % (unsigned)(g.nt - 2));
-    i = 1 + (int)(w / (unsigned)(g.nt - 2));
-  } else if constexpr (MAP == 2) {
-    if (w < 2u * (unsigned)g.nr) {
-      i = (int)(w >> 1);
-      j = (w & 1u) ? g.nt - 1 : 0;
-    } else {
-      const unsigned w2 = w - 2u * (unsigned)g.nr;
-      j = 1 + (int)(w2 >> 1);
-      i = (w2 & 1u) ? g.nr - 1 : 0;
-    }
-  } else {
-    j = (int)(w % g.nt);
-    i = (int)(w / g.nt);
-  }
+  const int j = (int)(w % g.nt), i = (int)(w / g.nt);
   const int t = threadIdx.x;
   const Out &o = a.o;
   if (PART != 1 && o.mode == 0) { // boundary-normal faces of x that no phi line owns
@@ -1128,32 +971,18 @@ __device__ __forceinline__ void phi_body(const PassArgs &a, unsigned w, double *
     }
     if (!g.periodic && t == 0) x.uf[idx_f(g, i, j, 0)] = 0.0;
   }
-  if constexpr (MAP == 1) {
-    const auto u = SrcSelIn<W, PT, P>::get(a);
-    if (PART != 1) part_block_line<PM, TR>(g, a.m, u, a.rhs, o, i, j, a.tau, lds, a.status);
-    if (PART != 0) {
-      if constexpr (TR) {
-        part_scalar_line<PM, 0, TR>(g, a.m, u, a.rhs, o, i, j, a.tau, lds, a.status);
-        part_scalar_line<PM, 1, TR>(g, a.m, u, a.rhs, o, i, j, a.tau, lds, a.status);
-      } else {
-        part_scalar_lines2<PM>(g, a.m, u, a.rhs, o, i, j, a.tau, lds, a.status);
-      }
-    }
-  } else {
-    // W: forced pass (wall velocities); PT: perturbation-pressure form
-    decltype(auto) u = SrcSel<W, PT>::get(a);
-    if (PART != 1) part_block_line<PM, TR>(g, a.m, u, a.rhs, o, i, j, a.tau, lds, a.status);
-    if (PART != 0) {
-      if (i >= 1) part_scalar_line<PM, 0, TR>(g, a.m, u, a.rhs, o, i, j, a.tau, lds, a.status);
-      if (j >= 1) part_scalar_line<PM, 1, TR>(g, a.m, u, a.rhs, o, i, j, a.tau, lds, a.status);
-    }
+  decltype(auto) u = SrcSel<W, PT>::get(a);
+  if (PART != 1) part_block_line<PM, TR>(g, a.m, u, a.rhs, o, i, j, a.tau, lds, a.status);
+  if (PART != 0) {
+    if (i >= 1) part_scalar_line<PM, 0, TR>(g, a.m, u, a.rhs, o, i, j, a.tau, lds, a.status);
+    if (j >= 1) part_scalar_line<PM, 1, TR>(g, a.m, u, a.rhs, o, i, j, a.tau, lds, a.status);
   }
 }
 
-// The scalar lines of slot (i, j) read the cells of slots (i - 1, j) and
-// (i, j - 1) too: the scalar launch numbers its slots XCD-contiguously.
-// Measured on the global grid: the phi pass 1.93 -> 1.87 ms; renumbering the
-// block launch as well is slower.
+// Grids whose byte offsets outgrow 32 bits (one grid or a batch; PT:
+// perturbation-pressure form, one grid).  The scalar lines of slot (i, j) read
+// the cells of slots (i - 1, j) and (i, j - 1) too: the scalar launch numbers
+// its slots XCD-contiguously.
 template <int PM, bool B, int PART>
 __global__ void __launch_bounds__(256) DSW_OCC(DSW_WAVES_PHI) k_phi_part(PassArgs a, Batch bt) {
   extern __shared__ double lds[];
@@ -1165,22 +994,17 @@ __global__ void __launch_bounds__(256) DSW_OCC(DSW_WAVES_PHI) k_phi_part(PassArg
     phi_body<PM, false, PART>(a, w, lds);
   }
 }
-
-// perturbation-pressure form, one grid (as the plain pass of one grid)
 template <int PM, int PART>
 __global__ void __launch_bounds__(256) DSW_OCC(DSW_WAVES_PHI) k_phi_partP(PassArgs a) {
   extern __shared__ double lds[];
-  const unsigned w = PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
-  phi_body<PM, false, PART, false, 0, false, true>(a, w, lds);
+  phi_body<PM, false, PART, false, true>(a, PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x, lds);
 }
 
-// forced split step, one grid: as the plain sweep, all three lines of a slot
-// in one launch, or from PHI_SPLIT_SLOTS slots on the block lines and the
-// scalar lines as two
-template <int PM, int PART, int MAP, bool P = false>
+// forced split step, one grid
+template <int PM, int PART>
 __global__ void __launch_bounds__(256) DSW_OCC(DSW_WAVES_PHI) k_phi_partF(PassArgs a) {
   extern __shared__ double lds[];
-  phi_body<PM, false, PART, true, MAP, P>(a, blockIdx.x, lds);
+  phi_body<PM, false, PART, true>(a, blockIdx.x, lds);
 }
 
 // transposed systems (adjoint), one grid: each chunk walks the rows of the
@@ -1226,11 +1050,6 @@ size_t phi_part_lds(const Geo &g, int pm) {
   return sizeof(double) * 24 * (size_t)T;
 }
 
-// From this many line slots on, the block and the scalar lines run as two
-// launches (measured: 1.99 -> 1.93 ms on 32768 slots of 512 cells, 0.27 ->
-// 0.31 ms on 8192 slots of 256 cells).
-constexpr unsigned PHI_SPLIT_SLOTS = 16384;
-
 // Workgroup width of the fast kernels: the narrowest whose lanes the slots'
 // chunks fill to within 5 % of what any width reaches (narrower workgroups
 // wait less at their barriers; 34 chunks fill 238 of 256 lanes but 34 of 64).
@@ -1248,39 +1067,24 @@ unsigned phi_fast_blocks(const Geo &g, int pm, unsigned threads) { return 2 * ph
 size_t phi_fast_lds(unsigned threads) { return sizeof(double) * SEP_REC * (size_t)threads; }
 
 // the block lines, then the scalar lines (their LDS: the exchange and
-// reduction arrays, 5 doubles per chunk, or the staged line, PM per chunk),
-// or all in one launch
+// reduction arrays, 5 doubles per chunk, or the staged line, PM per chunk)
+template <int PM>
+static void launch_phi_part(const PassArgs &a, const Batch &b, const dim3 &gr, const dim3 &bl, size_t lds,
+                            hipStream_t st) {
+  const size_t lds_s = sizeof(double) * 5 * (size_t)bl.x;
+  if (b.tab) {
+    hipLaunchKernelGGL((k_phi_part<PM, true, 0>), gr, bl, lds, st, a, b);
+    hipLaunchKernelGGL((k_phi_part<PM, true, 1>), gr, bl, lds_s, st, a, b);
+  } else {
+    hipLaunchKernelGGL((k_phi_part<PM, false, 0>), gr, bl, lds, st, a, b);
+    hipLaunchKernelGGL((k_phi_part<PM, false, 1>), gr, bl, lds_s, st, a, b);
+  }
+}
+
 void launch_phi_pass(int pm, const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads,
                      size_t lds, hipStream_t st) {
-  const dim3 gr(blocks), bl(threads);
-  const size_t lds_s = sizeof(double) * (size_t)(pm > 5 ? pm : 5) * threads;
-  if (blocks < PHI_SPLIT_SLOTS) {
-    if (b.tab) {
-      if (pm == 2) hipLaunchKernelGGL((k_phi_part<2, true, 2>), gr, bl, lds, st, a, b);
-      else hipLaunchKernelGGL((k_phi_part<4, true, 2>), gr, bl, lds, st, a, b);
-    } else {
-      if (pm == 2) hipLaunchKernelGGL((k_phi_part<2, false, 2>), gr, bl, lds, st, a, b);
-      else hipLaunchKernelGGL((k_phi_part<4, false, 2>), gr, bl, lds, st, a, b);
-    }
-    return;
-  }
-  if (b.tab) {
-    if (pm == 2) {
-      hipLaunchKernelGGL((k_phi_part<2, true, 0>), gr, bl, lds, st, a, b);
-      hipLaunchKernelGGL((k_phi_part<2, true, 1>), gr, bl, lds_s, st, a, b);
-    } else {
-      hipLaunchKernelGGL((k_phi_part<4, true, 0>), gr, bl, lds, st, a, b);
-      hipLaunchKernelGGL((k_phi_part<4, true, 1>), gr, bl, lds_s, st, a, b);
-    }
-  } else {
-    if (pm == 2) {
-      hipLaunchKernelGGL((k_phi_part<2, false, 0>), gr, bl, lds, st, a, b);
-      hipLaunchKernelGGL((k_phi_part<2, false, 1>), gr, bl, lds_s, st, a, b);
-    } else {
-      hipLaunchKernelGGL((k_phi_part<4, false, 0>), gr, bl, lds, st, a, b);
-      hipLaunchKernelGGL((k_phi_part<4, false, 1>), gr, bl, lds_s, st, a, b);
-    }
-  }
+  if (pm == 2) launch_phi_part<2>(a, b, dim3(blocks), dim3(threads), lds, st);
+  else launch_phi_part<4>(a, b, dim3(blocks), dim3(threads), lds, st);
 }
 
 // From this many workgroups on, the block and the scalar lines run as two
@@ -1288,13 +1092,13 @@ void launch_phi_pass(int pm, const PassArgs &a, const Batch &b, unsigned blocks,
 // third of their LDS); below it one launch runs both side by side.
 constexpr unsigned PHI_FAST_SPLIT = 1024;
 
-template <int PM, bool CYC, bool PT>
+template <int PM, bool CYC, bool W, bool PT>
 static void launch_phi_fast(const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads, size_t lds,
                             hipStream_t st) {
   const size_t lds_s = sizeof(double) * 8 * (size_t)threads;
   const dim3 gr(blocks), half(blocks / 2), bl(threads);
   if (b.tab) {
-    if constexpr (!PT) {
+    if constexpr (!W && !PT) {
       if (blocks < PHI_FAST_SPLIT) {
         hipLaunchKernelGGL((k_phi_fastB<PM, 2, CYC>), gr, bl, lds, st, a, b);
       } else {
@@ -1303,44 +1107,39 @@ static void launch_phi_fast(const PassArgs &a, const Batch &b, unsigned blocks, 
       }
     }
   } else if (blocks < PHI_FAST_SPLIT) {
-    hipLaunchKernelGGL((k_phi_fast<PM, 2, CYC, PT>), gr, bl, lds, st, a);
+    hipLaunchKernelGGL((k_phi_fast<PM, 2, CYC, W, PT>), gr, bl, lds, st, a);
   } else {
-    hipLaunchKernelGGL((k_phi_fast<PM, 0, CYC, PT>), half, bl, lds, st, a);
-    hipLaunchKernelGGL((k_phi_fast<PM, 1, CYC, PT>), half, bl, lds_s, st, a);
+    hipLaunchKernelGGL((k_phi_fast<PM, 0, CYC, W, PT>), half, bl, lds, st, a);
+    hipLaunchKernelGGL((k_phi_fast<PM, 1, CYC, false, PT>), half, bl, lds_s, st, a);
   }
 }
 
-template <bool PT>
+template <bool W, bool PT>
 static void launch_phi_fast_pm(int pm, bool periodic, const PassArgs &a, const Batch &b, unsigned blocks,
                                unsigned threads, size_t lds, hipStream_t st) {
   if (pm == 2) {
-    if (periodic) launch_phi_fast<2, true, PT>(a, b, blocks, threads, lds, st);
-    else launch_phi_fast<2, false, PT>(a, b, blocks, threads, lds, st);
+    if (periodic) launch_phi_fast<2, true, W, PT>(a, b, blocks, threads, lds, st);
+    else launch_phi_fast<2, false, W, PT>(a, b, blocks, threads, lds, st);
   } else {
-    if (periodic) launch_phi_fast<4, true, PT>(a, b, blocks, threads, lds, st);
-    else launch_phi_fast<4, false, PT>(a, b, blocks, threads, lds, st);
+    if (periodic) launch_phi_fast<4, true, W, PT>(a, b, blocks, threads, lds, st);
+    else launch_phi_fast<4, false, W, PT>(a, b, blocks, threads, lds, st);
   }
 }
 
 void launch_phi_pass_c(int pm, bool periodic, const PassArgs &a, const Batch &b, unsigned blocks,
                        unsigned threads, size_t lds, hipStream_t st) {
-  launch_phi_fast_pm<false>(pm, periodic, a, b, blocks, threads, lds, st);
+  launch_phi_fast_pm<false, false>(pm, periodic, a, b, blocks, threads, lds, st);
 }
 
 void launch_phi_pert_c(int pm, bool periodic, const PassArgs &a, unsigned blocks, unsigned threads, size_t lds,
                        hipStream_t st) {
-  launch_phi_fast_pm<true>(pm, periodic, a, Batch{nullptr, nullptr, 0}, blocks, threads, lds, st);
+  launch_phi_fast_pm<false, true>(pm, periodic, a, Batch{nullptr, nullptr, 0}, blocks, threads, lds, st);
 }
 
 void launch_phi_pert(int pm, const PassArgs &a, unsigned blocks, unsigned threads, size_t lds,
                      hipStream_t st) {
   const dim3 gr(blocks), bl(threads);
-  const size_t lds_s = sizeof(double) * (size_t)(pm > 5 ? pm : 5) * threads;
-  if (blocks < PHI_SPLIT_SLOTS) {
-    if (pm == 2) hipLaunchKernelGGL((k_phi_partP<2, 2>), gr, bl, lds, st, a);
-    else hipLaunchKernelGGL((k_phi_partP<4, 2>), gr, bl, lds, st, a);
-    return;
-  }
+  const size_t lds_s = sizeof(double) * 5 * (size_t)threads;
   if (pm == 2) {
     hipLaunchKernelGGL((k_phi_partP<2, 0>), gr, bl, lds, st, a);
     hipLaunchKernelGGL((k_phi_partP<2, 1>), gr, bl, lds_s, st, a);
@@ -1350,55 +1149,24 @@ void launch_phi_pert(int pm, const PassArgs &a, unsigned blocks, unsigned thread
   }
 }
 
-// one launch of the forced phi pass over a slot set (MAP) and a part
-template <int PM, int MAP>
-static void launch_phi_forced_map(const PassArgs &a, unsigned blocks, unsigned threads, size_t lds,
-                                  size_t lds_s, bool split, hipStream_t st) {
-  if (!blocks) return;
-  // the interior slots solve both scalar lines at once: 10 doubles per thread
-  if (MAP == 1) lds_s = std::max(lds_s, sizeof(double) * 10 * (size_t)threads);
-  const dim3 gr(blocks), bl(threads);
-  if constexpr (MAP == 1) {
-    if (a.g.periodic) {
-      if (!split) hipLaunchKernelGGL((k_phi_partF<PM, 2, MAP, true>), gr, bl, lds, st, a);
-      else {
-        hipLaunchKernelGGL((k_phi_partF<PM, 0, MAP, true>), gr, bl, lds, st, a);
-        hipLaunchKernelGGL((k_phi_partF<PM, 1, MAP, true>), gr, bl, lds_s, st, a);
-      }
-      return;
-    }
-  }
-  if (!split) {
-    hipLaunchKernelGGL((k_phi_partF<PM, 2, MAP>), gr, bl, lds, st, a);
-  } else {
-    hipLaunchKernelGGL((k_phi_partF<PM, 0, MAP>), gr, bl, lds, st, a);
-    hipLaunchKernelGGL((k_phi_partF<PM, 1, MAP>), gr, bl, lds_s, st, a);
-  }
-}
-
-// The interior slots with the interior source, the rest with the general
-// one (its ghost code across r and theta walls costs the block kernel a
-// wave per SIMD); every slot with the general one when 32-bit indices do
-// not reach.
-void launch_phi_forced(int pm, const PassArgs &a, unsigned blocks, unsigned threads, size_t lds,
-                       hipStream_t st) {
+// forced: as the plain pass; one slot per workgroup through the general source
+// where byte offsets outgrow 32 bits
+void launch_phi_forced(int pm, const PassArgs &a, hipStream_t st) {
   const Geo &g = a.g;
-  const size_t lds_s = sizeof(double) * (size_t)(pm > 5 ? pm : 5) * threads;
-  const bool split = blocks >= PHI_SPLIT_SLOTS;
-  const bool in32 = (long)(g.nr + 1) * (g.nt + 1) * g.npf < 0x7fffffffL;
-  if (!in32) {
-    if (pm == 2) launch_phi_forced_map<2, 0>(a, blocks, threads, lds, lds_s, split, st);
-    else launch_phi_forced_map<4, 0>(a, blocks, threads, lds, lds_s, split, st);
+  if (off32_ok(g)) {
+    const unsigned th = phi_fast_threads(g, pm);
+    launch_phi_fast_pm<true, false>(pm, g.periodic != 0, a, Batch{nullptr, nullptr, 0}, phi_fast_blocks(g, pm, th), th,
+                                    phi_fast_lds(th), st);
     return;
   }
-  const unsigned nin = (unsigned)(g.nr - 2) * (unsigned)(g.nt - 2);
-  const unsigned nbd = 2u * (unsigned)g.nr + 2u * (unsigned)(g.nt - 2);
+  const dim3 gr((unsigned)g.nr * (unsigned)g.nt), bl(phi_part_threads(g, pm));
+  const size_t lds = phi_part_lds(g, pm), lds_s = sizeof(double) * (size_t)(pm > 5 ? pm : 5) * bl.x;
   if (pm == 2) {
-    launch_phi_forced_map<2, 1>(a, nin, threads, lds, lds_s, split, st);
-    launch_phi_forced_map<2, 2>(a, nbd, threads, lds, lds_s, split, st);
+    hipLaunchKernelGGL((k_phi_partF<2, 0>), gr, bl, lds, st, a);
+    hipLaunchKernelGGL((k_phi_partF<2, 1>), gr, bl, lds_s, st, a);
   } else {
-    launch_phi_forced_map<4, 1>(a, nin, threads, lds, lds_s, split, st);
-    launch_phi_forced_map<4, 2>(a, nbd, threads, lds, lds_s, split, st);
+    hipLaunchKernelGGL((k_phi_partF<4, 0>), gr, bl, lds, st, a);
+    hipLaunchKernelGGL((k_phi_partF<4, 1>), gr, bl, lds_s, st, a);
   }
 }
 

@@ -301,8 +301,9 @@ __device__ __forceinline__ void rt_block_lines(const Geo &g, const Mat &m, const
 // ------------------------------------------- block lines, plain and pert --
 // The block lines [line0, line0 + L) of sweep D with every input of a chunk's
 // rows loaded before the first row is eliminated (rows_fast.hpp); mode 0.
-// PT: perturbation-pressure form.  Byte offsets in 32 bits (off32_ok).
-template <int D, int PM, bool PT>
+// W: a forced pass, whose ghosts across a wall are 2 g - u (the r lines read
+// none); PT: perturbation-pressure form.  Byte offsets in 32 bits (off32_ok).
+template <int D, int PM, bool W, bool PT>
 __device__ __forceinline__ void rt_block_fast(const PassArgs &a, unsigned line0, double *lds) {
   const Geo &g = a.g;
   const Mat &m = a.m;
@@ -357,6 +358,10 @@ __device__ __forceinline__ void rt_block_fast(const PassArgs &a, unsigned line0,
         const unsigned o = oC + (unsigned)min(max(s, 0), n - 1) * sC;
         const double v = 0.5 * (ldo(u_r, o) + ldo(u_r, o + up));
         va[q + 1] = s < 0 ? sgl * v : (s >= n ? sgh * v : v);
+        if constexpr (W) {
+          const double *w = s < 0 ? (g.pole_lo ? nullptr : a.wall.ur_t1) : (s >= n && !g.pole_hi ? a.wall.ur_t2 : nullptr);
+          if (w) va[q + 1] += w[(long)pa * g.np + k] + w[(long)(pa + 1) * g.np + k];
+        }
       }
       const unsigned pT = 8u * (unsigned)((g.nt + 1) * g.np);
       const bool lo = pa == 0, hi = pa == g.nr - 1;
@@ -367,6 +372,11 @@ __device__ __forceinline__ void rt_block_fast(const PassArgs &a, unsigned line0,
         const double x = ldo(u_t, om + ro), y = ldo(u_t, op + ro);
         tim[q] = lo ? -x : x;
         tip[q] = hi ? -y : y;
+        if constexpr (W) {
+          const long f = (long)row(q) * g.np + k;
+          if (lo) tim[q] += 2.0 * wallv(a.wall.ut_r1, f);
+          if (hi) tip[q] += 2.0 * wallv(a.wall.ut_r2, f);
+        }
       }
     }
 #pragma unroll
@@ -798,7 +808,7 @@ __device__ __forceinline__ void rt_body(const PassArgs &a, unsigned w, double *l
   if (w < nbw) {
     if constexpr (PART != 1) {
       const unsigned L = bs / (unsigned)rt_chunks<PM>(families(g, D).n);
-      if constexpr (!W && !TR) rt_block_fast<D, PM, PT>(a, w * L, lds);
+      if constexpr (!TR) rt_block_fast<D, PM, W, PT>(a, w * L, lds);
       else rt_block_lines<D, PM, TR>(g, a.m, u, a.rhs, a.o, (long)w * L, a.tau, lds, a.status);
     }
     return;
@@ -807,7 +817,7 @@ __device__ __forceinline__ void rt_body(const PassArgs &a, unsigned w, double *l
     const unsigned w2 = w - nbw;
     const unsigned L = bs / (unsigned)rt_chunks<RT_PMS>(families(g, D).n);
     const unsigned nwa = rt_scalar_wgs_a(g, D, bs);
-    if constexpr (!W && !TR) rt_scalar_fast<D, RT_PMS, PT>(a, w2 < nwa ? 0 : 1, (w2 < nwa ? w2 : w2 - nwa) * L, lds);
+    if constexpr (!TR) rt_scalar_fast<D, RT_PMS, PT>(a, w2 < nwa ? 0 : 1, (w2 < nwa ? w2 : w2 - nwa) * L, lds);
     else if (w2 < nwa) rt_scalar_lines<D, 0, RT_PMS, TR>(g, a.m, u, a.rhs, a.o, (long)w2 * L, a.tau, lds, a.status);
     else rt_scalar_lines<D, 1, RT_PMS, TR>(g, a.m, u, a.rhs, a.o, (long)(w2 - nwa) * L, a.tau, lds, a.status);
   }
@@ -827,10 +837,12 @@ __global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_part(Pass
   }
 }
 
-template <int D, int PM, int PART>
-__global__ void __launch_bounds__(256) k_rt_partF(PassArgs a) {
+// forced theta sweep, one grid: the block lines (PART 0), or with the scalar
+// lines (2; those see no wall data, nor do the r lines)
+template <int PM, int PART>
+__global__ void __launch_bounds__(256) DSW_OCC(2) k_rt_partF(PassArgs a) {
   extern __shared__ double lds[];
-  rt_body<D, PM, PART, true>(a, xcd_contiguous(blockIdx.x, gridDim.x), lds);
+  rt_body<1, PM, PART, true>(a, xcd_contiguous(blockIdx.x, gridDim.x), lds);
 }
 
 // perturbation-pressure form, one grid
@@ -985,22 +997,17 @@ int rt_default_pm(const Geo &g, int d) {
   return rt_part_supported(g, d, 256, 4) && rt_block_chunks(families(g, d).n, 4) <= 64 ? 4 : 0;
 }
 
-template <int D, int PM>
-static void launch_rt_forced_d(const PassArgs &a, unsigned threads, hipStream_t st) {
-  const size_t lds = rt_part_lds(threads), lds_s = sizeof(double) * 4 * (size_t)threads;
-  const unsigned nbw = rt_block_wgs(a.g, D, threads, PM), nsw = rt_scalar_wgs(a.g, D, threads);
-  if (nbw + nsw < RT_SPLIT_WGS) {
-    hipLaunchKernelGGL((k_rt_partF<D, PM, 2>), dim3(nbw + nsw), dim3(threads), lds, st, a);
-    return;
-  }
-  hipLaunchKernelGGL((k_rt_partF<D, PM, 0>), dim3(nbw), dim3(threads), lds, st, a);
-  hipLaunchKernelGGL((k_rt_partF<D, PM, 1>), dim3(nsw), dim3(threads), lds_s, st, a);
-}
-
 void launch_rt_forced(int d, int pm, const PassArgs &a, unsigned threads, hipStream_t st) {
-  (void)pm;
-  if (d == 0) launch_rt_forced_d<0, 4>(a, threads, st);
-  else launch_rt_forced_d<1, 4>(a, threads, st);
+  const Batch none{nullptr, nullptr, 0};
+  const unsigned nbw = rt_block_wgs(a.g, d, threads, pm), nsw = rt_scalar_wgs(a.g, d, threads);
+  if (d == 0) {
+    launch_rt_pass(0, pm, a, none, nbw + nsw, threads, st);
+  } else if (nbw + nsw < RT_SPLIT_WGS) {
+    hipLaunchKernelGGL((k_rt_partF<4, 2>), dim3(nbw + nsw), dim3(threads), rt_part_lds(threads), st, a);
+  } else {
+    hipLaunchKernelGGL((k_rt_partF<4, 0>), dim3(nbw), dim3(threads), rt_part_lds(threads), st, a);
+    launch_rt_scalar_pass(1, a, none, nsw, threads, st);
+  }
 }
 
 } // namespace dsw
