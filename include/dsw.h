@@ -335,8 +335,8 @@ int dsw_adjoint_trajectory(dsw_grid *grid, const dsw_fields *ckpts, int32_t nste
  *                         cannot take (more than 256 chunks; a cyclic line
  *                         takes a power-of-two count of chunks, some of them
  *                         a row shorter) fall back to one thread per line.
- *                         The transposed phi solves of the adjoint take two
- *                         rows per thread wherever the line allows it.
+ *                         The transposed phi solves of the adjoint take the
+ *                         same solver.
  *   rows_per_thread_r/_theta
  *                         r / theta sweeps: 4 = partitioned solver (each
  *                         workgroup on a few neighbouring lines split into
@@ -351,13 +351,14 @@ int dsw_adjoint_trajectory(dsw_grid *grid, const dsw_fields *ckpts, int32_t nste
  *                         rows (64 chunks), else two-ended (in an ensemble,
  *                         member by member).  Lines of more than
  *                         4 x sweep_block rows take the two-ended solver.
- *                         The transposed r solves of the adjoint take the
- *                         same solver on lines of at most 128 rows; the
- *                         transposed theta solves always the two-ended one.
- *                         Measured: partitioned r 0.11 ms, theta 0.13 ms
- *                         against 0.20 / 0.30 ms two-ended on the
- *                         256 x 128 x 64 sector; on the 512 x 256 x 128
- *                         sphere r 0.98 / 1.37 ms and theta 1.01 / 1.37 ms.
+ *                         The transposed r and theta solves of the adjoint
+ *                         take the same solvers.  Measured: partitioned r
+ *                         0.11 ms, theta 0.13 ms against 0.20 / 0.30 ms
+ *                         two-ended on the 256 x 128 x 64 sector; on the
+ *                         512 x 256 x 128 sphere r 0.98 / 1.37 ms and theta
+ *                         1.01 / 1.37 ms; transposed there 1.03 and 1.31
+ *                         against 1.49 (partitioned a row at a time) and
+ *                         1.66 (two-ended).
  * Default {64, 256, 256, 4, -1, -1}.  dsw_set_config returns DSW_EINVAL for
  * other values.  dsw_ensemble_tune times candidate shapes per pass and keeps
  * each pass's best; its result is also kept for the process per set of member

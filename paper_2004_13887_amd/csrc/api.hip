@@ -988,17 +988,16 @@ extern "C" int dsw_get_status(dsw_grid *G, void *stream) {
 // transposed line solve of direction d on one grid: phi lines by the
 // partitioned solver when the configuration and the line allow it
 static void launch_T(const dsw_grid *G, int d, const Pass &p, hipStream_t st) {
-  if (d == 2 && (p.kind == PK_SW2_PART || p.kind == PK_SW2_CP || p.kind == PK_SW2_CN)) {
+  if (d == 2 && (p.kind == PK_SW2_CP || p.kind == PK_SW2_CN)) {
+    launch_phi_T_c(G->cfg.phi_pm, p.a, st);
+  } else if (d == 2 && p.kind == PK_SW2_PART) {
     // two rows per chunk where the line allows it: twice the chunks in
     // flight for the same line (measured faster than four on the transposed
     // systems, whose row windows hold more registers)
     const int pm = phi_part_supported(G->geo, 2) ? 2 : G->cfg.phi_pm;
     launch_phi_T(pm, p.a, (unsigned)G->geo.nr * (unsigned)G->geo.nt, phi_part_threads(G->geo, pm),
                  phi_part_lds(G->geo, pm), st);
-  } else if (d == 0 && p.kind == PK_SW0P && families(G->geo, 0).n <= 128) {
-    // the transposed theta lines keep the two-ended solver: their row window
-    // costs the partitioned kernel its second wave per SIMD (theta 0.59 ms
-    // against 0.37 ms on the 256 x 128 x 64 sector; r 0.20 against 0.33 ms)
+  } else if (p.kind == PK_SW0P || p.kind == PK_SW1P) {
     launch_rt_T(d, p.a, (unsigned)G->cfg.sweep_bs[d], st);
   } else if (d < 2 && families(G->geo, d).nb < TWIST_LINES) {
     const unsigned bs = (unsigned)G->cfg.sweep_bs[d];

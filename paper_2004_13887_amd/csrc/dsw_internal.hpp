@@ -167,7 +167,7 @@ struct WallMix {
 void launch_wall_mix(const WallMix &w, hipStream_t st);
 void launch_phi_forced(int pm, const PassArgs &a, hipStream_t st);
 void launch_rt_forced(int d, int pm, const PassArgs &a, unsigned threads, hipStream_t st);
-// transposed r systems (adjoint) by the partitioned solver (d = 0 only)
+// transposed r and theta systems (adjoint) by the partitioned solver
 void launch_rt_T(int d, const PassArgs &a, unsigned threads, hipStream_t st);
 // the scalar lines of an r or theta sweep alone, partitioned (one grid or a
 // batch; workgroups numbered from 0 per grid)
@@ -224,6 +224,7 @@ size_t phi_part_lds(const Geo &g, int pm);
 // accumulate into acc), and elementwise helpers
 void launch_sweep_T(int d, const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st);
 void launch_sweep2_T(int d, const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st);
+void launch_phi_T_c(int pm, const PassArgs &a, hipStream_t st);
 void launch_phi_T(int pm, const PassArgs &a, unsigned blocks, unsigned threads, size_t lds,
                   hipStream_t st);
 void launch_residual_vjp(const Geo &g, const Mat &m, const Fields &Ub, double tau, const Fields &mu,

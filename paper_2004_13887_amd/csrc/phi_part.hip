@@ -15,18 +15,20 @@
 //   3. interior rows are filled in from the separators.
 // All intermediates stay in registers and LDS: no scratch traffic.
 //
-// The plain and the perturbation-pressure sweeps take the *_fast bodies: a
-// workgroup on as many neighbouring slots as its lanes hold, every input of a
-// chunk loaded before its first row is eliminated, ghosts by clamped 32-bit
+// Grids whose byte offsets fit 32 bits take the *_fast bodies: a workgroup on as
+// many neighbouring slots as its lanes hold, every input of a chunk loaded before its first row is eliminated, ghosts by clamped 32-bit
 // offsets and signs instead of branches (so no slot needs a launch or a
 // source of its own).  Line solves, one row at a time against this: 512 x 256
 // x 128 sphere 1.24 -> 0.98 ms, 200 x 200 x 200 cells 0.66 -> 0.51, 150 x 101
-// x 37 84 -> 55 us, 32 x 32 x 16 28 -> 14 us.  The block lines are bound by
+// x 37 84 -> 55 us, 32 x 32 x 16 28 -> 14 us; transposed, on the sphere 2.00 ->
+// 0.97 ms, on the 256 x 128 x 64 sector 0.262 -> 0.144 (2 rows per chunk, the
+// better choice a row at a time, 0.167).  The block lines are bound by
 // their FP64 work at two waves per SIMD (a third of it the cyclic reduction)
 // and its barriers, the scalar lines by their reads; the scalar reductions
 // keep each quantity contiguous over the lanes (a record per lane, as the
 // block reductions have, put 16 lanes on one bank: 0.55 against 0.45 ms).
 #include <algorithm>
+#include <type_traits>
 
 #include "rows_fast.hpp"
 
@@ -434,7 +436,7 @@ __device__ __forceinline__ void part_scalar_line(const Geo &g, const Mat &m, con
   __syncthreads();
 }
 
-// ---------------------------------------- plain and perturbation sweeps --
+// ------------------------------------------------- 32-bit byte offsets --
 // A workgroup takes L = blockDim / T neighbouring slots; thread t = l T + c
 // holds chunk c of slot l's lines.  Ghosts across r and theta are a clamped
 // index and a sign per lane, across phi the wrap (CYC) or the same.
@@ -478,10 +480,12 @@ __device__ __forceinline__ unsigned phi_pos(const Geo &g, int s) {
   return 8u * (unsigned)s;
 }
 
-// The block line of every slot of the workgroup.  W: a forced pass, whose
-// ghosts across a wall are 2 g - u (the scalar lines read none); PT:
-// perturbation-pressure form.  LDS SEP_REC doubles per thread.
-template <int PM, bool CYC, bool W, bool PT>
+// The block line of every slot of the workgroup.  TR: the transposed systems
+// (adjoint), whose rows take blocks of the rows on either side, so a chunk
+// loads one more row at each end; W: a forced pass, whose ghosts across a wall
+// are 2 g - u (the scalar lines read none); PT: perturbation-pressure form.
+// LDS SEP_REC doubles per thread.
+template <int PM, bool CYC, bool TR, bool W, bool PT>
 __device__ __forceinline__ void phi_block_fast(const PassArgs &a, unsigned w, double *lds) {
   const Geo &g = a.g;
   const Mat &m = a.m;
@@ -492,16 +496,18 @@ __device__ __forceinline__ void phi_block_fast(const PassArgs &a, unsigned w, do
   const int i = (int)(pc.line / (unsigned)g.nt), j = (int)pc.line - i * g.nt;
   const double ir = g.irc[i], is = g.isc[j], ct = g.ctc[j], irs = ir * is;
   const double h = irs * g.idp;  // 1 / spacing; dp = h, dm = -h
-  // per row: v = u_r + cot u_theta at rows -1 .. PM, e = Grr + Gtt; per face:
-  // own velocity uw, wf the r and theta differences of u_phi
-  double v[PM + 2], e[PM], uw[PM + 1], wf[PM + 1], P[PM + 1], Te[PM + 1], b0[PM], b1[PM], b2[PM];
+  // row q at index q + X.  Per row: v = u_r + cot u_theta there and one further
+  // at each end, e = Grr + Gtt; per face: own velocity uw, wf the r and theta
+  // differences of u_phi
+  constexpr int X = TR ? 1 : 0, NQ = PM + 2 * X;
+  double v[NQ + 2], e[NQ], uw[NQ + 1], wf[NQ + 1], P[NQ + 1], Te[NQ + 1], b0[PM], b1[PM], b2[PM];
   {
-    unsigned pos[PM + 2];  // cells s0 - 1 .. s0 + PM
+    unsigned pos[NQ + 2];  // cells s0 - 1 - X .. s0 + PM + X
 #pragma unroll
-    for (int q = 0; q < PM + 2; q++) pos[q] = phi_pos<CYC>(g, s0 + q - 1);
-    unsigned fpos[PM + 1];  // faces s0 .. s0 + PM (a bounded line has face np)
+    for (int q = 0; q < NQ + 2; q++) pos[q] = phi_pos<CYC>(g, s0 + q - 1 - X);
+    unsigned fpos[NQ + 1];  // faces s0 - X .. s0 + PM + X (a bounded line has face np)
 #pragma unroll
-    for (int q = 0; q <= PM; q++) fpos[q] = CYC ? pos[q + 1] : 8u * (unsigned)max(s0 + q, 0);
+    for (int q = 0; q <= NQ; q++) fpos[q] = CYC ? pos[q + 1] : 8u * (unsigned)min(max(s0 + q - X, 0), np);
     const double *u_r = a.u.a[F_UR], *u_t = a.u.a[F_UT], *u_f = a.u.a[F_UF];
     const unsigned oC = pc.line * N8, pl = (unsigned)g.nt * N8;
     const unsigned oT = (unsigned)(i * (g.nt + 1) + j) * N8, oF = pc.line * F8, pF = (unsigned)g.nt * F8;
@@ -513,22 +519,22 @@ __device__ __forceinline__ void phi_block_fast(const PassArgs &a, unsigned w, do
     const double kr = 0.5 * g.idr, kt = 0.5 * ir * g.idt * ct;
     const double kip = kr * sip, kim = kr * sim, kjp = kt * sjp, kjm = kt * sjm;
 #pragma unroll
-    for (int q = 0; q <= PM; q++) uw[q] = ldo(u_f, oF + fpos[q]);
+    for (int q = 0; q <= NQ; q++) uw[q] = ldo(u_f, oF + fpos[q]);
 #pragma unroll
-    for (int q = 0; q <= PM; q++) wf[q] = kip * ldo(u_f, oip + fpos[q]);
+    for (int q = 0; q <= NQ; q++) wf[q] = kip * ldo(u_f, oip + fpos[q]);
 #pragma unroll
-    for (int q = 0; q <= PM; q++) wf[q] = fma_(-kim, ldo(u_f, oim + fpos[q]), wf[q]);
+    for (int q = 0; q <= NQ; q++) wf[q] = fma_(-kim, ldo(u_f, oim + fpos[q]), wf[q]);
 #pragma unroll
-    for (int q = 0; q <= PM; q++) wf[q] = fma_(kjp, ldo(u_f, ojp + fpos[q]), wf[q]);
+    for (int q = 0; q <= NQ; q++) wf[q] = fma_(kjp, ldo(u_f, ojp + fpos[q]), wf[q]);
 #pragma unroll
-    for (int q = 0; q <= PM; q++) wf[q] = fma_(-kjm, ldo(u_f, ojm + fpos[q]), wf[q]);
+    for (int q = 0; q <= NQ; q++) wf[q] = fma_(-kjm, ldo(u_f, ojm + fpos[q]), wf[q]);
     if constexpr (W) {
       const Wall &wl = a.wall;
       const unsigned fj = (unsigned)j * F8, fi = (unsigned)i * F8;
-      auto add = [&](const double *v, unsigned o, double s) {
-        if (!v) return;
+      auto add = [&](const double *w_, unsigned o, double sc) {
+        if (!w_) return;
 #pragma unroll
-        for (int q = 0; q <= PM; q++) wf[q] = fma_(s, ldo(v, o + fpos[q]), wf[q]);
+        for (int q = 0; q <= NQ; q++) wf[q] = fma_(sc, ldo(w_, o + fpos[q]), wf[q]);
       };
       if (i == 0) add(wl.uf_r1, fj, -2.0 * kr);
       if (i == g.nr - 1) add(wl.uf_r2, fj, 2.0 * kr);
@@ -536,40 +542,40 @@ __device__ __forceinline__ void phi_block_fast(const PassArgs &a, unsigned w, do
       if (j == g.nt - 1 && !g.pole_hi) add(wl.uf_t2, fi, 2.0 * kt);
     }
 #pragma unroll
-    for (int q = 0; q < PM + 2; q++) {
+    for (int q = 0; q < NQ + 2; q++) {
+      const int s = s0 + q - 1 - X;
       const double r0 = ldo(u_r, oC + pos[q]), r1 = ldo(u_r, oC + pl + pos[q]);
       const double t0 = ldo(u_t, oT + pos[q]), t1 = ldo(u_t, oT + N8 + pos[q]);
       const double ur = 0.5 * (r0 + r1), ut = 0.5 * (t0 + t1);
       v[q] = fma_(ut, ct, ur);
-      if (!CYC && (s0 + q - 1 < 0 || s0 + q - 1 >= np)) {  // no slip
+      if (!CYC && (s < 0 || s >= np)) {  // no slip
         v[q] = -v[q];
         if constexpr (W) {
-          const bool lo = s0 + q - 1 < 0;
+          const bool lo = s < 0;
           const double *wr = lo ? a.wall.ur_p1 : a.wall.ur_p2, *wt = lo ? a.wall.ut_p1 : a.wall.ut_p2;
           const int wi = i * g.nt + j, wj = i * (g.nt + 1) + j;
           v[q] += wallv(wr, wi) + wallv(wr, wi + g.nt) + ct * (wallv(wt, wj) + wallv(wt, wj + 1));
         }
       }
-      if (q >= 1 && q <= PM) e[q - 1] = (r1 - r0) * g.idr + fma_(t1 - t0, g.idt, ur) * ir;
+      if (q >= 1 && q <= NQ) e[q - 1] = (r1 - r0) * g.idr + fma_(t1 - t0, g.idt, ur) * ir;
     }
 #pragma unroll
-    for (int q = 0; q <= PM; q++) P[q] = ldo(a.u.a[F_P], oC + pos[q + 1]);
+    for (int q = 0; q <= NQ; q++) P[q] = ldo(a.u.a[F_P], oC + pos[q + 1]);
 #pragma unroll
-    for (int q = 0; q <= PM; q++) Te[q] = ldo(a.u.a[F_T], oC + pos[q + 1]);
+    for (int q = 0; q <= NQ; q++) Te[q] = ldo(a.u.a[F_T], oC + pos[q + 1]);
 #pragma unroll
-    for (int q = 0; q < PM; q++) b0[q] = ldo(a.rhs.p, oC + pos[q + 1]);
+    for (int q = 0; q < PM; q++) b0[q] = ldo(a.rhs.p, oC + pos[q + 1 + X]);
 #pragma unroll
-    for (int q = 0; q < PM; q++) b1[q] = ldo(a.rhs.T, oC + pos[q + 1]);
+    for (int q = 0; q < PM; q++) b1[q] = ldo(a.rhs.T, oC + pos[q + 1 + X]);
 #pragma unroll
-    for (int q = 0; q < PM; q++) b2[q] = ldo(a.rhs.uf, oF + fpos[q + 1]);
-    double add = m.pinf;
+    for (int q = 0; q < PM; q++) b2[q] = ldo(a.rhs.uf, oF + fpos[q + 1 + X]);
     if constexpr (PT) {
       const double pr = a.pref[i];
 #pragma unroll
-      for (int q = 0; q <= PM; q++) P[q] += pr;
+      for (int q = 0; q <= NQ; q++) P[q] += pr;
     }
 #pragma unroll
-    for (int q = 0; q <= PM; q++) P[q] += add;
+    for (int q = 0; q <= NQ; q++) P[q] += m.pinf;
   }
   RowMetric x;
   x.h = h;
@@ -578,31 +584,51 @@ __device__ __forceinline__ void phi_block_fast(const PassArgs &a, unsigned w, do
   x.lp = x.lm = h * h;
   x.wp = x.wm = (-4.0 / 3.0) * (h * h);
   x.w0 = (8.0 / 3.0) * (h * h);
+  // row q of the line (TR: -1 .. PM, without the fillers)
   auto assemble = [&](int q, FRow &R) {
+    const int z = q + X;
     RowIn in;
-    in.vel = 0.5 * (uw[q] + uw[q + 1]);
-    in.un = uw[q + 1];
-    in.G = fma_(uw[q + 1] - uw[q], h, v[q + 1] * ir);
-    in.tr = e[q] + in.G;
-    in.gg = (-0.5 * ir) * (0.5 * (wf[q] + wf[q + 1]) + (v[q + 2] - v[q]) * (0.5 * h) - in.vel * (ir * (1.0 + ct * ct)));
-    in.P = P[q];
-    in.T = Te[q];
-    in.irho = 2.0 * m.Rg * Te[q] * Te[q + 1] * rcp_nr(P[q] * Te[q + 1] + P[q + 1] * Te[q]);
-    in.b0 = b0[q];
-    in.b1 = b1[q];
-    in.b2 = b2[q];
-    frow(m, hs, in, x, !CYC && s0 + q == 0, !CYC && q == PM - 1 && c == T - 1, !CYC && q == PM - 2 && c == T - 1,
-         q >= pc.pad, R);
+    in.vel = 0.5 * (uw[z] + uw[z + 1]);
+    in.un = uw[z + 1];
+    in.G = fma_(uw[z + 1] - uw[z], h, v[z + 1] * ir);
+    in.tr = e[z] + in.G;
+    in.gg = (-0.5 * ir) * (0.5 * (wf[z] + wf[z + 1]) + (v[z + 2] - v[z]) * (0.5 * h) - in.vel * (ir * (1.0 + ct * ct)));
+    in.P = P[z];
+    in.T = Te[z];
+    in.irho = 2.0 * m.Rg * Te[z] * Te[z + 1] * rcp_nr(P[z] * Te[z + 1] + P[z + 1] * Te[z]);
+    const bool own = q >= 0 && q < PM;
+    in.b0 = own ? b0[own ? q : 0] : 0.0;
+    in.b1 = own ? b1[own ? q : 0] : 0.0;
+    in.b2 = own ? b2[own ? q : 0] : 0.0;
+    const bool before = !CYC && (TR ? s0 + q == np - 2 : (q == PM - 2 && c == T - 1));
+    frow(m, hs, in, x, !CYC && s0 + q == 0, !CYC && q == PM - 1 && c == T - 1, before, TR || q >= pc.pad, R);
+  };
+  using Row = std::conditional_t<TR, TRow, FRow>;
+  FRow M_, R_;  // TR: the rows before and at the one in turn
+  if constexpr (TR) {
+    assemble(-1, M_);
+    assemble(0, R_);
+  }
+  auto next = [&](int q, Row &R) {
+    if constexpr (TR) {
+      FRow N_;
+      assemble(q + 1, N_);
+      trow(M_, R_, N_, !CYC && s0 + q == 0, !CYC && q == PM - 1 && c == T - 1, q >= pc.pad, R);
+      M_ = R_;
+      R_ = N_;
+    } else {
+      assemble(q, R);
+    }
   };
   Chunk<PM> ch;
 #pragma unroll
   for (int q = 0; q < PM - 1; q++) {
-    FRow R;
-    assemble(q, R);
+    Row R;
+    next(q, R);
     ch.eliminate(q, R);
   }
-  FRow S;
-  assemble(PM - 1, S);
+  Row S;
+  next(PM - 1, S);
   ch.back();
   // the first row of the chunk, for the chunk before it (a circle's first
   // chunk follows its last one, and uneven chunks start after their fillers)
@@ -705,8 +731,9 @@ __device__ __forceinline__ void phi_block_fast(const PassArgs &a, unsigned w, do
 
 // Both scalar lines of every slot: u_r on its r face (i >= 1) and u_theta on
 // its theta face (j >= 1).  The two lines share the slot's own cell and u_phi
-// loads and one set of barriers.  LDS 8 doubles per thread.
-template <int PM, bool CYC, bool PT>
+// loads and one set of barriers.  TR: the transposed systems, row s (c_{s-1},
+// b_s, a_{s+1}).  LDS 8 doubles per thread.
+template <int PM, bool CYC, bool TR, bool PT>
 __device__ __forceinline__ void phi_scalar_fast(const PassArgs &a, unsigned w, double *lds) {
   const Geo &g = a.g;
   const Mat &m = a.m;
@@ -718,62 +745,77 @@ __device__ __forceinline__ void phi_scalar_fast(const PassArgs &a, unsigned w, d
   const int im = max(i - 1, 0), jm = max(j - 1, 0);
   double ra[2][PM], rb[2][PM], rc[2][PM], rr[2][PM];
   {
-    unsigned pos[PM], fpos[PM + 1];
+    constexpr int X = TR ? 1 : 0, NQ = PM + 2 * X;
+    unsigned pos[NQ], fpos[NQ + 1];
 #pragma unroll
-    for (int q = 0; q < PM; q++) pos[q] = phi_pos<CYC>(g, s0 + q);
+    for (int q = 0; q < NQ; q++) pos[q] = phi_pos<CYC>(g, s0 + q - X);
 #pragma unroll
-    for (int q = 0; q <= PM; q++) fpos[q] = CYC ? phi_pos<true>(g, s0 + q) : 8u * (unsigned)max(s0 + q, 0);
+    for (int q = 0; q <= NQ; q++)
+      fpos[q] = CYC ? phi_pos<true>(g, s0 + q - X) : 8u * (unsigned)min(max(s0 + q - X, 0), np);
     const unsigned l0 = pc.line, li = (unsigned)(im * g.nt + j), lj = (unsigned)(i * g.nt + jm);
     const double *u_f = a.u.a[F_UF], *Pp = a.u.a[F_P], *Tp = a.u.a[F_T];
-    double f[3][PM + 1];
+    double f[3][NQ + 1];
 #pragma unroll
-    for (int q = 0; q <= PM; q++) f[0][q] = ldo(u_f, l0 * F8 + fpos[q]);
+    for (int q = 0; q <= NQ; q++) f[0][q] = ldo(u_f, l0 * F8 + fpos[q]);
 #pragma unroll
-    for (int q = 0; q <= PM; q++) f[1][q] = ldo(u_f, li * F8 + fpos[q]);
+    for (int q = 0; q <= NQ; q++) f[1][q] = ldo(u_f, li * F8 + fpos[q]);
 #pragma unroll
-    for (int q = 0; q <= PM; q++) f[2][q] = ldo(u_f, lj * F8 + fpos[q]);
-    double P[3][PM], Te[3][PM];
+    for (int q = 0; q <= NQ; q++) f[2][q] = ldo(u_f, lj * F8 + fpos[q]);
+    double P[3][NQ], Te[3][NQ];
 #pragma unroll
     for (int z = 0; z < 3; z++) {
       const unsigned o = (z == 0 ? l0 : z == 1 ? li : lj) * N8;
 #pragma unroll
-      for (int q = 0; q < PM; q++) P[z][q] = ldo(Pp, o + pos[q]);
+      for (int q = 0; q < NQ; q++) P[z][q] = ldo(Pp, o + pos[q]);
 #pragma unroll
-      for (int q = 0; q < PM; q++) Te[z][q] = ldo(Tp, o + pos[q]);
+      for (int q = 0; q < NQ; q++) Te[z][q] = ldo(Tp, o + pos[q]);
     }
     const unsigned oT = (unsigned)(i * (g.nt + 1) + j) * N8;
 #pragma unroll
-    for (int q = 0; q < PM; q++) rr[0][q] = ldo(a.rhs.ur, l0 * N8 + pos[q]);
+    for (int q = 0; q < PM; q++) rr[0][q] = ldo(a.rhs.ur, l0 * N8 + pos[q + X]);
 #pragma unroll
-    for (int q = 0; q < PM; q++) rr[1][q] = ldo(a.rhs.ut, oT + pos[q]);
+    for (int q = 0; q < PM; q++) rr[1][q] = ldo(a.rhs.ut, oT + pos[q + X]);
     if constexpr (PT) {
       const double p0 = a.pref[i], pm = a.pref[im];
 #pragma unroll
-      for (int q = 0; q < PM; q++) { P[0][q] += p0; P[1][q] += pm; P[2][q] += p0; }
+      for (int q = 0; q < NQ; q++) { P[0][q] += p0; P[1][q] += pm; P[2][q] += p0; }
     }
 #pragma unroll
     for (int z = 0; z < 3; z++)
 #pragma unroll
-      for (int q = 0; q < PM; q++) P[z][q] += m.pinf;
+      for (int q = 0; q < NQ; q++) P[z][q] += m.pinf;
 #pragma unroll
     for (int z = 0; z < 2; z++) {
       // u_r: 1 / r of its face; u_theta: 1 / sin of its face (0 at a pole,
       // whose line is not solved)
       const double h = (z == 0 ? g.irf[i] * g.isc[j] : g.irc[i] * g.isf[j]) * g.idp;
       const double hv = 0.125 * hs * h, hn = hs * m.mu * 2.0 * m.Rg * (h * h);
+      double ca[NQ], cn[NQ];
+#pragma unroll
+      for (int y = 0; y < NQ; y++) {
+        const int q = y - X;
+        const double Ta = Te[0][y], Tb = Te[1 + z][y];
+        const double nu = hn * Ta * Tb * rcp_nr(P[0][y] * Tb + P[1 + z][y] * Ta);
+        const double ua = hv * ((f[0][y] + f[0][y + 1]) + (f[1 + z][y] + f[1 + z][y + 1]));
+        ca[y] = -ua - nu;
+        cn[y] = ua - nu;
+        if (q < 0 || q >= PM) continue;
+        double cb = 2.0 * nu;
+        if (!CYC && s0 + q == 0) { cb -= ca[y]; if (!TR) ca[y] = 0.0; }
+        if (!CYC && q == PM - 1 && c == T - 1) { cb -= cn[y]; if (!TR) cn[y] = 0.0; }
+        const bool real = q >= pc.pad;
+        rb[z][q] = real ? 1.0 + cb : 1.0;
+        rr[z][q] = real ? rr[z][q] : 0.0;
+      }
 #pragma unroll
       for (int q = 0; q < PM; q++) {
-        const double Ta = Te[0][q], Tb = Te[1 + z][q];
-        const double nu = hn * Ta * Tb * rcp_nr(P[0][q] * Tb + P[1 + z][q] * Ta);
-        const double ua = hv * ((f[0][q] + f[0][q + 1]) + (f[1 + z][q] + f[1 + z][q + 1]));
-        double ca = -ua - nu, cb = 2.0 * nu, cn = ua - nu;
-        if (!CYC && s0 + q == 0) { cb -= ca; ca = 0.0; }
-        if (!CYC && q == PM - 1 && c == T - 1) { cb -= cn; cn = 0.0; }
-        const bool real = q >= pc.pad;
-        ra[z][q] = real ? ca : -1.0;
-        rb[z][q] = real ? 1.0 + cb : 1.0;
-        rc[z][q] = real ? cn : 0.0;
-        rr[z][q] = real ? rr[z][q] : 0.0;
+        double lo = ca[q + X], up = cn[q + X];
+        if constexpr (TR) {  // c_{s-1}, a_{s+1}; none past the ends of an open line
+          lo = !CYC && s0 + q == 0 ? 0.0 : cn[q];
+          up = !CYC && q == PM - 1 && c == T - 1 ? 0.0 : ca[q + 2];
+        }
+        ra[z][q] = q >= pc.pad ? lo : -1.0;
+        rc[z][q] = q >= pc.pad ? up : 0.0;
       }
     }
   }
@@ -905,7 +947,7 @@ __host__ __device__ inline unsigned phi_fast_wgs(const Geo &g, int pm, unsigned 
 // PART 0: the block lines; 1: the scalar lines; 2: both, the block lines in the
 // first half of the workgroups.  COMB: workgroups numbered as for PART 2
 // whatever the part (a batched launch's member table counts both halves).
-template <int PM, int PART, bool CYC, bool W, bool PT, bool COMB>
+template <int PM, int PART, bool CYC, bool TR, bool W, bool PT, bool COMB>
 __device__ __forceinline__ void phi_fast_body(const PassArgs &a, unsigned w, double *lds) {
   const Geo &g = a.g;
   const unsigned nbw = PART == 2 || COMB ? phi_fast_wgs(g, PM, blockDim.x) : 0u;
@@ -927,26 +969,33 @@ __device__ __forceinline__ void phi_fast_body(const PassArgs &a, unsigned w, dou
           if (!CYC && pc.c == 0) x.uf[idx_f(g, i, j, 0)] = 0.0;
         }
       }
-      phi_block_fast<PM, CYC, W, PT>(a, w, lds);
+      phi_block_fast<PM, CYC, TR, W, PT>(a, w, lds);
       return;
     }
   }
   if constexpr (PART != 0) {
     if (COMB && w < nbw) return;
-    phi_scalar_fast<PM, CYC, PT>(a, PART == 2 || COMB ? w - nbw : w, lds);
+    phi_scalar_fast<PM, CYC, TR, PT>(a, PART == 2 || COMB ? w - nbw : w, lds);
   }
 }
 
 template <int PM, int PART, bool CYC, bool W, bool PT>
 __global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_phi_fast(PassArgs a) {
   extern __shared__ double lds[];
-  phi_fast_body<PM, PART, CYC, W, PT, false>(a, PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x, lds);
+  phi_fast_body<PM, PART, CYC, false, W, PT, false>(a, PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x, lds);
+}
+// transposed systems (adjoint), one grid
+template <int PM, int PART, bool CYC>
+__global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_phi_fastT(PassArgs a) {
+  extern __shared__ double lds[];
+  phi_fast_body<PM, PART, CYC, true, false, false, false>(
+      a, PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x, lds);
 }
 template <int PM, int PART, bool CYC>
 __global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_phi_fastB(PassArgs a, Batch bt) {
   extern __shared__ double lds[];
   const int mb = batch_member(bt, blockIdx.x);
-  phi_fast_body<PM, PART, CYC, false, false, true>(batch_args(bt, mb), blockIdx.x - bt.woff[mb], lds);
+  phi_fast_body<PM, PART, CYC, false, false, false, true>(batch_args(bt, mb), blockIdx.x - bt.woff[mb], lds);
 }
 
 // one workgroup per (i, j): block line (i, j), u_r line on r-face i (i >= 1),
@@ -1146,6 +1195,29 @@ void launch_phi_pert(int pm, const PassArgs &a, unsigned blocks, unsigned thread
   } else {
     hipLaunchKernelGGL((k_phi_partP<4, 0>), gr, bl, lds, st, a);
     hipLaunchKernelGGL((k_phi_partP<4, 1>), gr, bl, lds_s, st, a);
+  }
+}
+
+// transposed: as the plain pass
+template <int PM, bool CYC>
+static void launch_phi_fast_T(const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st) {
+  const size_t lds = phi_fast_lds(threads), lds_s = sizeof(double) * 8 * (size_t)threads;
+  if (blocks < PHI_FAST_SPLIT) {
+    hipLaunchKernelGGL((k_phi_fastT<PM, 2, CYC>), dim3(blocks), dim3(threads), lds, st, a);
+    return;
+  }
+  hipLaunchKernelGGL((k_phi_fastT<PM, 0, CYC>), dim3(blocks / 2), dim3(threads), lds, st, a);
+  hipLaunchKernelGGL((k_phi_fastT<PM, 1, CYC>), dim3(blocks / 2), dim3(threads), lds_s, st, a);
+}
+
+void launch_phi_T_c(int pm, const PassArgs &a, hipStream_t st) {
+  const unsigned th = phi_fast_threads(a.g, pm), nb = phi_fast_blocks(a.g, pm, th);
+  if (pm == 2) {
+    if (a.g.periodic) launch_phi_fast_T<2, true>(a, nb, th, st);
+    else launch_phi_fast_T<2, false>(a, nb, th, st);
+  } else {
+    if (a.g.periodic) launch_phi_fast_T<4, true>(a, nb, th, st);
+    else launch_phi_fast_T<4, false>(a, nb, th, st);
   }
 }
 

@@ -126,14 +126,66 @@ __device__ __forceinline__ bool inv3d(const FRow &R, double *X) {
   return !(det != 0.0) || !isfinite(det);
 }
 
-// products with the sparse blocks of a row: C = R.L X (3x3), y = R.L x, and
-// C = A R.U, C = A R.L for a full A
+// A row of the transposed line: lower block U_{s-1}^T, diagonal D_s^T, upper
+// block L_{s+1}^T, the right-hand side at row s's unknowns.
+struct TRow {
+  double l0, l1, l4, l6, l8;      // U_{s-1}
+  double D0, D1, D2, D4, D5, D6, D8;
+  double u0, u1, u2, u4, u5, u8;  // L_{s+1}
+  double b0, b1, b2;
+};
+// from the rows before, at and after it; first / last of an open line: no row
+// on that side; real: as in frow
+__device__ __forceinline__ void trow(const FRow &M, const FRow &R, const FRow &P, bool first, bool last, bool real,
+                                     TRow &t) {
+  t.l0 = M.U0; t.l1 = M.U1; t.l4 = M.U4; t.l6 = M.U6; t.l8 = M.U8;
+  t.D0 = R.D0; t.D1 = R.D1; t.D2 = R.D2; t.D4 = R.D4; t.D5 = R.D5; t.D6 = R.D6; t.D8 = R.D8;
+  t.u0 = P.L0; t.u1 = P.L1; t.u2 = P.L2; t.u4 = P.L4; t.u5 = P.L5; t.u8 = P.L8;
+  t.b0 = R.b0; t.b1 = R.b1; t.b2 = R.b2;
+  if (first) t.l0 = t.l1 = t.l4 = t.l6 = t.l8 = 0.0;
+  if (last || !real) t.u0 = t.u1 = t.u2 = t.u4 = t.u5 = t.u8 = 0.0;
+  if (!real) {
+    t.l0 = t.l4 = t.l8 = -1.0;
+    t.l1 = t.l6 = 0.0;
+    t.D0 = t.D4 = t.D8 = 1.0;
+    t.D1 = t.D2 = t.D5 = t.D6 = 0.0;
+    t.b0 = t.b1 = t.b2 = 0.0;
+  }
+}
+__device__ __forceinline__ bool inv3d(const TRow &t, double *X) {
+  FRow R;
+  R.D0 = t.D0; R.D1 = t.D1; R.D2 = t.D2; R.D4 = t.D4; R.D5 = t.D5; R.D6 = t.D6; R.D8 = t.D8;
+  double Y[9];
+  const bool sing = inv3d(R, Y);
+#pragma unroll
+  for (int r = 0; r < 3; r++)
+#pragma unroll
+    for (int c = 0; c < 3; c++) X[r * 3 + c] = Y[c * 3 + r];
+  return sing;
+}
+
+// Products with the sparse blocks of a row: C = L X, C = U X, B -= L X,
+// y -= L x, y -= U x, C = A L, C = A U (A, X full), and the diagonal block.
+__device__ __forceinline__ void diag3(const FRow &R, double *D) {
+  D[0] = R.D0; D[1] = R.D1; D[2] = R.D2; D[3] = 0.0; D[4] = R.D4; D[5] = R.D5; D[6] = R.D6; D[7] = 0.0; D[8] = R.D8;
+}
+__device__ __forceinline__ void diag3(const TRow &R, double *D) {
+  D[0] = R.D0; D[1] = 0.0; D[2] = R.D6; D[3] = R.D1; D[4] = R.D4; D[5] = 0.0; D[6] = R.D2; D[7] = R.D5; D[8] = R.D8;
+}
 __device__ __forceinline__ void mulL(const FRow &R, const double *X, double *C) {
 #pragma unroll
   for (int c = 0; c < 3; c++) {
     C[c] = fma_(R.L2, X[6 + c], fma_(R.L1, X[3 + c], R.L0 * X[c]));
     C[3 + c] = fma_(R.L5, X[6 + c], R.L4 * X[3 + c]);
     C[6 + c] = R.L8 * X[6 + c];
+  }
+}
+__device__ __forceinline__ void mulL(const TRow &R, const double *X, double *C) {
+#pragma unroll
+  for (int c = 0; c < 3; c++) {
+    C[c] = fma_(R.l6, X[6 + c], R.l0 * X[c]);
+    C[3 + c] = fma_(R.l4, X[3 + c], R.l1 * X[c]);
+    C[6 + c] = R.l8 * X[6 + c];
   }
 }
 __device__ __forceinline__ void mulU(const FRow &R, const double *X, double *C) {
@@ -144,6 +196,50 @@ __device__ __forceinline__ void mulU(const FRow &R, const double *X, double *C) 
     C[6 + c] = fma_(R.U8, X[6 + c], R.U6 * X[c]);
   }
 }
+__device__ __forceinline__ void mulU(const TRow &R, const double *X, double *C) {
+#pragma unroll
+  for (int c = 0; c < 3; c++) {
+    C[c] = R.u0 * X[c];
+    C[3 + c] = fma_(R.u4, X[3 + c], R.u1 * X[c]);
+    C[6 + c] = fma_(R.u8, X[6 + c], fma_(R.u5, X[3 + c], R.u2 * X[c]));
+  }
+}
+__device__ __forceinline__ void subL(const FRow &R, const double *X, double *B) {
+#pragma unroll
+  for (int c = 0; c < 3; c++) {
+    B[c] = fma_(-R.L2, X[6 + c], fma_(-R.L1, X[3 + c], fma_(-R.L0, X[c], B[c])));
+    B[3 + c] = fma_(-R.L5, X[6 + c], fma_(-R.L4, X[3 + c], B[3 + c]));
+    B[6 + c] = fma_(-R.L8, X[6 + c], B[6 + c]);
+  }
+}
+__device__ __forceinline__ void subL(const TRow &R, const double *X, double *B) {
+#pragma unroll
+  for (int c = 0; c < 3; c++) {
+    B[c] = fma_(-R.l6, X[6 + c], fma_(-R.l0, X[c], B[c]));
+    B[3 + c] = fma_(-R.l4, X[3 + c], fma_(-R.l1, X[c], B[3 + c]));
+    B[6 + c] = fma_(-R.l8, X[6 + c], B[6 + c]);
+  }
+}
+__device__ __forceinline__ void subLv(const FRow &R, const double *x, double *y) {
+  y[0] = fma_(-R.L2, x[2], fma_(-R.L1, x[1], fma_(-R.L0, x[0], y[0])));
+  y[1] = fma_(-R.L5, x[2], fma_(-R.L4, x[1], y[1]));
+  y[2] = fma_(-R.L8, x[2], y[2]);
+}
+__device__ __forceinline__ void subLv(const TRow &R, const double *x, double *y) {
+  y[0] = fma_(-R.l6, x[2], fma_(-R.l0, x[0], y[0]));
+  y[1] = fma_(-R.l4, x[1], fma_(-R.l1, x[0], y[1]));
+  y[2] = fma_(-R.l8, x[2], y[2]);
+}
+__device__ __forceinline__ void subUv(const FRow &R, const double *x, double *y) {
+  y[0] = fma_(-R.U1, x[1], fma_(-R.U0, x[0], y[0]));
+  y[1] = fma_(-R.U4, x[1], y[1]);
+  y[2] = fma_(-R.U8, x[2], fma_(-R.U6, x[0], y[2]));
+}
+__device__ __forceinline__ void subUv(const TRow &R, const double *x, double *y) {
+  y[0] = fma_(-R.u0, x[0], y[0]);
+  y[1] = fma_(-R.u4, x[1], fma_(-R.u1, x[0], y[1]));
+  y[2] = fma_(-R.u8, x[2], fma_(-R.u5, x[1], fma_(-R.u2, x[0], y[2])));
+}
 __device__ __forceinline__ void mul_rU(const double *A, const FRow &R, double *C) {
 #pragma unroll
   for (int r = 0; r < 3; r++) {
@@ -152,12 +248,28 @@ __device__ __forceinline__ void mul_rU(const double *A, const FRow &R, double *C
     C[r * 3 + 2] = A[r * 3 + 2] * R.U8;
   }
 }
+__device__ __forceinline__ void mul_rU(const double *A, const TRow &R, double *C) {
+#pragma unroll
+  for (int r = 0; r < 3; r++) {
+    C[r * 3] = fma_(A[r * 3 + 2], R.u2, fma_(A[r * 3 + 1], R.u1, A[r * 3] * R.u0));
+    C[r * 3 + 1] = fma_(A[r * 3 + 2], R.u5, A[r * 3 + 1] * R.u4);
+    C[r * 3 + 2] = A[r * 3 + 2] * R.u8;
+  }
+}
 __device__ __forceinline__ void mul_rL(const double *A, const FRow &R, double *C) {
 #pragma unroll
   for (int r = 0; r < 3; r++) {
     C[r * 3] = A[r * 3] * R.L0;
     C[r * 3 + 1] = fma_(A[r * 3 + 1], R.L4, A[r * 3] * R.L1);
     C[r * 3 + 2] = fma_(A[r * 3 + 2], R.L8, fma_(A[r * 3 + 1], R.L5, A[r * 3] * R.L2));
+  }
+}
+__device__ __forceinline__ void mul_rL(const double *A, const TRow &R, double *C) {
+#pragma unroll
+  for (int r = 0; r < 3; r++) {
+    C[r * 3] = fma_(A[r * 3 + 1], R.l1, A[r * 3] * R.l0);
+    C[r * 3 + 1] = A[r * 3 + 1] * R.l4;
+    C[r * 3 + 2] = fma_(A[r * 3 + 2], R.l8, A[r * 3] * R.l6);
   }
 }
 // acc -= A B, y -= A x, A <- -(A B) for full blocks, one rounding per term
@@ -191,23 +303,17 @@ template <int PM>
 struct Chunk {
   double C[PM - 1][9], E[PM - 1][9], Y[PM - 1][3];
   bool sing = false;
-  __device__ __forceinline__ void eliminate(int q, const FRow &R) {
+  template <class Row>
+  __device__ __forceinline__ void eliminate(int q, const Row &R) {
     double Ai[9], rr[3] = {R.b0, R.b1, R.b2};
     if (q == 0) {
       sing |= inv3d(R, Ai);
       mul_rL(Ai, R, E[0]);
     } else {
-      const double *Cp = C[q - 1], *Yp = Y[q - 1];
-      double Dp[9] = {R.D0, R.D1, R.D2, 0.0, R.D4, R.D5, R.D6, 0.0, R.D8}, Lx[9];
-#pragma unroll
-      for (int c = 0; c < 3; c++) {
-        Dp[c] = fma_(-R.L2, Cp[6 + c], fma_(-R.L1, Cp[3 + c], fma_(-R.L0, Cp[c], Dp[c])));
-        Dp[3 + c] = c == 0 ? fma_(-R.L5, Cp[6], -R.L4 * Cp[3]) : fma_(-R.L5, Cp[6 + c], fma_(-R.L4, Cp[3 + c], Dp[3 + c]));
-        Dp[6 + c] = c == 1 ? -R.L8 * Cp[7] : fma_(-R.L8, Cp[6 + c], Dp[6 + c]);
-      }
-      rr[0] = fma_(-R.L2, Yp[2], fma_(-R.L1, Yp[1], fma_(-R.L0, Yp[0], rr[0])));
-      rr[1] = fma_(-R.L5, Yp[2], fma_(-R.L4, Yp[1], rr[1]));
-      rr[2] = fma_(-R.L8, Yp[2], rr[2]);
+      double Dp[9], Lx[9];
+      diag3(R, Dp);
+      subL(R, C[q - 1], Dp);
+      subLv(R, Y[q - 1], rr);
       mulL(R, E[q - 1], Lx);
       sing |= inv3q(Dp, Ai);
 #pragma unroll
@@ -237,25 +343,24 @@ struct Chunk {
   }
   // the separator's row, the last interior row substituted and the first
   // interior row (g, V, W) of the chunk after: A x_left + B x + Cc x_next = r
-  __device__ __forceinline__ void reduce(const FRow &S, const double *gn, const double *Vn, const double *Wn,
+  template <class Row>
+  __device__ __forceinline__ void reduce(const Row &S, const double *gn, const double *Vn, const double *Wn,
                                          double *A, double *B, double *Cc, double *r) {
-    const double *Yl = Y[PM - 2];
     double t9[9];
     mulL(S, E[PM - 2], A);
     mulL(S, C[PM - 2], t9);
-    const double D[9] = {S.D0, S.D1, S.D2, 0.0, S.D4, S.D5, S.D6, 0.0, S.D8};
+    diag3(S, B);
 #pragma unroll
-    for (int z = 0; z < 9; z++) B[z] = z == 3 || z == 7 ? t9[z] : D[z] + t9[z];
+    for (int z = 0; z < 9; z++) B[z] += t9[z];
     mulU(S, Vn, t9);
 #pragma unroll
     for (int z = 0; z < 9; z++) B[z] += t9[z];
     mulU(S, Wn, Cc);
-    r[0] = fma_(-S.L2, Yl[2], fma_(-S.L1, Yl[1], fma_(-S.L0, Yl[0], S.b0)));
-    r[1] = fma_(-S.L5, Yl[2], fma_(-S.L4, Yl[1], S.b1));
-    r[2] = fma_(-S.L8, Yl[2], S.b2);
-    r[0] = fma_(-S.U1, gn[1], fma_(-S.U0, gn[0], r[0]));
-    r[1] = fma_(-S.U4, gn[1], r[1]);
-    r[2] = fma_(-S.U8, gn[2], fma_(-S.U6, gn[0], r[2]));
+    r[0] = S.b0;
+    r[1] = S.b1;
+    r[2] = S.b2;
+    subLv(S, Y[PM - 2], r);
+    subUv(S, gn, r);
   }
   __device__ __forceinline__ void fill(int q, const double *xl, const double *xs, double *v) const {
 #pragma unroll

@@ -17,18 +17,21 @@
 // Every intermediate stays in registers and LDS: no scratch array, so the
 // pass moves one read of its inputs and one write of its result.
 //
-// The plain and the perturbation-pressure sweeps take the *_fast bodies: every
-// input of a chunk loaded before its first row is eliminated, 32-bit byte
-// offsets from uniform bases, metric factors from per-row tables, no row under
-// a branch.  The bodies that assemble a row at a time under a branch on the
-// chunk's length (the forced and the transposed sweeps keep them) spent half
-// of their instructions on addresses, ghost cases and register moves, and one
-// memory latency per row.  Line solves, before -> after: 512 x 256 x 128
+// Every input of a chunk is loaded before its first row is eliminated, byte
+// offsets are 32-bit from uniform bases, metric factors come from per-row
+// tables, and no row stands under a branch.  Assembling a row at a time under
+// a branch on the chunk's length spent half of the instructions on addresses,
+// ghost cases and register moves, and one memory latency per row.  Line
+// solves, a row at a time against this form: 512 x 256 x 128
 // sphere r 1.34 -> 0.98, theta 1.80 -> 1.01 ms; 256 x 128 x 64 sector r 0.145
-// -> 0.109, theta 0.183 -> 0.130 ms; 32 x 32 x 16 theta 19.6 -> 13.8 us.  The
+// -> 0.109, theta 0.183 -> 0.130 ms; 32 x 32 x 16 theta 19.6 -> 13.8 us;
+// transposed on the sphere r 1.49 -> 1.03 ms, theta (two-ended before) 1.66 ->
+// 1.31, on the sector 0.163 -> 0.108 and 0.282 -> 0.151.  The
 // block lines stay at two waves per SIMD (256 registers: 63 doubles of
 // intermediates and the reduction's 30) and are bound by their FP64 work and
 // the reduction's barriers; the scalar lines by their reads.
+#include <type_traits>
+
 #include "rows_fast.hpp"
 
 namespace dsw {
@@ -39,272 +42,15 @@ constexpr int RT_PMS = 8;  // rows per thread, scalar lines
 template <int PM>
 __host__ __device__ inline int rt_chunks(int n) { return (n + PM - 1) / PM; }
 
-// --------------------------------------------------- reduction over lines --
-// Parallel cyclic reduction of the separator rows A x_{c-1} + B x_c +
-// C x_{c+1} = r of every line of the workgroup; separator (l, c) is held by
-// thread c * L + l (act: a separator of a real line).  Each step, every
-// separator publishes B^{-1} A, B^{-1} C and B^{-1} r (21 doubles of LDS per
-// thread) and folds in its neighbours h chunks away.  Non-cyclic lines: the
-// couplings past either end are zero from the start and stay zero.
-__device__ __forceinline__ void rt_pcr_block(int c, int l, int T, int L, bool act, double *A, double *B,
-                                             double *C, double *r, double *lds, double *x, int *status) {
-  const int nt = T * L, t = c * L + l;
-  double *sA = lds, *sC = lds + 9 * nt, *sR = lds + 18 * nt;
-  for (int h = 1; h < T; h *= 2) {
-    if (act) {
-      double Bi[9];
-      inv3(B, Bi, status);
-      mm3(Bi, A, &sA[t * 9]);
-      mm3(Bi, C, &sC[t * 9]);
-      mv3(Bi, r, &sR[t * 3]);
-    }
-    __syncthreads();
-    if (act) {
-      // x_{c-h} = R' - A' x_{c-2h} - C' x_c and x_{c+h} alike: B' = B -
-      // A C'(c-h) - C A'(c+h), r' alike, A' = -A A'(c-h), C' = -C C'(c+h)
-      const bool has_lo = c - h >= 0, has_hi = c + h < T;
-      const int ul = (c - h) * L + l, uh = (c + h) * L + l;
-      if (has_lo) { mm3_sub(A, &sC[ul * 9], B); mv3_sub(A, &sR[ul * 3], r); }
-      if (has_hi) { mm3_sub(C, &sA[uh * 9], B); mv3_sub(C, &sR[uh * 3], r); }
-      if (has_lo) mm3_neg_inplace(A, &sA[ul * 9]);
-      else {
-#pragma unroll
-        for (int q = 0; q < 9; q++) A[q] = 0.0;
-      }
-      if (has_hi) mm3_neg_inplace(C, &sC[uh * 9]);
-      else {
-#pragma unroll
-        for (int q = 0; q < 9; q++) C[q] = 0.0;
-      }
-    }
-    __syncthreads();
-  }
-  if (act) {
-    double Bi[9];
-    inv3(B, Bi, status);
-    mv3(Bi, r, x);
-  }
-}
-
-__device__ __forceinline__ void rt_pcr_scalar(int c, int l, int T, int L, bool act, double &A, double &B,
-                                              double &C, double &r, double *lds, double &x, int *status) {
-  const int nt = T * L, t = c * L + l;
-  double *sA = lds, *sC = lds + nt, *sR = lds + 2 * nt;
-  for (int h = 1; h < T; h *= 2) {
-    if (act) {
-      if (!(B != 0.0)) status[ST_SINGULAR] = 1;
-      const double ib = rcp_nr(B);
-      sA[t] = A * ib;
-      sC[t] = C * ib;
-      sR[t] = r * ib;
-    }
-    __syncthreads();
-    if (act) {
-      double nA = 0.0, nC = 0.0;
-      if (c - h >= 0) {
-        const int u = (c - h) * L + l;
-        nA = -A * sA[u];
-        B -= A * sC[u];
-        r -= A * sR[u];
-      }
-      if (c + h < T) {
-        const int u = (c + h) * L + l;
-        nC = -C * sC[u];
-        B -= C * sA[u];
-        r -= C * sR[u];
-      }
-      A = nA;
-      C = nC;
-    }
-    __syncthreads();
-  }
-  if (act) {
-    if (!(B != 0.0)) status[ST_SINGULAR] = 1;
-    x = r * rcp_nr(B);
-  }
-}
-
 // ------------------------------------------------------------ block lines --
-// The block lines [line0, line0 + L) of sweep D (line = a * np + b); LDS
-// 24 doubles per thread.
-// TR: the transposed system (adjoint): each chunk walks its rows once and
-// forms the transposed rows from them (TrWalk; u is then the plain source).
-template <int D, int PM, bool TR, class US>
-__device__ __forceinline__ void rt_block_lines(const Geo &g, const Mat &m, const US &u, const Fields &rhs,
-                                               const Out &o, long line0, double hs, double *lds,
-                                               int *status) {
-  const Families F = families(g, D);
-  const int n = F.n, T = rt_chunks<PM>(n), L = (int)blockDim.x / T;
-  const int t = threadIdx.x, c = t / L, l = t % L;
-  const long line = line0 + l;
-  const bool act = c < T && line < F.nb;
-  int pa = 0, pb = 0;
-  if (act) { pa = (int)(line / g.np); pb = (int)(line % g.np); }
-  if (act && c == 0 && o.mode == 0) zero_bnd<D>(g, o.x, pa, pb);
-  const int a0 = c * PM;
-  const int len = act ? min(PM, n - a0) : 0;
-  double Cm[PM - 1][9], Em[PM - 1][9], Ym[PM - 1][3];
-  // structural non-zeros of the row blocks (transposed rows: L = U^T, U = L^T)
-  constexpr unsigned mL = TR ? nz_tr(NZ_U) : NZ_L, mU = TR ? nz_tr(NZ_L) : NZ_U;
-  TrWalk<D> tw;
-  if constexpr (TR) {
-    if (act) tw.init(g, m, u, rhs, pa, pb, a0, n, 0, hs);
-  }
-  // a zero pivot is recorded after the loop: a store inside it would hold
-  // the next row's loads back
-  bool sing = false;
-  // 1. forward elimination over the interior rows with the left spike
-#pragma unroll
-  for (int q = 0; q < PM - 1; q++) {
-    if (q < len - 1) {
-      BRow R;
-      if constexpr (TR) tw.next(g, m, u, rhs, pa, pb, n, 0, hs, R);
-      else block_row<D>(g, m, u, rhs, pa, pb, a0 + q, n, 0, hs, R);
-      double Dp[9], rr[3], Lx[9], Ai[9];
-      if (q == 0) {
-#pragma unroll
-        for (int z = 0; z < 9; z++) Dp[z] = R.D[z];
-#pragma unroll
-        for (int z = 0; z < 3; z++) rr[z] = R.b[z];
-      } else {
-        double t9[9], t3[3];
-        mm3m<mL, NZ_ALL>(R.L, Cm[q - 1], t9);
-#pragma unroll
-        for (int z = 0; z < 9; z++) Dp[z] = R.D[z] - t9[z];
-        mv3m<mL>(R.L, Ym[q - 1], t3);
-#pragma unroll
-        for (int z = 0; z < 3; z++) rr[z] = R.b[z] - t3[z];
-        mm3m<mL, NZ_ALL>(R.L, Em[q - 1], t9);
-#pragma unroll
-        for (int z = 0; z < 9; z++) Lx[z] = -t9[z];
-      }
-      sing |= inv3q(Dp, Ai);
-      mm3m<NZ_ALL, mU>(Ai, R.U, Cm[q]);
-      mv3(Ai, rr, Ym[q]);
-      if (q == 0) mm3m<NZ_ALL, mL>(Ai, R.L, Em[q]);
-      else mm3(Ai, Lx, Em[q]);
-    }
-  }
-  if (sing) status[ST_SINGULAR] = 1;
-  BRow S;  // separator row (last row of the chunk)
-  if (act) {
-    if constexpr (TR) tw.next(g, m, u, rhs, pa, pb, n, 0, hs, S);
-    else block_row<D>(g, m, u, rhs, pa, pb, a0 + len - 1, n, 0, hs, S);
-  }
-  // backward sweep: (Y, E, C) -> (g, V, W)
-#pragma unroll
-  for (int q = PM - 2; q >= 0; q--) {
-    if (q == len - 2) {
-#pragma unroll
-      for (int z = 0; z < 9; z++) { Em[q][z] = -Em[q][z]; Cm[q][z] = -Cm[q][z]; }
-    } else if (q < len - 2) {
-      double t9[9], t3[3];
-      mv3(Cm[q], Ym[q + 1], t3);
-#pragma unroll
-      for (int z = 0; z < 3; z++) Ym[q][z] -= t3[z];
-      mm3(Cm[q], Em[q + 1], t9);
-#pragma unroll
-      for (int z = 0; z < 9; z++) Em[q][z] = -Em[q][z] - t9[z];
-      mm3(Cm[q], Cm[q + 1], t9);
-#pragma unroll
-      for (int z = 0; z < 9; z++) Cm[q][z] = -t9[z];
-    }
-  }
-  // 2. the first interior row of every chunk to the chunk before it
-  const int nt = T * L;
-  double *sG = lds, *sV = lds + 3 * nt, *sW = lds + 12 * nt, *sL = lds + 21 * nt;
-  if (act) {
-    sL[t] = (double)len;
-    if (len >= 2) {
-#pragma unroll
-      for (int z = 0; z < 3; z++) sG[t * 3 + z] = Ym[0][z];
-#pragma unroll
-      for (int z = 0; z < 9; z++) { sV[t * 9 + z] = Em[0][z]; sW[t * 9 + z] = Cm[0][z]; }
-    }
-  }
-  __syncthreads();
-  double A[9], B[9], Cc[9], r[3];
-  if (act) {
-    const int tn = t + L;  // chunk c + 1 of the same line
-    const int nlen = c + 1 < T ? (int)sL[tn] : 0;
-    double Gl[3] = {0, 0, 0}, Vl[9], Wl[9];
-#pragma unroll
-    for (int z = 0; z < 9; z++) { Vl[z] = 0.0; Wl[z] = 0.0; }
-#pragma unroll
-    for (int q = 0; q < PM - 1; q++)
-      if (q == len - 2) {
-#pragma unroll
-        for (int z = 0; z < 3; z++) Gl[z] = Ym[q][z];
-#pragma unroll
-        for (int z = 0; z < 9; z++) { Vl[z] = Em[q][z]; Wl[z] = Cm[q][z]; }
-      }
-    double t9[9], t3[3];
-#pragma unroll
-    for (int z = 0; z < 9; z++) B[z] = S.D[z];
-#pragma unroll
-    for (int z = 0; z < 3; z++) r[z] = S.b[z];
-    if (len >= 2) {
-      mm3m<mL, NZ_ALL>(S.L, Vl, A);
-      mm3m<mL, NZ_ALL>(S.L, Wl, t9);
-#pragma unroll
-      for (int z = 0; z < 9; z++) B[z] += t9[z];
-      mv3m<mL>(S.L, Gl, t3);
-#pragma unroll
-      for (int z = 0; z < 3; z++) r[z] -= t3[z];
-    } else {
-#pragma unroll
-      for (int z = 0; z < 9; z++) A[z] = S.L[z];
-    }
-    if (nlen >= 2) {
-      mm3m<mU, NZ_ALL>(S.U, &sV[tn * 9], t9);
-#pragma unroll
-      for (int z = 0; z < 9; z++) B[z] += t9[z];
-      mm3m<mU, NZ_ALL>(S.U, &sW[tn * 9], Cc);
-      mv3m<mU>(S.U, &sG[tn * 3], t3);
-#pragma unroll
-      for (int z = 0; z < 3; z++) r[z] -= t3[z];
-    } else {
-#pragma unroll
-      for (int z = 0; z < 9; z++) Cc[z] = S.U[z];
-    }
-  }
-  __syncthreads();  // the exchange area is reused by the reduction
-  double xs[3] = {0, 0, 0};
-  rt_pcr_block(c, l, T, L, act, A, B, Cc, r, lds, xs, status);
-  // 3. fill in the interior rows from the separators on either side
-  double *sX = lds + 21 * nt;
-  if (act) {
-#pragma unroll
-    for (int z = 0; z < 3; z++) sX[t * 3 + z] = xs[z];
-  }
-  __syncthreads();
-  if (!act) return;
-  double xl[3] = {0, 0, 0};
-  if (c > 0) {
-#pragma unroll
-    for (int z = 0; z < 3; z++) xl[z] = sX[(t - L) * 3 + z];
-  }
-#pragma unroll
-  for (int q = 0; q < PM - 1; q++) {
-    if (q < len - 1) {
-      double v[3], t3[3];
-      mv3(Em[q], xl, v);
-      mv3(Cm[q], xs, t3);
-#pragma unroll
-      for (int z = 0; z < 3; z++) v[z] += Ym[q][z] + t3[z];
-      block_store<D>(g, o, pa, pb, a0 + q, v);
-    }
-  }
-  block_store<D>(g, o, pa, pb, a0 + len - 1, xs);
-}
-
-// ------------------------------------------- block lines, plain and pert --
 // The block lines [line0, line0 + L) of sweep D with every input of a chunk's
 // rows loaded before the first row is eliminated (rows_fast.hpp); mode 0.
-// W: a forced pass, whose ghosts across a wall are 2 g - u (the r lines read
-// none); PT: perturbation-pressure form.  Byte offsets in 32 bits (off32_ok).
-template <int D, int PM, bool W, bool PT>
-__device__ __forceinline__ void rt_block_fast(const PassArgs &a, unsigned line0, double *lds) {
+// TR: the transposed systems (adjoint), whose rows take blocks of the rows on
+// either side, so a chunk loads one more row at each end; W: a forced pass,
+// whose ghosts across a wall are 2 g - u (the r lines read none); PT:
+// perturbation-pressure form.  Byte offsets in 32 bits (off32_ok).
+template <int D, int PM, bool TR, bool W, bool PT>
+__device__ __forceinline__ void rt_block_lines(const PassArgs &a, unsigned line0, double *lds) {
   const Geo &g = a.g;
   const Mat &m = a.m;
   const double hs = a.tau;
@@ -332,63 +78,68 @@ __device__ __forceinline__ void rt_block_fast(const PassArgs &a, unsigned line0,
   const double *u_r = a.u.a[F_UR], *u_t = a.u.a[F_UT], *u_f = a.u.a[F_UF];
   const double *mt = D == 0 ? g.mr : g.mt;
   // per row what its coefficients need, P and T one cell further: held from
-  // here to the row's elimination
-  double gG[PM], gGG[PM], gTR[PM], P[PM + 1], Te[PM + 1], b0[PM], b1[PM], b2[PM];
-  double uw[PM + 1];  // the line's own velocity on the faces before row 0 .. after row PM - 1
+  // here to the row's elimination (row q at index q + X)
+  constexpr int X = TR ? 1 : 0, NQ = PM + 2 * X;
+  double gG[NQ], gGG[NQ], gTR[NQ], P[NQ + 1], Te[NQ + 1], b0[PM], b1[PM], b2[PM];
+  double uw[NQ + 1];  // the line's own velocity on the faces around the rows
+  // line index of row q, of its faces and of its neighbours; fillers and rows
+  // past the ends read the nearest
+  auto row = [&](int q) { return (unsigned)(TR ? min(max(s0 + q, 0), n - 1) : max(s0 + q, 0)); };
+  auto face = [&](int q) { return (unsigned)(TR ? min(max(s0 + q, 0), n) : max(s0 + q, 0)); };
   {
-    // offsets of row q (fillers read row 0)
-    auto row = [&](int q) { return (unsigned)max(s0 + q, 0); };
     const double irk = D == 0 ? 0.0 : g.irc[pa];
     const double ctk = D == 0 ? g.ctc[pa] : 0.0, isk = D == 0 ? g.isc[pa] : 0.0;
     if constexpr (D == 0) {
 #pragma unroll
-      for (int q = 0; q <= PM; q++) uw[q] = ldo(u_r, oC + row(q) * sC);
+      for (int q = 0; q <= NQ; q++) uw[q] = ldo(u_r, oC + face(q - X) * sC);
     } else {
 #pragma unroll
-      for (int q = 0; q <= PM; q++) uw[q] = ldo(u_t, oT + row(q) * sT);
+      for (int q = 0; q <= NQ; q++) uw[q] = ldo(u_t, oT + face(q - X) * sT);
     }
     const unsigned up = 8u * (unsigned)(g.nt * g.np);  // one r plane of u_r
-    double va[PM + 2];  // D 1: the centre-averaged u_r of rows -1 .. PM
-    double tim[PM + 1], tip[PM + 1];  // D 1: u_theta on the planes i - 1, i + 1
+    double va[NQ + 2];  // D 1: the centre-averaged u_r of the rows and one more at each end
+    double tim[NQ + 1], tip[NQ + 1];  // D 1: u_theta on the planes i - 1, i + 1
     if constexpr (D == 1) {
       const double sgl = g.pole_lo ? 1.0 : -1.0, sgh = g.pole_hi ? 1.0 : -1.0;
 #pragma unroll
-      for (int q = -1; q <= PM; q++) {
-        const int s = s0 + q;
+      for (int q = 0; q < NQ + 2; q++) {
+        const int s = s0 + q - 1 - X;
         const unsigned o = oC + (unsigned)min(max(s, 0), n - 1) * sC;
         const double v = 0.5 * (ldo(u_r, o) + ldo(u_r, o + up));
-        va[q + 1] = s < 0 ? sgl * v : (s >= n ? sgh * v : v);
+        va[q] = s < 0 ? sgl * v : (s >= n ? sgh * v : v);
         if constexpr (W) {
           const double *w = s < 0 ? (g.pole_lo ? nullptr : a.wall.ur_t1) : (s >= n && !g.pole_hi ? a.wall.ur_t2 : nullptr);
-          if (w) va[q + 1] += w[(long)pa * g.np + k] + w[(long)(pa + 1) * g.np + k];
+          if (w) va[q] += w[(long)pa * g.np + k] + w[(long)(pa + 1) * g.np + k];
         }
       }
       const unsigned pT = 8u * (unsigned)((g.nt + 1) * g.np);
       const bool lo = pa == 0, hi = pa == g.nr - 1;
       const unsigned om = lo ? oT : oT - pT, op = hi ? oT : oT + pT;
 #pragma unroll
-      for (int q = 0; q <= PM; q++) {
-        const unsigned ro = row(q) * sT;
+      for (int q = 0; q <= NQ; q++) {
+        const unsigned ro = face(q - X) * sT;
         const double x = ldo(u_t, om + ro), y = ldo(u_t, op + ro);
         tim[q] = lo ? -x : x;
         tip[q] = hi ? -y : y;
         if constexpr (W) {
-          const long f = (long)row(q) * g.np + k;
+          const long f = (long)face(q - X) * g.np + k;
           if (lo) tim[q] += 2.0 * wallv(a.wall.ut_r1, f);
           if (hi) tip[q] += 2.0 * wallv(a.wall.ut_r2, f);
         }
       }
     }
 #pragma unroll
-    for (int q = 0; q < PM; q++) {
-      const unsigned s = row(q), o = oC + s * sC;
+    for (int q = 0; q < NQ; q++) {
+      const unsigned s = row(q - X), o = oC + s * sC;
       const unsigned of = oF + s * sF;
       const double f0 = ldo(u_f, of), f1 = ldo(u_f, of + (unsigned)dF);
       P[q] = ldo(a.u.a[F_P], o);
       Te[q] = ldo(a.u.a[F_T], o);
-      b0[q] = ldo(a.rhs.p, o);
-      b1[q] = ldo(a.rhs.T, o);
-      b2[q] = D == 0 ? ldo(a.rhs.ur, o + sC) : ldo(a.rhs.ut, oT + s * sT + sT);
+      if (q >= X && q < PM + X) {
+        b0[q - X] = ldo(a.rhs.p, o);
+        b1[q - X] = ldo(a.rhs.T, o);
+        b2[q - X] = D == 0 ? ldo(a.rhs.ur, o + sC) : ldo(a.rhs.ut, oT + s * sT + sT);
+      }
       if constexpr (D == 0) {
         const unsigned ot = oT + s * sT;
         const double t0 = ldo(u_t, ot), t1 = ldo(u_t, ot + 8u * (unsigned)g.np), ir = ldo(mt, 64u * s + 40u);
@@ -415,18 +166,19 @@ __device__ __forceinline__ void rt_block_fast(const PassArgs &a, unsigned line0,
       P[q] += m.pinf;
     }
     {
-      const unsigned s = (unsigned)min(s0 + PM, n - 1), o = oC + s * sC;
-      P[PM] = ldo(a.u.a[F_P], o);
-      Te[PM] = ldo(a.u.a[F_T], o);
-      if constexpr (PT) P[PM] += a.pref[D == 0 ? (int)s : pa];
-      P[PM] += m.pinf;
+      const unsigned s = (unsigned)min(s0 + PM + X, n - 1), o = oC + s * sC;
+      P[NQ] = ldo(a.u.a[F_P], o);
+      Te[NQ] = ldo(a.u.a[F_T], o);
+      if constexpr (PT) P[NQ] += a.pref[D == 0 ? (int)s : pa];
+      P[NQ] += m.pinf;
     }
   }
   const double irl = D == 0 ? 1.0 : g.irc[pa];
   const double h = D == 0 ? g.idr : irl * g.idt;
+  // row q of the line (TR: -1 .. PM)
   auto assemble = [&](int q, FRow &R) {
-    const int s = s0 + q;
-    const unsigned o = 64u * (unsigned)max(s, 0);
+    const int s = s0 + q, z = q + X;
+    const unsigned o = 64u * row(q);
     RowMetric x;
     const double2 d = ldo2(mt, o), w = ldo2(mt, o + 16);
     x.h = h;
@@ -439,28 +191,50 @@ __device__ __forceinline__ void rt_block_fast(const PassArgs &a, unsigned line0,
     x.w0 = w.y * w2;
     x.wm = ldo(mt, o + 32) * w2;
     RowIn in;
-    in.vel = 0.5 * (uw[q] + uw[q + 1]);
-    in.un = uw[q + 1];
-    in.G = D == 0 ? (uw[q + 1] - uw[q]) * g.idr : gG[q];
-    in.tr = in.G + gTR[q];
-    in.gg = gGG[q];
-    in.P = P[q];
-    in.T = Te[q];
-    in.irho = 2.0 * m.Rg * Te[q] * Te[q + 1] * rcp_nr(P[q] * Te[q + 1] + P[q + 1] * Te[q]);
-    in.b0 = b0[q];
-    in.b1 = b1[q];
-    in.b2 = b2[q];
-    frow(m, hs, in, x, s == 0, q == PM - 1 && cc == T - 1, q == PM - 2 && cc == T - 1, s >= 0, R);
+    in.vel = 0.5 * (uw[z] + uw[z + 1]);
+    in.un = uw[z + 1];
+    in.G = D == 0 ? (uw[z + 1] - uw[z]) * g.idr : gG[z];
+    in.tr = in.G + gTR[z];
+    in.gg = gGG[z];
+    in.P = P[z];
+    in.T = Te[z];
+    in.irho = 2.0 * m.Rg * Te[z] * Te[z + 1] * rcp_nr(P[z] * Te[z + 1] + P[z + 1] * Te[z]);
+    const bool own = q >= 0 && q < PM;
+    in.b0 = own ? b0[own ? q : 0] : 0.0;
+    in.b1 = own ? b1[own ? q : 0] : 0.0;
+    in.b2 = own ? b2[own ? q : 0] : 0.0;
+    // the end rows of the line: row PM - 1 of the last chunk and the one before
+    // it (TR: also as the row before a chunk)
+    const bool end = q == PM - 1 && cc == T - 1;
+    const bool before = TR ? s == n - 2 : (q == PM - 2 && cc == T - 1);
+    frow(m, hs, in, x, s == 0, end, before, TR || s >= 0, R);
+  };
+  using Row = std::conditional_t<TR, TRow, FRow>;
+  FRow M_, R_;  // TR: the rows before and at the one in turn
+  if constexpr (TR) {
+    assemble(-1, M_);
+    assemble(0, R_);
+  }
+  auto next = [&](int q, Row &R) {
+    if constexpr (TR) {
+      FRow N_;
+      assemble(q + 1, N_);
+      trow(M_, R_, N_, s0 + q == 0, q == PM - 1 && cc == T - 1, s0 + q >= 0, R);
+      M_ = R_;
+      R_ = N_;
+    } else {
+      assemble(q, R);
+    }
   };
   Chunk<PM> ch;
 #pragma unroll
   for (int q = 0; q < PM - 1; q++) {
-    FRow R;
-    assemble(q, R);
+    Row R;
+    next(q, R);
     ch.eliminate(q, R);
   }
-  FRow S;
-  assemble(PM - 1, S);
+  Row S;
+  next(PM - 1, S);
   ch.back();
   double *rec = lds + (size_t)t * SEP_REC;
   if (c < T) {
@@ -517,16 +291,17 @@ __device__ __forceinline__ void rt_block_fast(const PassArgs &a, unsigned line0,
   }
 }
 
-// ------------------------------------------ scalar lines, plain and pert --
+// ----------------------------------------------------------- scalar lines --
 // The lines [line0, line0 + L) of both scalar families in one form: the row
 // of a line reads the two cells on either side of its face (their mean
 // density) and the sum of the sweep direction's velocity over the same two
 // columns on the row's two faces, so the families differ in byte offsets
 // only.  Inputs of all rows of a chunk are loaded first, chunks are aligned to
 // their ends (fillers: a = -1, b = 1, c = 0, r = 0), as on the block lines.
-// LDS 4 doubles per thread; mode 0.
-template <int D, int PM, bool PT>
-__device__ __forceinline__ void rt_scalar_fast(const PassArgs &a, int fam, unsigned line0, double *lds) {
+// TR: the transposed systems, row s (c_{s-1}, b_s, a_{s+1}).  LDS 4 doubles per
+// thread; mode 0.
+template <int D, int PM, bool TR, bool PT>
+__device__ __forceinline__ void rt_scalar_lines(const PassArgs &a, int fam, unsigned line0, double *lds) {
   const Geo &g = a.g;
   const Mat &m = a.m;
   const double hs = a.tau;
@@ -579,16 +354,18 @@ __device__ __forceinline__ void rt_scalar_fast(const PassArgs &a, int fam, unsig
   if (D == 1 && fam == 0) { sglo = g.pole_lo ? 1.0 : -1.0; sghi = g.pole_hi ? 1.0 : -1.0; }
   double ra[PM], rb[PM], rc[PM], rr[PM];
   {
-    double vs[PM + 1];
+    constexpr int X = TR ? 1 : 0, NQ = PM + 2 * X;
+    double vs[NQ + 1], ca[NQ], cn[NQ];
 #pragma unroll
-    for (int q = 0; q <= PM; q++) {
-      const unsigned o = (unsigned)max(s0 + q, 0) * sV;
+    for (int q = 0; q <= NQ; q++) {
+      const int f = s0 + q - X;
+      const unsigned o = (unsigned)(TR ? min(max(f, 0), n) : max(f, 0)) * sV;
       vs[q] = ldo(V, vA + o) + ldo(V, vB + o);
     }
 #pragma unroll
-    for (int q = 0; q < PM; q++) {
-      const int s = s0 + q;
-      const unsigned sc = (unsigned)max(s, 0), o = sc * sC;
+    for (int z = 0; z < NQ; z++) {
+      const int q = z - X, s = s0 + q;
+      const unsigned sc = (unsigned)(TR ? min(max(s, 0), n - 1) : max(s, 0)), o = sc * sC;
       double Pa = ldo(a.u.a[F_P], oA + o), Pb = ldo(a.u.a[F_P], oB + o);
       const double Ta = ldo(a.u.a[F_T], oA + o), Tb = ldo(a.u.a[F_T], oB + o);
       if constexpr (PT) {
@@ -600,16 +377,29 @@ __device__ __forceinline__ void rt_scalar_fast(const PassArgs &a, int fam, unsig
       Pb += m.pinf;
       const double2 d = ldo2(mt, 64u * sc);
       const double nu = hn * Ta * Tb * rcp_nr(Pa * Tb + Pb * Ta);  // tau/2 mu / rho times h
-      const double ua = hv * (vs[q] + vs[q + 1]), qp = nu * d.x, qm = nu * d.y;
-      double ca = qm - ua, cb = qp - qm, cn = ua - qp, r = ldo(Rh, oX + sc * sX);
-      if (s == 0) { cb += sglo * ca; ca = 0.0; }
-      if (q == PM - 1 && cc == T - 1) { cb += sghi * cn; cn = 0.0; }
+      const double ua = hv * (vs[z] + vs[z + 1]), qp = nu * d.x, qm = nu * d.y;
+      ca[z] = qm - ua;
+      cn[z] = ua - qp;
+      if (q < 0 || q >= PM) continue;
+      double cb = qp - qm;
+      const double r = ldo(Rh, oX + sc * sX);
+      if (s == 0) { cb += sglo * ca[z]; if (!TR) ca[z] = 0.0; }
+      if (q == PM - 1 && cc == T - 1) { cb += sghi * cn[z]; if (!TR) cn[z] = 0.0; }
       cb += 1.0;
       const bool real = s >= 0;
-      ra[q] = real ? ca : -1.0;
       rb[q] = real ? cb : 1.0;
-      rc[q] = real ? cn : 0.0;
       rr[q] = real ? r : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < PM; q++) {
+      const int s = s0 + q;
+      double lo = ca[q + X], up = cn[q + X];
+      if constexpr (TR) {  // c_{s-1}, a_{s+1}; none past the ends
+        lo = s == 0 ? 0.0 : cn[q];
+        up = q == PM - 1 && cc == T - 1 ? 0.0 : ca[q + 2];
+      }
+      ra[q] = s >= 0 ? lo : -1.0;
+      rc[q] = s >= 0 ? up : 0.0;
     }
   }
   // eliminate: x_q = Y_q - C_q x_{q+1} - E_q x_left, then to (g, V, W)
@@ -676,102 +466,6 @@ __device__ __forceinline__ void rt_scalar_fast(const PassArgs &a, int fam, unsig
   }
 }
 
-// ----------------------------------------------------------- scalar lines --
-// Lines [line0, line0 + L) of scalar family FAM of sweep D; LDS 4 doubles
-// per thread.
-template <int D, int FAM, int PM, bool TR, class US>
-__device__ __forceinline__ void rt_scalar_lines(const Geo &g, const Mat &m, const US &u, const Fields &rhs,
-                                                const Out &o, long line0, double hs, double *lds,
-                                                int *status) {
-  const Families F = families(g, D);
-  const int n = F.n, T = rt_chunks<PM>(n), L = (int)blockDim.x / T;
-  const int t = threadIdx.x, c = t / L, l = t % L;
-  const long line = line0 + l;
-  const long nl = FAM == 0 ? F.na : F.nbb;
-  const bool act = c < T && line < nl;
-  const int nkf = g.periodic ? g.np : g.np - 1, kf0 = g.periodic ? 0 : 1;
-  int pa = FAM == 0 ? 1 : 0, pb = FAM == 0 ? 0 : kf0;
-  if (act) {
-    if (FAM == 0) { pa = 1 + (int)(line / g.np); pb = (int)(line % g.np); }
-    else { pa = (int)(line / nkf); pb = kf0 + (int)(line % nkf); }
-  }
-  int ofid;
-  if (D == 0) ofid = FAM == 0 ? F_UT : F_UF;
-  else ofid = FAM == 0 ? F_UR : F_UF;
-  const int a0 = c * PM;
-  const int len = act ? min(PM, n - a0) : 0;
-  double Cm[PM - 1], Em[PM - 1], Ym[PM - 1];
-  long xi;
-  double *arr;
-  TrWalkS<D, FAM> tw;
-  if constexpr (TR) {
-    if (act) tw.init(g, m, u, rhs, pa, pb, a0, n, 0, hs);
-  }
-#pragma unroll
-  for (int q = 0; q < PM - 1; q++) {
-    if (q < len - 1) {
-      SRow R;
-      if constexpr (TR) tw.next(g, m, u, rhs, pa, pb, n, 0, hs, R);
-      else scalar_row<D, FAM>(g, m, u, rhs, pa, pb, a0 + q, n, 0, hs, R, xi, arr);
-      double dp = R.b, rr = R.r, lx = R.a;
-      if (q > 0) { dp -= R.a * Cm[q - 1]; rr -= R.a * Ym[q - 1]; lx = -R.a * Em[q - 1]; }
-      if (!(dp != 0.0)) status[ST_SINGULAR] = 1;
-      const double id = rcp_nr(dp);
-      Cm[q] = R.c * id;
-      Ym[q] = rr * id;
-      Em[q] = lx * id;
-    }
-  }
-  SRow S{0, 1, 0, 0};
-  if (act) {
-    if constexpr (TR) tw.next(g, m, u, rhs, pa, pb, n, 0, hs, S);
-    else scalar_row<D, FAM>(g, m, u, rhs, pa, pb, a0 + len - 1, n, 0, hs, S, xi, arr);
-  }
-#pragma unroll
-  for (int q = PM - 2; q >= 0; q--) {
-    if (q == len - 2) { Em[q] = -Em[q]; Cm[q] = -Cm[q]; }
-    else if (q < len - 2) {
-      Ym[q] -= Cm[q] * Ym[q + 1];
-      Em[q] = -Em[q] - Cm[q] * Em[q + 1];
-      Cm[q] = -Cm[q] * Cm[q + 1];
-    }
-  }
-  const int nt = T * L;
-  double *sG = lds, *sV = lds + nt, *sW = lds + 2 * nt, *sL = lds + 3 * nt;
-  if (act) {
-    sL[t] = (double)len;
-    if (len >= 2) { sG[t] = Ym[0]; sV[t] = Em[0]; sW[t] = Cm[0]; }
-  }
-  __syncthreads();
-  double A = 0.0, B = 1.0, C = 0.0, r = 0.0;
-  if (act) {
-    const int tn = t + L;
-    const int nlen = c + 1 < T ? (int)sL[tn] : 0;
-    double Gl = 0.0, Vl = 0.0, Wl = 0.0;
-#pragma unroll
-    for (int q = 0; q < PM - 1; q++)
-      if (q == len - 2) { Gl = Ym[q]; Vl = Em[q]; Wl = Cm[q]; }
-    B = S.b;
-    r = S.r;
-    if (len >= 2) { A = S.a * Vl; B += S.a * Wl; r -= S.a * Gl; }
-    else A = S.a;
-    if (nlen >= 2) { B += S.c * sV[tn]; C = S.c * sW[tn]; r -= S.c * sG[tn]; }
-    else C = S.c;
-  }
-  __syncthreads();
-  double xs = 0.0;
-  rt_pcr_scalar(c, l, T, L, act, A, B, C, r, lds, xs, status);
-  double *sX = lds + 3 * nt;
-  if (act) sX[t] = xs;
-  __syncthreads();
-  if (!act) return;
-  const double xl = c > 0 ? sX[t - L] : 0.0;
-#pragma unroll
-  for (int q = 0; q < PM - 1; q++)
-    if (q < len - 1) put(o, ofid, scalar_index<D, FAM>(g, pa, pb, a0 + q), Ym[q] + Em[q] * xl + Cm[q] * xs);
-  put(o, ofid, scalar_index<D, FAM>(g, pa, pb, a0 + len - 1), xs);
-}
-
 // ------------------------------------------------------------ the passes --
 
 // pm: rows per thread on the block lines
@@ -798,18 +492,16 @@ __host__ __device__ inline unsigned rt_scalar_wgs(const Geo &g, int d, unsigned 
 // workgroups [0, nbw), then the scalar lines.  COMB: workgroups numbered as
 // for PART 2 whatever the part (a batched launch's member table counts both
 // kinds), those of the other part leaving at once; else PART 1 numbers the
-// scalar workgroups from 0.  W: a forced pass.
+// scalar workgroups from 0.
 template <int D, int PM, int PART, bool W = false, bool TR = false, bool PT = false, bool COMB = false>
 __device__ __forceinline__ void rt_body(const PassArgs &a, unsigned w, double *lds) {
   const Geo &g = a.g;
-  decltype(auto) u = SrcSel<W, PT>::get(a);  // the plain source when TR
   const unsigned bs = blockDim.x;
   const unsigned nbw = (PART == 1 && !COMB) ? 0u : rt_block_wgs(g, D, bs, PM);
   if (w < nbw) {
     if constexpr (PART != 1) {
       const unsigned L = bs / (unsigned)rt_chunks<PM>(families(g, D).n);
-      if constexpr (!TR) rt_block_fast<D, PM, W, PT>(a, w * L, lds);
-      else rt_block_lines<D, PM, TR>(g, a.m, u, a.rhs, a.o, (long)w * L, a.tau, lds, a.status);
+      rt_block_lines<D, PM, TR, W, PT>(a, w * L, lds);
     }
     return;
   }
@@ -817,9 +509,7 @@ __device__ __forceinline__ void rt_body(const PassArgs &a, unsigned w, double *l
     const unsigned w2 = w - nbw;
     const unsigned L = bs / (unsigned)rt_chunks<RT_PMS>(families(g, D).n);
     const unsigned nwa = rt_scalar_wgs_a(g, D, bs);
-    if constexpr (!TR) rt_scalar_fast<D, RT_PMS, PT>(a, w2 < nwa ? 0 : 1, (w2 < nwa ? w2 : w2 - nwa) * L, lds);
-    else if (w2 < nwa) rt_scalar_lines<D, 0, RT_PMS, TR>(g, a.m, u, a.rhs, a.o, (long)w2 * L, a.tau, lds, a.status);
-    else rt_scalar_lines<D, 1, RT_PMS, TR>(g, a.m, u, a.rhs, a.o, (long)(w2 - nwa) * L, a.tau, lds, a.status);
+    rt_scalar_lines<D, RT_PMS, TR, PT>(a, w2 < nwa ? 0 : 1, (w2 < nwa ? w2 : w2 - nwa) * L, lds);
   }
 }
 
@@ -854,7 +544,7 @@ __global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_partP(Pas
 
 // transposed systems (adjoint), one grid
 template <int D, int PM, int PART>
-__global__ void __launch_bounds__(256) k_rt_partT(PassArgs a) {
+__global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_partT(PassArgs a) {
   extern __shared__ double lds[];
   rt_body<D, PM, PART, false, true>(a, xcd_contiguous(blockIdx.x, gridDim.x), lds);
 }
@@ -938,8 +628,8 @@ void launch_rt_pert(int d, const PassArgs &a, unsigned threads, hipStream_t st) 
 }
 
 void launch_rt_T(int d, const PassArgs &a, unsigned threads, hipStream_t st) {
-  (void)d;  // r only: see the transposed solve's launcher in the host code
-  launch_rt_T_d<0, 4>(a, threads, st);
+  if (d == 0) launch_rt_T_d<0, 4>(a, threads, st);
+  else launch_rt_T_d<1, 4>(a, threads, st);
 }
 
 // Where the scalar lines of a two-ended sweep run apart, by the partitioned

@@ -2,8 +2,9 @@
 row off a multiple of the rows per chunk (fillers at the head of the first
 chunk), a single chunk, the longest line the default takes and the first it
 does not, workgroups that the lines do not fill, lanes whose lines straddle the
-phi ends of a plane, poles and walls.  Bar: the parity tests' 1e-11 relative
-L2 per field against the oracle."""
+phi ends of a plane, poles and walls.  Bars: the parity tests' 1e-11 relative
+L2 per field against the oracle; for the transposed systems, which take the
+same chunks, the adjoint tests' 1e-10 on <M^-T y, b> = <y, M^-1 b>."""
 import numpy as np
 import pytest
 import torch
@@ -42,7 +43,16 @@ def test_chunk_edges(nr, nt, np_, sphere):
             gg.get_status()
             e = compare(f"d={d} bs={bs}", dsw.to_host(x), ref)
             assert max(e.values()) <= 1e-11
+            hx = dsw.to_host(x)
             for k in ("ur", "ut"):  # boundary-normal faces are zero
-                h = dsw.to_host(x)[k]
-                faces = (h[0], h[-1]) if k == "ur" else (h[:, 0], h[:, -1])
+                faces = (hx[k][0], hx[k][-1]) if k == "ur" else (hx[k][:, 0], hx[k][:, -1])
                 assert not np.any(faces[0]) and not np.any(faces[1])
+            y = I.random_fields(spec, 51 + d)
+            gg.line_solve_T(d, dU0, tau, dsw.to_device(y), x)
+            torch.cuda.synchronize()
+            gg.get_status()
+            hz = dsw.to_host(x)
+            lhs = sum(float(np.vdot(hz[k], rhs[k])) for k in hx)
+            both = sum(float(np.vdot(y[k], hx[k])) for k in hx)
+            size = sum(float(np.linalg.norm(y[k]) * np.linalg.norm(hx[k])) for k in hx)
+            assert abs(lhs - both) <= 1e-10 * size, (d, bs)
