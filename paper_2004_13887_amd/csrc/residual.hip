@@ -196,15 +196,16 @@ __device__ __forceinline__ double forced(const S &s, int fid, long x, double F) 
   else return F;
 }
 
-// residual at the centre (i,j,k) and the three faces with the same indices
-template <class S, bool WRITE_UB>
+// residual at the centre (i,j,k) and the three faces with the same indices;
+// PART 0 .. 3: the centre or the r, theta or phi face alone
+template <class S, bool WRITE_UB, int PART = -1>
 __device__ __forceinline__ void residual_point(const Geo &g, const Mat &m, const S &s, const Diff &dU,
                                                double tau, const Fields &R, const Fields &Ub,
                                                int *status, int i, int j, int k) {
   if (k >= g.npf) return;
   const bool kc = k < g.np;
   double chk = 0.0; // the sum of this point's residuals: non-finite iff one of them is
-  if (i < g.nr && j < g.nt && kc) { // cell centre
+  if ((PART < 0 || PART == 0) && i < g.nr && j < g.nt && kc) { // cell centre
     const long x = idx_c(g, i, j, k);
     const double ubp = s.ld(F_P, x), ubT = s.ld(F_T, x);
     if (WRITE_UB) { Ub.p[x] = ubp; Ub.T[x] = ubT; }
@@ -221,21 +222,21 @@ __device__ __forceinline__ void residual_point(const Geo &g, const Mat &m, const
     R.T[x] = rT;
     chk = rp + rT;
   }
-  if (j < g.nt && kc) { // r face i
+  if ((PART < 0 || PART == 1) && j < g.nt && kc) { // r face i
     const long x = idx_r(g, i, j, k);
     if (WRITE_UB) Ub.ur[x] = s.ld(F_UR, x);
     const double r = (i >= 1 && i < g.nr) ? -dU.at(F_UR, x) - tau * forced(s, F_UR, x, F_ur(g, m, s, i, j, k)) : 0.0;
     R.ur[x] = r;
     chk += r;
   }
-  if (i < g.nr && kc) { // theta face j
+  if ((PART < 0 || PART == 2) && i < g.nr && kc) { // theta face j
     const long x = idx_t(g, i, j, k);
     if (WRITE_UB) Ub.ut[x] = s.ld(F_UT, x);
     const double r = (j >= 1 && j < g.nt) ? -dU.at(F_UT, x) - tau * forced(s, F_UT, x, F_ut(g, m, s, i, j, k)) : 0.0;
     R.ut[x] = r;
     chk += r;
   }
-  if (i < g.nr && j < g.nt) { // phi face k
+  if ((PART < 0 || PART == 3) && i < g.nr && j < g.nt) { // phi face k
     const long x = idx_f(g, i, j, k);
     if (WRITE_UB) Ub.uf[x] = s.ld(F_UF, x);
     const bool interior = g.periodic || (k >= 1 && k < g.np);
@@ -267,13 +268,24 @@ __host__ __device__ inline unsigned res_interior_blocks(const Geo &g, int bs) {
 // The (i, j) pairs the general launch takes when the interior launch runs:
 // the shell around the interior, i in {0, nr-1, nr} for every j, then j in
 // {0, nt-1, nt} for 1 <= i <= nr-2; else every pair.  Workgroups per pair:
-// the phi blocks.
+// the phi blocks, res_parts for each.
 __host__ __device__ inline unsigned res_shell_pairs(const Geo &g) {
   return 3u * (unsigned)(g.nt + 1) + 3u * (unsigned)(g.nr - 2);
 }
+__host__ __device__ inline unsigned res_pairs(const Geo &g, int bs) {
+  return res_interior_blocks(g, bs) ? res_shell_pairs(g) : (unsigned)(g.nt + 1) * (unsigned)(g.nr + 1);
+}
+// Workgroups that share a point of the general launch: one per kind of row
+// where that still leaves wave slots free, else one.  The four rows of a point
+// one after the other are four memory latencies: 13 us for the shell of
+// 32 x 32 x 16 cells against 6.5 split, 135 x 45 x 15 forced 26 against 13,
+// 128 x 64 x 32 12.9 against 8.5; but on the 360 x 180 x 40 and 512 x 256 x 128
+// spheres (3942 and 9192 workgroups) 25 and 46 us against 31 and 61 split.
+__host__ __device__ inline unsigned res_parts(const Geo &g, int bs) {
+  return (unsigned)res_nk(g, bs) * res_pairs(g, bs) * (unsigned)(bs / 64) <= 2048u ? 4u : 1u;
+}
 __host__ __device__ inline unsigned res_general_blocks(const Geo &g, int bs) {
-  const unsigned pairs = res_interior_blocks(g, bs) ? res_shell_pairs(g) : (unsigned)(g.nt + 1) * (unsigned)(g.nr + 1);
-  return (unsigned)res_nk(g, bs) * pairs;
+  return res_parts(g, bs) * (unsigned)res_nk(g, bs) * res_pairs(g, bs);
 }
 
 // the pair of workgroup pair number rest of the general launch
@@ -296,16 +308,22 @@ __device__ __forceinline__ void res_pair(const Geo &g, unsigned rest, bool shell
 // W: a forced pass (wall velocities and source term); PT: the
 // perturbation-pressure form
 template <bool W = false, bool PT = false>
-__device__ __forceinline__ void residual_body(const PassArgs &a, unsigned w) {
+__device__ __forceinline__ void residual_body(const PassArgs &a, unsigned w4) {
   const Geo &g = a.g;
   const int bs = (int)blockDim.x;
-  const unsigned nkb = (unsigned)res_nk(g, bs);
+  const unsigned nkb = (unsigned)res_nk(g, bs), parts = res_parts(g, bs);
+  const unsigned w = parts == 4 ? w4 >> 2 : w4, part = parts == 4 ? w4 & 3u : 4u;
   const unsigned kb = w % nkb, rest = w / nkb;
   int i, j;
   res_pair(g, rest, res_interior_blocks(g, bs) > 0, i, j);  // the shell where the interior launch does the rest
   decltype(auto) s = SrcSel<W, PT>::get(a);
-  residual_point<std::decay_t<decltype(s)>, false>(g, a.m, s, a.d, a.tau, a.R, Fields{}, a.status, i, j,
-                                                   (int)(kb * blockDim.x + threadIdx.x));
+  using S = std::decay_t<decltype(s)>;
+  const int k = (int)(kb * blockDim.x + threadIdx.x);
+  if (part == 0) residual_point<S, false, 0>(g, a.m, s, a.d, a.tau, a.R, Fields{}, a.status, i, j, k);
+  else if (part == 1) residual_point<S, false, 1>(g, a.m, s, a.d, a.tau, a.R, Fields{}, a.status, i, j, k);
+  else if (part == 2) residual_point<S, false, 2>(g, a.m, s, a.d, a.tau, a.R, Fields{}, a.status, i, j, k);
+  else if (part == 3) residual_point<S, false, 3>(g, a.m, s, a.d, a.tau, a.R, Fields{}, a.status, i, j, k);
+  else residual_point<S, false>(g, a.m, s, a.d, a.tau, a.R, Fields{}, a.status, i, j, k);
 }
 
 // residual_point for the interior launch (1 <= i <= nr-2, 1 <= j <= nt-2,

@@ -40,3 +40,40 @@ def test_residual_both_paths(name, odd):
     assert max(residual_errors(name, dsw.to_host(R), R_o, tau, w).values()) <= 1e-11
     for k, v in dsw.to_host(Ub).items():
         assert np.array_equal(v, Ub_o[k]), k
+
+
+@pytest.mark.parametrize("form", ["plain", "pert", "forced"])
+@pytest.mark.parametrize("nt", [120, 360])
+def test_shell_forms(nt, form):
+    """the residual's boundary shell with a workgroup per kind of row (120
+    theta rows) and with one for all of them (360): one step, K = 1"""
+    from helpers import random_wall
+    from paper_2004_13887_amd import dsw
+    spec = I.sector(3, nt, 200, 4e-4, 5e-4)
+    w = I.Workload("shell", spec, mach=1e-2, amplitude=0.5, steps=1, K=1, seed=611)
+    print(f"[shell] {spec.nr}x{nt}x{spec.np} {form}", flush=True)
+    U0, tau = I.initial_state(w)
+    og, om = oracle.Grid(*spec.args()), oracle.Material(*w.material.astuple())
+    gg = dsw.Grid.from_spec(spec, w.material)
+    out = gg.empty()
+    if form == "plain":
+        ref = oracle.split_step(og, om, U0, tau, 1)
+        gg.split_step(dsw.to_device(U0), out, tau, 1)
+    elif form == "pert":
+        pbar, Tbar = I.reference_column(spec, w.material, I.T0)
+        U0["p"] = np.ascontiguousarray(U0["p"] - pbar[:, None, None] + I.random_fields(spec, 612)["p"])
+        ref = oracle.split_step_pert(og, om, U0, pbar, Tbar, tau, 1)
+        gg.set_reference(pbar, Tbar)
+        gg.split_step_pert(dsw.to_device(U0), out, tau, 1)
+    else:
+        wall, src = random_wall(spec, 613, scale=3.0), I.random_fields(spec, 614)
+        ref = oracle.split_step(og, om, U0, tau, 1, wall0=wall, wall1=wall, src=src)
+        gg.split_step_forced(dsw.to_device(U0), out, tau, 1, src=dsw.to_device(src), wall0=dsw.to_device(wall),
+                             wall1=dsw.to_device(wall))
+    torch.cuda.synchronize()
+    gg.get_status()
+    h = dsw.to_host(out)
+    for k in h:
+        e = np.linalg.norm(h[k] - ref[k]) / np.linalg.norm(ref[k])
+        print(f"[shell] {form} {k}: {e:.2e}", flush=True)
+        assert e <= 1e-11, k
