@@ -1136,10 +1136,13 @@ void launch_phi_pass(int pm, const PassArgs &a, const Batch &b, unsigned blocks,
   else launch_phi_part<4>(a, b, dim3(blocks), dim3(threads), lds, st);
 }
 
-// From this many workgroups on, the block and the scalar lines run as two
-// launches (the scalar lines need half of the block lines' registers and a
-// third of their LDS); below it one launch runs both side by side.
-constexpr unsigned PHI_FAST_SPLIT = 1024;
+// From this many lanes on, the block and the scalar lines run as two launches
+// (the scalar lines need half of the block lines' registers and a third of
+// their LDS); below it one launch runs both side by side.  Measured, one launch
+// against two: 128 x 64 x 32 sphere (2^17 lanes) 17.9 / 22.2 us, 128 x 64 x 64
+// sector (2^18) 29.6 / 35.1, 256 x 128 x 32 (2^19) 54.9 / 58.8, 256 x 128 x 64
+// (2^20) 101 / 102; transposed 18.2 / 23.0, 38.2 / 41.6, 73.6 / 72.2, 131 / 126.
+constexpr unsigned PHI_SPLIT_LANES = 1u << 19;
 
 template <int PM, bool CYC, bool W, bool PT>
 static void launch_phi_fast(const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads, size_t lds,
@@ -1148,14 +1151,14 @@ static void launch_phi_fast(const PassArgs &a, const Batch &b, unsigned blocks, 
   const dim3 gr(blocks), half(blocks / 2), bl(threads);
   if (b.tab) {
     if constexpr (!W && !PT) {
-      if (blocks < PHI_FAST_SPLIT) {
+      if ((unsigned long)blocks * threads < PHI_SPLIT_LANES) {
         hipLaunchKernelGGL((k_phi_fastB<PM, 2, CYC>), gr, bl, lds, st, a, b);
       } else {
         hipLaunchKernelGGL((k_phi_fastB<PM, 0, CYC>), gr, bl, lds, st, a, b);
         hipLaunchKernelGGL((k_phi_fastB<PM, 1, CYC>), gr, bl, lds_s, st, a, b);
       }
     }
-  } else if (blocks < PHI_FAST_SPLIT) {
+  } else if ((unsigned long)blocks * threads < PHI_SPLIT_LANES) {
     hipLaunchKernelGGL((k_phi_fast<PM, 2, CYC, W, PT>), gr, bl, lds, st, a);
   } else {
     hipLaunchKernelGGL((k_phi_fast<PM, 0, CYC, W, PT>), half, bl, lds, st, a);
@@ -1202,7 +1205,7 @@ void launch_phi_pert(int pm, const PassArgs &a, unsigned blocks, unsigned thread
 template <int PM, bool CYC>
 static void launch_phi_fast_T(const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st) {
   const size_t lds = phi_fast_lds(threads), lds_s = sizeof(double) * 8 * (size_t)threads;
-  if (blocks < PHI_FAST_SPLIT) {
+  if ((unsigned long)blocks * threads < PHI_SPLIT_LANES) {
     hipLaunchKernelGGL((k_phi_fastT<PM, 2, CYC>), dim3(blocks), dim3(threads), lds, st, a);
     return;
   }
