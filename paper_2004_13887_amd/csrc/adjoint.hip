@@ -15,16 +15,9 @@
 // last bits of the result, may differ from run to run.
 #include "dsw_common.hpp"
 #include "dsw_internal.hpp"
-#include "rows.hpp"
+#include "rows_fast.hpp"
 
 namespace dsw {
-
-#ifndef DSW_ADJ_JT
-#define DSW_ADJ_JT 4   // theta rows per workgroup of the column-tiled reverse
-#endif
-#ifndef DSW_ADJ_SEG
-#define DSW_ADJ_SEG 8  // r planes per workgroup of the column-tiled reverse
-#endif
 
 // Scatter targets.  add(g, fid, i, j, k, v) adds v to array fid at its own
 // index triple (cells: centre (i, j, k); r faces: (face, j, k); theta faces:
@@ -33,6 +26,7 @@ namespace dsw {
 // GAcc: FP64 atomics straight into the global arrays.
 struct GAcc {
   Fields A;
+  static constexpr bool RAW = false;
   __device__ __forceinline__ void add(const Geo &g, int fid, int i, int j, int k, double v) const {
     if (g.periodic) k = wrapk(g, k);
     double *p;
@@ -49,6 +43,7 @@ struct GAcc {
 
 template <class Acc>
 __device__ __forceinline__ void sC(const Geo &g, const Acc &A, int fid, int i, int j, int k, double v) {
+  if constexpr (Acc::RAW) return A.add(g, fid, i, j, k, v);
   i = clampi(i, 0, g.nr - 1);
   j = clampi(j, 0, g.nt - 1);
   if (!g.periodic) k = clampi(k, 0, g.np - 1);
@@ -56,6 +51,7 @@ __device__ __forceinline__ void sC(const Geo &g, const Acc &A, int fid, int i, i
 }
 template <class Acc>
 __device__ __forceinline__ void sR(const Geo &g, const Acc &A, int f, int j, int k, double v) {
+  if constexpr (Acc::RAW) return A.add(g, F_UR, f, j, k, v);
   double sg = 1.0;
   if (!g.periodic && (k < 0 || k >= g.np)) { sg = -sg; k = k < 0 ? 0 : g.np - 1; }
   if (j < 0) { if (!g.pole_lo) sg = -sg; j = 0; }
@@ -64,6 +60,7 @@ __device__ __forceinline__ void sR(const Geo &g, const Acc &A, int f, int j, int
 }
 template <class Acc>
 __device__ __forceinline__ void sT(const Geo &g, const Acc &A, int i, int f, int k, double v) {
+  if constexpr (Acc::RAW) return A.add(g, F_UT, i, f, k, v);
   double sg = 1.0;
   if (!g.periodic && (k < 0 || k >= g.np)) { sg = -sg; k = k < 0 ? 0 : g.np - 1; }
   if (i < 0) { sg = -sg; i = 0; }
@@ -72,6 +69,7 @@ __device__ __forceinline__ void sT(const Geo &g, const Acc &A, int i, int f, int
 }
 template <class Acc>
 __device__ __forceinline__ void sF(const Geo &g, const Acc &A, int i, int j, int f, double v) {
+  if constexpr (Acc::RAW) return A.add(g, F_UF, i, j, f, v);
   double sg = 1.0;
   if (j < 0) { sg = -sg; j = 0; }
   else if (j >= g.nt) { sg = -sg; j = g.nt - 1; }
@@ -102,9 +100,9 @@ template <class S, class Acc>
 __device__ __forceinline__ void rho_rev(const Geo &g, const Mat &m, const S &s, const Acc &A, int i,
                                         int j, int k, double rb) {
   const double P = gC(g, s, F_P, i, j, k) + m.pinf, T = gC(g, s, F_T, i, j, k);
-  const double iRT = 1.0 / (m.Rg * T);
-  sC(g, A, F_P, i, j, k, rb * iRT);
-  sC(g, A, F_T, i, j, k, -rb * P * iRT / T);
+  const double iRT = rcp_nr(m.Rg * T), pb = rb * iRT;
+  sC(g, A, F_P, i, j, k, pb);
+  sC(g, A, F_T, i, j, k, -pb * P * (m.Rg * iRT));
 }
 
 // divc (compact divergence at a centre), reversed
@@ -171,8 +169,9 @@ __device__ __forceinline__ void centre_rev(const Geo &g, const Mat &m, const S &
   r1 += g.idr * Grr;  // Grr
   r0 -= g.idr * Grr;
   // chi = (gamma - 1) T / P
-  sC(g, A, F_P, i, j, k, cb.P - c.chi / c.P * cb.chi);
-  sC(g, A, F_T, i, j, k, cb.T + (m.gam - 1.0) / c.P * cb.chi);
+  const double chb = cb.chi * rcp_nr(c.P);
+  sC(g, A, F_P, i, j, k, cb.P - c.chi * chb);
+  sC(g, A, F_T, i, j, k, cb.T + (m.gam - 1.0) * chb);
   r0 += 0.5 * ur; r1 += 0.5 * ur;
   t0 += 0.5 * ut; t1 += 0.5 * ut;
   f0 += 0.5 * uf; f1 += 0.5 * uf;
@@ -258,19 +257,19 @@ __device__ __forceinline__ void F_p_T_rev(const Geo &g, const Mat &m, const S &s
 // The three momentum rows reversed.  Contributions that land on the same
 // load are summed before the one atomic add of that load.  Extra inputs
 // (from the two scalar line rows through the same face, which read the same
-// face density and the same transverse averages): rfx, the adjoint of the
-// face density rho_f = (rho_a + rho_b)/2; uax, ubx, of the two transverse
-// averages ua, ub.
+// face viscosity mu/rho and the same transverse averages): nubx, the adjoint of
+// that viscosity; uax, ubx, of the two transverse averages ua, ub.
 
 // radial momentum row at interior r-face (f, j, k) (F_ur of residual.hip)
 template <class S, class Acc>
 __device__ __forceinline__ void F_ur_rev(const Geo &g, const Mat &m, const S &s, int f, int j, int k, double w,
-                         const Acc &A, double rfx = 0.0, double uax = 0.0, double ubx = 0.0) {
+                         const Acc &A, double nubx = 0.0, double uax = 0.0, double ubx = 0.0) {
   const double irF = g.irf[f], is = g.isc[j];
   const double Pa = gC(g, s, F_P, f, j, k) + m.pinf, Ta = gC(g, s, F_T, f, j, k);
   const double Pb_ = gC(g, s, F_P, f - 1, j, k) + m.pinf, Tb_ = gC(g, s, F_T, f - 1, j, k);
-  const double rho_a = Pa / (m.Rg * Ta), rho_b = Pb_ / (m.Rg * Tb_);
-  const double irho = 1.0 / (0.5 * (rho_b + rho_a));
+  const double iRTa = rcp_nr(m.Rg * Ta), iRTb = rcp_nr(m.Rg * Tb_);
+  const double rho_a = Pa * iRTa, rho_b = Pb_ * iRTb;
+  const double irho = rcp_nr(0.5 * (rho_b + rho_a));
   const double nu = m.mu * irho;
   const double un = gR(g, s, f, j, k);
   const double T00 = gT(g, s, f - 1, j, k), T01 = gT(g, s, f - 1, j + 1, k);
@@ -291,7 +290,7 @@ __device__ __forceinline__ void F_ur_rev(const Geo &g, const Mat &m, const S &s,
   const double C = ((g.sf[j + 1] * wp1 - g.sf[j] * wp0) * g.idt - (wt1 - wt0) * g.idp) * (irF * is);
   const double vis = gd - C;
   // reverse of F = N - nu vis - nu/3 gd + g_r, vis = gd - C
-  const double Nb = w, visb = -nu * w, gdb = -nu / 3.0 * w + visb, nub = -(vis + gd / 3.0) * w;
+  const double Nb = w, visb = -nu * w, gdb = nu * w * (-1.0 / 3.0) + visb, nub = nubx - (vis + gd * (1.0 / 3.0)) * w;
   double uab = uax, ubb = ubx - 2.0 * m.omega * g.sc[j] * Nb, unb = 0.0;
   double aT00 = 0.0, aT01 = 0.0, aT10 = 0.0, aT11 = 0.0, aF00 = 0.0, aF01 = 0.0, aF10 = 0.0, aF11 = 0.0;
   double aRf = 0.0, aRfp = 0.0, aRfm = 0.0;
@@ -332,10 +331,10 @@ __device__ __forceinline__ void F_ur_rev(const Geo &g, const Mat &m, const S &s,
   uab += -2.0 * ua * irF * Nb;
   ubb += -2.0 * ub * irF * Nb;
   irhob += m.mu * nub;
-  const double rhob = 0.5 * (rfx - irho * irho * irhob); // each of the two cells
-  aPa += rhob / (m.Rg * Ta);
-  aPb += rhob / (m.Rg * Tb_);
-  const double aTa = -rhob * rho_a / Ta, aTb = -rhob * rho_b / Tb_;
+  const double rhob = -0.5 * irho * irho * irhob; // each of the two cells
+  aPa += rhob * iRTa;
+  aPb += rhob * iRTb;
+  const double aTa = -rhob * rho_a * (m.Rg * iRTa), aTb = -rhob * rho_b * (m.Rg * iRTb);
   aT00 += 0.25 * uab; aT01 += 0.25 * uab; aT10 += 0.25 * uab; aT11 += 0.25 * uab;
   aF00 += 0.25 * ubb; aF01 += 0.25 * ubb; aF10 += 0.25 * ubb; aF11 += 0.25 * ubb;
   sR(g, A, f, j, k, unb + aRf);
@@ -362,13 +361,14 @@ __device__ __forceinline__ void F_ur_rev(const Geo &g, const Mat &m, const S &s,
 // colatitudinal momentum row at interior theta-face (i, f, k) (F_ut)
 template <class S, class Acc>
 __device__ __forceinline__ void F_ut_rev(const Geo &g, const Mat &m, const S &s, int i, int f, int k, double w,
-                         const Acc &A, double rfx = 0.0, double uax = 0.0, double ubx = 0.0) {
+                         const Acc &A, double nubx = 0.0, double uax = 0.0, double ubx = 0.0) {
   const double ir = g.irc[i], isF = g.isf[f], ctF = g.ctf[f];
   const int j0 = f - 1, j1 = f;
   const double P1 = gC(g, s, F_P, i, j1, k) + m.pinf, T1 = gC(g, s, F_T, i, j1, k);
   const double P0 = gC(g, s, F_P, i, j0, k) + m.pinf, T0 = gC(g, s, F_T, i, j0, k);
-  const double rho1 = P1 / (m.Rg * T1), rho0 = P0 / (m.Rg * T0);
-  const double irho = 1.0 / (0.5 * (rho0 + rho1));
+  const double iRT1 = rcp_nr(m.Rg * T1), iRT0 = rcp_nr(m.Rg * T0);
+  const double rho1 = P1 * iRT1, rho0 = P0 * iRT0;
+  const double irho = rcp_nr(0.5 * (rho0 + rho1));
   const double nu = m.mu * irho;
   const double un = gT(g, s, i, f, k);
   const double R00 = gR(g, s, i, j0, k), R01 = gR(g, s, i, j1, k);
@@ -389,7 +389,7 @@ __device__ __forceinline__ void F_ut_rev(const Geo &g, const Mat &m, const S &s,
   const double wp1 = (xp - un) * g.idr + 0.5 * (xp + un) * irb - (R11 - R10) * (irb * g.idt);
   const double C = (wr1 - wr0) * (ir * isF * g.idp) - (g.rf[i + 1] * wp1 - g.rf[i] * wp0) * (ir * g.idr);
   const double vis = gd - C;
-  const double Nb = w, visb = -nu * w, gdb = -nu / 3.0 * w + visb, nub = -(vis + gd / 3.0) * w;
+  const double Nb = w, visb = -nu * w, gdb = nu * w * (-1.0 / 3.0) + visb, nub = nubx - (vis + gd * (1.0 / 3.0)) * w;
   double uab = uax, ubb = ubx - 2.0 * m.omega * g.cf[f] * Nb, unb = 0.0;
   double aR00 = 0.0, aR01 = 0.0, aR10 = 0.0, aR11 = 0.0, aF00 = 0.0, aF01 = 0.0, aF10 = 0.0, aF11 = 0.0;
   double aTf = 0.0, aTfp = 0.0, aTfm = 0.0;
@@ -431,10 +431,10 @@ __device__ __forceinline__ void F_ut_rev(const Geo &g, const Mat &m, const S &s,
   uab += un * ir * Nb;
   ubb += -2.0 * ub * ctF * ir * Nb;
   irhob += m.mu * nub;
-  const double rhob = 0.5 * (rfx - irho * irho * irhob);
-  aP1 += rhob / (m.Rg * T1);
-  aP0 += rhob / (m.Rg * T0);
-  const double aT1 = -rhob * rho1 / T1, aT0 = -rhob * rho0 / T0;
+  const double rhob = -0.5 * irho * irho * irhob;
+  aP1 += rhob * iRT1;
+  aP0 += rhob * iRT0;
+  const double aT1 = -rhob * rho1 * (m.Rg * iRT1), aT0 = -rhob * rho0 * (m.Rg * iRT0);
   aR00 += 0.25 * uab; aR01 += 0.25 * uab; aR10 += 0.25 * uab; aR11 += 0.25 * uab;
   aF00 += 0.25 * ubb; aF01 += 0.25 * ubb; aF10 += 0.25 * ubb; aF11 += 0.25 * ubb;
   sT(g, A, i, f, k, unb + aTf);
@@ -461,13 +461,16 @@ __device__ __forceinline__ void F_ut_rev(const Geo &g, const Mat &m, const S &s,
 // azimuthal momentum row at phi-face (i, j, f) (F_uf)
 template <class S, class Acc>
 __device__ __forceinline__ void F_uf_rev(const Geo &g, const Mat &m, const S &s, int i, int j, int f, double w,
-                         const Acc &A, double rfx = 0.0, double uax = 0.0, double ubx = 0.0) {
+                         const Acc &A, double nubx = 0.0, double uax = 0.0, double ubx = 0.0) {
   const double ir = g.irc[i], is = g.isc[j], ct = g.ctc[j], ir2 = ir * ir;
-  const int k0 = g.periodic ? wrapk(g, f - 1) : f - 1, k1 = g.periodic ? wrapk(g, f) : f;
+  // (interior sources wrap at the load)
+  const bool wrap = !S::INTERIOR && g.periodic;
+  const int k0 = wrap ? wrapk(g, f - 1) : f - 1, k1 = wrap ? wrapk(g, f) : f;
   const double P1 = gC(g, s, F_P, i, j, k1) + m.pinf, T1 = gC(g, s, F_T, i, j, k1);
   const double P0 = gC(g, s, F_P, i, j, k0) + m.pinf, T0 = gC(g, s, F_T, i, j, k0);
-  const double rho1 = P1 / (m.Rg * T1), rho0 = P0 / (m.Rg * T0);
-  const double irho = 1.0 / (0.5 * (rho0 + rho1));
+  const double iRT1 = rcp_nr(m.Rg * T1), iRT0 = rcp_nr(m.Rg * T0);
+  const double rho1 = P1 * iRT1, rho0 = P0 * iRT0;
+  const double irho = rcp_nr(0.5 * (rho0 + rho1));
   const double nu = m.mu * irho;
   const double un = gF(g, s, i, j, f);
   const double R00 = gR(g, s, i, j, k0), R01 = gR(g, s, i, j, k1);
@@ -528,7 +531,7 @@ __device__ __forceinline__ void F_uf_rev(const Geo &g, const Mat &m, const S &s,
     aT11 -= g.idp * e1; aT10 += g.idp * e1;
   }
   // reverse of F = N - nu vis - nu/3 gd, vis = gd - C off the poles
-  const double Nb = w, gdb = -nu / 3.0 * w + (pole_row ? 0.0 : visb), nub = -(vis + gd / 3.0) * w;
+  const double Nb = w, gdb = nu * w * (-1.0 / 3.0) + (pole_row ? 0.0 : visb), nub = nubx - (vis + gd * (1.0 / 3.0)) * w;
   double ubb = ubx + 2.0 * m.omega * g.cc[j] * Nb, uab = uax + 2.0 * m.omega * g.sc[j] * Nb;
   double aFf = 0.0, aFfp = 0.0, aFfm = 0.0;
   {  // divergences at cells (i, j, k1) (+) and (i, j, k0) (-); their phi
@@ -553,10 +556,10 @@ __device__ __forceinline__ void F_uf_rev(const Geo &g, const Mat &m, const S &s,
   uab += un * ir * Nb;
   ubb += un * ct * ir * Nb;
   irhob += m.mu * nub;
-  const double rhob = 0.5 * (rfx - irho * irho * irhob);
-  aP1 += rhob / (m.Rg * T1);
-  aP0 += rhob / (m.Rg * T0);
-  const double aT1 = -rhob * rho1 / T1, aT0 = -rhob * rho0 / T0;
+  const double rhob = -0.5 * irho * irho * irhob;
+  aP1 += rhob * iRT1;
+  aP0 += rhob * iRT0;
+  const double aT1 = -rhob * rho1 * (m.Rg * iRT1), aT0 = -rhob * rho0 * (m.Rg * iRT0);
   aR00 += 0.25 * uab; aR01 += 0.25 * uab; aR10 += 0.25 * uab; aR11 += 0.25 * uab;
   aT00 += 0.25 * ubb; aT01 += 0.25 * ubb; aT10 += 0.25 * ubb; aT11 += 0.25 * ubb;
   sF(g, A, i, j, f, unb + aFf);
@@ -619,10 +622,13 @@ void launch_residual_vjp(const Geo &g, const Mat &m, const Fields &Ub, double ta
 
 // Reverse of block_row<D> (rows.hpp) for the coefficient entries: EL, ED, EU
 // are the adjoints of the final (scaled) L, D, U blocks of row s.
-template <int D, class Acc>
-__device__ __forceinline__ void block_row_rev_cb(const Geo &g, const Mat &m, const SrcOne &u, int a, int b, int s, int n,
+// Contributions to the own centre go into cb.
+template <int D, class S, class Acc>
+__device__ __forceinline__ void block_row_rev_cb(const Geo &g, const Mat &m, const S &u, int a, int b, int s, int n,
                                  int cyc, double hs, const double *EL, const double *ED, const double *EU,
                                  const Cent &c, Cent &cb, const Acc &A) {
+  // rows of an interior source: neither end of an r or theta line
+  constexpr bool IN = S::INTERIOR && D < 2;
   int i, j, k;
   if (D == 0) { i = s; j = a; k = b; }
   else if (D == 1) { i = a; j = s; k = b; }
@@ -648,10 +654,10 @@ __device__ __forceinline__ void block_row_rev_cb(const Geo &g, const Mat &m, con
     lp = ir2 * is * is * g.idp * g.idp;
     lm = lp;
   }
-  const bool first = !cyc && s == 0, last = !cyc && s == n - 1;
+  const bool first = !IN && !cyc && s == 0, last = !IN && !cyc && s == n - 1;
   if (first) lm = 0.0;
   if (last) lp = 0.0;
-  const bool w_unknown = cyc || s < n - 1;
+  const bool w_unknown = IN || cyc || s < n - 1;
   double ap, am;
   if (D == 0) {
     const double gg = (c.Gtt + c.Gff) * ir;
@@ -720,9 +726,9 @@ __device__ __forceinline__ void block_row_rev_cb(const Geo &g, const Mat &m, con
     const double ira2 = g.irc[i] * g.irc[i], irb2 = g.irc[i + 1] * g.irc[i + 1];
     G = g.idr;
     hc = 0.5 * g.idr;
-    ap_ = -rb2 * irF2 * d2 - g.rf[i + 2] * g.rf[i + 2] * irb2 * d2 / 3.0;
-    a0_ = (rb2 + ra2) * irF2 * d2 + rF2 * (irb2 + ira2) * d2 / 3.0;
-    am_ = -ra2 * irF2 * d2 - g.rf[i] * g.rf[i] * ira2 * d2 / 3.0;
+    ap_ = -rb2 * irF2 * d2 - g.rf[i + 2] * g.rf[i + 2] * irb2 * d2 * (1.0 / 3.0);
+    a0_ = (rb2 + ra2) * irF2 * d2 + rF2 * (irb2 + ira2) * d2 * (1.0 / 3.0);
+    am_ = -ra2 * irF2 * d2 - g.rf[i] * g.rf[i] * ira2 * d2 * (1.0 / 3.0);
     i1 = i + 1;
     wf = F_UR; wi = f;
   } else if (D == 1) {
@@ -731,29 +737,34 @@ __device__ __forceinline__ void block_row_rev_cb(const Geo &g, const Mat &m, con
     const double sa = g.sc[j], sb = g.sc[j + 1], isa = g.isc[j], isb = g.isc[j + 1];
     G = ir * g.idt;
     hc = 0.5 * ir * g.idt;
-    ap_ = -sb * r2d2 * isF - g.sf[j + 2] * r2d2 * isb / 3.0;
-    a0_ = (sb + sa) * r2d2 * isF + sF_ * (isb + isa) * r2d2 / 3.0;
-    am_ = -sa * r2d2 * isF - g.sf[j] * r2d2 * isa / 3.0;
+    ap_ = -sb * r2d2 * isF - g.sf[j + 2] * r2d2 * isb * (1.0 / 3.0);
+    a0_ = (sb + sa) * r2d2 * isF + sF_ * (isb + isa) * r2d2 * (1.0 / 3.0);
+    am_ = -sa * r2d2 * isF - g.sf[j] * r2d2 * isa * (1.0 / 3.0);
     j1 = j + 1;
     wf = F_UT; wj = f;
   } else {
     const double q2 = ir2 * is * is * g.idp * g.idp;
     G = ir * is * g.idp;
     hc = 0.5 * ir * is * g.idp;
-    ap_ = -4.0 * q2 / 3.0;
-    a0_ = 8.0 * q2 / 3.0;
-    am_ = -4.0 * q2 / 3.0;
+    ap_ = q2 * (-4.0 / 3.0);
+    a0_ = q2 * (8.0 / 3.0);
+    am_ = q2 * (-4.0 / 3.0);
     k1 = k + 1;
     wf = F_UF; wk = k + 1; // unwrapped
   }
-  const double irho = 1.0 / (0.5 * (rho_at(g, m, u, i, j, k) + rho_at(g, m, u, i1, j1, k1)));
+  const double P1 = gC(g, u, F_P, i1, j1, k1) + m.pinf, T1 = gC(g, u, F_T, i1, j1, k1);
+  const double irho = 2.0 * m.Rg * c.T * T1 * rcp_nr(c.P * T1 + P1 * c.T);
   double irhob = G * (U[6] - Dg[6]);
   const double unb = hc * (U8 - L[8]);
   const double nub = ap_ * U8 + a0_ * Dg[8] + am_ * L[8];
   irhob += m.mu * nub;
   const double rhob = -0.5 * irho * irho * irhob;
-  rho_rev(g, m, u, A, i, j, k, rhob);
-  rho_rev(g, m, u, A, i1, j1, k1, rhob);
+  const double iRT0 = rcp_nr(m.Rg * c.T), iRT1 = rcp_nr(m.Rg * T1);
+  const double pb0 = rhob * iRT0, pb1 = rhob * iRT1;
+  cb.P += pb0;
+  cb.T -= pb0 * c.P * (m.Rg * iRT0);
+  sC(g, A, F_P, i1, j1, k1, pb1);
+  sC(g, A, F_T, i1, j1, k1, -pb1 * P1 * (m.Rg * iRT1));
   A.add(g, wf, wi, wj, wk, unb);
 }
 
@@ -772,98 +783,79 @@ __device__ __forceinline__ void block_row_rev(const Geo &g, const Mat &m, const 
 }
 
 // Reverse of scalar_row<D, FAM> for its entries: ea, eb, ec are the adjoints
-// of the final a, b, c of row s.
-// The reverse is returned as rfb, the adjoint of the face density
-// rho_f = (rho_c0 + rho_c1)/2, and uab, that of the transverse average
-// (scalar_row_parts); scalar_row_rev also scatters them into A.
-template <int D, int FAM>
-__device__ __forceinline__ void scalar_row_parts(const Geo &g, const Mat &m, const SrcOne &u, int a, int b, int s, int n,
-                                 int cyc, double hs, double ea, double eb, double ec, double &rfb,
-                                 double &uab, int *cells, long *ix, int &bfid) {
+// of the final a, b, c of row s.  Returned as nub, the adjoint of the face
+// viscosity mu / rho_f, rho_f = (rho_c0 + rho_c1)/2, and uab, that of the
+// transverse average.  INR: the caller guarantees that the row is neither end
+// of an r or theta line.
+template <int D, int FAM, bool INR>
+__device__ __forceinline__ void scalar_row_parts(const Geo &g, int a, int b, int s, int n, int cyc, double hs,
+                                                 double ea, double eb, double ec, double &nub, double &uab) {
   double h, qa, qb, qc, sglo = -1.0, sghi = -1.0;
-  int ci0, cj0, ck0, ci1, cj1, ck1; // the two cells of the face density
   if (D == 0) {
     const int i = s;
     const double ir = g.irc[i], r2d2 = ir * ir * g.idr * g.idr;
     const double fp = g.rf[i + 1] * g.rf[i + 1], fm = g.rf[i] * g.rf[i];
     h = 0.5 * g.idr; qa = fm * r2d2; qb = (fp + fm) * r2d2; qc = fp * r2d2;
-    bfid = F_UR;
-    if (FAM == 0) {
-      const int jf = a, k = b;
-      ix[0] = idx_r(g, i, jf - 1, k); ix[1] = idx_r(g, i, jf, k);
-      ix[2] = idx_r(g, i + 1, jf - 1, k); ix[3] = idx_r(g, i + 1, jf, k);
-      ci0 = i; cj0 = jf - 1; ck0 = k; ci1 = i; cj1 = jf; ck1 = k;
-    } else {
-      const int j = a, kf = b;
-      const int k0 = g.periodic ? wrapk(g, kf - 1) : kf - 1, k1 = g.periodic ? wrapk(g, kf) : kf;
-      ix[0] = idx_r(g, i, j, k0); ix[1] = idx_r(g, i, j, k1);
-      ix[2] = idx_r(g, i + 1, j, k0); ix[3] = idx_r(g, i + 1, j, k1);
-      ci0 = i; cj0 = j; ck0 = k0; ci1 = i; cj1 = j; ck1 = k1;
-    }
   } else if (D == 1) {
     const int j = s;
     const double is = g.isc[j];
-    double irr;
-    bfid = F_UT;
+    const double irr = FAM == 0 ? g.irf[a] : g.irc[a];
     if (FAM == 0) {
-      const int fr = a, k = b;
-      irr = g.irf[fr];
-      ix[0] = idx_t(g, fr - 1, j, k); ix[1] = idx_t(g, fr - 1, j + 1, k);
-      ix[2] = idx_t(g, fr, j, k); ix[3] = idx_t(g, fr, j + 1, k);
-      ci0 = fr - 1; cj0 = j; ck0 = k; ci1 = fr; cj1 = j; ck1 = k;
       sglo = g.pole_lo ? 1.0 : -1.0;
       sghi = g.pole_hi ? 1.0 : -1.0;
-    } else {
-      const int i = a, kf = b;
-      irr = g.irc[i];
-      const int k0 = g.periodic ? wrapk(g, kf - 1) : kf - 1, k1 = g.periodic ? wrapk(g, kf) : kf;
-      ix[0] = idx_t(g, i, j, k0); ix[1] = idx_t(g, i, j, k1);
-      ix[2] = idx_t(g, i, j + 1, k0); ix[3] = idx_t(g, i, j + 1, k1);
-      ci0 = i; cj0 = j; ck0 = k0; ci1 = i; cj1 = j; ck1 = k1;
     }
     const double q = irr * irr * is * g.idt * g.idt;
     h = 0.5 * irr * g.idt; qa = g.sf[j] * q; qb = (g.sf[j + 1] + g.sf[j]) * q; qc = g.sf[j + 1] * q;
   } else {
-    const int k = s;
-    const int kp = g.periodic ? wrapk(g, k + 1) : k + 1;
-    double irr, iss;
-    bfid = F_UF;
-    if (FAM == 0) {
-      const int fr = a, j = b;
-      irr = g.irf[fr]; iss = g.isc[j];
-      ix[0] = idx_f(g, fr - 1, j, k); ix[1] = idx_f(g, fr - 1, j, kp);
-      ix[2] = idx_f(g, fr, j, k); ix[3] = idx_f(g, fr, j, kp);
-      ci0 = fr - 1; cj0 = j; ck0 = k; ci1 = fr; cj1 = j; ck1 = k;
-    } else {
-      const int i = a, ft = b;
-      irr = g.irc[i]; iss = g.isf[ft];
-      ix[0] = idx_f(g, i, ft - 1, k); ix[1] = idx_f(g, i, ft - 1, kp);
-      ix[2] = idx_f(g, i, ft, k); ix[3] = idx_f(g, i, ft, kp);
-      ci0 = i; cj0 = ft - 1; ck0 = k; ci1 = i; cj1 = ft; ck1 = k;
-    }
+    const double irr = FAM == 0 ? g.irf[a] : g.irc[a], iss = FAM == 0 ? g.isc[b] : g.isf[b];
     const double q = irr * irr * iss * iss * g.idp * g.idp;
     h = 0.5 * irr * iss * g.idp; qa = q; qb = 2.0 * q; qc = q;
   }
-  const bool first = !cyc && s == 0, last = !cyc && s == n - 1;
+  constexpr bool IN = INR && D < 2;
+  const bool first = !IN && !cyc && s == 0, last = !IN && !cyc && s == n - 1;
   const double cab = first ? hs * sglo * eb : hs * ea;
   const double cbb = hs * eb;
   const double ccb = last ? hs * sghi * eb : hs * ec;
   uab = h * (ccb - cab);
-  const double nub = -qa * cab + qb * cbb - qc * ccb;
-  const double rho = 0.5 * (rho_at(g, m, u, ci0, cj0, ck0) + rho_at(g, m, u, ci1, cj1, ck1));
-  rfb = -m.mu / (rho * rho) * nub;
-  cells[0] = ci0; cells[1] = cj0; cells[2] = ck0; cells[3] = ci1; cells[4] = cj1; cells[5] = ck1;
+  nub = -qa * cab + qb * cbb - qc * ccb;
 }
 
+// the same scattered into A: the two cells of the face density, the four
+// faces of the transverse average
 template <int D, int FAM>
 __device__ __forceinline__ void scalar_row_rev(const Geo &g, const Mat &m, const SrcOne &u, int a, int b, int s, int n,
                                int cyc, double hs, double ea, double eb, double ec, const GAcc &A) {
-  double rfb, uab;
-  int c[6], bfid;
+  double nub, uab;
+  scalar_row_parts<D, FAM, false>(g, a, b, s, n, cyc, hs, ea, eb, ec, nub, uab);
+  int bfid, i0, j0, k0, i1, j1, k1;
   long ix[4];
-  scalar_row_parts<D, FAM>(g, m, u, a, b, s, n, cyc, hs, ea, eb, ec, rfb, uab, c, ix, bfid);
-  rho_rev(g, m, u, A, c[0], c[1], c[2], 0.5 * rfb);
-  rho_rev(g, m, u, A, c[3], c[4], c[5], 0.5 * rfb);
+  const auto wr = [&](int k) { return g.periodic ? wrapk(g, k) : k; };
+  if (D == 0) {
+    bfid = F_UR;
+    i0 = i1 = s;
+    if (FAM == 0) { j0 = a - 1; j1 = a; k0 = k1 = b; }
+    else { j0 = j1 = a; k0 = wr(b - 1); k1 = wr(b); }
+    ix[0] = idx_r(g, s, j0, k0); ix[1] = idx_r(g, s, j1, k1);
+    ix[2] = idx_r(g, s + 1, j0, k0); ix[3] = idx_r(g, s + 1, j1, k1);
+  } else if (D == 1) {
+    bfid = F_UT;
+    j0 = j1 = s;
+    if (FAM == 0) { i0 = a - 1; i1 = a; k0 = k1 = b; }
+    else { i0 = i1 = a; k0 = wr(b - 1); k1 = wr(b); }
+    ix[0] = idx_t(g, i0, s, k0); ix[1] = idx_t(g, i0, s + 1, k0);
+    ix[2] = idx_t(g, i1, s, k1); ix[3] = idx_t(g, i1, s + 1, k1);
+  } else {
+    bfid = F_UF;
+    k0 = k1 = s;
+    if (FAM == 0) { i0 = a - 1; i1 = a; j0 = j1 = b; }
+    else { i0 = i1 = a; j0 = b - 1; j1 = b; }
+    ix[0] = idx_f(g, i0, j0, s); ix[1] = idx_f(g, i0, j0, wr(s + 1));
+    ix[2] = idx_f(g, i1, j1, s); ix[3] = idx_f(g, i1, j1, wr(s + 1));
+  }
+  const double rho = 0.5 * (rho_at(g, m, u, i0, j0, k0) + rho_at(g, m, u, i1, j1, k1));
+  const double rfb = -m.mu / (rho * rho) * nub;
+  rho_rev(g, m, u, A, i0, j0, k0, 0.5 * rfb);
+  rho_rev(g, m, u, A, i1, j1, k1, 0.5 * rfb);
   double *base = fsel(A.A, bfid);
 #pragma unroll
   for (int q = 0; q < 4; q++) unsafeAtomicAdd(base + ix[q], 0.25 * uab);
@@ -979,239 +971,464 @@ void launch_line_vjp(int d, const Geo &g, const Mat &m, const Fields &Ub, double
 
 // For dsw_adjoint_step: acc += (d(-tau F_h)/dUbar)^T mu[0]
 //                              - sum_d (d(M_d(Ubar) X[d])/dUbar)^T mu[d]
-// (d = 0 r, 1 theta, 2 phi).  PART 0: every cell, with the p and T rows and
-// the three block rows through the cell sharing one evaluation of the centre
-// coefficients and one reverse of it; PART 1, 2, 3: the r, theta, phi faces,
-// each with its momentum row and the two scalar rows through it.
+// (d = 0 r, 1 theta, 2 phi).  At every index: the cell (its p and T rows and
+// the three block rows through it share one evaluation of the centre
+// coefficients and one reverse of them) and the r, theta, phi faces (each its
+// momentum row and the two scalar rows through it).
 struct AdjIn {
   Fields X[3], mu[3];
 };
+struct AdjArgs {
+  Geo g;
+  Mat m;
+  const double *u[5];
+  double tau;
+  AdjIn in;
+  Fields A;
+  int seg;
+};
 
-template <int D, class Acc>
-__device__ __forceinline__ void cell_block_row(const Geo &g, const Mat &m, const SrcOne &u, double hs,
-                                               const AdjIn &in, int i, int j, int k, const Cent &c,
-                                               Cent &cb, const Acc &A) {
+// The arguments, read from the kernel's argument block.  The reverse of one
+// index takes 35 arrays and 15 tables: more scalar registers than there are,
+// and what does not fit is moved through vector lanes at every use (2500 lane
+// moves of 12400 instructions when each array was an ordinary parameter).  So
+// each piece of the work passes the block's address through an empty asm and
+// reads what it needs again (scalar loads that hit the cache).
+#define DSW_AS1 __attribute__((address_space(1)))
+#define DSW_AS4 __attribute__((address_space(4)))
+using KPtr = const DSW_AS4 char *;
+
+template <class T>
+__device__ __forceinline__ T karg(KPtr p, unsigned off) { return *(const DSW_AS4 T *)(p + off); }
+__device__ __forceinline__ const double *ktab(KPtr p, unsigned off) { // a table: constant, scalar loads
+  return (const double *)karg<const DSW_AS4 double *>(p, off);
+}
+__device__ __forceinline__ double *karr(KPtr p, unsigned off) {
+  return (double *)karg<DSW_AS1 double *>(p, off);
+}
+__device__ __forceinline__ Fields kfields(KPtr p, unsigned off) {
+  return {karr(p, off), karr(p, off + 8), karr(p, off + 16), karr(p, off + 24), karr(p, off + 32)};
+}
+
+__device__ __forceinline__ Geo kgeo(KPtr p) {
+  Geo g;
+#define DSW_KI(f) g.f = karg<int>(p, offsetof(AdjArgs, g) + offsetof(Geo, f))
+#define DSW_KD(f) g.f = karg<double>(p, offsetof(AdjArgs, g) + offsetof(Geo, f))
+#define DSW_KT(f) g.f = ktab(p, offsetof(AdjArgs, g) + offsetof(Geo, f))
+  DSW_KI(nr); DSW_KI(nt); DSW_KI(np); DSW_KI(npf); DSW_KI(periodic); DSW_KI(pole_lo); DSW_KI(pole_hi);
+  DSW_KD(dr); DSW_KD(dt); DSW_KD(dp); DSW_KD(idr); DSW_KD(idt); DSW_KD(idp);
+  DSW_KT(rc); DSW_KT(rf); DSW_KT(sc); DSW_KT(cc); DSW_KT(sf); DSW_KT(cf); DSW_KT(irc); DSW_KT(irf);
+  DSW_KT(isc); DSW_KT(ctc); DSW_KT(isf); DSW_KT(ctf); DSW_KT(scx); DSW_KT(mr); DSW_KT(mt);
+#undef DSW_KI
+#undef DSW_KD
+#undef DSW_KT
+  return g;
+}
+__device__ __forceinline__ Mat kmat(KPtr p) {
+  Mat m;
+#define DSW_KM(f) m.f = karg<double>(p, offsetof(AdjArgs, m) + offsetof(Mat, f))
+  DSW_KM(gam); DSW_KM(Rg); DSW_KM(pinf); DSW_KM(mu); DSW_KM(kap); DSW_KM(omega); DSW_KM(g_r);
+#undef DSW_KM
+  return m;
+}
+static_assert(offsetof(Fields, T) == 32 && offsetof(AdjIn, mu) == 120, "kfields, kctx read these layouts");
+
+// interior source: the row's base in scalar registers, the phi index a 32-bit
+// byte offset shared by all rows and arrays
+template <bool P>
+struct SrcRow {
+  const double *a[5];
+  static constexpr bool INTERIOR = true;
+  static constexpr bool PERIODIC = P;
+  static constexpr bool WALL = false;
+  static constexpr bool PERT = false;
+  using Row = long;
+  __device__ __forceinline__ double ld(int f, long x) const { return a[f][x]; }
+  __device__ __forceinline__ double ldk(int f, long row, int k) const { return ldo(a[f] + row, (unsigned)k * 8u); }
+};
+
+template <class S>
+struct AdjCtx {
+  Geo g;
+  Mat m;
+  S u;
+  double tau;
+  AdjIn in;
+};
+template <class S>
+__device__ __forceinline__ AdjCtx<S> kctx(KPtr p) {
+  AdjCtx<S> c;
+  c.g = kgeo(p);
+  c.m = kmat(p);
+#pragma unroll
+  for (int f = 0; f < 5; f++) c.u.a[f] = karr(p, offsetof(AdjArgs, u) + 8 * f);
+  c.tau = karg<double>(p, offsetof(AdjArgs, tau));
+#pragma unroll
+  for (int d = 0; d < 3; d++) {
+    c.in.X[d] = kfields(p, offsetof(AdjArgs, in) + 40 * d);
+    c.in.mu[d] = kfields(p, offsetof(AdjArgs, in) + 120 + 40 * d);
+  }
+  return c;
+}
+
+// The state with the ghost rules of dsw_common.hpp for the shell, by selects
+// on clamped indices: no load under a condition that differs between lanes.
+// (With early returns in divergent branches the compiler, clang 22 of ROCm 7.2,
+// left a uniform row index undefined in waves where no lane took the branch.)
+struct SrcShell {
+  const double *a[5];
+  static constexpr bool INTERIOR = false;
+  static constexpr bool PERIODIC = false;
+  static constexpr bool WALL = false;
+  static constexpr bool PERT = false;
+};
+__device__ __forceinline__ int phi_in(const Geo &g, int k) { return g.periodic ? wrapk(g, k) : clampi(k, 0, g.np - 1); }
+__device__ __forceinline__ double gC(const Geo &g, const SrcShell &s, int fid, int i, int j, int k) {
+  const long row = ((long)clampi(i, 0, g.nr - 1) * g.nt + clampi(j, 0, g.nt - 1)) * g.np;
+  return ldo(s.a[fid] + row, (unsigned)phi_in(g, k) * 8u);
+}
+__device__ __forceinline__ double gR(const Geo &g, const SrcShell &s, int f, int j, int k) {
+  const int kk = phi_in(g, k);
+  const bool flip = (j < 0 && !g.pole_lo) || (j >= g.nt && !g.pole_hi);
+  const double v = ldo(s.a[F_UR] + ((long)f * g.nt + clampi(j, 0, g.nt - 1)) * g.np, (unsigned)kk * 8u);
+  return flip != (!g.periodic && kk != k) ? -v : v;
+}
+__device__ __forceinline__ double gT(const Geo &g, const SrcShell &s, int i, int f, int k) {
+  const int kk = phi_in(g, k), ii = clampi(i, 0, g.nr - 1);
+  const double v = ldo(s.a[F_UT] + ((long)ii * (g.nt + 1) + f) * g.np, (unsigned)kk * 8u);
+  return (ii != i) != (!g.periodic && kk != k) ? -v : v;
+}
+__device__ __forceinline__ double gF(const Geo &g, const SrcShell &s, int i, int j, int f) {
+  const int ff = g.periodic ? wrapk(g, f) : f, ii = clampi(i, 0, g.nr - 1), jj = clampi(j, 0, g.nt - 1);
+  const double v = ldo(s.a[F_UF] + ((long)ii * g.nt + jj) * g.npf, (unsigned)ff * 8u);
+  return (ii != i) != (jj != j) ? -v : v;
+}
+
+// load3 and load1 in the same form: the rows beside (i, j, k), zero outside a
+// line that ends; IN: i and j lie inside the arrays
+template <int D, class S>
+__device__ __forceinline__ bool line_in(const Geo &g, int &i, int &j, int &k) {
+  const int i0 = i, j0 = j, k0 = k;
+  if constexpr (D == 0 && !S::INTERIOR) i = clampi(i, 0, g.nr - 1);
+  if constexpr (D == 1 && !S::INTERIOR) j = clampi(j, 0, g.nt - 1);
+  if constexpr (D == 2) {
+    const bool per = S::INTERIOR ? S::PERIODIC : (bool)g.periodic;
+    k = per ? wrapk(g, k) : clampi(k, 0, g.np - 1);
+    return per || k == k0;
+  }
+  return i == i0 && j == j0;
+}
+template <int D, class S>
+__device__ __forceinline__ void load3_at(const Geo &g, const Fields &X, int i, int j, int k, double *v) {
+  const bool on = line_in<D, S>(g, i, j, k);
+  const long row = ((long)i * g.nt + j) * g.np;
+  const unsigned o = (unsigned)k * 8u;
+  const double p = ldo(X.p + row, o), T = ldo(X.T + row, o);
+  double w;
+  bool won;  // the face after the last row of a line that ends is not unknown
+  if constexpr (D == 0) {
+    w = ldo(X.ur + ((long)(i + 1) * g.nt + j) * g.np, o);
+    won = i < g.nr - 1;
+  } else if constexpr (D == 1) {
+    w = ldo(X.ut + ((long)i * (g.nt + 1) + j + 1) * g.np, o);
+    won = j < g.nt - 1;
+  } else {
+    const bool per = S::INTERIOR ? S::PERIODIC : (bool)g.periodic;
+    w = ldo(X.uf + ((long)i * g.nt + j) * g.npf, (unsigned)(per ? wrapk(g, k + 1) : k + 1) * 8u);
+    won = per || k < g.np - 1;
+  }
+  v[0] = on ? p : 0.0;
+  v[1] = on ? T : 0.0;
+  v[2] = on && won ? w : 0.0;
+}
+template <int D, int FAM, class S>
+__device__ __forceinline__ double load1_at(const Geo &g, const Fields &X, int i, int j, int k) {
+  // the row's line index is bounded by the cells of its direction
+  const bool on = line_in<D, S>(g, i, j, k);
+  constexpr int f = D == 0 ? (FAM == 0 ? F_UT : F_UF) : (D == 1 ? (FAM == 0 ? F_UR : F_UF) : (FAM == 0 ? F_UR : F_UT));
+  const long row = f == F_UT ? ((long)i * (g.nt + 1) + j) * g.np : ((long)i * g.nt + j) * (f == F_UF ? g.npf : g.np);
+  const double v = ldo((f == F_UR ? X.ur : (f == F_UT ? X.ut : X.uf)) + row, (unsigned)k * 8u);
+  return on ? v : 0.0;
+}
+
+template <int D, class S, class Acc>
+__device__ __forceinline__ void cell_block_row(const AdjCtx<S> &x, int i, int j, int k, const Cent &c, Cent &cb,
+                                               const Acc &A) {
+  const Geo &g = x.g;
   int a, b, s, n;
   if (D == 0) { a = j; b = k; s = i; n = g.nr; }
   else if (D == 1) { a = i; b = k; s = j; n = g.nt; }
   else { a = i; b = j; s = k; n = g.np; }
-  const int cyc = (D == 2 && g.periodic) ? 1 : 0;
+  const int cyc = D == 2 && (S::INTERIOR ? S::PERIODIC : (bool)g.periodic) ? 1 : 0;
   double mv[3], xm[3], x0[3], xp[3], EL[9], ED[9], EU[9];
-  load3<D>(g, in.mu[D], a, b, s, n, cyc, mv);
-  load3<D>(g, in.X[D], a, b, s - 1, n, cyc, xm);
-  load3<D>(g, in.X[D], a, b, s, n, cyc, x0);
-  load3<D>(g, in.X[D], a, b, s + 1, n, cyc, xp);
+  load3_at<D, S>(g, x.in.mu[D], i, j, k, mv);
+  load3_at<D, S>(g, x.in.X[D], i - (D == 0), j - (D == 1), k - (D == 2), xm);
+  load3_at<D, S>(g, x.in.X[D], i, j, k, x0);
+  load3_at<D, S>(g, x.in.X[D], i + (D == 0), j + (D == 1), k + (D == 2), xp);
+  const double hs = 0.5 * x.tau;
+#pragma unroll
+  for (int r = 0; r < 3; r++) mv[r] *= -hs;
 #pragma unroll
   for (int r = 0; r < 3; r++)
 #pragma unroll
     for (int q = 0; q < 3; q++) {
-      EL[r * 3 + q] = -mv[r] * xm[q];
-      ED[r * 3 + q] = -mv[r] * x0[q];
-      EU[r * 3 + q] = -mv[r] * xp[q];
+      EL[r * 3 + q] = mv[r] * xm[q];
+      ED[r * 3 + q] = mv[r] * x0[q];
+      EU[r * 3 + q] = mv[r] * xp[q];
     }
-  block_row_rev_cb<D>(g, m, u, a, b, s, n, cyc, hs, EL, ED, EU, c, cb, A);
+  block_row_rev_cb<D>(g, x.m, x.u, a, b, s, n, cyc, 1.0, EL, ED, EU, c, cb, A);
 }
 
-// the scalar row of family FAM in direction D through a face: adds the
-// adjoints of the face density and of the transverse average it reads to
-// rfb, uab (the momentum row of the face reads the same ones)
-template <int D, int FAM>
-__device__ __forceinline__ void face_scalar_row(const Geo &g, const Mat &m, const SrcOne &u, double hs,
-                                                const AdjIn &in, int a, int b, int s, double &rfb,
-                                                double &uab) {
+// the scalar row of family FAM in direction D through the face at (i, j, k) of
+// its own array: adds the adjoints of the face viscosity and of the transverse
+// average it reads to nub, uab (the momentum row of the face reads the same)
+template <int D, int FAM, class S>
+__device__ __forceinline__ void face_scalar_row(const AdjCtx<S> &x, int i, int j, int k, double &nub, double &uab) {
+  const Geo &g = x.g;
   const int n = D == 0 ? g.nr : (D == 1 ? g.nt : g.np);
-  const int cyc = (D == 2 && g.periodic) ? 1 : 0;
-  const double mv = load1<D, FAM>(g, in.mu[D], a, b, s, n, cyc);
+  const int cyc = D == 2 && (S::INTERIOR ? S::PERIODIC : (bool)g.periodic) ? 1 : 0;
+  const int a = D == 0 ? j : i, b = D == 2 ? j : k, s = D == 0 ? i : (D == 1 ? j : k);
+  const double mv = -0.5 * x.tau * load1_at<D, FAM, S>(g, x.in.mu[D], i, j, k);
+  const double xm = load1_at<D, FAM, S>(g, x.in.X[D], i - (D == 0), j - (D == 1), k - (D == 2));
+  const double x0 = load1_at<D, FAM, S>(g, x.in.X[D], i, j, k);
+  const double xp = load1_at<D, FAM, S>(g, x.in.X[D], i + (D == 0), j + (D == 1), k + (D == 2));
   double r, ua;
-  int c[6], bfid;
-  long ix[4];
-  scalar_row_parts<D, FAM>(g, m, u, a, b, s, n, cyc, hs, -mv * load1<D, FAM>(g, in.X[D], a, b, s - 1, n, cyc),
-                           -mv * load1<D, FAM>(g, in.X[D], a, b, s, n, cyc),
-                           -mv * load1<D, FAM>(g, in.X[D], a, b, s + 1, n, cyc), r, ua, c, ix, bfid);
-  rfb += r;
+  scalar_row_parts<D, FAM, S::INTERIOR>(g, a, b, s, n, cyc, 1.0, mv * xm, mv * x0, mv * xp, r, ua);
+  nub += r;
   uab += ua;
 }
 
-// the reverse at one index (i, j, k) of the rows of one kind (PART 0: the
-// cell, 1: r-face i, 2: theta-face j, 3: phi-face k), when that row exists
-template <int PART, class Acc>
-__device__ __forceinline__ void adj_point(const Geo &g, const Mat &m, const SrcOne &u, double tau,
-                                          const AdjIn &in, int i, int j, int k, const Acc &A) {
-  const double hs = 0.5 * tau;
-  const Fields &mu1 = in.mu[0];
-  const bool kc = k < g.np;
-  if (PART == 0 && i < g.nr && j < g.nt && kc) {
-    Cent c, cb{};
-    centre(g, m, u, i, j, k, c);
-    const long x = idx_c(g, i, j, k);
-    F_p_T_rev_cb(g, m, u, i, j, k, c, -tau * mu1.p[x], -tau * mu1.T[x], cb, A);
-    cell_block_row<0>(g, m, u, hs, in, i, j, k, c, cb, A);
-    cell_block_row<1>(g, m, u, hs, in, i, j, k, c, cb, A);
-    cell_block_row<2>(g, m, u, hs, in, i, j, k, c, cb, A);
-    centre_rev(g, m, u, i, j, k, c, cb, A);
-  }
-  double rfb = 0.0, uab = 0.0, ubb = 0.0;
-  if (PART == 1 && j < g.nt && kc && i >= 1 && i < g.nr) {
-    face_scalar_row<1, 0>(g, m, u, hs, in, i, k, j, rfb, uab); // u_r along theta: reads ua (u_theta)
-    face_scalar_row<2, 0>(g, m, u, hs, in, i, j, k, rfb, ubb); // u_r along phi: reads ub (u_phi)
-    F_ur_rev(g, m, u, i, j, k, -tau * mu1.ur[idx_r(g, i, j, k)], A, rfb, uab, ubb);
-  }
-  if (PART == 2 && i < g.nr && kc && j >= 1 && j < g.nt) {
-    face_scalar_row<0, 0>(g, m, u, hs, in, j, k, i, rfb, uab); // u_theta along r: ua (u_r)
-    face_scalar_row<2, 1>(g, m, u, hs, in, i, j, k, rfb, ubb); // u_theta along phi: ub (u_phi)
-    F_ut_rev(g, m, u, i, j, k, -tau * mu1.ut[idx_t(g, i, j, k)], A, rfb, uab, ubb);
-  }
-  if (PART == 3 && i < g.nr && j < g.nt && (g.periodic || (k >= 1 && k < g.np))) {
-    face_scalar_row<0, 1>(g, m, u, hs, in, j, k, i, rfb, uab); // u_phi along r: ua (u_r)
-    face_scalar_row<1, 1>(g, m, u, hs, in, i, k, j, rfb, ubb); // u_phi along theta: ub (u_theta)
-    F_uf_rev(g, m, u, i, j, k, -tau * mu1.uf[idx_f(g, i, j, k)], A, rfb, uab, ubb);
-  }
-}
-
-// The cell rows in four pieces, each with its own evaluation of the centre
-// coefficients and its own reverse of them (centre_rev is linear in the
-// adjoints, so the pieces add up to the fused form): P = 0 the p and T rows,
-// P = 1, 2, 3 the block rows of the r, theta, phi lines.  Fewer values live at
-// once than in the fused form.
-template <int P, class Acc>
-__device__ __forceinline__ void adj_cell_piece(const Geo &g, const Mat &m, const SrcOne &u, double tau,
-                                               const AdjIn &in, int i, int j, int k, const Acc &A) {
-  if (!(i < g.nr && j < g.nt && k < g.np)) return;
-  const double hs = 0.5 * tau;
-  Cent c, cb{};
-  centre(g, m, u, i, j, k, c);
-  if constexpr (P == 0) {
-    const long x = idx_c(g, i, j, k);
-    F_p_T_rev_cb(g, m, u, i, j, k, c, -tau * in.mu[0].p[x], -tau * in.mu[0].T[x], cb, A);
+// the rows of face kind PART (1 r, 2 theta, 3 phi) at (i, j, k), when they exist
+template <int PART, class S, class Acc>
+__device__ __forceinline__ void adj_face(const AdjCtx<S> &x, int i, int j, int k, const Acc &A) {
+  const Geo &g = x.g;
+  const Fields &mu1 = x.in.mu[0];
+  double nub = 0.0, uab = 0.0, ubb = 0.0;
+  const auto mu_at = [&](const double *q, long row) { return -x.tau * ldo(q + row, (unsigned)k * 8u); };
+  if constexpr (PART == 1) {
+    if (!S::INTERIOR && i < 1) return;
+    face_scalar_row<1, 0>(x, i, j, k, nub, uab); // u_r along theta: reads ua (u_theta)
+    face_scalar_row<2, 0>(x, i, j, k, nub, ubb); // u_r along phi: reads ub (u_phi)
+    F_ur_rev(g, x.m, x.u, i, j, k, mu_at(mu1.ur, ((long)i * g.nt + j) * g.np), A, nub, uab, ubb);
+  } else if constexpr (PART == 2) {
+    if (!S::INTERIOR && j < 1) return;
+    face_scalar_row<0, 0>(x, i, j, k, nub, uab); // u_theta along r: ua (u_r)
+    face_scalar_row<2, 1>(x, i, j, k, nub, ubb); // u_theta along phi: ub (u_phi)
+    F_ut_rev(g, x.m, x.u, i, j, k, mu_at(mu1.ut, ((long)i * (g.nt + 1) + j) * g.np), A, nub, uab, ubb);
   } else {
-    cell_block_row<P - 1>(g, m, u, hs, in, i, j, k, c, cb, A);
+    if (!(S::INTERIOR ? S::PERIODIC : (bool)g.periodic) && k < 1) return;
+    face_scalar_row<0, 1>(x, i, j, k, nub, uab); // u_phi along r: ua (u_r)
+    face_scalar_row<1, 1>(x, i, j, k, nub, ubb); // u_phi along theta: ub (u_theta)
+    F_uf_rev(g, x.m, x.u, i, j, k, mu_at(mu1.uf, ((long)i * g.nt + j) * g.npf), A, nub, uab, ubb);
   }
-  centre_rev(g, m, u, i, j, k, c, cb, A);
 }
 
-// One thread per index, FP64 atomics straight into the global arrays.
-template <int PART>
-__global__ void __launch_bounds__(256) k_adj_local(Geo g, Mat m, SrcOne u, double tau, AdjIn in,
-                                                   Fields A) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x, j = blockIdx.y, i = blockIdx.z;
-  if (k >= g.npf) return;
-  adj_point<PART>(g, m, u, tau, in, i, j, k, GAcc{A});
+// the adjoints gathered so far are values, not sums still to be formed
+__device__ __forceinline__ void cent_pin(Cent &c) {
+  asm volatile("" : "+v"(c.ur), "+v"(c.ut), "+v"(c.uf), "+v"(c.P), "+v"(c.T), "+v"(c.chi), "+v"(c.Grr), "+v"(c.Gtt),
+               "+v"(c.Gff), "+v"(c.Srt), "+v"(c.Srf), "+v"(c.Stf), "+v"(c.tr), "+v"(c.div));
 }
 
-// Column-tiled variant: a workgroup owns 64 (phi) x JT (theta) indices and
-// walks a segment of r planes, doing all four kinds of rows at each plane.
-// Every scatter target lies within one index of the source in each direction
-// (in its own array's index space), so the adds go into an LDS window of
-// three r planes x (JT + 2) x 66 per field (phi indices unwrapped, so a
-// periodic neighbour across phi = 0 stays in the window); after plane i is
-// done, plane i - 1 can receive nothing more from this workgroup and is added
-// to the global arrays (one atomic per non-zero window entry) and cleared for
-// plane i + 2.  Global atomics drop from ~100 per cell to ~10.
+template <class S, class Acc>
+__device__ __forceinline__ void adj_pT(const AdjCtx<S> &x, int i, int j, int k, const Cent &c, Cent &cb, const Acc &A) {
+  const long row = ((long)i * x.g.nt + j) * x.g.np;
+  const unsigned o = (unsigned)k * 8u;
+  F_p_T_rev_cb(x.g, x.m, x.u, i, j, k, c, -x.tau * ldo(x.in.mu[0].p + row, o), -x.tau * ldo(x.in.mu[0].T + row, o), cb,
+               A);
+}
+
+// Indexes (i, j) of which a stencil leaves the arrays in r or theta: the shell
+// i = 0, nr - 1 and j = 0, nt - 1; the rest is the interior.
+__host__ __device__ inline long adj_shell_rows(int nr, int nt) {
+  return nr > 2 && nt > 2 ? 2L * nt + 2L * (nr - 2) : (long)nr * nt;
+}
+
+// The shell: one wave per 64 phi indices, (i, j) and piece of the work (the
+// p and T rows, the three block rows, the three faces; centre_rev is linear in
+// the adjoints, so the pieces of a cell add up), ghost rules at every load,
+// FP64 atomics straight into the global arrays.  A few per cent of the
+// indices.
+template <int PIECE>
+__device__ __forceinline__ void adj_shell_piece(KPtr kp, int i, int j, int k) {
+  asm volatile("" : "+s"(kp), "+s"(i), "+s"(j), "+v"(k));
+  const AdjCtx<SrcShell> x = kctx<SrcShell>(kp);
+  const GAcc A{kfields(kp, offsetof(AdjArgs, A))};
+  if constexpr (PIECE >= 4) {
+    adj_face<PIECE - 3>(x, i, j, k, A);
+  } else {
+    Cent c, cb{};
+    centre(x.g, x.m, x.u, i, j, k, c);
+    if constexpr (PIECE == 0) adj_pT(x, i, j, k, c, cb, A);
+    else cell_block_row<PIECE - 1>(x, i, j, k, c, cb, A);
+    centre_rev(x.g, x.m, x.u, i, j, k, c, cb, A);
+  }
+}
+
+__global__ void __launch_bounds__(64) DSW_OCC(2) k_adj_shell(AdjArgs) {
+  KPtr kp = (KPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  const int nr = karg<int>(kp, offsetof(AdjArgs, g) + offsetof(Geo, nr));
+  const int nt = karg<int>(kp, offsetof(AdjArgs, g) + offsetof(Geo, nt));
+  const int np = karg<int>(kp, offsetof(AdjArgs, g) + offsetof(Geo, np));
+  const int k = blockIdx.x * 64 + threadIdx.x;
+  int r = blockIdx.y, i, j;
+  if (nr > 2 && nt > 2) {
+    if (r < 2 * nt) { i = r < nt ? 0 : nr - 1; j = r < nt ? r : r - nt; }
+    else { r -= 2 * nt; i = 1 + (r >> 1); j = (r & 1) ? nt - 1 : 0; }
+  } else { i = r / nt; j = r - i * nt; }
+  if (k >= np) return;
+  switch (blockIdx.z) {
+    case 0: adj_shell_piece<0>(kp, i, j, k); break;
+    case 1: adj_shell_piece<1>(kp, i, j, k); break;
+    case 2: adj_shell_piece<2>(kp, i, j, k); break;
+    case 3: adj_shell_piece<3>(kp, i, j, k); break;
+    case 4: adj_shell_piece<4>(kp, i, j, k); break;
+    case 5: adj_shell_piece<5>(kp, i, j, k); break;
+    default: adj_shell_piece<6>(kp, i, j, k); break;
+  }
+}
+
+// The interior, column-tiled: a workgroup owns 64 (phi) x JT (theta) indices
+// and walks a segment of r planes, doing all rows of each plane.  Every
+// scatter target lies within one index of the source in each direction (in its
+// own array's index space, a phi ghost at its own place), so the adds go into
+// an LDS window of three r planes x (JT + 2) x 66 per field at offsets known
+// at compile time; after plane i is done, plane i - 1 can receive nothing more
+// from this workgroup and is added to the global arrays (one atomic per
+// non-zero window entry, the ghost columns through the phi boundary rule) and
+// cleared for plane i + 2.
+// Bound by the instruction count: about 4100 per plane and wave, 2900 of them
+// vector, 112 LDS adds.  With ghost rules and clamps at every load and add, an
+// IEEE division per quotient, the cell's rows each with a centre of their own
+// and every array an ordinary parameter it was 12400: a 64 x 128 x 256 region
+// took 750 us per iteration, now 362 and 134 for the shell.
 constexpr int ACOL_K = 64;
 constexpr int ACOL_W = ACOL_K + 2;
 
 template <int JT>
 struct TileAcc {
-  Fields A;
-  double *lds;         // [5 fields][3 slots][JT + 2][ACOL_W]
-  int i0, j0, k0;      // current plane, first theta row and phi column of the tile
-  int sl0, sl1, sl2;   // LDS slots of planes i0 - 1, i0, i0 + 1
-  __device__ __forceinline__ void add(const Geo &, int fid, int i, int j, int k, double v) const {
-    // in the window by construction; the clamps only keep LDS addresses in
-    // bounds
-    const int di = min(max(i - i0 + 1, 0), 2), jj = min(max(j - j0 + 1, 0), JT + 1);
-    const int kk = min(max(k - k0 + 1, 0), ACOL_W - 1);
-    const int sl = di == 0 ? sl0 : (di == 1 ? sl1 : sl2);
-    __hip_atomic_fetch_add(&lds[((fid * 3 + sl) * (JT + 2) + jj) * ACOL_W + kk], v, __ATOMIC_RELAXED,
+  static constexpr bool RAW = true;
+  static constexpr int PER = (JT + 2) * ACOL_W;
+  // this lane's window entry (j - 1, k - 1) of field 0 in planes i - 1, i, i + 1
+  double *w0, *w1, *w2;
+  int i, j, k;
+  __device__ __forceinline__ void add(const Geo &, int fid, int i_, int j_, int k_, double v) const {
+    double *w = i_ - i < 0 ? w0 : (i_ - i == 0 ? w1 : w2);
+    __hip_atomic_fetch_add(w + (fid * 3 * PER + (j_ - j + 1) * ACOL_W + (k_ - k + 1)), v, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_WORKGROUP);
   }
 };
 
-// add LDS slot sl (plane p) to the global arrays and clear it
-template <int JT>
-__device__ __forceinline__ void acol_flush(const Geo &g, const Fields &A, double *lds, int sl, int p, int j0,
-                                           int k0, int tid, int nth) {
-  constexpr int PER = (JT + 2) * ACOL_W;
-  for (int e = tid; e < 5 * PER; e += nth) {
-    const int fid = e / PER, r = e - fid * PER, jj = r / ACOL_W, kk = r - jj * ACOL_W;
-    double *q = &lds[(fid * 3 + sl) * PER + r];
-    const double v = *q;
-    *q = 0.0;
-    if (v == 0.0) continue;
-    const int j = j0 - 1 + jj;
-    int k = k0 - 1 + kk;
-    if (g.periodic) k = wrapk(g, k);
-    const int ni = fid == F_UR ? g.nr + 1 : g.nr, nj = fid == F_UT ? g.nt + 1 : g.nt;
-    const int nk = fid == F_UF ? g.npf : g.np;
-    if (p >= 0 && p < ni && j >= 0 && j < nj && k >= 0 && k < nk) GAcc{A}.add(g, fid, p, j, k, v);
+// add window plane w (of r plane p) to the global arrays and clear it
+template <int JT, bool P>
+__device__ __forceinline__ void acol_flush(KPtr kp, double *w, int p, int j0, int k0, int tid) {
+  constexpr int PER = (JT + 2) * ACOL_W, NTH = ACOL_K * JT;
+  const Geo g = kgeo(kp);
+  const Fields A = kfields(kp, offsetof(AdjArgs, A));
+  for (int e = tid; e < PER; e += NTH) {
+    const int jj = e / ACOL_W, kk = e - jj * ACOL_W;
+    const int j = j0 - 1 + jj, kr = k0 - 1 + kk;
+    const bool gh = kr < 0 || kr >= g.np;
+    const int k = P ? wrapk(g, kr) : clampi(kr, 0, g.np - 1);
+    const double sg = !P && gh ? -1.0 : 1.0;
+    // the window's last columns beyond np (np + 1 and on) never receive a value
+    const long row = (long)p * g.nt + j, rt = (long)p * (g.nt + 1) + j;
+#pragma unroll
+    for (int fid = 0; fid < 5; fid++) {
+      double *q = w + fid * 3 * PER + e;
+      const double v = *q;
+      *q = 0.0;
+      if (v == 0.0) continue;
+      if (fid == F_P) unsafeAtomicAdd(A.p + row * g.np + k, v);
+      else if (fid == F_T) unsafeAtomicAdd(A.T + row * g.np + k, v);
+      else if (fid == F_UR) unsafeAtomicAdd(A.ur + row * g.np + k, sg * v);
+      else if (fid == F_UT) unsafeAtomicAdd(A.ut + rt * g.np + k, sg * v);
+      else unsafeAtomicAdd(A.uf + row * g.npf + (P ? k : kr), v);
+    }
   }
 }
 
-template <int JT>
-__global__ void __launch_bounds__(64 * JT) k_adj_col(Geo g, Mat m, SrcOne u, double tau, AdjIn in,
-                                                     Fields A, int seg) {
-  __shared__ double lds[5 * 3 * (JT + 2) * ACOL_W];
-  const int tid = threadIdx.y * ACOL_K + threadIdx.x, nth = ACOL_K * JT;
-  const int k0 = blockIdx.x * ACOL_K, j0 = blockIdx.y * JT;
+template <int JT, bool P>
+__global__ void __launch_bounds__(64 * JT) DSW_OCC(2) k_adj_col(AdjArgs) {
+  constexpr int PER = (JT + 2) * ACOL_W;
+  __shared__ double lds[5 * 3 * PER];
+  KPtr kp = (KPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  const int tid = threadIdx.y * ACOL_K + threadIdx.x;
+  const int nr = karg<int>(kp, offsetof(AdjArgs, g) + offsetof(Geo, nr));
+  const int nt = karg<int>(kp, offsetof(AdjArgs, g) + offsetof(Geo, nt));
+  const int np = karg<int>(kp, offsetof(AdjArgs, g) + offsetof(Geo, np));
+  const int seg = karg<int>(kp, offsetof(AdjArgs, seg));
+  const int k0 = blockIdx.x * ACOL_K, j0 = 1 + blockIdx.y * JT;
   // one wave per theta row (blockDim.x is the wave size): j is wave-uniform
   const int k = k0 + threadIdx.x, j = __builtin_amdgcn_readfirstlane(j0 + (int)threadIdx.y);
-  const int ib = blockIdx.z * seg, ie = min(g.nr, ib + seg);
-  for (int e = tid; e < 5 * 3 * (JT + 2) * ACOL_W; e += nth) lds[e] = 0.0;
+  const int ib = 1 + blockIdx.z * seg, ie = min(nr - 1, ib + seg);
+  for (int e = tid; e < 5 * 3 * PER; e += ACOL_K * JT) lds[e] = 0.0;
   __syncthreads();
-  // plane p lives in slot (p - ib + 1) % 3
-  TileAcc<JT> ta{A, lds, 0, j0, k0, 0, 0, 0};
-  const bool on = j < g.nt && k < g.np;
+  const bool on = j < nt - 1 && k < np;
+  // window planes of r planes i - 1, i, i + 1
+  int s0 = 0, s1 = PER, s2 = 2 * PER;
+  const int lane = threadIdx.y * ACOL_W + threadIdx.x;
 #pragma nounroll
   for (int i = ib; i < ie; i++) {
-    ta.i0 = i;
-    ta.sl0 = (i - ib) % 3;
-    ta.sl1 = (i - ib + 1) % 3;
-    ta.sl2 = (i - ib + 2) % 3;
     if (on) {
-      // the indices pass through an empty asm before each piece, so that
-      // nothing derived from them is hoisted out of the loop or shared
-      // between pieces (either keeps hundreds of registers live)
-      int jv, kv;
-#define DSW_ACOL_PIECE(CALL)                  \
-      jv = j; kv = k;                         \
-      asm volatile("" : "+s"(jv), "+v"(kv));  \
-      CALL;
-      DSW_ACOL_PIECE((adj_cell_piece<0>(g, m, u, tau, in, i, jv, kv, ta)))
-      DSW_ACOL_PIECE((adj_cell_piece<1>(g, m, u, tau, in, i, jv, kv, ta)))
-      DSW_ACOL_PIECE((adj_cell_piece<2>(g, m, u, tau, in, i, jv, kv, ta)))
-      DSW_ACOL_PIECE((adj_cell_piece<3>(g, m, u, tau, in, i, jv, kv, ta)))
-      DSW_ACOL_PIECE((adj_point<1>(g, m, u, tau, in, i, jv, kv, ta)))
-      DSW_ACOL_PIECE((adj_point<2>(g, m, u, tau, in, i, jv, kv, ta)))
-      DSW_ACOL_PIECE((adj_point<3>(g, m, u, tau, in, i, jv, kv, ta)))
+      // the indices and the argument block pass through an empty asm before
+      // each piece, so that nothing derived from them is hoisted out of the
+      // loop or shared between pieces (either keeps hundreds of registers live)
+      KPtr p = kp;
+      int iv = i, jv = j, kv = k;
+#define DSW_ACOL_PIECE(CALL)                                               \
+      {                                                                    \
+        asm volatile("" : "+s"(p), "+s"(iv), "+s"(jv), "+v"(kv));          \
+        const AdjCtx<SrcRow<P>> x = kctx<SrcRow<P>>(p);                    \
+        const TileAcc<JT> A{lds + s0 + lane, lds + s1 + lane, lds + s2 + lane, iv, jv, kv}; \
+        CALL;                                                              \
+      }
+      Cent c, cb{};
+      DSW_ACOL_PIECE((centre(x.g, x.m, x.u, iv, jv, kv, c), (void)A))
+      cent_pin(c);
+      DSW_ACOL_PIECE((adj_pT(x, iv, jv, kv, c, cb, A)))
+      cent_pin(cb);
+      DSW_ACOL_PIECE((cell_block_row<0>(x, iv, jv, kv, c, cb, A)))
+      cent_pin(cb);
+      DSW_ACOL_PIECE((cell_block_row<1>(x, iv, jv, kv, c, cb, A)))
+      cent_pin(cb);
+      DSW_ACOL_PIECE((cell_block_row<2>(x, iv, jv, kv, c, cb, A)))
+      cent_pin(cb);
+      DSW_ACOL_PIECE((centre_rev(x.g, x.m, x.u, iv, jv, kv, c, cb, A)))
+      DSW_ACOL_PIECE((adj_face<1>(x, iv, jv, kv, A)))
+      DSW_ACOL_PIECE((adj_face<2>(x, iv, jv, kv, A)))
+      DSW_ACOL_PIECE((adj_face<3>(x, iv, jv, kv, A)))
 #undef DSW_ACOL_PIECE
     }
     __syncthreads();
-    if (i - 1 >= 0) acol_flush<JT>(g, A, lds, (i - ib) % 3, i - 1, j0, k0, tid, nth);
+    acol_flush<JT, P>(kp, lds + s0, i - 1, j0, k0, tid);
     __syncthreads();
+    const int t = s0;
+    s0 = s1; s1 = s2; s2 = t;
   }
-  acol_flush<JT>(g, A, lds, (ie - ib) % 3, ie - 1, j0, k0, tid, nth);
-  if (ie <= g.nr) acol_flush<JT>(g, A, lds, (ie - ib + 1) % 3, ie, j0, k0, tid, nth);
+  acol_flush<JT, P>(kp, lds + s0, ie - 1, j0, k0, tid);
+  acol_flush<JT, P>(kp, lds + s1, ie, j0, k0, tid);
 }
+
+constexpr int ADJ_JT = 4;  // theta rows per workgroup of the column-tiled reverse
+constexpr int ADJ_SEG = 8; // r planes per workgroup
 
 void launch_adj_local(const Geo &g, const Mat &m, const Fields &Ub, double tau, const Fields *X,
                       const Fields *mu, const Fields &acc_, hipStream_t st) {
-  SrcOne u;
-  u.a[F_P] = Ub.p; u.a[F_UR] = Ub.ur; u.a[F_UT] = Ub.ut; u.a[F_UF] = Ub.uf; u.a[F_T] = Ub.T;
-  AdjIn in;
-  for (int d = 0; d < 3; d++) { in.X[d] = X[d]; in.mu[d] = mu[d]; }
-#ifndef DSW_ADJ_ATOMIC
-  constexpr int JT = DSW_ADJ_JT;
-  const int seg = DSW_ADJ_SEG;
-  const dim3 grid((g.np + ACOL_K - 1) / ACOL_K, (g.nt + JT - 1) / JT, (g.nr + seg - 1) / seg),
-      block(ACOL_K, JT);
-  hipLaunchKernelGGL(k_adj_col<JT>, grid, block, 0, st, g, m, u, tau, in, acc_, seg);
-#else
-  const dim3 grid((g.npf + 63) / 64, g.nt + 1, g.nr + 1), block(64);
-  hipLaunchKernelGGL(k_adj_local<0>, grid, block, 0, st, g, m, u, tau, in, acc_);
-  hipLaunchKernelGGL(k_adj_local<1>, grid, block, 0, st, g, m, u, tau, in, acc_);
-  hipLaunchKernelGGL(k_adj_local<2>, grid, block, 0, st, g, m, u, tau, in, acc_);
-  hipLaunchKernelGGL(k_adj_local<3>, grid, block, 0, st, g, m, u, tau, in, acc_);
-#endif
+  AdjArgs a{};
+  a.g = g;
+  a.m = m;
+  a.u[F_P] = Ub.p; a.u[F_UR] = Ub.ur; a.u[F_UT] = Ub.ut; a.u[F_UF] = Ub.uf; a.u[F_T] = Ub.T;
+  a.tau = tau;
+  for (int d = 0; d < 3; d++) { a.in.X[d] = X[d]; a.in.mu[d] = mu[d]; }
+  a.A = acc_;
+  a.seg = ADJ_SEG;
+  const unsigned nk = (g.np + ACOL_K - 1) / ACOL_K;
+  if (g.nr > 2 && g.nt > 2) {
+    const dim3 grid(nk, (g.nt - 2 + ADJ_JT - 1) / ADJ_JT, (g.nr - 2 + ADJ_SEG - 1) / ADJ_SEG), block(ACOL_K, ADJ_JT);
+    if (g.periodic) hipLaunchKernelGGL((k_adj_col<ADJ_JT, true>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((k_adj_col<ADJ_JT, false>), grid, block, 0, st, a);
+  }
+  hipLaunchKernelGGL(k_adj_shell, dim3(nk, (unsigned)adj_shell_rows(g.nr, g.nt), 7), dim3(64), 0, st, a);
 }
 
 // --------------------------------------------------- elementwise helpers --

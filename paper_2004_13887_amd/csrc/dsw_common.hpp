@@ -68,7 +68,9 @@ struct SrcOneT {
   static constexpr bool PERIODIC = P; // interior sources: phi periodic (known at compile time)
   static constexpr bool WALL = false;  // tangential wall velocities are zero
   static constexpr bool PERT = false;  // p holds the full pressure
+  using Row = int;
   __device__ __forceinline__ double ld(int f, long x) const { return a[f][x]; }
+  __device__ __forceinline__ double ldk(int f, int row, int k) const { return a[f][row + k]; }
 };
 using SrcOne = SrcOneT<false>;
 using SrcInN = SrcOneT<true, false>; // interior, phi bounded by walls
@@ -119,7 +121,9 @@ struct SrcInW {
   static constexpr bool PERIODIC = P;
   static constexpr bool WALL = true;
   static constexpr bool PERT = false;
+  using Row = int;
   __device__ __forceinline__ double ld(int fid, long x) const { return a[fid][x]; }
+  __device__ __forceinline__ double ldk(int fid, int row, int k) const { return a[fid][row + k]; }
 };
 
 // The perturbation-pressure form of a plain source (dsw_split_step_pert):
@@ -189,7 +193,7 @@ template <class S>
 __device__ __forceinline__ double gC(const Geo &g, const S &s, int fid, int i, int j, int k) {
   if constexpr (S::INTERIOR) {
     const int kk = S::PERIODIC ? wrapk(g, k) : clampi(k, 0, g.np - 1);
-    return s.ld(fid, (i * g.nt + j) * g.np + kk);
+    return s.ldk(fid, ((typename S::Row)i * g.nt + j) * g.np, kk);
   }
   i = clampi(i, 0, g.nr - 1);
   j = clampi(j, 0, g.nt - 1);
@@ -200,9 +204,9 @@ __device__ __forceinline__ double gC(const Geo &g, const S &s, int fid, int i, i
 template <class S>
 __device__ __forceinline__ double gR(const Geo &g, const S &s, int f, int j, int k) {
   if constexpr (S::INTERIOR) {
-    if constexpr (S::PERIODIC) return s.ld(F_UR, (f * g.nt + j) * g.np + wrapk(g, k));
+    if constexpr (S::PERIODIC) return s.ldk(F_UR, ((typename S::Row)f * g.nt + j) * g.np, wrapk(g, k));
     const int kk = clampi(k, 0, g.np - 1);
-    const double v = s.ld(F_UR, (f * g.nt + j) * g.np + kk);
+    const double v = s.ldk(F_UR, ((typename S::Row)f * g.nt + j) * g.np, kk);
     if constexpr (S::WALL) return kk == k ? v : 2.0 * wallv(k < 0 ? s.w.ur_p1 : s.w.ur_p2, (long)f * g.nt + j) - v;
     return kk == k ? v : -v;
   }
@@ -220,9 +224,9 @@ __device__ __forceinline__ double gR(const Geo &g, const S &s, int f, int j, int
 template <class S>
 __device__ __forceinline__ double gT(const Geo &g, const S &s, int i, int f, int k) {
   if constexpr (S::INTERIOR) {
-    if constexpr (S::PERIODIC) return s.ld(F_UT, (i * (g.nt + 1) + f) * g.np + wrapk(g, k));
+    if constexpr (S::PERIODIC) return s.ldk(F_UT, ((typename S::Row)i * (g.nt + 1) + f) * g.np, wrapk(g, k));
     const int kk = clampi(k, 0, g.np - 1);
-    const double v = s.ld(F_UT, (i * (g.nt + 1) + f) * g.np + kk);
+    const double v = s.ldk(F_UT, ((typename S::Row)i * (g.nt + 1) + f) * g.np, kk);
     if constexpr (S::WALL) return kk == k ? v : 2.0 * wallv(k < 0 ? s.w.ut_p1 : s.w.ut_p2, (long)i * (g.nt + 1) + f) - v;
     return kk == k ? v : -v;
   }
@@ -239,7 +243,7 @@ __device__ __forceinline__ double gT(const Geo &g, const S &s, int i, int f, int
 // u_phi at phi-face f, ghosts across r and theta boundaries (poles included)
 template <class S>
 __device__ __forceinline__ double gF(const Geo &g, const S &s, int i, int j, int f) {
-  if constexpr (S::INTERIOR) return s.ld(F_UF, (i * g.nt + j) * g.npf + (S::PERIODIC ? wrapk(g, f) : f));
+  if constexpr (S::INTERIOR) return s.ldk(F_UF, ((typename S::Row)i * g.nt + j) * g.npf, S::PERIODIC ? wrapk(g, f) : f);
   if constexpr (S::WALL) return gF_wall(g, s, i, j, f);
   double sg = 1.0;
   if (g.periodic) f = wrapk(g, f);
