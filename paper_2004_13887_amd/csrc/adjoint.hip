@@ -1237,86 +1237,141 @@ __device__ __forceinline__ void adj_pT(const AdjCtx<S> &x, int i, int j, int k, 
                A);
 }
 
-// Indexes (i, j) of which a stencil leaves the arrays in r or theta: the shell
-// i = 0, nr - 1 and j = 0, nt - 1; the rest is the interior.
-__host__ __device__ inline long adj_shell_rows(int nr, int nt) {
-  return nr > 2 && nt > 2 ? 2L * nt + 2L * (nr - 2) : (long)nr * nt;
-}
-
-// The shell: one wave per 64 phi indices, (i, j) and piece of the work (the
-// p and T rows, the three block rows, the three faces; centre_rev is linear in
-// the adjoints, so the pieces of a cell add up), ghost rules at every load,
-// FP64 atomics straight into the global arrays.  A few per cent of the
-// indices.
-template <int PIECE>
-__device__ __forceinline__ void adj_shell_piece(KPtr kp, int i, int j, int k) {
-  asm volatile("" : "+s"(kp), "+s"(i), "+s"(j), "+v"(k));
-  const AdjCtx<SrcShell> x = kctx<SrcShell>(kp);
-  const GAcc A{kfields(kp, offsetof(AdjArgs, A))};
-  if constexpr (PIECE >= 4) {
-    adj_face<PIECE - 3>(x, i, j, k, A);
-  } else {
-    Cent c, cb{};
-    centre(x.g, x.m, x.u, i, j, k, c);
-    if constexpr (PIECE == 0) adj_pT(x, i, j, k, c, cb, A);
-    else cell_block_row<PIECE - 1>(x, i, j, k, c, cb, A);
-    centre_rev(x.g, x.m, x.u, i, j, k, c, cb, A);
-  }
-}
-
-__global__ void __launch_bounds__(64) DSW_OCC(2) k_adj_shell(AdjArgs) {
-  KPtr kp = (KPtr)__builtin_amdgcn_kernarg_segment_ptr();
-  const int nr = karg<int>(kp, offsetof(AdjArgs, g) + offsetof(Geo, nr));
-  const int nt = karg<int>(kp, offsetof(AdjArgs, g) + offsetof(Geo, nt));
-  const int np = karg<int>(kp, offsetof(AdjArgs, g) + offsetof(Geo, np));
-  const int k = blockIdx.x * 64 + threadIdx.x;
-  int r = blockIdx.y, i, j;
-  if (nr > 2 && nt > 2) {
-    if (r < 2 * nt) { i = r < nt ? 0 : nr - 1; j = r < nt ? r : r - nt; }
-    else { r -= 2 * nt; i = 1 + (r >> 1); j = (r & 1) ? nt - 1 : 0; }
-  } else { i = r / nt; j = r - i * nt; }
-  if (k >= np) return;
-  switch (blockIdx.z) {
-    case 0: adj_shell_piece<0>(kp, i, j, k); break;
-    case 1: adj_shell_piece<1>(kp, i, j, k); break;
-    case 2: adj_shell_piece<2>(kp, i, j, k); break;
-    case 3: adj_shell_piece<3>(kp, i, j, k); break;
-    case 4: adj_shell_piece<4>(kp, i, j, k); break;
-    case 5: adj_shell_piece<5>(kp, i, j, k); break;
-    default: adj_shell_piece<6>(kp, i, j, k); break;
-  }
-}
-
-// The interior, column-tiled: a workgroup owns 64 (phi) x JT (theta) indices
-// and walks a segment of r planes, doing all rows of each plane.  Every
-// scatter target lies within one index of the source in each direction (in its
-// own array's index space, a phi ghost at its own place), so the adds go into
-// an LDS window of three r planes x (JT + 2) x 66 per field at offsets known
-// at compile time; after plane i is done, plane i - 1 can receive nothing more
-// from this workgroup and is added to the global arrays (one atomic per
-// non-zero window entry, the ghost columns through the phi boundary rule) and
-// cleared for plane i + 2.
-// Bound by the instruction count: about 4100 per plane and wave, 2900 of them
-// vector, 112 LDS adds.  With ghost rules and clamps at every load and add, an
-// IEEE division per quotient, the cell's rows each with a centre of their own
-// and every array an ordinary parameter it was 12400: a 64 x 128 x 256 region
-// took 750 us per iteration, now 362 and 134 for the shell.
-constexpr int ACOL_K = 64;
+// The rows at the indices of a workgroup's waves.  Every scatter target lies
+// within one index of the source in each direction (in its own array's index
+// space, a ghost at its own place), so the adds go into an LDS window at
+// offsets known at compile time.
+constexpr int ACOL_K = 64;          // phi indices per workgroup
 constexpr int ACOL_W = ACOL_K + 2;
 
-template <int JT>
+// FS: doubles per field of the window.  w0, w1, w2: this lane's entry (j - 1,
+// k - 1) of field 0 in the window planes i - 1, i, i + 1
+template <int FS>
 struct TileAcc {
   static constexpr bool RAW = true;
-  static constexpr int PER = (JT + 2) * ACOL_W;
-  // this lane's window entry (j - 1, k - 1) of field 0 in planes i - 1, i, i + 1
   double *w0, *w1, *w2;
   int i, j, k;
   __device__ __forceinline__ void add(const Geo &, int fid, int i_, int j_, int k_, double v) const {
     double *w = i_ - i < 0 ? w0 : (i_ - i == 0 ? w1 : w2);
-    __hip_atomic_fetch_add(w + (fid * 3 * PER + (j_ - j + 1) * ACOL_W + (k_ - k + 1)), v, __ATOMIC_RELAXED,
+    __hip_atomic_fetch_add(w + (fid * FS + (j_ - j + 1) * ACOL_W + (k_ - k + 1)), v, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_WORKGROUP);
   }
 };
+
+// The indices and the argument block pass through an empty asm before each
+// piece, so that nothing derived from them is hoisted out of a loop or shared
+// between pieces (either keeps hundreds of registers live).
+template <class S, int FS, bool CELL, bool FACE>
+__device__ __forceinline__ void adj_rows(KPtr p, double *w0, double *w1, double *w2, int i, int j, int k) {
+#define DSW_ACOL_PIECE(CALL)                                       \
+  {                                                                \
+    asm volatile("" : "+s"(p), "+s"(i), "+s"(j), "+v"(k));         \
+    const AdjCtx<S> x = kctx<S>(p);                                \
+    const TileAcc<FS> A{w0, w1, w2, i, j, k};                      \
+    CALL;                                                          \
+  }
+  if constexpr (CELL) {
+    Cent c, cb{};
+    DSW_ACOL_PIECE((centre(x.g, x.m, x.u, i, j, k, c), (void)A))
+    cent_pin(c);
+    DSW_ACOL_PIECE((adj_pT(x, i, j, k, c, cb, A)))
+    cent_pin(cb);
+    DSW_ACOL_PIECE((cell_block_row<0>(x, i, j, k, c, cb, A)))
+    cent_pin(cb);
+    DSW_ACOL_PIECE((cell_block_row<1>(x, i, j, k, c, cb, A)))
+    cent_pin(cb);
+    DSW_ACOL_PIECE((cell_block_row<2>(x, i, j, k, c, cb, A)))
+    cent_pin(cb);
+    DSW_ACOL_PIECE((centre_rev(x.g, x.m, x.u, i, j, k, c, cb, A)))
+  }
+  if constexpr (FACE) {
+    DSW_ACOL_PIECE((adj_face<1>(x, i, j, k, A)))
+    DSW_ACOL_PIECE((adj_face<2>(x, i, j, k, A)))
+    DSW_ACOL_PIECE((adj_face<3>(x, i, j, k, A)))
+  }
+#undef DSW_ACOL_PIECE
+}
+
+// The shell: the indices i = 0, nr - 1 and j = 0, nt - 1, of which a stencil
+// leaves the arrays in r or theta.  A workgroup owns 64 phi indices of four
+// rows (along theta in the planes i = 0, nr - 1, along r on the theta walls)
+// and does either their cells or their faces (blockIdx.z): few workgroups, one
+// pass of each, so the time is that of the longest wave.  Ghost rules at every
+// load; adds to a ghost are folded when the window is written back.  With one
+// wave per row and kind of row and the adds as global atomics (212 per cell)
+// the shell of a 64 x 128 x 256 region took 134 us, now 40.
+__global__ void __launch_bounds__(256) DSW_OCC(2) k_adj_shell(AdjArgs) {
+  constexpr int FS = 18 * ACOL_W;
+  __shared__ double lds[5 * FS];
+  KPtr kp = (KPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  const int nr = karg<int>(kp, offsetof(AdjArgs, g) + offsetof(Geo, nr));
+  const int nt = karg<int>(kp, offsetof(AdjArgs, g) + offsetof(Geo, nt));
+  const int np = karg<int>(kp, offsetof(AdjArgs, g) + offsetof(Geo, np));
+  const int tid = threadIdx.y * ACOL_K + threadIdx.x;
+  const int ty = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
+  const int k0 = blockIdx.x * ACOL_K, k = k0 + threadIdx.x;
+  const int gt = (nt + 3) / 4, gr = (nr - 2 + 3) / 4;
+  int q = blockIdx.y;
+  const bool plane = q < 2 * gt; // 3 x 6 window rows (planes by theta rows), else 6 x 3
+  int i0, j0;
+  if (plane) {
+    i0 = q < gt ? 0 : nr - 1;
+    j0 = 4 * (q < gt ? q : q - gt);
+  } else {
+    q -= 2 * gt;
+    j0 = q < gr ? 0 : nt - 1;
+    i0 = 1 + 4 * (q < gr ? q : q - gr);
+  }
+  const int dj = plane ? 6 : 3; // theta rows per window plane
+  const int i = plane ? i0 : i0 + ty, j = plane ? j0 + ty : j0;
+  for (int e = tid; e < 5 * FS; e += 256) lds[e] = 0.0;
+  __syncthreads();
+  if (i < (plane ? nr : nr - 1) && j < nt && k < np) {
+    double *w = lds + (plane ? ty : ty * dj) * ACOL_W + threadIdx.x;
+    if (blockIdx.z == 0) adj_rows<SrcShell, FS, true, false>(kp, w, w + dj * ACOL_W, w + 2 * dj * ACOL_W, i, j, k);
+    else adj_rows<SrcShell, FS, false, true>(kp, w, w + dj * ACOL_W, w + 2 * dj * ACOL_W, i, j, k);
+  }
+  __syncthreads();
+  const Geo g = kgeo(kp);
+  const Fields A = kfields(kp, offsetof(AdjArgs, A));
+  for (int e = tid; e < FS; e += 256) {
+    const int r = e / ACOL_W, kk = e - r * ACOL_W;
+    const int di = plane ? (r >= 6 ? (r >= 12 ? 2 : 1) : 0) : r / 3;
+    const int p = i0 - 1 + di, jr = j0 - 1 + r - di * dj, kr = k0 - 1 + kk;
+    const int pc = clampi(p, 0, nr - 1), jc = clampi(jr, 0, nt - 1), kc = phi_in(g, kr);
+    const bool sk = !g.periodic && kc != kr; // odd in a phi wall
+    const bool sj = (jr < 0 && !g.pole_lo) || (jr >= nt && !g.pole_hi);
+#pragma unroll
+    for (int f = 0; f < 5; f++) {
+      const double v = lds[f * FS + e];
+      if (v == 0.0) continue;
+      if (f == F_P) unsafeAtomicAdd(A.p + idx_c(g, pc, jc, kc), v);
+      else if (f == F_T) unsafeAtomicAdd(A.T + idx_c(g, pc, jc, kc), v);
+      else if (f == F_UR) unsafeAtomicAdd(A.ur + idx_r(g, p, jc, kc), sk != sj ? -v : v);
+      else if (f == F_UT) unsafeAtomicAdd(A.ut + idx_t(g, pc, jr, kc), sk != (pc != p) ? -v : v);
+      else unsafeAtomicAdd(A.uf + idx_f(g, pc, jc, g.periodic ? kc : kr), (pc != p) != (jc != jr) ? -v : v);
+    }
+  }
+}
+
+// The interior: a workgroup owns 64 (phi) x JT (theta) indices and walks a
+// segment of r planes; its window holds three planes of (JT + 2) x 66 per
+// field.  After plane i is done, plane i - 1 can receive nothing more from
+// this workgroup and is added to the global arrays (one atomic per non-zero
+// window entry, the ghost columns through the phi boundary rule) and cleared
+// for plane i + 2.
+// Bound by the instruction count: about 4100 per plane and wave, 2900 of them
+// vector, 112 LDS adds.  With ghost rules and clamps at every load and add, an
+// IEEE division per quotient, the cell's rows each with a centre of their own
+// and every array an ordinary parameter it was 12400: a 64 x 128 x 256 region
+// took 750 us per iteration, now 339 (eight theta rows and planes: 321, but
+// 164 instead of 80 on the 24 x 90 x 180 sphere, which they leave half empty).
+constexpr int ADJ_JT = 4; // theta rows per workgroup: three workgroups per CU
+// r planes per workgroup: a segment costs two more planes of write-back, but
+// fewer segments than wave slots leave CUs idle.  64 x 128 x 256 takes 343,
+// 339, 366 us with 2, 4, 8 planes; 37 x 101 x 150 112, 111, 154; the sphere 80,
+// 93, 131.
+constexpr int ADJ_SEG = 4, ADJ_SEG_SMALL = 2, ADJ_FULL_WGS = 3 * 256;
 
 // add window plane w (of r plane p) to the global arrays and clear it
 template <int JT, bool P>
@@ -1330,7 +1385,7 @@ __device__ __forceinline__ void acol_flush(KPtr kp, double *w, int p, int j0, in
     const bool gh = kr < 0 || kr >= g.np;
     const int k = P ? wrapk(g, kr) : clampi(kr, 0, g.np - 1);
     const double sg = !P && gh ? -1.0 : 1.0;
-    // the window's last columns beyond np (np + 1 and on) never receive a value
+    // the window's columns beyond np never receive a value
     const long row = (long)p * g.nt + j, rt = (long)p * (g.nt + 1) + j;
 #pragma unroll
     for (int fid = 0; fid < 5; fid++) {
@@ -1369,36 +1424,7 @@ __global__ void __launch_bounds__(64 * JT) DSW_OCC(2) k_adj_col(AdjArgs) {
   const int lane = threadIdx.y * ACOL_W + threadIdx.x;
 #pragma nounroll
   for (int i = ib; i < ie; i++) {
-    if (on) {
-      // the indices and the argument block pass through an empty asm before
-      // each piece, so that nothing derived from them is hoisted out of the
-      // loop or shared between pieces (either keeps hundreds of registers live)
-      KPtr p = kp;
-      int iv = i, jv = j, kv = k;
-#define DSW_ACOL_PIECE(CALL)                                               \
-      {                                                                    \
-        asm volatile("" : "+s"(p), "+s"(iv), "+s"(jv), "+v"(kv));          \
-        const AdjCtx<SrcRow<P>> x = kctx<SrcRow<P>>(p);                    \
-        const TileAcc<JT> A{lds + s0 + lane, lds + s1 + lane, lds + s2 + lane, iv, jv, kv}; \
-        CALL;                                                              \
-      }
-      Cent c, cb{};
-      DSW_ACOL_PIECE((centre(x.g, x.m, x.u, iv, jv, kv, c), (void)A))
-      cent_pin(c);
-      DSW_ACOL_PIECE((adj_pT(x, iv, jv, kv, c, cb, A)))
-      cent_pin(cb);
-      DSW_ACOL_PIECE((cell_block_row<0>(x, iv, jv, kv, c, cb, A)))
-      cent_pin(cb);
-      DSW_ACOL_PIECE((cell_block_row<1>(x, iv, jv, kv, c, cb, A)))
-      cent_pin(cb);
-      DSW_ACOL_PIECE((cell_block_row<2>(x, iv, jv, kv, c, cb, A)))
-      cent_pin(cb);
-      DSW_ACOL_PIECE((centre_rev(x.g, x.m, x.u, iv, jv, kv, c, cb, A)))
-      DSW_ACOL_PIECE((adj_face<1>(x, iv, jv, kv, A)))
-      DSW_ACOL_PIECE((adj_face<2>(x, iv, jv, kv, A)))
-      DSW_ACOL_PIECE((adj_face<3>(x, iv, jv, kv, A)))
-#undef DSW_ACOL_PIECE
-    }
+    if (on) adj_rows<SrcRow<P>, 3 * PER, true, true>(kp, lds + s0 + lane, lds + s1 + lane, lds + s2 + lane, i, j, k);
     __syncthreads();
     acol_flush<JT, P>(kp, lds + s0, i - 1, j0, k0, tid);
     __syncthreads();
@@ -1409,9 +1435,6 @@ __global__ void __launch_bounds__(64 * JT) DSW_OCC(2) k_adj_col(AdjArgs) {
   acol_flush<JT, P>(kp, lds + s1, ie, j0, k0, tid);
 }
 
-constexpr int ADJ_JT = 4;  // theta rows per workgroup of the column-tiled reverse
-constexpr int ADJ_SEG = 8; // r planes per workgroup
-
 void launch_adj_local(const Geo &g, const Mat &m, const Fields &Ub, double tau, const Fields *X,
                       const Fields *mu, const Fields &acc_, hipStream_t st) {
   AdjArgs a{};
@@ -1421,14 +1444,15 @@ void launch_adj_local(const Geo &g, const Mat &m, const Fields &Ub, double tau, 
   a.tau = tau;
   for (int d = 0; d < 3; d++) { a.in.X[d] = X[d]; a.in.mu[d] = mu[d]; }
   a.A = acc_;
-  a.seg = ADJ_SEG;
-  const unsigned nk = (g.np + ACOL_K - 1) / ACOL_K;
-  if (g.nr > 2 && g.nt > 2) {
-    const dim3 grid(nk, (g.nt - 2 + ADJ_JT - 1) / ADJ_JT, (g.nr - 2 + ADJ_SEG - 1) / ADJ_SEG), block(ACOL_K, ADJ_JT);
-    if (g.periodic) hipLaunchKernelGGL((k_adj_col<ADJ_JT, true>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((k_adj_col<ADJ_JT, false>), grid, block, 0, st, a);
-  }
-  hipLaunchKernelGGL(k_adj_shell, dim3(nk, (unsigned)adj_shell_rows(g.nr, g.nt), 7), dim3(64), 0, st, a);
+  const unsigned nk = (g.np + ACOL_K - 1) / ACOL_K, nj = (g.nt - 2 + ADJ_JT - 1) / ADJ_JT;
+  const auto segs = [&](int n) { return (unsigned)((g.nr - 2 + n - 1) / n); };
+  a.seg = (long)nk * nj * segs(ADJ_SEG) >= ADJ_FULL_WGS ? ADJ_SEG : ADJ_SEG_SMALL;
+  // every cell count is at least 3, so there is an interior
+  const dim3 grid(nk, nj, segs(a.seg)), block(ACOL_K, ADJ_JT);
+  if (g.periodic) hipLaunchKernelGGL((k_adj_col<ADJ_JT, true>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((k_adj_col<ADJ_JT, false>), grid, block, 0, st, a);
+  const unsigned rows = 2 * ((g.nt + 3) / 4 + (g.nr + 1) / 4);
+  hipLaunchKernelGGL(k_adj_shell, dim3(nk, rows, 2), dim3(ACOL_K, 4), 0, st, a);
 }
 
 // --------------------------------------------------- elementwise helpers --
