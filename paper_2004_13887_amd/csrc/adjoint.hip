@@ -15,6 +15,7 @@
 // last bits of the result, may differ from run to run.
 #include "dsw_common.hpp"
 #include "dsw_internal.hpp"
+#include "kargs.hpp"
 #include "rows_fast.hpp"
 
 namespace dsw {
@@ -988,50 +989,11 @@ struct AdjArgs {
   int seg;
 };
 
-// The arguments, read from the kernel's argument block.  The reverse of one
-// index takes 35 arrays and 15 tables: more scalar registers than there are,
-// and what does not fit is moved through vector lanes at every use (2500 lane
-// moves of 12400 instructions when each array was an ordinary parameter).  So
-// each piece of the work passes the block's address through an empty asm and
-// reads what it needs again (scalar loads that hit the cache).
-#define DSW_AS1 __attribute__((address_space(1)))
-#define DSW_AS4 __attribute__((address_space(4)))
-using KPtr = const DSW_AS4 char *;
-
-template <class T>
-__device__ __forceinline__ T karg(KPtr p, unsigned off) { return *(const DSW_AS4 T *)(p + off); }
-__device__ __forceinline__ const double *ktab(KPtr p, unsigned off) { // a table: constant, scalar loads
-  return (const double *)karg<const DSW_AS4 double *>(p, off);
-}
-__device__ __forceinline__ double *karr(KPtr p, unsigned off) {
-  return (double *)karg<DSW_AS1 double *>(p, off);
-}
-__device__ __forceinline__ Fields kfields(KPtr p, unsigned off) {
-  return {karr(p, off), karr(p, off + 8), karr(p, off + 16), karr(p, off + 24), karr(p, off + 32)};
-}
-
-__device__ __forceinline__ Geo kgeo(KPtr p) {
-  Geo g;
-#define DSW_KI(f) g.f = karg<int>(p, offsetof(AdjArgs, g) + offsetof(Geo, f))
-#define DSW_KD(f) g.f = karg<double>(p, offsetof(AdjArgs, g) + offsetof(Geo, f))
-#define DSW_KT(f) g.f = ktab(p, offsetof(AdjArgs, g) + offsetof(Geo, f))
-  DSW_KI(nr); DSW_KI(nt); DSW_KI(np); DSW_KI(npf); DSW_KI(periodic); DSW_KI(pole_lo); DSW_KI(pole_hi);
-  DSW_KD(dr); DSW_KD(dt); DSW_KD(dp); DSW_KD(idr); DSW_KD(idt); DSW_KD(idp);
-  DSW_KT(rc); DSW_KT(rf); DSW_KT(sc); DSW_KT(cc); DSW_KT(sf); DSW_KT(cf); DSW_KT(irc); DSW_KT(irf);
-  DSW_KT(isc); DSW_KT(ctc); DSW_KT(isf); DSW_KT(ctf); DSW_KT(scx); DSW_KT(mr); DSW_KT(mt);
-#undef DSW_KI
-#undef DSW_KD
-#undef DSW_KT
-  return g;
-}
-__device__ __forceinline__ Mat kmat(KPtr p) {
-  Mat m;
-#define DSW_KM(f) m.f = karg<double>(p, offsetof(AdjArgs, m) + offsetof(Mat, f))
-  DSW_KM(gam); DSW_KM(Rg); DSW_KM(pinf); DSW_KM(mu); DSW_KM(kap); DSW_KM(omega); DSW_KM(g_r);
-#undef DSW_KM
-  return m;
-}
-static_assert(offsetof(Fields, T) == 32 && offsetof(AdjIn, mu) == 120, "kfields, kctx read these layouts");
+// The reverse of one index takes 35 arrays and 15 tables, more scalar
+// registers than there are: each piece of the work reads what it needs from
+// the argument block again (kargs.hpp; with every array an ordinary parameter,
+// 2500 of 12400 instructions moved scalars through vector lanes).
+static_assert(offsetof(AdjIn, mu) == 120, "kctx reads this layout");
 
 // interior source: the row's base in scalar registers, the phi index a 32-bit
 // byte offset shared by all rows and arrays
@@ -1042,6 +1004,7 @@ struct SrcRow {
   static constexpr bool PERIODIC = P;
   static constexpr bool WALL = false;
   static constexpr bool PERT = false;
+  static constexpr bool WIN = false;
   using Row = long;
   __device__ __forceinline__ double ld(int f, long x) const { return a[f][x]; }
   __device__ __forceinline__ double ldk(int f, long row, int k) const { return ldo(a[f] + row, (unsigned)k * 8u); }
@@ -1058,8 +1021,8 @@ struct AdjCtx {
 template <class S>
 __device__ __forceinline__ AdjCtx<S> kctx(KPtr p) {
   AdjCtx<S> c;
-  c.g = kgeo(p);
-  c.m = kmat(p);
+  c.g = kgeo(p, offsetof(AdjArgs, g));
+  c.m = kmat(p, offsetof(AdjArgs, m));
 #pragma unroll
   for (int f = 0; f < 5; f++) c.u.a[f] = karr(p, offsetof(AdjArgs, u) + 8 * f);
   c.tau = karg<double>(p, offsetof(AdjArgs, tau));
@@ -1081,6 +1044,7 @@ struct SrcShell {
   static constexpr bool PERIODIC = false;
   static constexpr bool WALL = false;
   static constexpr bool PERT = false;
+  static constexpr bool WIN = false;
 };
 __device__ __forceinline__ int phi_in(const Geo &g, int k) { return g.periodic ? wrapk(g, k) : clampi(k, 0, g.np - 1); }
 __device__ __forceinline__ double gC(const Geo &g, const SrcShell &s, int fid, int i, int j, int k) {
@@ -1332,7 +1296,7 @@ __global__ void __launch_bounds__(256) DSW_OCC(2) k_adj_shell(AdjArgs) {
     else adj_rows<SrcShell, FS, false, true>(kp, w, w + dj * ACOL_W, w + 2 * dj * ACOL_W, i, j, k);
   }
   __syncthreads();
-  const Geo g = kgeo(kp);
+  const Geo g = kgeo(kp, offsetof(AdjArgs, g));
   const Fields A = kfields(kp, offsetof(AdjArgs, A));
   for (int e = tid; e < FS; e += 256) {
     const int r = e / ACOL_W, kk = e - r * ACOL_W;
@@ -1377,7 +1341,7 @@ constexpr int ADJ_SEG = 4, ADJ_SEG_SMALL = 2, ADJ_FULL_WGS = 3 * 256;
 template <int JT, bool P>
 __device__ __forceinline__ void acol_flush(KPtr kp, double *w, int p, int j0, int k0, int tid) {
   constexpr int PER = (JT + 2) * ACOL_W, NTH = ACOL_K * JT;
-  const Geo g = kgeo(kp);
+  const Geo g = kgeo(kp, offsetof(AdjArgs, g));
   const Fields A = kfields(kp, offsetof(AdjArgs, A));
   for (int e = tid; e < PER; e += NTH) {
     const int jj = e / ACOL_W, kk = e - jj * ACOL_W;

@@ -472,7 +472,7 @@ static void plan_step(const dsw_grid *G, const Work &W, const Fields &un, const 
     // midpoint state of this iteration: U^n itself at the first one, else the
     // one written by the previous iteration's phi sweep
     const Fields ubar = it == 0 ? un : ubuf[(it - 1) % 2];
-    Pass r{G->geo.periodic ? PK_RES_INP : PK_RES_IN, 0, base_args(G)};
+    Pass r{res_in_kind(G->geo), 0, base_args(G)};
     r.a.u = src1(ubar);
     r.a.d = diff(un, it == 0 ? un : uk);
     r.a.tau = tau;
@@ -497,6 +497,8 @@ static unsigned kind_threads(int kind, const Geo &g, const Cfg &c) {
   case PK_RES:
   case PK_RES_IN:
   case PK_RES_INP: return (unsigned)c.res_bs;
+  case PK_RES_MN:
+  case PK_RES_MP: return 256u;
   case PK_SW0:
   case PK_SW0T:
   case PK_SW0B:
@@ -522,6 +524,8 @@ static unsigned kind_blocks(int kind, const Geo &g, const Cfg &c, unsigned threa
   case PK_RES: return residual_general_blocks(g, (int)threads);
   case PK_RES_IN:
   case PK_RES_INP: return residual_interior_blocks(g, (int)threads);
+  case PK_RES_MN:
+  case PK_RES_MP: return residual_march_blocks(g);
   case PK_SW0: return cdiv(sweep_lines(g, 0), threads);
   case PK_SW1: return cdiv(sweep_lines(g, 1), threads);
   case PK_SW0T: return sweep2_blocks(g, 0, threads);
@@ -553,6 +557,8 @@ static void launch_kind(int kind, const Cfg &c, const PassArgs &a, const Batch &
   case PK_RES: launch_residual_pass(a, b, blocks, threads, st); break;
   case PK_RES_IN: launch_residual_in_pass(false, a, b, blocks, threads, st); break;
   case PK_RES_INP: launch_residual_in_pass(true, a, b, blocks, threads, st); break;
+  case PK_RES_MN: launch_residual_march(false, a, b, blocks, st); break;
+  case PK_RES_MP: launch_residual_march(true, a, b, blocks, st); break;
   case PK_SW0: launch_sweep_pass(0, a, b, blocks, threads, st); break;
   case PK_SW1: launch_sweep_pass(1, a, b, blocks, threads, st); break;
   case PK_SW0T:
@@ -638,8 +644,7 @@ extern "C" int dsw_split_step(dsw_grid *G, const dsw_fields *Un, dsw_fields *Unp
     }
     size_t e = q + 1;
     while (e < plan.size() && plan[e].tk == plan[q].tk && plan[e].kind != plan[q].kind &&
-           (plan[q].kind == PK_RES_IN || plan[q].kind == PK_RES_INP || plan[q].kind == PK_SW0B ||
-            plan[q].kind == PK_SW1B))
+           (is_res_in(plan[q].kind) || plan[q].kind == PK_SW0B || plan[q].kind == PK_SW1B))
       e++;
     timed(G, plan[q].tk, st, [&] {
       for (size_t r = q; r < e; r++) launch_single(G, plan[r], st);
@@ -682,7 +687,7 @@ extern "C" int dsw_split_step_pert(dsw_grid *G, const dsw_fields *Un, dsw_fields
                               "which has no perturbation form");
   hipStream_t st = (hipStream_t)stream;
   for (const Pass &p : plan) {
-    if (p.kind == PK_RES_IN || p.kind == PK_RES_INP) continue;  // inside the PK_RES launch below
+    if (is_res_in(p.kind)) continue;  // inside the PK_RES launch below
     if (p.kind == PK_SW0S || p.kind == PK_SW1S || p.kind == PK_NONE) continue;  // inside the two-ended launch below
     PassArgs a = p.a;
     a.pref = G->ref_mem;
@@ -1176,7 +1181,7 @@ static void adj_record_iter(const dsw_grid *G, const Fields &un, double tau, int
                             const Fields &U, const Scratch &scr, hipStream_t st, bool keep_last = true) {
   const Fields none{};
   const Fields ubk = t.ub[k];
-  Pass r{G->geo.periodic ? PK_RES_INP : PK_RES_IN, 0, base_args(G)};
+  Pass r{res_in_kind(G->geo), 0, base_args(G)};
   r.a.u = src1(ubk);
   r.a.d = diff(un, k == 0 ? un : U);
   r.a.tau = tau;

@@ -68,6 +68,7 @@ struct SrcOneT {
   static constexpr bool PERIODIC = P; // interior sources: phi periodic (known at compile time)
   static constexpr bool WALL = false;  // tangential wall velocities are zero
   static constexpr bool PERT = false;  // p holds the full pressure
+  static constexpr bool WIN = false;   // arrays, not a window of them in LDS
   using Row = int;
   __device__ __forceinline__ double ld(int f, long x) const { return a[f][x]; }
   __device__ __forceinline__ double ldk(int f, int row, int k) const { return a[f][row + k]; }
@@ -81,6 +82,7 @@ struct SrcMid {
   static constexpr bool PERIODIC = false;
   static constexpr bool WALL = false;
   static constexpr bool PERT = false;
+  static constexpr bool WIN = false;
   __device__ __forceinline__ double ld(int f, long x) const { return 0.5 * (k[f][x] + n[f][x]); }
 };
 
@@ -107,6 +109,7 @@ struct SrcW {
   static constexpr bool PERIODIC = false;
   static constexpr bool WALL = true;
   static constexpr bool PERT = false;
+  static constexpr bool WIN = false;
   __device__ __forceinline__ double ld(int fid, long x) const { return a[fid][x]; }
 };
 
@@ -121,6 +124,7 @@ struct SrcInW {
   static constexpr bool PERIODIC = P;
   static constexpr bool WALL = true;
   static constexpr bool PERT = false;
+  static constexpr bool WIN = false;
   using Row = int;
   __device__ __forceinline__ double ld(int fid, long x) const { return a[fid][x]; }
   __device__ __forceinline__ double ldk(int fid, int row, int k) const { return a[fid][row + k]; }
@@ -191,6 +195,7 @@ __device__ __forceinline__ double gF_wall(const Geo &g, const S &s, int i, int j
 // p or T at a (possibly ghost) centre
 template <class S>
 __device__ __forceinline__ double gC(const Geo &g, const S &s, int fid, int i, int j, int k) {
+  if constexpr (S::WIN) return s.at(fid, i, j, k);
   if constexpr (S::INTERIOR) {
     const int kk = S::PERIODIC ? wrapk(g, k) : clampi(k, 0, g.np - 1);
     return s.ldk(fid, ((typename S::Row)i * g.nt + j) * g.np, kk);
@@ -203,6 +208,7 @@ __device__ __forceinline__ double gC(const Geo &g, const S &s, int fid, int i, i
 // u_r at r-face f (0..nr), ghosts across theta and phi boundaries
 template <class S>
 __device__ __forceinline__ double gR(const Geo &g, const S &s, int f, int j, int k) {
+  if constexpr (S::WIN) return s.at(F_UR, f, j, k);
   if constexpr (S::INTERIOR) {
     if constexpr (S::PERIODIC) return s.ldk(F_UR, ((typename S::Row)f * g.nt + j) * g.np, wrapk(g, k));
     const int kk = clampi(k, 0, g.np - 1);
@@ -223,6 +229,7 @@ __device__ __forceinline__ double gR(const Geo &g, const S &s, int f, int j, int
 // u_theta at theta-face f (0..nt), ghosts across r and phi boundaries
 template <class S>
 __device__ __forceinline__ double gT(const Geo &g, const S &s, int i, int f, int k) {
+  if constexpr (S::WIN) return s.at(F_UT, i, f, k);
   if constexpr (S::INTERIOR) {
     if constexpr (S::PERIODIC) return s.ldk(F_UT, ((typename S::Row)i * (g.nt + 1) + f) * g.np, wrapk(g, k));
     const int kk = clampi(k, 0, g.np - 1);
@@ -243,6 +250,7 @@ __device__ __forceinline__ double gT(const Geo &g, const S &s, int i, int f, int
 // u_phi at phi-face f, ghosts across r and theta boundaries (poles included)
 template <class S>
 __device__ __forceinline__ double gF(const Geo &g, const S &s, int i, int j, int f) {
+  if constexpr (S::WIN) return s.at(F_UF, i, j, f);
   if constexpr (S::INTERIOR) return s.ldk(F_UF, ((typename S::Row)i * g.nt + j) * g.npf, S::PERIODIC ? wrapk(g, f) : f);
   if constexpr (S::WALL) return gF_wall(g, s, i, j, f);
   double sg = 1.0;

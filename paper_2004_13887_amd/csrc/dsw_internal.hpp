@@ -144,7 +144,9 @@ struct Cfg {
 enum PassKind { PK_BND = 0, PK_RES = 1, PK_SW0 = 2, PK_SW1 = 3, PK_SW2_LINE = 4, PK_SW2_PART = 5,
                 PK_RES_IN = 6, PK_SW0T = 7, PK_SW1T = 8, PK_RES_INP = 9, PK_SW0P = 10, PK_SW1P = 11,
                 PK_SW0B = 12, PK_SW1B = 13, PK_SW0S = 14, PK_SW1S = 15, PK_NONE = 16,
-                PK_SW2_CP = 17, PK_SW2_CN = 18 };
+                PK_SW2_CP = 17, PK_SW2_CN = 18, PK_RES_MN = 19, PK_RES_MP = 20 };
+// PK_RES_IN / PK_RES_INP: the interior of the residual (bounded / periodic
+// phi); PK_RES_MN / PK_RES_MP: the same by the kernel for large grids.
 // PK_SW2_CP / PK_SW2_CN: the partitioned phi pass with 32-bit byte offsets
 // (periodic / bounded phi); PK_SW2_PART: the same on grids beyond them.
 
@@ -191,6 +193,17 @@ void launch_residual_pass(const PassArgs &a, const Batch &b, unsigned blocks, un
 void launch_residual_in_pass(bool periodic, const PassArgs &a, const Batch &b, unsigned blocks,
                              unsigned threads, hipStream_t st);
 unsigned residual_interior_blocks(const Geo &g, int bs); // workgroups of the interior launch
+// the interior launch of a large grid
+bool residual_marches(const Geo &g);  // whether the grid takes it
+unsigned residual_march_blocks(const Geo &g);
+void launch_residual_march(bool periodic, const PassArgs &a, const Batch &b, unsigned blocks, hipStream_t st);
+inline int res_in_kind(const Geo &g) {
+  if (residual_marches(g)) return g.periodic ? PK_RES_MP : PK_RES_MN;
+  return g.periodic ? PK_RES_INP : PK_RES_IN;
+}
+inline bool is_res_in(int kind) {
+  return kind == PK_RES_IN || kind == PK_RES_INP || kind == PK_RES_MN || kind == PK_RES_MP;
+}
 // workgroups of the general residual launch (the shell when the interior
 // launch runs, else every point)
 unsigned residual_general_blocks(const Geo &g, int bs);

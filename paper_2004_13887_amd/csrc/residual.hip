@@ -33,6 +33,8 @@
 
 #include "dsw_common.hpp"
 #include "dsw_internal.hpp"
+#include "kargs.hpp"
+#include "rows_fast.hpp"
 
 namespace dsw {
 
@@ -99,8 +101,8 @@ __device__ __forceinline__ double F_ur(const Geo &g, const Mat &m, const S &s, i
     // with rho - rhobar = (p' Tbar - (pbar + pi_inf)(T - Tbar)) / (R T Tbar)
     const double Ta = gC(g, s, F_T, f - 1, j, k), Tb = gC(g, s, F_T, f, j, k);
     const double ta = s.tref[f - 1], tb = s.tref[f];
-    const double da = (gC(g, s, F_P, f - 1, j, k) * ta - (s.pref[f - 1] + m.pinf) * (Ta - ta)) / (m.Rg * Ta * ta);
-    const double db = (gC(g, s, F_P, f, j, k) * tb - (s.pref[f] + m.pinf) * (Tb - tb)) / (m.Rg * Tb * tb);
+    const double da = (gC(g, s, F_P, f - 1, j, k) * ta - (s.pref[f - 1] + m.pinf) * (Ta - ta)) * rcp_nr(m.Rg * Ta * ta);
+    const double db = (gC(g, s, F_P, f, j, k) * tb - (s.pref[f] + m.pinf) * (Tb - tb)) * rcp_nr(m.Rg * Tb * tb);
     return N - nu * vis - nu * (1.0 / 3.0) * gd + m.g_r * (0.5 * (da + db)) * irho;
   } else {
     return N - nu * vis - nu * (1.0 / 3.0) * gd + m.g_r;
@@ -145,7 +147,9 @@ __device__ __forceinline__ double F_ut(const Geo &g, const Mat &m, const S &s, i
 template <class S>
 __device__ __forceinline__ double F_uf(const Geo &g, const Mat &m, const S &s, int i, int j, int f) {
   const double ir = g.irc[i], is = g.isc[j], ct = g.ctc[j], ir2 = ir * ir;
-  const int k0 = g.periodic ? wrapk(g, f - 1) : f - 1, k1 = g.periodic ? wrapk(g, f) : f;
+  // (a window holds the ghost columns at their own places)
+  const bool wrap = !S::WIN && g.periodic;
+  const int k0 = wrap ? wrapk(g, f - 1) : f - 1, k1 = wrap ? wrapk(g, f) : f;
   const double irho = irho_mean(g, m, s, i, j, k0, i, j, k1);
   const double nu = m.mu * irho;
   const double un = gF(g, s, i, j, f);
@@ -436,9 +440,13 @@ __global__ void __launch_bounds__(256) k_residual_in_pert(PassArgs a) {
 }
 __global__ void __launch_bounds__(256) k_residual_pert(PassArgs a) { residual_body<false, true>(a, blockIdx.x); }
 
+static void march_one(bool periodic, bool pert, const PassArgs &a, hipStream_t st);
+
 void launch_residual_pert(const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st) {
   const unsigned nin = res_interior_blocks(a.g, (int)threads);
-  if (nin) {
+  if (residual_marches(a.g)) {
+    march_one(a.g.periodic != 0, true, a, st);
+  } else if (nin) {
     if (a.g.periodic) hipLaunchKernelGGL(k_residual_in_pert<true>, dim3(nin), dim3(threads), 0, st, a);
     else hipLaunchKernelGGL(k_residual_in_pert<false>, dim3(nin), dim3(threads), 0, st, a);
   }
@@ -459,6 +467,239 @@ __global__ void __launch_bounds__(256) k_residual_in(PassArgs a, Batch bt) {
     // of even uniform integers runs on the vector unit)
     residual_at_in<SI>(a, blockIdx.x, 1 + (int)blockIdx.y, 1 + (int)blockIdx.z);
   }
+}
+
+// The interior of a large grid: a workgroup owns 64 (phi) x 4 (theta) points
+// and walks a segment of r planes.  The window of the state that its stencils
+// read, three planes of 6 x 66 per field, stands in LDS, ghost columns
+// included; the plane after next is loaded to registers before a plane's rows
+// are evaluated and written to the fourth slot after them, so its latency
+// passes under the arithmetic.  Bound by HBM: 16 to 25 fields' worth of traffic
+// (the state, the two iterates of the difference, the result) at 5 TB/s.
+constexpr int RM_J = 4, RM_W = 66, RM_FS = (RM_J + 2) * RM_W, RM_PL = 5 * RM_FS;
+
+// the window around (i, j, k): w0, w1, w2 the entries (j - 1, k - 1) of field
+// 0 in planes i - 1, i, i + 1
+template <bool P>
+struct SrcWin {
+  const double *w0, *w1, *w2;
+  int i, j, k;
+  static constexpr bool INTERIOR = true;
+  static constexpr bool PERIODIC = P;
+  static constexpr bool WALL = false;
+  static constexpr bool PERT = false;
+  static constexpr bool WIN = true;
+  using Row = int;
+  __device__ __forceinline__ double at(int f, int i_, int j_, int k_) const {
+    const double *w = i_ - i < 0 ? w0 : (i_ - i == 0 ? w1 : w2);
+    return w[f * RM_FS + (j_ - j + 1) * RM_W + (k_ - k + 1)];
+  }
+  __device__ __forceinline__ double ld(int, long) const { return 0.0; }      // never called
+  __device__ __forceinline__ double ldk(int, int, int) const { return 0.0; } // never called
+};
+
+// kp: the PassArgs of the grid; (bx, by, bz): phi block, theta tile, r segment
+template <bool P, bool PT>
+__device__ __forceinline__ void residual_march(KPtr kp, double *lds, int bx, int by, int bz, int seg) {
+  using SI = std::conditional_t<PT, SrcPert<SrcWin<P>>, SrcWin<P>>;
+  constexpr unsigned GEO = offsetof(PassArgs, g);
+  const int tid = threadIdx.y * 64 + threadIdx.x;
+  const int k0 = bx * 64, j0 = 1 + by * RM_J;
+  const int k = k0 + threadIdx.x, j = __builtin_amdgcn_readfirstlane(j0 + (int)threadIdx.y);
+  const int ib = 1 + bz * seg, ie = min(karg<int>(kp, GEO + offsetof(Geo, nr)) - 1, ib + seg);
+  // the two window entries this thread stages: byte offsets within a plane of
+  // the centres (and r faces), theta faces, phi faces
+  unsigned oc[2], ot[2], of[2];
+  bool flip[2], on;
+  {
+    const Geo g = kgeo(kp, GEO);
+    on = j < g.nt - 1 && k < g.np;
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+      const int e = min(tid + 256 * q, RM_FS - 1), jj = e / RM_W, kr = k0 - 1 + e - jj * RM_W;
+      const int jc = min(j0 - 1 + jj, g.nt - 1), jt = min(j0 - 1 + jj, g.nt);
+      const int kc = P ? min(wrapk(g, kr), g.np - 1) : clampi(kr, 0, g.np - 1);
+      const int kf = P ? kc : clampi(kr, 0, g.np);
+      oc[q] = (unsigned)(jc * g.np + kc) * 8u;
+      ot[q] = (unsigned)(jt * g.np + kc) * 8u;
+      of[q] = (unsigned)(jc * g.npf + kf) * 8u;
+      flip[q] = !P && kc != kr; // no slip at a phi wall
+    }
+  }
+  const bool two = tid + 256 < RM_FS;
+  double st[2][5];
+  const auto stage = [&](int p) {
+    KPtr q = kp;
+    asm volatile("" : "+s"(q), "+s"(p));
+    const int nt = karg<int>(q, GEO + offsetof(Geo, nt)), np = karg<int>(q, GEO + offsetof(Geo, np));
+    const int npf = karg<int>(q, GEO + offsetof(Geo, npf));
+    const long pc = (long)p * nt * np;
+    const unsigned u = offsetof(PassArgs, u);
+    const double *bp = karr(q, u + 8 * F_P) + pc, *br = karr(q, u + 8 * F_UR) + pc, *bT = karr(q, u + 8 * F_T) + pc;
+    const double *bt = karr(q, u + 8 * F_UT) + (long)p * (nt + 1) * np, *bf = karr(q, u + 8 * F_UF) + (long)p * nt * npf;
+#pragma unroll
+    for (int e = 0; e < 2; e++) {
+      st[e][F_P] = ldo(bp, oc[e]);
+      st[e][F_UR] = ldo(br, oc[e]);
+      st[e][F_UT] = ldo(bt, ot[e]);
+      st[e][F_UF] = ldo(bf, of[e]);
+      st[e][F_T] = ldo(bT, oc[e]);
+    }
+  };
+  const auto commit = [&](int slot) {
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+      if (q == 1 && !two) continue;
+      double *w = lds + slot + tid + 256 * q;
+#pragma unroll
+      for (int f = 0; f < 5; f++) w[f * RM_FS] = (f == F_UR || f == F_UT) && flip[q] ? -st[q][f] : st[q][f];
+    }
+  };
+#pragma nounroll
+  for (int q = 0; q < 3; q++) {
+    stage(ib - 1 + q);
+    commit(q * RM_PL);
+  }
+  __syncthreads();
+  int s0 = 0, s1 = RM_PL, s2 = 2 * RM_PL, s3 = 3 * RM_PL;
+  const int lane = threadIdx.y * RM_W + threadIdx.x;
+  // a lane or wave beyond the grid repeats the last point and stores nothing
+  const int jw = min(j, karg<int>(kp, GEO + offsetof(Geo, nt)) - 2);
+  const unsigned o = (unsigned)min(k, karg<int>(kp, GEO + offsetof(Geo, np)) - 1) * 8u;
+#pragma nounroll
+  for (int ii = ib; ii < ie; ii++) {
+    KPtr p = kp;
+    int i = ii;
+    asm volatile("" : "+s"(p), "+s"(i));
+    const Geo g = kgeo(p, GEO);
+    const long rc = ((long)i * g.nt + jw) * g.np, rt_ = ((long)i * (g.nt + 1) + jw) * g.np;
+    const long rf_ = ((long)i * g.nt + jw) * g.npf;
+    // loads in the order in which they are waited for: the rows' own
+    // differences, then the plane after next
+    double dk[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, dn[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    if (!karg<int>(p, offsetof(PassArgs, d) + offsetof(Diff, same))) {
+#pragma unroll
+      for (int f = 0; f < 5; f++) {
+        const long row = f == F_UT ? rt_ : (f == F_UF ? rf_ : rc);
+        dk[f] = ldo(karr(p, offsetof(PassArgs, d) + offsetof(Diff, k) + 8 * f) + row, o);
+        dn[f] = ldo(karr(p, offsetof(PassArgs, d) + offsetof(Diff, n) + 8 * f) + row, o);
+      }
+    }
+    stage(min(ii + 2, ie));
+    asm volatile("" ::: "memory"); // the loads stay ahead of the arithmetic
+    const Mat m = kmat(p, offsetof(PassArgs, m));
+    const double tau = karg<double>(p, offsetof(PassArgs, tau));
+    SI s;
+    s.w0 = lds + s0 + lane;
+    s.w1 = lds + s1 + lane;
+    s.w2 = lds + s2 + lane;
+    s.i = i; s.j = jw; s.k = k;
+    if constexpr (PT) {
+      s.pref = ktab(p, offsetof(PassArgs, pref));
+      s.tref = ktab(p, offsetof(PassArgs, tref));
+    }
+    double pfull = s.at(F_P, i, jw, k);
+    if constexpr (PT) pfull += s.pref[i];
+    const bool nonphys = s.at(F_T, i, jw, k) <= 0.0 || pfull + m.pinf <= 0.0;
+    double FT;
+    const double Fp = F_p_T(g, m, s, i, jw, k, &FT);
+    const double Fr = F_ur(g, m, s, i, jw, k);
+    const double Ft = F_ut(g, m, s, i, jw, k);
+    const double Ff = F_uf(g, m, s, i, jw, k);
+    double rp = -(dk[F_P] - dn[F_P]) - tau * Fp;
+    double rT = -(dk[F_T] - dn[F_T]) - tau * FT;
+    double rr = -(dk[F_UR] - dn[F_UR]) - tau * Fr;
+    double rt = -(dk[F_UT] - dn[F_UT]) - tau * Ft;
+    double rf = -(dk[F_UF] - dn[F_UF]) - tau * Ff;
+    if (!P && k == 0) rf = 0.0;
+    // and the window is written after it, ahead of the stores (whose end the
+    // next wait for a load would else wait for)
+    asm volatile("" : "+v"(rp), "+v"(rT), "+v"(rr), "+v"(rt), "+v"(rf) : : "memory");
+    commit(s3);
+    asm volatile("" ::: "memory");
+    if (on) {
+      const Fields R = kfields(p, offsetof(PassArgs, R));
+      sto(R.p + rc, o, rp);
+      sto(R.T + rc, o, rT);
+      sto(R.ur + rc, o, rr);
+      sto(R.ut + rt_, o, rt);
+      sto(R.uf + rf_, o, rf);
+      if (!P && k == g.np - 1) sto(R.uf + rf_, o + 8u, 0.0);
+      int *status = (int *)karg<DSW_AS1 int *>(p, offsetof(PassArgs, status));
+      if (nonphys) status[ST_NONPHYS] = 1;  // plain vector stores
+      // the sum of this point's residuals: non-finite iff one of them is
+      if (!isfinite(rf + (rp + rT + rr + rt))) status[ST_DIVERGED] = 1;
+    }
+    __syncthreads();
+    const int t = s0;
+    s0 = s1; s1 = s2; s2 = s3; s3 = t;
+  }
+}
+
+// r planes per segment: a segment loads two planes more than it evaluates, but
+// too few leave CUs idle.  Measured with 8, 16, 32 planes: 512 x 256 x 128
+// sphere 527, 506, 500 us per residual, 200 x 200 x 100 sector 171, 161, 162;
+// with 8, 16 planes 360 x 180 x 40 102, 107; with 2, 4 planes 128 x 64 x 32
+// 14.5, 17.5, 150 x 101 x 37 35, 34, 180 x 90 x 24 37, 35.
+__host__ __device__ inline unsigned march_tiles(const Geo &g) {
+  return (unsigned)((g.np + 63) / 64) * (unsigned)((g.nt - 2 + RM_J - 1) / RM_J);
+}
+__host__ __device__ inline unsigned march_wgs(const Geo &g, int seg) {
+  return march_tiles(g) * (unsigned)((g.nr - 2 + seg - 1) / seg);
+}
+__host__ __device__ inline int march_seg(const Geo &g) {
+  int seg = 16;
+  while (seg > 4 && march_wgs(g, seg) < 1024u) seg /= 2;
+  return march_wgs(g, seg) < 384u ? 2 : seg;
+}
+
+template <bool P, bool PT>
+__global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_march(PassArgs, int seg) {
+  __shared__ double lds[4 * RM_PL];
+  residual_march<P, PT>((KPtr)__builtin_amdgcn_kernarg_segment_ptr(), lds, blockIdx.x, blockIdx.y, blockIdx.z, seg);
+}
+// a batch of grids: workgroups in one dimension, phi block fastest, then theta
+template <bool P>
+__global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_marchB(Batch bt) {
+  __shared__ double lds[4 * RM_PL];
+  const int mb = batch_member(bt, blockIdx.x);
+  KPtr kp = (KPtr)(bt.tab + mb);
+  const Geo g = kgeo(kp, offsetof(PassArgs, g));
+  const int w = (int)(blockIdx.x - bt.woff[mb]), nk = (g.np + 63) / 64, nj = (g.nt - 2 + RM_J - 1) / RM_J;
+  const int r = w / nk;
+  residual_march<P, false>(kp, lds, w - r * nk, r % nj, r / nj, march_seg(g));
+}
+
+// Where it is taken: from 450 workgroups of two planes.  Below that the window
+// is a latency more than it saves: one launch with every load up front against
+// the window 6.3 against 10.1 us on 32 x 32 x 16 cells (112 workgroups), but
+// 17.4 against 14.5 on 128 x 64 x 32 (480), 40 against 34 on 150 x 101 x 37,
+// 162 against 102 on 360 x 180 x 40, 262 against 161 on 200 x 200 x 100, 900
+// against 506 on 512 x 256 x 128 (the perturbation form of 100 m columns on
+// 200 x 200 x 200: 620 against 329).
+bool residual_marches(const Geo &g) {
+  return off32_ok(g) && g.nr >= 3 && g.nt >= 3 && march_wgs(g, 2) >= 450u;
+}
+unsigned residual_march_blocks(const Geo &g) { return march_wgs(g, march_seg(g)); }
+
+static void march_one(bool periodic, bool pert, const PassArgs &a, hipStream_t st) {
+  const Geo &g = a.g;
+  const int seg = march_seg(g);
+  const dim3 gr((unsigned)((g.np + 63) / 64), (unsigned)((g.nt - 2 + RM_J - 1) / RM_J),
+                (unsigned)((g.nr - 2 + seg - 1) / seg)), bl(64, RM_J);
+  if (periodic) {
+    if (pert) hipLaunchKernelGGL((k_residual_march<true, true>), gr, bl, 0, st, a, seg);
+    else hipLaunchKernelGGL((k_residual_march<true, false>), gr, bl, 0, st, a, seg);
+  } else {
+    if (pert) hipLaunchKernelGGL((k_residual_march<false, true>), gr, bl, 0, st, a, seg);
+    else hipLaunchKernelGGL((k_residual_march<false, false>), gr, bl, 0, st, a, seg);
+  }
+}
+
+void launch_residual_march(bool periodic, const PassArgs &a, const Batch &b, unsigned blocks, hipStream_t st) {
+  if (!b.tab) march_one(periodic, false, a, st);
+  else if (periodic) hipLaunchKernelGGL(k_residual_marchB<true>, dim3(blocks), dim3(64, RM_J), 0, st, b);
+  else hipLaunchKernelGGL(k_residual_marchB<false>, dim3(blocks), dim3(64, RM_J), 0, st, b);
 }
 
 // public form on a small grid: the midpoint formed on the fly from Un and Uk
@@ -550,7 +791,8 @@ void launch_residual(const Geo &g, const Mat &m, const Fields &Un, const Fields 
   a.R = R;
   a.status = status;
   const Batch none{nullptr, nullptr, 0};
-  launch_residual_in_pass(g.periodic != 0, a, none, residual_interior_blocks(g, (int)th), th, st);
+  if (residual_marches(g)) march_one(g.periodic != 0, false, a, st);
+  else launch_residual_in_pass(g.periodic != 0, a, none, residual_interior_blocks(g, (int)th), th, st);
   launch_residual_pass(a, none, residual_general_blocks(g, (int)th), th, st);
 }
 
