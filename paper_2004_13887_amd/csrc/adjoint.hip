@@ -1034,40 +1034,6 @@ __device__ __forceinline__ AdjCtx<S> kctx(KPtr p) {
   return c;
 }
 
-// The state with the ghost rules of dsw_common.hpp for the shell, by selects
-// on clamped indices: no load under a condition that differs between lanes.
-// (With early returns in divergent branches the compiler, clang 22 of ROCm 7.2,
-// left a uniform row index undefined in waves where no lane took the branch.)
-struct SrcShell {
-  const double *a[5];
-  static constexpr bool INTERIOR = false;
-  static constexpr bool PERIODIC = false;
-  static constexpr bool WALL = false;
-  static constexpr bool PERT = false;
-  static constexpr bool WIN = false;
-};
-__device__ __forceinline__ int phi_in(const Geo &g, int k) { return g.periodic ? wrapk(g, k) : clampi(k, 0, g.np - 1); }
-__device__ __forceinline__ double gC(const Geo &g, const SrcShell &s, int fid, int i, int j, int k) {
-  const long row = ((long)clampi(i, 0, g.nr - 1) * g.nt + clampi(j, 0, g.nt - 1)) * g.np;
-  return ldo(s.a[fid] + row, (unsigned)phi_in(g, k) * 8u);
-}
-__device__ __forceinline__ double gR(const Geo &g, const SrcShell &s, int f, int j, int k) {
-  const int kk = phi_in(g, k);
-  const bool flip = (j < 0 && !g.pole_lo) || (j >= g.nt && !g.pole_hi);
-  const double v = ldo(s.a[F_UR] + ((long)f * g.nt + clampi(j, 0, g.nt - 1)) * g.np, (unsigned)kk * 8u);
-  return flip != (!g.periodic && kk != k) ? -v : v;
-}
-__device__ __forceinline__ double gT(const Geo &g, const SrcShell &s, int i, int f, int k) {
-  const int kk = phi_in(g, k), ii = clampi(i, 0, g.nr - 1);
-  const double v = ldo(s.a[F_UT] + ((long)ii * (g.nt + 1) + f) * g.np, (unsigned)kk * 8u);
-  return (ii != i) != (!g.periodic && kk != k) ? -v : v;
-}
-__device__ __forceinline__ double gF(const Geo &g, const SrcShell &s, int i, int j, int f) {
-  const int ff = g.periodic ? wrapk(g, f) : f, ii = clampi(i, 0, g.nr - 1), jj = clampi(j, 0, g.nt - 1);
-  const double v = ldo(s.a[F_UF] + ((long)ii * g.nt + jj) * g.npf, (unsigned)ff * 8u);
-  return (ii != i) != (jj != j) ? -v : v;
-}
-
 // load3 and load1 in the same form: the rows beside (i, j, k), zero outside a
 // line that ends; IN: i and j lie inside the arrays
 template <int D, class S>

@@ -580,6 +580,7 @@ static void launch_kind(int kind, const Cfg &c, const PassArgs &a, const Batch &
 static void launch_single(const dsw_grid *G, const Pass &p, hipStream_t st) {
   if (p.kind == PK_NONE) return;
   const unsigned th = kind_threads(p.kind, G->geo, G->cfg);
+  if (p.kind == PK_RES && residual_interior_blocks(G->geo, (int)th)) return;  // with the interior
   const unsigned nb = kind_blocks(p.kind, G->geo, G->cfg, th);
   if (nb == 0) return;  // e.g. no interior workgroups on a tiny grid
   const Batch none{nullptr, nullptr, 0};
@@ -696,7 +697,7 @@ extern "C" int dsw_split_step_pert(dsw_grid *G, const dsw_fields *Un, dsw_fields
       const unsigned th = kind_threads(p.kind, g, G->cfg);
       switch (p.kind) {
       case PK_BND: launch_single(G, p, st); break;
-      case PK_RES: launch_residual_pert(a, kind_blocks(PK_RES, g, G->cfg, th), th, st); break;
+      case PK_RES: launch_residual_pert(a, th, st); break;
       case PK_SW0P: launch_rt_pert(0, a, th, st); break;
       case PK_SW1P: launch_rt_pert(1, a, th, st); break;
       case PK_SW0T:
@@ -857,7 +858,7 @@ extern "C" int dsw_split_step_forced(dsw_grid *G, const dsw_fields *Un, dsw_fiel
     r.R = G->r;
     r.wall = w;
     if (src) r.fsrc = F(src);
-    launch_residual_forced(r, residual_general_blocks(g, (int)rbs), rbs, st);
+    launch_residual_forced(r, rbs, st);
     Out o1{}, o2{}, o3{};
     o1.x = G->x1; o1.mode = 0;
     o2.x = G->x2; o2.mode = 0;

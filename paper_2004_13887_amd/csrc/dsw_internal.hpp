@@ -154,7 +154,7 @@ enum PassKind { PK_BND = 0, PK_RES = 1, PK_SW0 = 2, PK_SW1 = 3, PK_SW2_LINE = 4,
 // time level): one grid, the general residual over every point, the
 // two-ended r and theta sweeps and the partitioned phi solver
 void launch_bnd_forced(const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st);
-void launch_residual_forced(const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st);
+void launch_residual_forced(const PassArgs &a, unsigned threads, hipStream_t st);
 void launch_sweep2_forced(int d, const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st);
 // first iteration of a forced step: rhs -= tau/2 D_d(Ubar) X_b for the change
 // X_b of the boundary data (a.d0 - a.src on the boundary-normal faces, dw on
@@ -257,7 +257,7 @@ void launch_adj_mix(const Geo &g, const long *cnt, const Fields &L, const Fields
 // general launches), the partitioned r / theta solver, the two-ended
 // r / theta solver and the partitioned phi solver with the reference column
 // (a.pref, a.tref) of the state's pressure
-void launch_residual_pert(const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st);
+void launch_residual_pert(const PassArgs &a, unsigned threads, hipStream_t st);
 void launch_rt_pert(int d, const PassArgs &a, unsigned threads, hipStream_t st);
 void launch_sweep2_pert(int d, const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st);
 void launch_phi_pert(int pm, const PassArgs &a, unsigned blocks, unsigned threads, size_t lds, hipStream_t st);

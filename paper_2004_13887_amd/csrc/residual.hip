@@ -251,15 +251,11 @@ __device__ __forceinline__ void residual_point(const Geo &g, const Mat &m, const
   if (!isfinite(chk)) status[ST_DIVERGED] = 1; // plain vector store
 }
 
-// split-step form: the midpoint is resident; flat grid of workgroups over
-// (phi block, theta index, r index).  B: a batch of grids, each workgroup
-// reads its grid's arguments from the batch table; else one grid by value.
-// The split-step residual runs as two launches.  The interior launch covers
-// the workgroups whose points and all their stencil neighbours lie inside the
-// arrays in r and theta (1 <= i <= nr-2, 1 <= j <= nt-2), every phi block;
-// its accessors apply the phi ghost rules without branches and use 32-bit
-// indices, which roughly halves its registers.  The general launch covers
-// the whole index space and leaves those workgroups at once.
+// The interior (1 <= i <= nr-2, 1 <= j <= nt-2, every phi index) is the points
+// whose stencils lie inside the arrays in r and theta: its sources apply the
+// phi ghost rules without branches, with 32-bit indices.  The shell around it
+// takes the ghost rules at every load.  One grid runs both in one launch, a
+// batch in two; grids beyond 32-bit indices take the general rules everywhere.
 __host__ __device__ inline bool res_interior_ok(const Geo &g) {
   return (long)(g.nr + 1) * (g.nt + 1) * g.npf < 0x7fffffffL;
 }
@@ -269,15 +265,14 @@ __host__ __device__ inline unsigned res_interior_blocks(const Geo &g, int bs) {
   return (unsigned)res_nk(g, bs) * (unsigned)(g.nt - 2) * (unsigned)(g.nr - 2);
 }
 
-// The (i, j) pairs the general launch takes when the interior launch runs:
-// the shell around the interior, i in {0, nr-1, nr} for every j, then j in
+// The (i, j) pairs of the shell, or of every point: the shell around the interior, i in {0, nr-1, nr} for every j, then j in
 // {0, nt-1, nt} for 1 <= i <= nr-2; else every pair.  Workgroups per pair:
 // the phi blocks, res_parts for each.
 __host__ __device__ inline unsigned res_shell_pairs(const Geo &g) {
   return 3u * (unsigned)(g.nt + 1) + 3u * (unsigned)(g.nr - 2);
 }
-__host__ __device__ inline unsigned res_pairs(const Geo &g, int bs) {
-  return res_interior_blocks(g, bs) ? res_shell_pairs(g) : (unsigned)(g.nt + 1) * (unsigned)(g.nr + 1);
+__host__ __device__ inline unsigned res_pairs(const Geo &g, bool shell) {
+  return shell ? res_shell_pairs(g) : (unsigned)(g.nt + 1) * (unsigned)(g.nr + 1);
 }
 // Workgroups that share a point of the general launch: one per kind of row
 // where that still leaves wave slots free, else one.  The four rows of a point
@@ -285,11 +280,11 @@ __host__ __device__ inline unsigned res_pairs(const Geo &g, int bs) {
 // 32 x 32 x 16 cells against 6.5 split, 135 x 45 x 15 forced 26 against 13,
 // 128 x 64 x 32 12.9 against 8.5; but on the 360 x 180 x 40 and 512 x 256 x 128
 // spheres (3942 and 9192 workgroups) 25 and 46 us against 31 and 61 split.
-__host__ __device__ inline unsigned res_parts(const Geo &g, int bs) {
-  return (unsigned)res_nk(g, bs) * res_pairs(g, bs) * (unsigned)(bs / 64) <= 2048u ? 4u : 1u;
+__host__ __device__ inline unsigned res_parts(const Geo &g, int bs, bool shell) {
+  return (unsigned)res_nk(g, bs) * res_pairs(g, shell) * (unsigned)(bs / 64) <= 2048u ? 4u : 1u;
 }
-__host__ __device__ inline unsigned res_general_blocks(const Geo &g, int bs) {
-  return res_parts(g, bs) * (unsigned)res_nk(g, bs) * res_pairs(g, bs);
+__host__ __device__ inline unsigned res_general_blocks(const Geo &g, int bs, bool shell) {
+  return res_parts(g, bs, shell) * (unsigned)res_nk(g, bs) * res_pairs(g, shell);
 }
 
 // the pair of workgroup pair number rest of the general launch
@@ -312,14 +307,14 @@ __device__ __forceinline__ void res_pair(const Geo &g, unsigned rest, bool shell
 // W: a forced pass (wall velocities and source term); PT: the
 // perturbation-pressure form
 template <bool W = false, bool PT = false>
-__device__ __forceinline__ void residual_body(const PassArgs &a, unsigned w4) {
+__device__ __forceinline__ void residual_body(const PassArgs &a, unsigned w4, bool shell) {
   const Geo &g = a.g;
   const int bs = (int)blockDim.x;
-  const unsigned nkb = (unsigned)res_nk(g, bs), parts = res_parts(g, bs);
+  const unsigned nkb = (unsigned)res_nk(g, bs), parts = res_parts(g, bs, shell);
   const unsigned w = parts == 4 ? w4 >> 2 : w4, part = parts == 4 ? w4 & 3u : 4u;
   const unsigned kb = w % nkb, rest = w / nkb;
   int i, j;
-  res_pair(g, rest, res_interior_blocks(g, bs) > 0, i, j);  // the shell where the interior launch does the rest
+  res_pair(g, rest, shell, i, j);
   decltype(auto) s = SrcSel<W, PT>::get(a);
   using S = std::decay_t<decltype(s)>;
   const int k = (int)(kb * blockDim.x + threadIdx.x);
@@ -406,67 +401,132 @@ __device__ __forceinline__ void residual_body_in(const PassArgs &a, unsigned w) 
 }
 
 template <bool B>
-__global__ void __launch_bounds__(256) DSW_OCC(DSW_WAVES_RES) k_residual(PassArgs a, Batch bt) {
+__global__ void __launch_bounds__(256) DSW_OCC(DSW_WAVES_RES) k_residual(PassArgs a, Batch bt, bool shell) {
   if constexpr (B) {
     const int mb = batch_member(bt, blockIdx.x);
-    residual_body(batch_args(bt, mb), blockIdx.x - bt.woff[mb]);
+    const PassArgs &am = batch_args(bt, mb);
+    residual_body(am, blockIdx.x - bt.woff[mb], res_interior_blocks(am.g, (int)blockDim.x) > 0);
   } else {
-    residual_body(a, blockIdx.x);
+    residual_body(a, blockIdx.x, shell);
   }
 }
 
-// forced split step, one grid: the interior workgroups (P: periodic), then
-// the rest
-template <bool P>
-__global__ void __launch_bounds__(256) k_residual_in_forced(PassArgs a) {
-  residual_body_in<SrcInW<P>>(a, blockIdx.x);
-}
-__global__ void __launch_bounds__(256) k_residual_forced(PassArgs a) { residual_body<true>(a, blockIdx.x); }
-
-void launch_residual_forced(const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st) {
-  const unsigned nin = res_interior_blocks(a.g, (int)threads);
-  if (nin) {
-    if (a.g.periodic) hipLaunchKernelGGL(k_residual_in_forced<true>, dim3(nin), dim3(threads), 0, st, a);
-    else hipLaunchKernelGGL(k_residual_in_forced<false>, dim3(nin), dim3(threads), 0, st, a);
+// One row (PART 0 .. 3: the centre, the r, theta, phi face) of the shell's
+// points k of pair number q: plain and perturbation form by selects, from the
+// argument block; forced by the general rules.
+template <bool W, bool PT>
+__device__ __forceinline__ void residual_shell(KPtr kp, const PassArgs &a, unsigned q, int part, int k) {
+  if constexpr (W) {
+    const Geo &g = a.g;
+    int i, j;
+    res_pair(g, q, true, i, j);
+    const SrcW s = SrcSel<true, false>::get(a);
+    if (part == 0) residual_point<SrcW, false, 0>(g, a.m, s, a.d, a.tau, a.R, Fields{}, a.status, i, j, k);
+    else if (part == 1) residual_point<SrcW, false, 1>(g, a.m, s, a.d, a.tau, a.R, Fields{}, a.status, i, j, k);
+    else if (part == 2) residual_point<SrcW, false, 2>(g, a.m, s, a.d, a.tau, a.R, Fields{}, a.status, i, j, k);
+    else residual_point<SrcW, false, 3>(g, a.m, s, a.d, a.tau, a.R, Fields{}, a.status, i, j, k);
+  } else {
+    using S = std::conditional_t<PT, SrcPert<SrcShell>, SrcShell>;
+    const Geo g = kgeo(kp, offsetof(PassArgs, g));
+    const Mat m = kmat(kp, offsetof(PassArgs, m));
+    S s;
+    s.g = g;
+    Diff d;
+#pragma unroll
+    for (int f = 0; f < 5; f++) {
+      s.a[f] = karr(kp, offsetof(PassArgs, u) + 8 * f);
+      d.k[f] = karr(kp, offsetof(PassArgs, d) + offsetof(Diff, k) + 8 * f);
+      d.n[f] = karr(kp, offsetof(PassArgs, d) + offsetof(Diff, n) + 8 * f);
+    }
+    d.same = karg<int>(kp, offsetof(PassArgs, d) + offsetof(Diff, same));
+    if constexpr (PT) {
+      s.pref = ktab(kp, offsetof(PassArgs, pref));
+      s.tref = ktab(kp, offsetof(PassArgs, tref));
+    }
+    const double tau = karg<double>(kp, offsetof(PassArgs, tau));
+    const Fields R = kfields(kp, offsetof(PassArgs, R));
+    int *status = (int *)karg<DSW_AS1 int *>(kp, offsetof(PassArgs, status));
+    int i, j;
+    res_pair(g, q, true, i, j);
+    if (part == 0) residual_point<S, false, 0>(g, m, s, d, tau, R, Fields{}, status, i, j, k);
+    else if (part == 1) residual_point<S, false, 1>(g, m, s, d, tau, R, Fields{}, status, i, j, k);
+    else if (part == 2) residual_point<S, false, 2>(g, m, s, d, tau, R, Fields{}, status, i, j, k);
+    else residual_point<S, false, 3>(g, m, s, d, tau, R, Fields{}, status, i, j, k);
   }
-  hipLaunchKernelGGL(k_residual_forced, dim3(blocks), dim3(threads), 0, st, a);
 }
 
-// perturbation-pressure form, one grid: the interior workgroups (P:
-// periodic), then the rest
-template <bool P>
-__global__ void __launch_bounds__(256) k_residual_in_pert(PassArgs a) {
-  residual_body_in<SrcPert<SrcOneT<true, P>>>(a, blockIdx.x);
+// One grid in one launch (P: periodic): a three-dimensional grid of workgroups
+// (phi block, j - 1, i - 1) for the interior, so that their indices need no
+// integer division (on this GPU a division of even uniform integers runs on
+// the vector unit), and behind its last plane the shell's, one per phi block,
+// pair and kind of row.  The two are independent, and on a small grid either
+// alone is a chain of latencies in a nearly empty chip: 32 x 32 x 16 cells
+// 6.4 and 6.3 us in two launches, 10.1 in one.
+template <class SI, bool W, bool PT>
+__device__ __forceinline__ void residual_both(const PassArgs &a) {
+  const Geo &g = a.g;
+  if ((int)blockIdx.z < g.nr - 2) {
+    residual_at_in<SI>(a, blockIdx.x, 1 + (int)blockIdx.y, 1 + (int)blockIdx.z);
+  } else {
+    const unsigned w = ((blockIdx.z - (unsigned)(g.nr - 2)) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    const unsigned nkb = gridDim.x, q = w / (4u * nkb), r = w - q * (4u * nkb);
+    if (q < res_shell_pairs(g))
+      residual_shell<W, PT>((KPtr)__builtin_amdgcn_kernarg_segment_ptr(), a, q, (int)(r & 3u),
+                            (int)((r >> 2) * blockDim.x + threadIdx.x));
+  }
 }
-__global__ void __launch_bounds__(256) k_residual_pert(PassArgs a) { residual_body<false, true>(a, blockIdx.x); }
+template <bool P>
+__global__ void __launch_bounds__(256) k_residual_one(PassArgs a) { residual_both<SrcOneT<true, P>, false, false>(a); }
+template <bool P>
+__global__ void __launch_bounds__(256) k_residual_one_forced(PassArgs a) { residual_both<SrcInW<P>, true, false>(a); }
+template <bool P>
+__global__ void __launch_bounds__(256) k_residual_one_pert(PassArgs a) {
+  residual_both<SrcPert<SrcOneT<true, P>>, false, true>(a);
+}
+// grids beyond the interior launch's 32-bit indices: every point by the general rules
+__global__ void __launch_bounds__(256) k_residual_forced(PassArgs a) { residual_body<true>(a, blockIdx.x, false); }
+__global__ void __launch_bounds__(256) k_residual_pert(PassArgs a, bool shell) {
+  residual_body<false, true>(a, blockIdx.x, shell);
+}
+
+static dim3 one_grid(const Geo &g, unsigned threads) {
+  const unsigned nk = (unsigned)res_nk(g, (int)threads), gy = (unsigned)(g.nt - 2);
+  const unsigned nsh = 4u * nk * res_shell_pairs(g);
+  return dim3(nk, gy, (unsigned)(g.nr - 2) + (nsh + nk * gy - 1) / (nk * gy));
+}
+// what a launch's y and z dimensions hold; else every point goes by the
+// general rules (as on grids beyond the interior's 32-bit indices)
+static bool one_fits(const Geo &g, unsigned threads) {
+  if (!res_interior_blocks(g, (int)threads)) return false;
+  const dim3 d = one_grid(g, threads);
+  return d.y <= 65535u && d.z <= 65535u;
+}
+
+void launch_residual_forced(const PassArgs &a, unsigned threads, hipStream_t st) {
+  const dim3 bl(threads);
+  if (!one_fits(a.g, threads))
+    hipLaunchKernelGGL(k_residual_forced, dim3(res_general_blocks(a.g, (int)threads, false)), bl, 0, st, a);
+  else if (a.g.periodic) hipLaunchKernelGGL(k_residual_one_forced<true>, one_grid(a.g, threads), bl, 0, st, a);
+  else hipLaunchKernelGGL(k_residual_one_forced<false>, one_grid(a.g, threads), bl, 0, st, a);
+}
 
 static void march_one(bool periodic, bool pert, const PassArgs &a, hipStream_t st);
 
-void launch_residual_pert(const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st) {
-  const unsigned nin = res_interior_blocks(a.g, (int)threads);
-  if (residual_marches(a.g)) {
-    march_one(a.g.periodic != 0, true, a, st);
-  } else if (nin) {
-    if (a.g.periodic) hipLaunchKernelGGL(k_residual_in_pert<true>, dim3(nin), dim3(threads), 0, st, a);
-    else hipLaunchKernelGGL(k_residual_in_pert<false>, dim3(nin), dim3(threads), 0, st, a);
-  }
-  hipLaunchKernelGGL(k_residual_pert, dim3(blocks), dim3(threads), 0, st, a);
+void launch_residual_pert(const PassArgs &a, unsigned threads, hipStream_t st) {
+  const dim3 bl(threads);
+  if (residual_marches(a.g)) march_one(a.g.periodic != 0, true, a, st);
+  else if (!one_fits(a.g, threads))
+    hipLaunchKernelGGL(k_residual_pert, dim3(res_general_blocks(a.g, (int)threads, false)), bl, 0, st, a, false);
+  else if (a.g.periodic) hipLaunchKernelGGL(k_residual_one_pert<true>, one_grid(a.g, threads), bl, 0, st, a);
+  else hipLaunchKernelGGL(k_residual_one_pert<false>, one_grid(a.g, threads), bl, 0, st, a);
 }
 
-// P: the grids of the launch are periodic in phi (full sphere)
-template <bool B, bool P>
-__global__ void __launch_bounds__(256) k_residual_in(PassArgs a, Batch bt) {
-  using SI = SrcOneT<true, P>;
-  if constexpr (B) {
-    const int mb = batch_member(bt, blockIdx.x);
-    const PassArgs am = batch_args(bt, mb);  // loaded once, before any store
-    residual_body_in<SI>(am, blockIdx.x - bt.woff[mb]);
-  } else {
-    // one grid: a three-dimensional launch (phi block, j - 1, i - 1), so the
-    // workgroup's indices need no integer division (on this GPU a division
-    // of even uniform integers runs on the vector unit)
-    residual_at_in<SI>(a, blockIdx.x, 1 + (int)blockIdx.y, 1 + (int)blockIdx.z);
-  }
+// the interior of a batch of grids (P: periodic)
+template <bool P>
+__global__ void __launch_bounds__(256) k_residual_in(Batch bt) {
+  const int mb = batch_member(bt, blockIdx.x);
+  const PassArgs am = batch_args(bt, mb);  // loaded once, before any store
+  residual_body_in<SrcOneT<true, P>>(am, blockIdx.x - bt.woff[mb]);
 }
 
 // The interior of a large grid: a workgroup owns 64 (phi) x 4 (theta) points
@@ -653,10 +713,24 @@ __host__ __device__ inline int march_seg(const Geo &g) {
   return march_wgs(g, seg) < 384u ? 2 : seg;
 }
 
+// One grid: the shell's workgroups (64 phi indices of a pair, a wave per kind
+// of row) behind the last segment.
 template <bool P, bool PT>
-__global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_march(PassArgs, int seg) {
+__global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_march(PassArgs a, int seg, int segs) {
   __shared__ double lds[4 * RM_PL];
-  residual_march<P, PT>((KPtr)__builtin_amdgcn_kernarg_segment_ptr(), lds, blockIdx.x, blockIdx.y, blockIdx.z, seg);
+  KPtr kp = (KPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  if ((int)blockIdx.z < segs) {
+    residual_march<P, PT>(kp, lds, blockIdx.x, blockIdx.y, blockIdx.z, seg);
+  } else {
+    const unsigned w = ((blockIdx.z - (unsigned)segs) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    const int npf = karg<int>(kp, offsetof(PassArgs, g) + offsetof(Geo, npf));
+    const unsigned nkb = (unsigned)(npf + 63) / 64u, q = w / nkb;
+    const unsigned pairs = 3u * (unsigned)(karg<int>(kp, offsetof(PassArgs, g) + offsetof(Geo, nt)) + 1) +
+                           3u * (unsigned)(karg<int>(kp, offsetof(PassArgs, g) + offsetof(Geo, nr)) - 2);
+    if (q < pairs)
+      residual_shell<false, PT>(kp, a, q, __builtin_amdgcn_readfirstlane((int)threadIdx.y),
+                                (int)((w - q * nkb) * 64u + threadIdx.x));
+  }
 }
 // a batch of grids: workgroups in one dimension, phi block fastest, then theta
 template <bool P>
@@ -670,6 +744,22 @@ __global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_marchB(Batch bt) {
   residual_march<P, false>(kp, lds, w - r * nk, r % nj, r / nj, march_seg(g));
 }
 
+// Workgroups of the shell up to which it joins the interior's launch, where
+// its latency is hidden but only two workgroups of it fit a CU: the
+// 360 x 180 x 40 sphere (3942) 102 + 25 us in two launches, 113 in one; the
+// 512 x 256 x 128 sphere (9192) and the 1024 x 512 x 64 sector (29325) are 1
+// and 2 % slower a step in one.
+constexpr unsigned RM_SHELL = 4096;
+static unsigned march_shell(const Geo &g) {
+  const unsigned n = (unsigned)((g.npf + 63) / 64) * res_shell_pairs(g);
+  return n <= RM_SHELL ? n : 0u;
+}
+static dim3 march_grid(const Geo &g, int seg) {
+  const unsigned nk = (unsigned)((g.np + 63) / 64), nj = (unsigned)((g.nt - 2 + RM_J - 1) / RM_J);
+  const unsigned nsh = march_shell(g);
+  return dim3(nk, nj, (unsigned)((g.nr - 2 + seg - 1) / seg) + (nsh + nk * nj - 1) / (nk * nj));
+}
+
 // Where it is taken: from 450 workgroups of two planes.  Below that the window
 // is a latency more than it saves: one launch with every load up front against
 // the window 6.3 against 10.1 us on 32 x 32 x 16 cells (112 workgroups), but
@@ -678,22 +768,27 @@ __global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_marchB(Batch bt) {
 // against 506 on 512 x 256 x 128 (the perturbation form of 100 m columns on
 // 200 x 200 x 200: 620 against 329).
 bool residual_marches(const Geo &g) {
-  return off32_ok(g) && g.nr >= 3 && g.nt >= 3 && march_wgs(g, 2) >= 450u;
+  if (!off32_ok(g) || g.nr < 3 || g.nt < 3 || march_wgs(g, 2) < 450u) return false;
+  const dim3 d = march_grid(g, march_seg(g));
+  return d.y <= 65535u && d.z <= 65535u;
 }
 unsigned residual_march_blocks(const Geo &g) { return march_wgs(g, march_seg(g)); }
 
 static void march_one(bool periodic, bool pert, const PassArgs &a, hipStream_t st) {
-  const Geo &g = a.g;
-  const int seg = march_seg(g);
-  const dim3 gr((unsigned)((g.np + 63) / 64), (unsigned)((g.nt - 2 + RM_J - 1) / RM_J),
-                (unsigned)((g.nr - 2 + seg - 1) / seg)), bl(64, RM_J);
+  const int seg = march_seg(a.g), segs = (a.g.nr - 2 + seg - 1) / seg;
+  const dim3 gr = march_grid(a.g, seg), bl(64, RM_J);
   if (periodic) {
-    if (pert) hipLaunchKernelGGL((k_residual_march<true, true>), gr, bl, 0, st, a, seg);
-    else hipLaunchKernelGGL((k_residual_march<true, false>), gr, bl, 0, st, a, seg);
+    if (pert) hipLaunchKernelGGL((k_residual_march<true, true>), gr, bl, 0, st, a, seg, segs);
+    else hipLaunchKernelGGL((k_residual_march<true, false>), gr, bl, 0, st, a, seg, segs);
   } else {
-    if (pert) hipLaunchKernelGGL((k_residual_march<false, true>), gr, bl, 0, st, a, seg);
-    else hipLaunchKernelGGL((k_residual_march<false, false>), gr, bl, 0, st, a, seg);
+    if (pert) hipLaunchKernelGGL((k_residual_march<false, true>), gr, bl, 0, st, a, seg, segs);
+    else hipLaunchKernelGGL((k_residual_march<false, false>), gr, bl, 0, st, a, seg, segs);
   }
+  if (march_shell(a.g)) return;
+  const dim3 sb(64), sg(res_general_blocks(a.g, 64, true));
+  const Batch none{nullptr, nullptr, 0};
+  if (pert) hipLaunchKernelGGL(k_residual_pert, sg, sb, 0, st, a, true);
+  else hipLaunchKernelGGL(k_residual<false>, sg, sb, 0, st, a, none, true);
 }
 
 void launch_residual_march(bool periodic, const PassArgs &a, const Batch &b, unsigned blocks, hipStream_t st) {
@@ -737,7 +832,7 @@ __global__ void __launch_bounds__(256) k_midpoint(MidArrays a) {
 }
 
 unsigned residual_interior_blocks(const Geo &g, int bs) { return res_interior_blocks(g, bs); }
-unsigned residual_general_blocks(const Geo &g, int bs) { return res_general_blocks(g, bs); }
+unsigned residual_general_blocks(const Geo &g, int bs) { return res_general_blocks(g, bs, res_interior_blocks(g, bs) > 0); }
 
 static void set5(const double **dst, const Fields &f) {
   dst[F_P] = f.p; dst[F_UR] = f.ur; dst[F_UT] = f.ut; dst[F_UF] = f.uf; dst[F_T] = f.T;
@@ -792,29 +887,28 @@ void launch_residual(const Geo &g, const Mat &m, const Fields &Un, const Fields 
   a.status = status;
   const Batch none{nullptr, nullptr, 0};
   if (residual_marches(g)) march_one(g.periodic != 0, false, a, st);
-  else launch_residual_in_pass(g.periodic != 0, a, none, residual_interior_blocks(g, (int)th), th, st);
-  launch_residual_pass(a, none, residual_general_blocks(g, (int)th), th, st);
+  else if (res_interior_blocks(g, (int)th)) launch_residual_in_pass(g.periodic != 0, a, none, 0, th, st);
+  else launch_residual_pass(a, none, res_general_blocks(g, (int)th, false), th, st);
 }
 
 void launch_residual_pass(const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads,
                           hipStream_t st) {
-  if (b.tab) hipLaunchKernelGGL(k_residual<true>, dim3(blocks), dim3(threads), 0, st, a, b);
-  else hipLaunchKernelGGL(k_residual<false>, dim3(blocks), dim3(threads), 0, st, a, b);
+  if (b.tab) hipLaunchKernelGGL(k_residual<true>, dim3(blocks), dim3(threads), 0, st, a, b, true);
+  else hipLaunchKernelGGL(k_residual<false>, dim3(blocks), dim3(threads), 0, st, a, b, false);
 }
 
+// one grid: the shell as well
 void launch_residual_in_pass(bool periodic, const PassArgs &a, const Batch &b, unsigned blocks,
                              unsigned threads, hipStream_t st) {
   const dim3 bl(threads);
-  // a batch numbers its members' workgroups in one dimension; one grid takes
-  // the same workgroups, in the same order, as (phi block, j - 1, i - 1)
-  const dim3 gr = b.tab ? dim3(blocks)
-                        : dim3((unsigned)res_nk(a.g, (int)threads), (unsigned)(a.g.nt - 2), (unsigned)(a.g.nr - 2));
-  if (periodic) {
-    if (b.tab) hipLaunchKernelGGL((k_residual_in<true, true>), gr, bl, 0, st, a, b);
-    else hipLaunchKernelGGL((k_residual_in<false, true>), gr, bl, 0, st, a, b);
+  if (b.tab) {
+    if (periodic) hipLaunchKernelGGL(k_residual_in<true>, dim3(blocks), bl, 0, st, b);
+    else hipLaunchKernelGGL(k_residual_in<false>, dim3(blocks), bl, 0, st, b);
+  } else if (!one_fits(a.g, threads)) {
+    launch_residual_pass(a, b, res_general_blocks(a.g, (int)threads, false), threads, st);
   } else {
-    if (b.tab) hipLaunchKernelGGL((k_residual_in<true, false>), gr, bl, 0, st, a, b);
-    else hipLaunchKernelGGL((k_residual_in<false, false>), gr, bl, 0, st, a, b);
+    if (periodic) hipLaunchKernelGGL(k_residual_one<true>, one_grid(a.g, threads), bl, 0, st, a);
+    else hipLaunchKernelGGL(k_residual_one<false>, one_grid(a.g, threads), bl, 0, st, a);
   }
 }
 

@@ -30,6 +30,49 @@ __device__ __forceinline__ void sto(double *base, unsigned off, double v) {
 
 __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
+// The state with the ghost rules of dsw_common.hpp for the rows of the boundary
+// shell at uniform (i, j), by selects on clamped indices: no load under a condition that differs between lanes.
+// (With early returns in divergent branches the compiler, clang 22 of ROCm 7.2,
+// left a uniform row index undefined in waves where no lane took the branch.)
+struct SrcShell {
+  const double *a[5];
+  Geo g;  // for at() alone
+  static constexpr bool INTERIOR = false;
+  static constexpr bool PERIODIC = false;
+  static constexpr bool WALL = false;
+  static constexpr bool PERT = false;
+  static constexpr bool WIN = true;
+  __device__ __forceinline__ double ld(int f, long x) const { return a[f][x]; }
+  __device__ __forceinline__ double at(int f, int i, int j, int k) const;
+};
+__device__ __forceinline__ int phi_in(const Geo &g, int k) { return g.periodic ? wrapk(g, k) : clampi(k, 0, g.np - 1); }
+__device__ __forceinline__ double gC(const Geo &g, const SrcShell &s, int fid, int i, int j, int k) {
+  const long row = ((long)clampi(i, 0, g.nr - 1) * g.nt + clampi(j, 0, g.nt - 1)) * g.np;
+  return ldo(s.a[fid] + row, (unsigned)phi_in(g, k) * 8u);
+}
+__device__ __forceinline__ double gR(const Geo &g, const SrcShell &s, int f, int j, int k) {
+  const int kk = phi_in(g, k);
+  const bool flip = (j < 0 && !g.pole_lo) || (j >= g.nt && !g.pole_hi);
+  const double v = ldo(s.a[F_UR] + ((long)f * g.nt + clampi(j, 0, g.nt - 1)) * g.np, (unsigned)kk * 8u);
+  return flip != (!g.periodic && kk != k) ? -v : v;
+}
+__device__ __forceinline__ double gT(const Geo &g, const SrcShell &s, int i, int f, int k) {
+  const int kk = phi_in(g, k), ii = clampi(i, 0, g.nr - 1);
+  const double v = ldo(s.a[F_UT] + ((long)ii * (g.nt + 1) + f) * g.np, (unsigned)kk * 8u);
+  return (ii != i) != (!g.periodic && kk != k) ? -v : v;
+}
+__device__ __forceinline__ double gF(const Geo &g, const SrcShell &s, int i, int j, int f) {
+  const int ff = g.periodic ? wrapk(g, f) : f, ii = clampi(i, 0, g.nr - 1), jj = clampi(j, 0, g.nt - 1);
+  const double v = ldo(s.a[F_UF] + ((long)ii * g.nt + jj) * g.npf, (unsigned)ff * 8u);
+  return (ii != i) != (jj != j) ? -v : v;
+}
+__device__ __forceinline__ double SrcShell::at(int f, int i, int j, int k) const {
+  if (f == F_UR) return gR(g, *this, i, j, k);
+  if (f == F_UT) return gT(g, *this, i, j, k);
+  if (f == F_UF) return gF(g, *this, i, j, k);
+  return gC(g, *this, f, i, j, k);
+}
+
 // One block row, scaled by tau/2 with the identity added, structural
 // non-zeros only (unknowns p, T, w).
 struct FRow {

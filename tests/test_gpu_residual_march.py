@@ -2,8 +2,9 @@
 a window in LDS, at the edges of its tiles: phi lines a tile wide and one off
 it, theta tiles and r segments that the grid does not fill, segments of two and
 of four planes, the smallest grid that takes it (450 workgroups of two planes)
-and one below.  Bar: the parity tests' 1e-11 relative L2 per field against the
-oracle; a batch gives bitwise the states of single steps."""
+and one below, the shell in the same launch and in one of its own.  Bar: the
+parity tests' 1e-11 relative L2 per field against the oracle; a batch gives
+bitwise the states of single steps."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +15,8 @@ from test_gpu_parity import residual_errors
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [(19, 66, 260), (20, 67, 321), (35, 130, 63), (36, 129, 64), (8, 146, 256), (5, 601, 65), (27, 141, 65)]
+SIZES = [(19, 66, 260), (20, 67, 321), (35, 130, 63), (36, 129, 64), (8, 146, 256), (5, 601, 65), (27, 141, 65),
+         (4, 700, 129)]
 
 
 def _workload(nr, nt, np_, sphere, K):
