@@ -119,6 +119,13 @@ template <bool P>
 struct SrcInW {
   const double *a[5];
   Wall w;
+  bool has[4];  // ur_p1, ur_p2, ut_p1, ut_p2 given; else the pointer is some array of at least that length
+  // a phi wall's value at a uniform index: no load under a condition, so that
+  // the loads of a row's stencil stay together
+  __device__ __forceinline__ double wu(int q, const double *p, long x) const {
+    const double v = p[x];
+    return has[q] ? v : 0.0;
+  }
   const double *f[5];
   static constexpr bool INTERIOR = true;
   static constexpr bool PERIODIC = P;
@@ -213,7 +220,10 @@ __device__ __forceinline__ double gR(const Geo &g, const S &s, int f, int j, int
     if constexpr (S::PERIODIC) return s.ldk(F_UR, ((typename S::Row)f * g.nt + j) * g.np, wrapk(g, k));
     const int kk = clampi(k, 0, g.np - 1);
     const double v = s.ldk(F_UR, ((typename S::Row)f * g.nt + j) * g.np, kk);
-    if constexpr (S::WALL) return kk == k ? v : 2.0 * wallv(k < 0 ? s.w.ur_p1 : s.w.ur_p2, (long)f * g.nt + j) - v;
+    if constexpr (S::WALL) {
+      const double w1 = s.wu(0, s.w.ur_p1, (long)f * g.nt + j), w2 = s.wu(1, s.w.ur_p2, (long)f * g.nt + j);
+      return kk == k ? v : 2.0 * (k < 0 ? w1 : w2) - v;
+    }
     return kk == k ? v : -v;
   }
   if constexpr (S::WALL) return gR_wall(g, s, f, j, k);
@@ -234,7 +244,10 @@ __device__ __forceinline__ double gT(const Geo &g, const S &s, int i, int f, int
     if constexpr (S::PERIODIC) return s.ldk(F_UT, ((typename S::Row)i * (g.nt + 1) + f) * g.np, wrapk(g, k));
     const int kk = clampi(k, 0, g.np - 1);
     const double v = s.ldk(F_UT, ((typename S::Row)i * (g.nt + 1) + f) * g.np, kk);
-    if constexpr (S::WALL) return kk == k ? v : 2.0 * wallv(k < 0 ? s.w.ut_p1 : s.w.ut_p2, (long)i * (g.nt + 1) + f) - v;
+    if constexpr (S::WALL) {
+      const double w1 = s.wu(2, s.w.ut_p1, (long)i * (g.nt + 1) + f), w2 = s.wu(3, s.w.ut_p2, (long)i * (g.nt + 1) + f);
+      return kk == k ? v : 2.0 * (k < 0 ? w1 : w2) - v;
+    }
     return kk == k ? v : -v;
   }
   if constexpr (S::WALL) return gT_wall(g, s, i, f, k);

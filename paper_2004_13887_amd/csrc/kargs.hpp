@@ -6,7 +6,7 @@
 // (scalar loads that hit the cache).  Passing the block's address through an
 // empty asm before a piece keeps the compiler from hoisting its reads.  The
 // pointers come with their address spaces: arrays in global memory, and the
-// grid's tables, which no kernel writes, in constant memory, so that an entry
+// grid's tables and walls, which the kernel does not write, in constant memory, so that an entry
 // at a uniform index is a scalar load also behind stores and atomics.
 //
 // The argument struct is the kernel's first parameter, so it starts at offset
@@ -56,6 +56,17 @@ __device__ __forceinline__ Mat kmat(KPtr p, unsigned at) {
   DSW_KM(gam); DSW_KM(Rg); DSW_KM(pinf); DSW_KM(mu); DSW_KM(kap); DSW_KM(omega); DSW_KM(g_r);
 #undef DSW_KM
   return m;
+}
+// the velocities on the phi walls are read at uniform indices
+__device__ __forceinline__ Wall kwall(KPtr p, unsigned at) {
+  Wall w;
+#define DSW_KT(f) w.f = ktab(p, at + offsetof(Wall, f))
+#define DSW_KA(f) w.f = karr(p, at + offsetof(Wall, f))
+  DSW_KT(ur_p1); DSW_KT(ur_p2); DSW_KT(ut_p1); DSW_KT(ut_p2);
+  DSW_KA(ur_t1); DSW_KA(ur_t2); DSW_KA(ut_r1); DSW_KA(ut_r2); DSW_KA(uf_r1); DSW_KA(uf_r2); DSW_KA(uf_t1); DSW_KA(uf_t2);
+#undef DSW_KT
+#undef DSW_KA
+  return w;
 }
 static_assert(offsetof(Fields, T) == 32, "kfields reads this layout");
 

@@ -371,33 +371,50 @@ __device__ __forceinline__ void residual_point_in(const Geo &g, const Mat &m, co
   if (!isfinite(chk)) status[ST_DIVERGED] = 1;  // plain vector store
 }
 
-template <class SI>
-__device__ __forceinline__ void residual_at_in(const PassArgs &a, unsigned kb, int j, int i) {
-  const Geo &g = a.g;
-  SI s;
+// the arguments of a pass from its PassArgs at kp
+template <class S>
+__device__ __forceinline__ void res_source(KPtr kp, S &s) {
 #pragma unroll
-  for (int q = 0; q < 5; q++) s.a[q] = a.u.a[q];
-  if constexpr (SI::WALL) {
-    s.w = a.wall;
-    s.f[F_P] = a.fsrc.p; s.f[F_UR] = a.fsrc.ur; s.f[F_UT] = a.fsrc.ut; s.f[F_UF] = a.fsrc.uf;
-    s.f[F_T] = a.fsrc.T;
+  for (int f = 0; f < 5; f++) s.a[f] = karr(kp, offsetof(PassArgs, u) + 8 * f);
+  if constexpr (S::WALL) {
+    s.w = kwall(kp, offsetof(PassArgs, wall));
+    const double **const pw[4] = {&s.w.ur_p1, &s.w.ur_p2, &s.w.ut_p1, &s.w.ut_p2};
+    const double *const any[2] = {ktab(kp, offsetof(PassArgs, u) + 8 * F_UR), ktab(kp, offsetof(PassArgs, u) + 8 * F_UT)};
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      s.has[q] = *pw[q] != nullptr;
+      *pw[q] = s.has[q] ? *pw[q] : any[q / 2];
+    }
+    const Fields q = kfields(kp, offsetof(PassArgs, fsrc));
+    s.f[F_P] = q.p; s.f[F_UR] = q.ur; s.f[F_UT] = q.ut; s.f[F_UF] = q.uf; s.f[F_T] = q.T;
   }
-  if constexpr (SI::PERT) {
-    s.pref = a.pref;
-    s.tref = a.tref;
+  if constexpr (S::PERT) {
+    s.pref = ktab(kp, offsetof(PassArgs, pref));
+    s.tref = ktab(kp, offsetof(PassArgs, tref));
   }
-  residual_point_in<SI>(g, a.m, s, a.d, a.tau, a.R, a.status, i, j, (int)(kb * blockDim.x + threadIdx.x));
+}
+__device__ __forceinline__ Diff res_diff(KPtr kp) {
+  Diff d;
+#pragma unroll
+  for (int f = 0; f < 5; f++) {
+    d.k[f] = karr(kp, offsetof(PassArgs, d) + offsetof(Diff, k) + 8 * f);
+    d.n[f] = karr(kp, offsetof(PassArgs, d) + offsetof(Diff, n) + 8 * f);
+  }
+  d.same = karg<int>(kp, offsetof(PassArgs, d) + offsetof(Diff, same));
+  return d;
+}
+__device__ __forceinline__ int *res_status(KPtr kp) {
+  return (int *)karg<DSW_AS1 int *>(kp, offsetof(PassArgs, status));
 }
 
-// workgroup w of a one-dimensional launch: phi block fastest, then j, then i
 template <class SI>
-__device__ __forceinline__ void residual_body_in(const PassArgs &a, unsigned w) {
-  const Geo &g = a.g;
-  const int bs = (int)blockDim.x;
-  const unsigned nkin = (unsigned)res_nk(g, bs);
-  const unsigned kb = w % nkin, rest = w / nkin;
-  const int j = 1 + (int)(rest % (unsigned)(g.nt - 2)), i = 1 + (int)(rest / (unsigned)(g.nt - 2));
-  residual_at_in<SI>(a, kb, j, i);
+__device__ __forceinline__ void residual_at_in(KPtr kp, unsigned kb, int j, int i) {
+  const Geo g = kgeo(kp, offsetof(PassArgs, g));
+  SI s;
+  res_source(kp, s);
+  residual_point_in<SI>(g, kmat(kp, offsetof(PassArgs, m)), s, res_diff(kp), karg<double>(kp, offsetof(PassArgs, tau)),
+                        kfields(kp, offsetof(PassArgs, R)), res_status(kp), i, j,
+                        (int)(kb * blockDim.x + threadIdx.x));
 }
 
 template <bool B>
@@ -411,48 +428,26 @@ __global__ void __launch_bounds__(256) DSW_OCC(DSW_WAVES_RES) k_residual(PassArg
   }
 }
 
-// One row (PART 0 .. 3: the centre, the r, theta, phi face) of the shell's
-// points k of pair number q: plain and perturbation form by selects, from the
-// argument block; forced by the general rules.
+// One row (part 0 .. 3: the centre, the r, theta, phi face) of the shell's
+// points k of pair number q.
 template <bool W, bool PT>
-__device__ __forceinline__ void residual_shell(KPtr kp, const PassArgs &a, unsigned q, int part, int k) {
-  if constexpr (W) {
-    const Geo &g = a.g;
-    int i, j;
-    res_pair(g, q, true, i, j);
-    const SrcW s = SrcSel<true, false>::get(a);
-    if (part == 0) residual_point<SrcW, false, 0>(g, a.m, s, a.d, a.tau, a.R, Fields{}, a.status, i, j, k);
-    else if (part == 1) residual_point<SrcW, false, 1>(g, a.m, s, a.d, a.tau, a.R, Fields{}, a.status, i, j, k);
-    else if (part == 2) residual_point<SrcW, false, 2>(g, a.m, s, a.d, a.tau, a.R, Fields{}, a.status, i, j, k);
-    else residual_point<SrcW, false, 3>(g, a.m, s, a.d, a.tau, a.R, Fields{}, a.status, i, j, k);
-  } else {
-    using S = std::conditional_t<PT, SrcPert<SrcShell>, SrcShell>;
-    const Geo g = kgeo(kp, offsetof(PassArgs, g));
-    const Mat m = kmat(kp, offsetof(PassArgs, m));
-    S s;
-    s.g = g;
-    Diff d;
-#pragma unroll
-    for (int f = 0; f < 5; f++) {
-      s.a[f] = karr(kp, offsetof(PassArgs, u) + 8 * f);
-      d.k[f] = karr(kp, offsetof(PassArgs, d) + offsetof(Diff, k) + 8 * f);
-      d.n[f] = karr(kp, offsetof(PassArgs, d) + offsetof(Diff, n) + 8 * f);
-    }
-    d.same = karg<int>(kp, offsetof(PassArgs, d) + offsetof(Diff, same));
-    if constexpr (PT) {
-      s.pref = ktab(kp, offsetof(PassArgs, pref));
-      s.tref = ktab(kp, offsetof(PassArgs, tref));
-    }
-    const double tau = karg<double>(kp, offsetof(PassArgs, tau));
-    const Fields R = kfields(kp, offsetof(PassArgs, R));
-    int *status = (int *)karg<DSW_AS1 int *>(kp, offsetof(PassArgs, status));
-    int i, j;
-    res_pair(g, q, true, i, j);
-    if (part == 0) residual_point<S, false, 0>(g, m, s, d, tau, R, Fields{}, status, i, j, k);
-    else if (part == 1) residual_point<S, false, 1>(g, m, s, d, tau, R, Fields{}, status, i, j, k);
-    else if (part == 2) residual_point<S, false, 2>(g, m, s, d, tau, R, Fields{}, status, i, j, k);
-    else residual_point<S, false, 3>(g, m, s, d, tau, R, Fields{}, status, i, j, k);
-  }
+__device__ __forceinline__ void residual_shell(KPtr kp, unsigned q, int part, int k) {
+  using S = std::conditional_t<W, SrcShellW, std::conditional_t<PT, SrcPert<SrcShell>, SrcShell>>;
+  const Geo g = kgeo(kp, offsetof(PassArgs, g));
+  const Mat m = kmat(kp, offsetof(PassArgs, m));
+  S s;
+  s.g = g;
+  res_source(kp, s);
+  const Diff d = res_diff(kp);
+  const double tau = karg<double>(kp, offsetof(PassArgs, tau));
+  const Fields R = kfields(kp, offsetof(PassArgs, R));
+  int *status = res_status(kp);
+  int i, j;
+  res_pair(g, q, true, i, j);
+  if (part == 0) residual_point<S, false, 0>(g, m, s, d, tau, R, Fields{}, status, i, j, k);
+  else if (part == 1) residual_point<S, false, 1>(g, m, s, d, tau, R, Fields{}, status, i, j, k);
+  else if (part == 2) residual_point<S, false, 2>(g, m, s, d, tau, R, Fields{}, status, i, j, k);
+  else residual_point<S, false, 3>(g, m, s, d, tau, R, Fields{}, status, i, j, k);
 }
 
 // One grid in one launch (P: periodic): a three-dimensional grid of workgroups
@@ -461,27 +456,32 @@ __device__ __forceinline__ void residual_shell(KPtr kp, const PassArgs &a, unsig
 // the vector unit), and behind its last plane the shell's, one per phi block,
 // pair and kind of row.  The two are independent, and on a small grid either
 // alone is a chain of latencies in a nearly empty chip: 32 x 32 x 16 cells
-// 6.4 and 6.3 us in two launches, 10.1 in one.
+// 6.4 and 6.3 us in two launches, 6.6 in one.
 template <class SI, bool W, bool PT>
-__device__ __forceinline__ void residual_both(const PassArgs &a) {
-  const Geo &g = a.g;
-  if ((int)blockIdx.z < g.nr - 2) {
-    residual_at_in<SI>(a, blockIdx.x, 1 + (int)blockIdx.y, 1 + (int)blockIdx.z);
+__device__ __forceinline__ void residual_both(KPtr kp) {
+  const int nt = karg<int>(kp, offsetof(PassArgs, g) + offsetof(Geo, nt));
+  const int nr = karg<int>(kp, offsetof(PassArgs, g) + offsetof(Geo, nr));
+  if ((int)blockIdx.z < nr - 2) {
+    residual_at_in<SI>(kp, blockIdx.x, 1 + (int)blockIdx.y, 1 + (int)blockIdx.z);
   } else {
-    const unsigned w = ((blockIdx.z - (unsigned)(g.nr - 2)) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    const unsigned w = ((blockIdx.z - (unsigned)(nr - 2)) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     const unsigned nkb = gridDim.x, q = w / (4u * nkb), r = w - q * (4u * nkb);
-    if (q < res_shell_pairs(g))
-      residual_shell<W, PT>((KPtr)__builtin_amdgcn_kernarg_segment_ptr(), a, q, (int)(r & 3u),
-                            (int)((r >> 2) * blockDim.x + threadIdx.x));
+    if (q < 3u * (unsigned)(nt + 1) + 3u * (unsigned)(nr - 2))  // res_shell_pairs
+      residual_shell<W, PT>(kp, q, (int)(r & 3u), (int)((r >> 2) * blockDim.x + threadIdx.x));
   }
 }
+// (the argument is read through the argument block)
 template <bool P>
-__global__ void __launch_bounds__(256) k_residual_one(PassArgs a) { residual_both<SrcOneT<true, P>, false, false>(a); }
+__global__ void __launch_bounds__(256) k_residual_one(PassArgs) {
+  residual_both<SrcOneT<true, P>, false, false>((KPtr)__builtin_amdgcn_kernarg_segment_ptr());
+}
 template <bool P>
-__global__ void __launch_bounds__(256) k_residual_one_forced(PassArgs a) { residual_both<SrcInW<P>, true, false>(a); }
+__global__ void __launch_bounds__(256) k_residual_one_forced(PassArgs) {
+  residual_both<SrcInW<P>, true, false>((KPtr)__builtin_amdgcn_kernarg_segment_ptr());
+}
 template <bool P>
-__global__ void __launch_bounds__(256) k_residual_one_pert(PassArgs a) {
-  residual_both<SrcPert<SrcOneT<true, P>>, false, true>(a);
+__global__ void __launch_bounds__(256) k_residual_one_pert(PassArgs) {
+  residual_both<SrcPert<SrcOneT<true, P>>, false, true>((KPtr)__builtin_amdgcn_kernarg_segment_ptr());
 }
 // grids beyond the interior launch's 32-bit indices: every point by the general rules
 __global__ void __launch_bounds__(256) k_residual_forced(PassArgs a) { residual_body<true>(a, blockIdx.x, false); }
@@ -525,8 +525,12 @@ void launch_residual_pert(const PassArgs &a, unsigned threads, hipStream_t st) {
 template <bool P>
 __global__ void __launch_bounds__(256) k_residual_in(Batch bt) {
   const int mb = batch_member(bt, blockIdx.x);
-  const PassArgs am = batch_args(bt, mb);  // loaded once, before any store
-  residual_body_in<SrcOneT<true, P>>(am, blockIdx.x - bt.woff[mb]);
+  KPtr kp = (KPtr)(bt.tab + mb);
+  const int nt = karg<int>(kp, offsetof(PassArgs, g) + offsetof(Geo, nt));
+  const int npf = karg<int>(kp, offsetof(PassArgs, g) + offsetof(Geo, npf)), bs = (int)blockDim.x;
+  // phi block fastest, then j, then i
+  const unsigned w = blockIdx.x - bt.woff[mb], nk = (unsigned)((npf + bs - 1) / bs), r = w / nk;
+  residual_at_in<SrcOneT<true, P>>(kp, w - r * nk, 1 + (int)(r % (unsigned)(nt - 2)), 1 + (int)(r / (unsigned)(nt - 2)));
 }
 
 // The interior of a large grid: a workgroup owns 64 (phi) x 4 (theta) points
@@ -716,7 +720,7 @@ __host__ __device__ inline int march_seg(const Geo &g) {
 // One grid: the shell's workgroups (64 phi indices of a pair, a wave per kind
 // of row) behind the last segment.
 template <bool P, bool PT>
-__global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_march(PassArgs a, int seg, int segs) {
+__global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_march(PassArgs, int seg, int segs) {
   __shared__ double lds[4 * RM_PL];
   KPtr kp = (KPtr)__builtin_amdgcn_kernarg_segment_ptr();
   if ((int)blockIdx.z < segs) {
@@ -728,7 +732,7 @@ __global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_march(PassArgs a, i
     const unsigned pairs = 3u * (unsigned)(karg<int>(kp, offsetof(PassArgs, g) + offsetof(Geo, nt)) + 1) +
                            3u * (unsigned)(karg<int>(kp, offsetof(PassArgs, g) + offsetof(Geo, nr)) - 2);
     if (q < pairs)
-      residual_shell<false, PT>(kp, a, q, __builtin_amdgcn_readfirstlane((int)threadIdx.y),
+      residual_shell<false, PT>(kp, q, __builtin_amdgcn_readfirstlane((int)threadIdx.y),
                                 (int)((w - q * nkb) * 64u + threadIdx.x));
   }
 }

@@ -73,6 +73,57 @@ __device__ __forceinline__ double SrcShell::at(int f, int i, int j, int k) const
   return gC(g, *this, f, i, j, k);
 }
 
+// the same for a forced pass: wall velocities (gR_wall and its like), source
+struct SrcShellW {
+  const double *a[5];
+  Geo g;
+  Wall w;
+  bool has[4];  // as SrcInW
+  __device__ __forceinline__ double wu(int q, const double *p, long x) const {
+    const double v = p[x];
+    return has[q] ? v : 0.0;
+  }
+  const double *f[5];
+  static constexpr bool INTERIOR = false;
+  static constexpr bool PERIODIC = false;
+  static constexpr bool WALL = true;
+  static constexpr bool PERT = false;
+  static constexpr bool WIN = true;
+  __device__ __forceinline__ double ld(int fid, long x) const { return a[fid][x]; }
+  __device__ __forceinline__ double at(int fid, int i, int j, int k) const {
+    if (fid == F_P || fid == F_T) {
+      const long row = ((long)clampi(i, 0, g.nr - 1) * g.nt + clampi(j, 0, g.nt - 1)) * g.np;
+      return ldo(a[fid] + row, (unsigned)phi_in(g, k) * 8u);
+    }
+    const int kk = fid == F_UF && !g.periodic ? k : phi_in(g, k), ii = clampi(i, 0, g.nr - 1), jj = clampi(j, 0, g.nt - 1);
+    const unsigned o = (unsigned)kk * 8u;
+    double sg = 1.0, add = 0.0;
+    if (fid != F_UF && !g.periodic) { // phi wall
+      const long x = fid == F_UR ? (long)i * g.nt + jj : (long)ii * (g.nt + 1) + j;
+      const double w1 = fid == F_UR ? wu(0, w.ur_p1, x) : wu(2, w.ut_p1, x);
+      const double w2 = fid == F_UR ? wu(1, w.ur_p2, x) : wu(3, w.ut_p2, x);
+      add = kk == k ? 0.0 : 2.0 * (k < 0 ? w1 : w2);
+      sg = kk == k ? 1.0 : -1.0;
+    }
+    if (fid != F_UT && jj != j) { // theta wall or pole
+      const bool pole = j < 0 ? g.pole_lo : g.pole_hi;
+      const long x = fid == F_UR ? (long)i * g.np : (long)ii * g.npf;
+      const double *p = fid == F_UR ? (j < 0 ? w.ur_t1 : w.ur_t2) : (j < 0 ? w.uf_t1 : w.uf_t2);
+      if (!pole && p) add += sg * 2.0 * ldo(p + x, o);
+      if (!pole || fid == F_UF) sg = -sg;
+    }
+    if (fid != F_UR && ii != i) { // r wall
+      const long x = fid == F_UT ? (long)j * g.np : (long)jj * g.npf;
+      const double *p = fid == F_UT ? (i < 0 ? w.ut_r1 : w.ut_r2) : (i < 0 ? w.uf_r1 : w.uf_r2);
+      if (p) add += sg * 2.0 * ldo(p + x, o);
+      sg = -sg;
+    }
+    const long row = fid == F_UR ? ((long)i * g.nt + jj) * g.np
+                                 : (fid == F_UT ? ((long)ii * (g.nt + 1) + j) * g.np : ((long)ii * g.nt + jj) * g.npf);
+    return add + sg * ldo(a[fid] + row, o);
+  }
+};
+
 // One block row, scaled by tau/2 with the identity added, structural
 // non-zeros only (unknowns p, T, w).
 struct FRow {
