@@ -23,10 +23,8 @@
 // Two variants:
 //   * inside a split step the midpoint is already resident (written by the
 //     previous iteration's last sweep, or U^n itself at the first iteration),
-//     so every neighbour read is a single load; the C-ABI call writes the
-//     midpoint first and then runs the same launches;
-//   * on a small grid the C-ABI call forms the midpoint on the fly from Un and
-//     Uk and writes it, in one launch.
+//     so every neighbour read is a single load;
+//   * the C-ABI call forms the midpoint from Un and Uk and writes it.
 #include <algorithm>
 #include <cstring>
 #include <type_traits>
@@ -562,8 +560,10 @@ struct SrcWin {
   __device__ __forceinline__ double ldk(int, int, int) const { return 0.0; } // never called
 };
 
-// kp: the PassArgs of the grid; (bx, by, bz): phi block, theta tile, r segment
-template <bool P, bool PT>
+// kp: the PassArgs of the grid; (bx, by, bz): phi block, theta tile, r segment.
+// MID: the state is the midpoint of the difference's two iterates (a.d), formed
+// as its planes are loaded and written to a.o.ub as well.
+template <bool P, bool PT, bool MID>
 __device__ __forceinline__ void residual_march(KPtr kp, double *lds, int bx, int by, int bz, int seg) {
   using SI = std::conditional_t<PT, SrcPert<SrcWin<P>>, SrcWin<P>>;
   constexpr unsigned GEO = offsetof(PassArgs, g);
@@ -591,23 +591,31 @@ __device__ __forceinline__ void residual_march(KPtr kp, double *lds, int bx, int
     }
   }
   const bool two = tid + 256 < RM_FS;
-  double st[2][5];
+  double st[2][5], sn[2][5];
   const auto stage = [&](int p) {
     KPtr q = kp;
     asm volatile("" : "+s"(q), "+s"(p));
     const int nt = karg<int>(q, GEO + offsetof(Geo, nt)), np = karg<int>(q, GEO + offsetof(Geo, np));
     const int npf = karg<int>(q, GEO + offsetof(Geo, npf));
     const long pc = (long)p * nt * np;
-    const unsigned u = offsetof(PassArgs, u);
-    const double *bp = karr(q, u + 8 * F_P) + pc, *br = karr(q, u + 8 * F_UR) + pc, *bT = karr(q, u + 8 * F_T) + pc;
-    const double *bt = karr(q, u + 8 * F_UT) + (long)p * (nt + 1) * np, *bf = karr(q, u + 8 * F_UF) + (long)p * nt * npf;
+    const long pt = (long)p * (nt + 1) * np, pf = (long)p * nt * npf;
 #pragma unroll
-    for (int e = 0; e < 2; e++) {
-      st[e][F_P] = ldo(bp, oc[e]);
-      st[e][F_UR] = ldo(br, oc[e]);
-      st[e][F_UT] = ldo(bt, ot[e]);
-      st[e][F_UF] = ldo(bf, of[e]);
-      st[e][F_T] = ldo(bT, oc[e]);
+    for (int f = 0; f < 5; f++) {
+      const long x = f == F_UT ? pt : (f == F_UF ? pf : pc);
+      const unsigned *o = f == F_UT ? ot : (f == F_UF ? of : oc);
+      if constexpr (MID) {
+        const double *bk = karr(q, offsetof(PassArgs, d) + offsetof(Diff, k) + 8 * f) + x;
+        const double *bn = karr(q, offsetof(PassArgs, d) + offsetof(Diff, n) + 8 * f) + x;
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+          st[e][f] = ldo(bk, o[e]);
+          sn[e][f] = ldo(bn, o[e]);
+        }
+      } else {
+        const double *bu = karr(q, offsetof(PassArgs, u) + 8 * f) + x;
+#pragma unroll
+        for (int e = 0; e < 2; e++) st[e][f] = ldo(bu, o[e]);
+      }
     }
   };
   const auto commit = [&](int slot) {
@@ -616,7 +624,10 @@ __device__ __forceinline__ void residual_march(KPtr kp, double *lds, int bx, int
       if (q == 1 && !two) continue;
       double *w = lds + slot + tid + 256 * q;
 #pragma unroll
-      for (int f = 0; f < 5; f++) w[f * RM_FS] = (f == F_UR || f == F_UT) && flip[q] ? -st[q][f] : st[q][f];
+      for (int f = 0; f < 5; f++) {
+        const double v = MID ? 0.5 * (st[q][f] + sn[q][f]) : st[q][f];
+        w[f * RM_FS] = (f == F_UR || f == F_UT) && flip[q] ? -v : v;
+      }
     }
   };
 #pragma nounroll
@@ -641,7 +652,7 @@ __device__ __forceinline__ void residual_march(KPtr kp, double *lds, int bx, int
     // loads in the order in which they are waited for: the rows' own
     // differences, then the plane after next
     double dk[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, dn[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (!karg<int>(p, offsetof(PassArgs, d) + offsetof(Diff, same))) {
+    if (MID || !karg<int>(p, offsetof(PassArgs, d) + offsetof(Diff, same))) {
 #pragma unroll
       for (int f = 0; f < 5; f++) {
         const long row = f == F_UT ? rt_ : (f == F_UF ? rf_ : rc);
@@ -676,6 +687,7 @@ __device__ __forceinline__ void residual_march(KPtr kp, double *lds, int bx, int
     double rt = -(dk[F_UT] - dn[F_UT]) - tau * Ft;
     double rf = -(dk[F_UF] - dn[F_UF]) - tau * Ff;
     if (!P && k == 0) rf = 0.0;
+    const double ubn = MID && !P ? s.at(F_UF, i, jw, k + 1) : 0.0;
     // and the window is written after it, ahead of the stores (whose end the
     // next wait for a load would else wait for)
     asm volatile("" : "+v"(rp), "+v"(rT), "+v"(rr), "+v"(rt), "+v"(rf) : : "memory");
@@ -689,6 +701,15 @@ __device__ __forceinline__ void residual_march(KPtr kp, double *lds, int bx, int
       sto(R.ut + rt_, o, rt);
       sto(R.uf + rf_, o, rf);
       if (!P && k == g.np - 1) sto(R.uf + rf_, o + 8u, 0.0);
+      if constexpr (MID) {
+        const Fields Ub = kfields(p, offsetof(PassArgs, o) + offsetof(Out, ub));
+        sto(Ub.p + rc, o, 0.5 * (dk[F_P] + dn[F_P]));
+        sto(Ub.T + rc, o, 0.5 * (dk[F_T] + dn[F_T]));
+        sto(Ub.ur + rc, o, 0.5 * (dk[F_UR] + dn[F_UR]));
+        sto(Ub.ut + rt_, o, 0.5 * (dk[F_UT] + dn[F_UT]));
+        sto(Ub.uf + rf_, o, 0.5 * (dk[F_UF] + dn[F_UF]));
+        if (!P && k == g.np - 1) sto(Ub.uf + rf_, o + 8u, ubn);
+      }
       int *status = (int *)karg<DSW_AS1 int *>(p, offsetof(PassArgs, status));
       if (nonphys) status[ST_NONPHYS] = 1;  // plain vector stores
       // the sum of this point's residuals: non-finite iff one of them is
@@ -724,7 +745,7 @@ __global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_march(PassArgs, int
   __shared__ double lds[4 * RM_PL];
   KPtr kp = (KPtr)__builtin_amdgcn_kernarg_segment_ptr();
   if ((int)blockIdx.z < segs) {
-    residual_march<P, PT>(kp, lds, blockIdx.x, blockIdx.y, blockIdx.z, seg);
+    residual_march<P, PT, false>(kp, lds, blockIdx.x, blockIdx.y, blockIdx.z, seg);
   } else {
     const unsigned w = ((blockIdx.z - (unsigned)segs) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     const int npf = karg<int>(kp, offsetof(PassArgs, g) + offsetof(Geo, npf));
@@ -736,6 +757,21 @@ __global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_march(PassArgs, int
                                 (int)((w - q * nkb) * 64u + threadIdx.x));
   }
 }
+// the public form: the midpoint formed on the way; the shell's points by a
+// launch that forms it at every load
+template <bool P>
+__global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_march_mid(PassArgs, int seg) {
+  __shared__ double lds[4 * RM_PL];
+  residual_march<P, false, true>((KPtr)__builtin_amdgcn_kernarg_segment_ptr(), lds, blockIdx.x, blockIdx.y, blockIdx.z,
+                                 seg);
+}
+__global__ void __launch_bounds__(64) k_residual_mid_shell(Geo g, Mat m, SrcMid s, Diff dU, double tau, Fields R,
+                                                           Fields Ub, int *status) {
+  const unsigned nk = (unsigned)(g.npf + 63) / 64u, q = blockIdx.x / nk;
+  int i, j;
+  res_pair(g, q, true, i, j);
+  residual_point<SrcMid, true>(g, m, s, dU, tau, R, Ub, status, i, j, (int)((blockIdx.x - q * nk) * 64u + threadIdx.x));
+}
 // a batch of grids: workgroups in one dimension, phi block fastest, then theta
 template <bool P>
 __global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_marchB(Batch bt) {
@@ -745,7 +781,7 @@ __global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_marchB(Batch bt) {
   const Geo g = kgeo(kp, offsetof(PassArgs, g));
   const int w = (int)(blockIdx.x - bt.woff[mb]), nk = (g.np + 63) / 64, nj = (g.nt - 2 + RM_J - 1) / RM_J;
   const int r = w / nk;
-  residual_march<P, false>(kp, lds, w - r * nk, r % nj, r / nj, march_seg(g));
+  residual_march<P, false, false>(kp, lds, w - r * nk, r % nj, r / nj, march_seg(g));
 }
 
 // Workgroups of the shell up to which it joins the interior's launch, where
@@ -842,29 +878,45 @@ static void set5(const double **dst, const Fields &f) {
   dst[F_P] = f.p; dst[F_UR] = f.ur; dst[F_UT] = f.ut; dst[F_UF] = f.uf; dst[F_T] = f.T;
 }
 
-// From this many interior workgroups (of 64 points) on, the public residual
-// writes the midpoint first and reads it back.  Forming it at every neighbour
-// read instead doubles the loads of the interior kernel, which then needs
-// more than 256 registers (one wave per SIMD; 2.06 ms on the 512 x 256 x 128
-// sphere).  Measured, one launch for every point against midpoint + interior +
-// shell: 512 x 256 x 128 sphere 2.82 -> 1.36 ms, 1024 x 512 x 64 sector 5.83 ->
-// 2.93 ms, 256 x 128 x 64 sector 0.364 -> 0.198 ms; on 32 x 32 x 16 the one
-// launch wins (15 against 23 us).
+// The public residual of a grid whose interior is walked forms the midpoint as
+// the planes are loaded: 1024 x 512 x 64 sector 1.79 ms, against 1.97 with a
+// pass that writes the midpoint first and 5.83 with it formed at every load.
+// Else (small grids, and those beyond the walk's 32-bit offsets), from this
+// many interior workgroups of 64 points on, it writes the midpoint first and
+// reads it back: 256 x 128 x 64 sector 0.364 -> 0.198 ms; on 32 x 32 x 16 the
+// one launch wins (15 against 23 us).
 constexpr unsigned RES_MID_SPLIT = 3000;
 
 void launch_residual(const Geo &g, const Mat &m, const Fields &Un, const Fields &Uk, double tau,
                      const Fields &R, const Fields &Ub, const long *cnt, int *status, hipStream_t st) {
   const unsigned th = 64;
+  PassArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.g = g;
+  a.m = m;
+  set5(a.u.a, Ub);
+  set5(a.d.n, Un);
+  set5(a.d.k, Uk);
+  a.tau = tau;
+  a.R = R;
+  a.o.ub = Ub;
+  a.status = status;
+  SrcMid s;
+  set5(s.n, Un);
+  set5(s.k, Uk);
+  if (residual_marches(g)) {
+    const int seg = march_seg(g);
+    const dim3 gr((unsigned)((g.np + 63) / 64), (unsigned)((g.nt - 2 + RM_J - 1) / RM_J),
+                  (unsigned)((g.nr - 2 + seg - 1) / seg)), bl(64, RM_J);
+    if (g.periodic) hipLaunchKernelGGL(k_residual_march_mid<true>, gr, bl, 0, st, a, seg);
+    else hipLaunchKernelGGL(k_residual_march_mid<false>, gr, bl, 0, st, a, seg);
+    const unsigned nsh = (unsigned)((g.npf + 63) / 64) * res_shell_pairs(g);
+    hipLaunchKernelGGL(k_residual_mid_shell, dim3(nsh), dim3(64), 0, st, g, m, s, a.d, tau, R, Ub, status);
+    return;
+  }
   if (res_interior_blocks(g, (int)th) < RES_MID_SPLIT) {
-    SrcMid s;
-    set5(s.n, Un);
-    set5(s.k, Uk);
-    Diff d;
-    set5(d.n, Un);
-    set5(d.k, Uk);
-    d.same = 0;
     const dim3 grid((unsigned)res_nk(g, (int)th), g.nt + 1, g.nr + 1);
-    hipLaunchKernelGGL(k_residual_mid, grid, dim3(th), 0, st, g, m, s, d, tau, R, Ub, status);
+    hipLaunchKernelGGL(k_residual_mid, grid, dim3(th), 0, st, g, m, s, a.d, tau, R, Ub, status);
     return;
   }
   MidArrays w;
@@ -879,19 +931,8 @@ void launch_residual(const Geo &g, const Mat &m, const Fields &Un, const Fields 
     w.pairs[f + 1] = w.pairs[f] + (cnt[f] + 1) / 2;
   }
   hipLaunchKernelGGL(k_midpoint, dim3((unsigned)((w.pairs[5] + 255) / 256)), dim3(256), 0, st, w);
-  PassArgs a;
-  std::memset(&a, 0, sizeof(a));
-  a.g = g;
-  a.m = m;
-  set5(a.u.a, Ub);
-  set5(a.d.n, Un);
-  set5(a.d.k, Uk);
-  a.tau = tau;
-  a.R = R;
-  a.status = status;
   const Batch none{nullptr, nullptr, 0};
-  if (residual_marches(g)) march_one(g.periodic != 0, false, a, st);
-  else if (res_interior_blocks(g, (int)th)) launch_residual_in_pass(g.periodic != 0, a, none, 0, th, st);
+  if (res_interior_blocks(g, (int)th)) launch_residual_in_pass(g.periodic != 0, a, none, 0, th, st);
   else launch_residual_pass(a, none, res_general_blocks(g, (int)th, false), th, st);
 }
 
