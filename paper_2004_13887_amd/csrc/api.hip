@@ -502,13 +502,13 @@ static unsigned kind_threads(int kind, const Geo &g, const Cfg &c) {
   case PK_SW0:
   case PK_SW0T:
   case PK_SW0B:
-  case PK_SW0S:
   case PK_SW0P: return (unsigned)c.sweep_bs[0];
+  case PK_SW0S: return rt_scalar_threads(g, 0, (unsigned)c.sweep_bs[0]);
   case PK_SW1:
   case PK_SW1T:
   case PK_SW1B:
-  case PK_SW1S:
   case PK_SW1P: return (unsigned)c.sweep_bs[1];
+  case PK_SW1S: return rt_scalar_threads(g, 1, (unsigned)c.sweep_bs[1]);
   case PK_SW2_PART: return phi_part_threads(g, c.phi_pm);
   case PK_SW2_CP:
   case PK_SW2_CN: return phi_fast_threads(g, c.phi_pm);

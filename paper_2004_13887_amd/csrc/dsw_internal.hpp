@@ -176,6 +176,7 @@ void launch_rt_T(int d, const PassArgs &a, unsigned threads, hipStream_t st);
 bool rt_scalar_supported(const Geo &g, int d, unsigned bs);
 unsigned rt_scalar_blocks(const Geo &g, int d, unsigned bs);
 size_t rt_scalar_lds(unsigned bs);
+unsigned rt_scalar_threads(const Geo &g, int d, unsigned bs);  // of a launch of scalar lines alone
 void launch_rt_scalar_pass(int d, const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads,
                            hipStream_t st);
 // the r / theta solver a grid takes by default (4 partitioned, 0 two-ended)

@@ -517,7 +517,7 @@ __device__ __forceinline__ void rt_body(const PassArgs &a, unsigned w, double *l
 // neighbouring lines of neighbouring workgroups (which share cache lines and
 // neighbour cells) meet in one L2.
 template <int D, int PM, int PART, bool B>
-__global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_part(PassArgs a, Batch bt) {
+__global__ void __launch_bounds__(PART == 1 ? 512 : 256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_part(PassArgs a, Batch bt) {
   extern __shared__ double lds[];
   if constexpr (B) {
     const int mb = batch_member(bt, blockIdx.x);
@@ -537,14 +537,14 @@ __global__ void __launch_bounds__(256) DSW_OCC(2) k_rt_partF(PassArgs a) {
 
 // perturbation-pressure form, one grid
 template <int D, int PM, int PART>
-__global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_partP(PassArgs a) {
+__global__ void __launch_bounds__(PART == 1 ? 512 : 256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_partP(PassArgs a) {
   extern __shared__ double lds[];
   rt_body<D, PM, PART, false, false, true>(a, xcd_contiguous(blockIdx.x, gridDim.x), lds);
 }
 
 // transposed systems (adjoint), one grid
 template <int D, int PM, int PART>
-__global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_partT(PassArgs a) {
+__global__ void __launch_bounds__(PART == 1 ? 512 : 256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_partT(PassArgs a) {
   extern __shared__ double lds[];
   rt_body<D, PM, PART, false, true>(a, xcd_contiguous(blockIdx.x, gridDim.x), lds);
 }
@@ -555,6 +555,16 @@ __global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_partT(Pas
 // sector (4084 workgroups): r 0.22 -> 0.16 ms, theta 0.28 -> 0.19 ms; the
 // same from 256 to 1024.
 constexpr unsigned RT_SPLIT_WGS = 1024;
+
+// Threads per workgroup of a launch of scalar lines: lines of more than 16
+// chunks (128 rows) take 512 where the blocks take 256, so that a row's loads
+// cover 16 neighbouring lines (128 bytes) up to 256 rows.  Measured, theta
+// scalar lines with 256, 512: 180 rows 57, 55 us, 200 rows 83, 71, 256 rows 312,
+// 279, 512 rows 875, 679.  (The block lines keep 256: at 512 one workgroup fits
+// a CU and nothing runs beside its barriers, 256 rows 699, 899 us.)
+unsigned rt_scalar_threads(const Geo &g, int d, unsigned bs) {
+  return bs == 256u && rt_chunks<RT_PMS>(families(g, d).n) > 16 ? 512u : bs;
+}
 
 bool rt_part_supported(const Geo &g, int d, unsigned bs, int pm) {
   const Families F = families(g, d);
@@ -586,9 +596,10 @@ static void launch_rt_d(const PassArgs &a, const Batch &b, unsigned blocks, unsi
     hipLaunchKernelGGL((k_rt_part<D, PM, 2, false>), dim3(blocks), dim3(threads), lds, st, a, b);
     return;
   }
-  const unsigned nbw = rt_block_wgs(a.g, D, threads, PM), nsw = rt_scalar_wgs(a.g, D, threads);
-  hipLaunchKernelGGL((k_rt_part<D, PM, 0, false>), dim3(nbw), dim3(threads), lds, st, a, b);
-  hipLaunchKernelGGL((k_rt_part<D, PM, 1, false>), dim3(nsw), dim3(threads), lds_s, st, a, b);
+  const unsigned ts = rt_scalar_threads(a.g, D, threads);
+  hipLaunchKernelGGL((k_rt_part<D, PM, 0, false>), dim3(rt_block_wgs(a.g, D, threads, PM)), dim3(threads), lds, st, a, b);
+  hipLaunchKernelGGL((k_rt_part<D, PM, 1, false>), dim3(rt_scalar_wgs(a.g, D, ts)), dim3(ts), rt_scalar_lds(ts), st, a,
+                     b);
 }
 
 void launch_rt_pass(int d, int pm, const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads,
@@ -600,26 +611,28 @@ void launch_rt_pass(int d, int pm, const PassArgs &a, const Batch &b, unsigned b
 
 template <int D, int PM>
 static void launch_rt_T_d(const PassArgs &a, unsigned threads, hipStream_t st) {
-  const size_t lds = rt_part_lds(threads), lds_s = sizeof(double) * 4 * (size_t)threads;
+  const size_t lds = rt_part_lds(threads);
   const unsigned nbw = rt_block_wgs(a.g, D, threads, PM), nsw = rt_scalar_wgs(a.g, D, threads);
   if (nbw + nsw < RT_SPLIT_WGS) {
     hipLaunchKernelGGL((k_rt_partT<D, PM, 2>), dim3(nbw + nsw), dim3(threads), lds, st, a);
     return;
   }
   hipLaunchKernelGGL((k_rt_partT<D, PM, 0>), dim3(nbw), dim3(threads), lds, st, a);
-  hipLaunchKernelGGL((k_rt_partT<D, PM, 1>), dim3(nsw), dim3(threads), lds_s, st, a);
+  const unsigned ts = rt_scalar_threads(a.g, D, threads);
+  hipLaunchKernelGGL((k_rt_partT<D, PM, 1>), dim3(rt_scalar_wgs(a.g, D, ts)), dim3(ts), rt_scalar_lds(ts), st, a);
 }
 
 template <int D, int PM>
 static void launch_rt_pert_d(const PassArgs &a, unsigned threads, hipStream_t st) {
-  const size_t lds = rt_part_lds(threads), lds_s = sizeof(double) * 4 * (size_t)threads;
+  const size_t lds = rt_part_lds(threads);
   const unsigned nbw = rt_block_wgs(a.g, D, threads, PM), nsw = rt_scalar_wgs(a.g, D, threads);
   if (nbw + nsw < RT_SPLIT_WGS) {
     hipLaunchKernelGGL((k_rt_partP<D, PM, 2>), dim3(nbw + nsw), dim3(threads), lds, st, a);
     return;
   }
   hipLaunchKernelGGL((k_rt_partP<D, PM, 0>), dim3(nbw), dim3(threads), lds, st, a);
-  hipLaunchKernelGGL((k_rt_partP<D, PM, 1>), dim3(nsw), dim3(threads), lds_s, st, a);
+  const unsigned ts = rt_scalar_threads(a.g, D, threads);
+  hipLaunchKernelGGL((k_rt_partP<D, PM, 1>), dim3(rt_scalar_wgs(a.g, D, ts)), dim3(ts), rt_scalar_lds(ts), st, a);
 }
 
 void launch_rt_pert(int d, const PassArgs &a, unsigned threads, hipStream_t st) {
@@ -654,7 +667,7 @@ size_t rt_scalar_lds(unsigned bs) { return sizeof(double) * 4 * (size_t)bs; }
 // the two-ended solve's scratch traffic drops by a sixth: theta on the
 // 512 x 256 x 128 sphere 1.53 -> 1.43 ms.
 template <int D, bool B>
-__global__ void __launch_bounds__(256) k_rt_scal(PassArgs a, Batch bt) {
+__global__ void __launch_bounds__(512) k_rt_scal(PassArgs a, Batch bt) {
   extern __shared__ double lds[];
   if constexpr (B) {
     const int mb = batch_member(bt, blockIdx.x);
@@ -696,7 +709,8 @@ void launch_rt_forced(int d, int pm, const PassArgs &a, unsigned threads, hipStr
     hipLaunchKernelGGL((k_rt_partF<4, 2>), dim3(nbw + nsw), dim3(threads), rt_part_lds(threads), st, a);
   } else {
     hipLaunchKernelGGL((k_rt_partF<4, 0>), dim3(nbw), dim3(threads), rt_part_lds(threads), st, a);
-    launch_rt_scalar_pass(1, a, none, nsw, threads, st);
+    const unsigned ts = rt_scalar_threads(a.g, 1, threads);
+    launch_rt_scalar_pass(1, a, none, rt_scalar_wgs(a.g, 1, ts), ts, st);
   }
 }
 
