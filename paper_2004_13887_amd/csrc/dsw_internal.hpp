@@ -146,13 +146,14 @@ enum PassKind { PK_BND = 0, PK_RES = 1, PK_SW0 = 2, PK_SW1 = 3, PK_SW2_LINE = 4,
                 PK_SW0B = 12, PK_SW1B = 13, PK_SW0S = 14, PK_SW1S = 15, PK_NONE = 16,
                 PK_SW2_CP = 17, PK_SW2_CN = 18, PK_RES_MN = 19, PK_RES_MP = 20 };
 // PK_RES_IN / PK_RES_INP: the interior of the residual (bounded / periodic
-// phi); PK_RES_MN / PK_RES_MP: the same by the kernel for large grids.
+// phi; one grid: the shell as well, and PK_RES launches nothing); PK_RES_MN /
+// PK_RES_MP: the same by the kernel for large grids.
 // PK_SW2_CP / PK_SW2_CN: the partitioned phi pass with 32-bit byte offsets
 // (periodic / bounded phi); PK_SW2_PART: the same on grids beyond them.
 
 // forced split step (source term, wall velocities, Dirichlet data at the new
-// time level): one grid, the general residual over every point, the
-// two-ended r and theta sweeps and the partitioned phi solver
+// time level): one grid; the same solvers as the plain step, their theta block
+// lines and phi lines with wall terms
 void launch_bnd_forced(const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st);
 void launch_residual_forced(const PassArgs &a, unsigned threads, hipStream_t st);
 void launch_sweep2_forced(int d, const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st);

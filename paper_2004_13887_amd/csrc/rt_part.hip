@@ -501,12 +501,12 @@ __device__ __forceinline__ void rt_body(const PassArgs &a, unsigned w, double *l
   if (w < nbw) {
     if constexpr (PART != 1) {
       const unsigned L = bs / (unsigned)rt_chunks<PM>(families(g, D).n);
-      rt_block_lines<D, PM, TR, W, PT>(a, w * L, lds);
+      rt_block_lines<D, PM, TR, W, PT>(a, (COMB ? xcd_contiguous(w, nbw) : w) * L, lds);
     }
     return;
   }
   if constexpr (PART != 0) {
-    const unsigned w2 = w - nbw;
+    const unsigned w2 = COMB ? xcd_contiguous(w - nbw, rt_scalar_wgs(g, D, bs)) : w - nbw;
     const unsigned L = bs / (unsigned)rt_chunks<RT_PMS>(families(g, D).n);
     const unsigned nwa = rt_scalar_wgs_a(g, D, bs);
     rt_scalar_lines<D, RT_PMS, TR, PT>(a, w2 < nwa ? 0 : 1, (w2 < nwa ? w2 : w2 - nwa) * L, lds);
@@ -515,7 +515,9 @@ __device__ __forceinline__ void rt_body(const PassArgs &a, unsigned w, double *l
 
 // Workgroups are numbered XCD-contiguously within a launch, so that the
 // neighbouring lines of neighbouring workgroups (which share cache lines and
-// neighbour cells) meet in one L2.
+// neighbour cells) meet in one L2; in a batch within each member's block lines
+// and within its scalar lines (over the whole launch the XCDs would get unequal
+// shares of the two).
 template <int D, int PM, int PART, bool B>
 __global__ void __launch_bounds__(PART == 1 ? 512 : 256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_part(PassArgs a, Batch bt) {
   extern __shared__ double lds[];
@@ -671,7 +673,8 @@ __global__ void __launch_bounds__(512) k_rt_scal(PassArgs a, Batch bt) {
   extern __shared__ double lds[];
   if constexpr (B) {
     const int mb = batch_member(bt, blockIdx.x);
-    rt_body<D, 4, 1>(batch_args(bt, mb), blockIdx.x - bt.woff[mb], lds);
+    const unsigned n = bt.woff[mb + 1] - bt.woff[mb];
+    rt_body<D, 4, 1>(batch_args(bt, mb), xcd_contiguous(blockIdx.x - bt.woff[mb], n), lds);
   } else {
     rt_body<D, 4, 1>(a, xcd_contiguous(blockIdx.x, gridDim.x), lds);
   }
