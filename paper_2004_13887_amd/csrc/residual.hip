@@ -482,7 +482,9 @@ __global__ void __launch_bounds__(256) k_residual_one_pert(PassArgs) {
   residual_both<SrcPert<SrcOneT<true, P>>, false, true>((KPtr)__builtin_amdgcn_kernarg_segment_ptr());
 }
 // grids beyond the interior launch's 32-bit indices: every point by the general rules
-__global__ void __launch_bounds__(256) k_residual_forced(PassArgs a) { residual_body<true>(a, blockIdx.x, false); }
+__global__ void __launch_bounds__(256) k_residual_forced(PassArgs a, bool shell) {
+  residual_body<true>(a, blockIdx.x, shell);
+}
 __global__ void __launch_bounds__(256) k_residual_pert(PassArgs a, bool shell) {
   residual_body<false, true>(a, blockIdx.x, shell);
 }
@@ -500,19 +502,20 @@ static bool one_fits(const Geo &g, unsigned threads) {
   return d.y <= 65535u && d.z <= 65535u;
 }
 
+static void march_one(bool periodic, bool pert, bool forced, const PassArgs &a, hipStream_t st);
+
 void launch_residual_forced(const PassArgs &a, unsigned threads, hipStream_t st) {
   const dim3 bl(threads);
-  if (!one_fits(a.g, threads))
-    hipLaunchKernelGGL(k_residual_forced, dim3(res_general_blocks(a.g, (int)threads, false)), bl, 0, st, a);
+  if (residual_marches(a.g)) march_one(a.g.periodic != 0, false, true, a, st);
+  else if (!one_fits(a.g, threads))
+    hipLaunchKernelGGL(k_residual_forced, dim3(res_general_blocks(a.g, (int)threads, false)), bl, 0, st, a, false);
   else if (a.g.periodic) hipLaunchKernelGGL(k_residual_one_forced<true>, one_grid(a.g, threads), bl, 0, st, a);
   else hipLaunchKernelGGL(k_residual_one_forced<false>, one_grid(a.g, threads), bl, 0, st, a);
 }
 
-static void march_one(bool periodic, bool pert, const PassArgs &a, hipStream_t st);
-
 void launch_residual_pert(const PassArgs &a, unsigned threads, hipStream_t st) {
   const dim3 bl(threads);
-  if (residual_marches(a.g)) march_one(a.g.periodic != 0, true, a, st);
+  if (residual_marches(a.g)) march_one(a.g.periodic != 0, true, false, a, st);
   else if (!one_fits(a.g, threads))
     hipLaunchKernelGGL(k_residual_pert, dim3(res_general_blocks(a.g, (int)threads, false)), bl, 0, st, a, false);
   else if (a.g.periodic) hipLaunchKernelGGL(k_residual_one_pert<true>, one_grid(a.g, threads), bl, 0, st, a);
@@ -562,8 +565,9 @@ struct SrcWin {
 
 // kp: the PassArgs of the grid; (bx, by, bz): phi block, theta tile, r segment.
 // MID: the state is the midpoint of the difference's two iterates (a.d), formed
-// as its planes are loaded and written to a.o.ub as well.
-template <bool P, bool PT, bool MID>
+// as its planes are loaded and written to a.o.ub as well.  W: a forced pass; the
+// ghost columns take the phi walls' velocities, the residual the source.
+template <bool P, bool PT, bool MID, bool W = false>
 __device__ __forceinline__ void residual_march(KPtr kp, double *lds, int bx, int by, int bz, int seg) {
   using SI = std::conditional_t<PT, SrcPert<SrcWin<P>>, SrcWin<P>>;
   constexpr unsigned GEO = offsetof(PassArgs, g);
@@ -574,7 +578,8 @@ __device__ __forceinline__ void residual_march(KPtr kp, double *lds, int bx, int
   // the two window entries this thread stages: byte offsets within a plane of
   // the centres (and r faces), theta faces, phi faces
   unsigned oc[2], ot[2], of[2];
-  bool flip[2], on;
+  bool flip[2], hi[2], on;
+  unsigned ow[2], owt[2]; // W: index of the entry's row in a plane of the walls' values
   {
     const Geo g = kgeo(kp, GEO);
     on = j < g.nt - 1 && k < g.np;
@@ -588,10 +593,13 @@ __device__ __forceinline__ void residual_march(KPtr kp, double *lds, int bx, int
       ot[q] = (unsigned)(jt * g.np + kc) * 8u;
       of[q] = (unsigned)(jc * g.npf + kf) * 8u;
       flip[q] = !P && kc != kr; // no slip at a phi wall
+      hi[q] = kr > 0;
+      ow[q] = (unsigned)jc * 8u;
+      owt[q] = (unsigned)jt * 8u;
     }
   }
   const bool two = tid + 256 < RM_FS;
-  double st[2][5], sn[2][5];
+  double st[2][5], sn[2][5], wr[2], wt[2];
   const auto stage = [&](int p) {
     KPtr q = kp;
     asm volatile("" : "+s"(q), "+s"(p));
@@ -617,6 +625,25 @@ __device__ __forceinline__ void residual_march(KPtr kp, double *lds, int bx, int
         for (int e = 0; e < 2; e++) st[e][f] = ldo(bu, o[e]);
       }
     }
+    if constexpr (W && !P) {
+      // an absent wall is zero; its pointer stands for an array at least as long
+      constexpr unsigned w = offsetof(PassArgs, wall);
+      const auto at = [&](unsigned off, int any) {
+        const double *x = karr(q, w + off);
+        return x ? x : (const double *)karr(q, offsetof(PassArgs, u) + 8 * any);
+      };
+      const bool has[4] = {karr(q, w + offsetof(Wall, ur_p1)) != nullptr, karr(q, w + offsetof(Wall, ur_p2)) != nullptr,
+                           karr(q, w + offsetof(Wall, ut_p1)) != nullptr, karr(q, w + offsetof(Wall, ut_p2)) != nullptr};
+      const double *r1 = at(offsetof(Wall, ur_p1), F_UR) + (long)p * nt, *r2 = at(offsetof(Wall, ur_p2), F_UR) + (long)p * nt;
+      const double *t1 = at(offsetof(Wall, ut_p1), F_UT) + (long)p * (nt + 1);
+      const double *t2 = at(offsetof(Wall, ut_p2), F_UT) + (long)p * (nt + 1);
+#pragma unroll
+      for (int e = 0; e < 2; e++) {
+        const double a1 = ldo(r1, ow[e]), a2 = ldo(r2, ow[e]), b1 = ldo(t1, owt[e]), b2 = ldo(t2, owt[e]);
+        wr[e] = hi[e] ? (has[1] ? a2 : 0.0) : (has[0] ? a1 : 0.0);
+        wt[e] = hi[e] ? (has[3] ? b2 : 0.0) : (has[2] ? b1 : 0.0);
+      }
+    }
   };
   const auto commit = [&](int slot) {
 #pragma unroll
@@ -626,7 +653,8 @@ __device__ __forceinline__ void residual_march(KPtr kp, double *lds, int bx, int
 #pragma unroll
       for (int f = 0; f < 5; f++) {
         const double v = MID ? 0.5 * (st[q][f] + sn[q][f]) : st[q][f];
-        w[f * RM_FS] = (f == F_UR || f == F_UT) && flip[q] ? -v : v;
+        const double gh = W && !P ? 2.0 * (f == F_UR ? wr[q] : wt[q]) - v : -v;
+        w[f * RM_FS] = (f == F_UR || f == F_UT) && flip[q] ? gh : v;
       }
     }
   };
@@ -677,10 +705,18 @@ __device__ __forceinline__ void residual_march(KPtr kp, double *lds, int bx, int
     if constexpr (PT) pfull += s.pref[i];
     const bool nonphys = s.at(F_T, i, jw, k) <= 0.0 || pfull + m.pinf <= 0.0;
     double FT;
-    const double Fp = F_p_T(g, m, s, i, jw, k, &FT);
-    const double Fr = F_ur(g, m, s, i, jw, k);
-    const double Ft = F_ut(g, m, s, i, jw, k);
-    const double Ff = F_uf(g, m, s, i, jw, k);
+    double Fp = F_p_T(g, m, s, i, jw, k, &FT);
+    double Fr = F_ur(g, m, s, i, jw, k);
+    double Ft = F_ut(g, m, s, i, jw, k);
+    double Ff = F_uf(g, m, s, i, jw, k);
+    if constexpr (W) {
+      const Fields q = kfields(p, offsetof(PassArgs, fsrc));
+      if (q.p) Fp -= ldo(q.p + rc, o);
+      if (q.T) FT -= ldo(q.T + rc, o);
+      if (q.ur) Fr -= ldo(q.ur + rc, o);
+      if (q.ut) Ft -= ldo(q.ut + rt_, o);
+      if (q.uf) Ff -= ldo(q.uf + rf_, o);
+    }
     double rp = -(dk[F_P] - dn[F_P]) - tau * Fp;
     double rT = -(dk[F_T] - dn[F_T]) - tau * FT;
     double rr = -(dk[F_UR] - dn[F_UR]) - tau * Fr;
@@ -740,12 +776,12 @@ __host__ __device__ inline int march_seg(const Geo &g) {
 
 // One grid: the shell's workgroups (64 phi indices of a pair, a wave per kind
 // of row) behind the last segment.
-template <bool P, bool PT>
+template <bool P, bool PT, bool W = false>
 __global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_march(PassArgs, int seg, int segs) {
   __shared__ double lds[4 * RM_PL];
   KPtr kp = (KPtr)__builtin_amdgcn_kernarg_segment_ptr();
   if ((int)blockIdx.z < segs) {
-    residual_march<P, PT, false>(kp, lds, blockIdx.x, blockIdx.y, blockIdx.z, seg);
+    residual_march<P, PT, false, W>(kp, lds, blockIdx.x, blockIdx.y, blockIdx.z, seg);
   } else {
     const unsigned w = ((blockIdx.z - (unsigned)segs) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     const int npf = karg<int>(kp, offsetof(PassArgs, g) + offsetof(Geo, npf));
@@ -753,7 +789,7 @@ __global__ void __launch_bounds__(256) DSW_OCC(2) k_residual_march(PassArgs, int
     const unsigned pairs = 3u * (unsigned)(karg<int>(kp, offsetof(PassArgs, g) + offsetof(Geo, nt)) + 1) +
                            3u * (unsigned)(karg<int>(kp, offsetof(PassArgs, g) + offsetof(Geo, nr)) - 2);
     if (q < pairs)
-      residual_shell<false, PT>(kp, q, __builtin_amdgcn_readfirstlane((int)threadIdx.y),
+      residual_shell<W, PT>(kp, q, __builtin_amdgcn_readfirstlane((int)threadIdx.y),
                                 (int)((w - q * nkb) * 64u + threadIdx.x));
   }
 }
@@ -806,7 +842,8 @@ static dim3 march_grid(const Geo &g, int seg) {
 // 17.4 against 14.5 on 128 x 64 x 32 (480), 40 against 34 on 150 x 101 x 37,
 // 162 against 102 on 360 x 180 x 40, 262 against 161 on 200 x 200 x 100, 900
 // against 506 on 512 x 256 x 128 (the perturbation form of 100 m columns on
-// 200 x 200 x 200: 620 against 329).
+// 200 x 200 x 200: 620 against 329; forced steps of two iterations 731 against
+// 672 us on 256 x 128 x 32, 2.46 against 2.23 ms on 240 x 256 x 64).
 bool residual_marches(const Geo &g) {
   if (!off32_ok(g) || g.nr < 3 || g.nt < 3 || march_wgs(g, 2) < 450u) return false;
   const dim3 d = march_grid(g, march_seg(g));
@@ -814,25 +851,28 @@ bool residual_marches(const Geo &g) {
 }
 unsigned residual_march_blocks(const Geo &g) { return march_wgs(g, march_seg(g)); }
 
-static void march_one(bool periodic, bool pert, const PassArgs &a, hipStream_t st) {
+static void march_one(bool periodic, bool pert, bool forced, const PassArgs &a, hipStream_t st) {
   const int seg = march_seg(a.g), segs = (a.g.nr - 2 + seg - 1) / seg;
   const dim3 gr = march_grid(a.g, seg), bl(64, RM_J);
   if (periodic) {
-    if (pert) hipLaunchKernelGGL((k_residual_march<true, true>), gr, bl, 0, st, a, seg, segs);
+    if (forced) hipLaunchKernelGGL((k_residual_march<true, false, true>), gr, bl, 0, st, a, seg, segs);
+    else if (pert) hipLaunchKernelGGL((k_residual_march<true, true>), gr, bl, 0, st, a, seg, segs);
     else hipLaunchKernelGGL((k_residual_march<true, false>), gr, bl, 0, st, a, seg, segs);
   } else {
-    if (pert) hipLaunchKernelGGL((k_residual_march<false, true>), gr, bl, 0, st, a, seg, segs);
+    if (forced) hipLaunchKernelGGL((k_residual_march<false, false, true>), gr, bl, 0, st, a, seg, segs);
+    else if (pert) hipLaunchKernelGGL((k_residual_march<false, true>), gr, bl, 0, st, a, seg, segs);
     else hipLaunchKernelGGL((k_residual_march<false, false>), gr, bl, 0, st, a, seg, segs);
   }
   if (march_shell(a.g)) return;
   const dim3 sb(64), sg(res_general_blocks(a.g, 64, true));
   const Batch none{nullptr, nullptr, 0};
-  if (pert) hipLaunchKernelGGL(k_residual_pert, sg, sb, 0, st, a, true);
+  if (forced) hipLaunchKernelGGL(k_residual_forced, sg, sb, 0, st, a, true);
+  else if (pert) hipLaunchKernelGGL(k_residual_pert, sg, sb, 0, st, a, true);
   else hipLaunchKernelGGL(k_residual<false>, sg, sb, 0, st, a, none, true);
 }
 
 void launch_residual_march(bool periodic, const PassArgs &a, const Batch &b, unsigned blocks, hipStream_t st) {
-  if (!b.tab) march_one(periodic, false, a, st);
+  if (!b.tab) march_one(periodic, false, false, a, st);
   else if (periodic) hipLaunchKernelGGL(k_residual_marchB<true>, dim3(blocks), dim3(64, RM_J), 0, st, b);
   else hipLaunchKernelGGL(k_residual_marchB<false>, dim3(blocks), dim3(64, RM_J), 0, st, b);
 }

@@ -80,3 +80,26 @@ def test_batch_is_bitwise_the_single_steps():
         torch.cuda.synchronize()
         g.get_status()
         assert all(torch.equal(o[k], one[k]) for k in o)
+
+
+@pytest.mark.parametrize("nr,nt,np_", [(19, 66, 260), (36, 129, 64), (4, 700, 129)])
+def test_forced_form(nr, nt, np_):
+    from helpers import random_wall
+    from paper_2004_13887_amd import dsw
+    w = _workload(nr, nt, np_, False, 1)
+    print(f"[march forced] {nr}x{nt}x{np_}", flush=True)
+    U0, tau = I.initial_state(w)
+    og, om = oracle.Grid(*w.grid.args()), oracle.Material(*w.material.astuple())
+    gg = dsw.Grid.from_spec(w.grid, w.material)
+    full, src = random_wall(w.grid, 721, scale=3.0), I.random_fields(w.grid, 722)
+    part = {k: v for k, v in full.items() if k in ("ur_p1", "ut_p2", "uf_r1")}  # the rest absent: zero
+    for wall in (full, part):
+        out = gg.empty()
+        ref = oracle.split_step(og, om, U0, tau, 1, wall0=wall, wall1=wall, src=src)
+        gg.split_step_forced(dsw.to_device(U0), out, tau, 1, src=dsw.to_device(src), wall0=dsw.to_device(wall),
+                             wall1=dsw.to_device(wall))
+        torch.cuda.synchronize()
+        gg.get_status()
+        h = dsw.to_host(out)
+        for k in h:
+            assert np.linalg.norm(h[k] - ref[k]) <= 1e-11 * np.linalg.norm(ref[k]), k
