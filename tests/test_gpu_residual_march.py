@@ -103,3 +103,36 @@ def test_forced_form(nr, nt, np_):
         h = dsw.to_host(out)
         for k in h:
             assert np.linalg.norm(h[k] - ref[k]) <= 1e-11 * np.linalg.norm(ref[k]), k
+
+
+@pytest.mark.parametrize("form", ["plain", "pert", "forced"])
+def test_more_rows_than_one_launch_numbers(form):
+    """a grid whose shell does not fit the interior's launch (its third
+    dimension holds 65535 workgroups): every point by the general rules"""
+    from helpers import random_wall
+    from paper_2004_13887_amd import dsw
+    w = _workload(6000, 3, 4, False, 1)
+    print(f"[rows] 6000x3x4 {form}", flush=True)
+    U0, tau = I.initial_state(w)
+    og, om = oracle.Grid(*w.grid.args()), oracle.Material(*w.material.astuple())
+    gg = dsw.Grid.from_spec(w.grid, w.material)
+    out = gg.empty()
+    if form == "plain":
+        ref = oracle.split_step(og, om, U0, tau, 1)
+        gg.split_step(dsw.to_device(U0), out, tau, 1)
+    elif form == "pert":
+        pbar, Tbar = I.reference_column(w.grid, w.material, I.T0)
+        U0["p"] = np.ascontiguousarray(U0["p"] - pbar[:, None, None] + I.random_fields(w.grid, 732)["p"])
+        ref = oracle.split_step_pert(og, om, U0, pbar, Tbar, tau, 1)
+        gg.set_reference(pbar, Tbar)
+        gg.split_step_pert(dsw.to_device(U0), out, tau, 1)
+    else:
+        wall, src = random_wall(w.grid, 733, scale=3.0), I.random_fields(w.grid, 734)
+        ref = oracle.split_step(og, om, U0, tau, 1, wall0=wall, wall1=wall, src=src)
+        gg.split_step_forced(dsw.to_device(U0), out, tau, 1, src=dsw.to_device(src), wall0=dsw.to_device(wall),
+                             wall1=dsw.to_device(wall))
+    torch.cuda.synchronize()
+    gg.get_status()
+    h = dsw.to_host(out)
+    for k in h:
+        assert np.linalg.norm(h[k] - ref[k]) <= 1e-11 * np.linalg.norm(ref[k]), k
