@@ -23,7 +23,7 @@ struct dsw_grid {
   Geo geo;
   Mat m;
   Cfg cfg{64, {256, 256}, 4, {-1, -1}}; // launch shapes
-  double *tables = nullptr; // rc | rf | sc | cc | sf | cf
+  double *tables = nullptr; // the row tables mr, mt (PassArgs), then those of geo
   Fields ub{}, ub2{}, r{}, x1{}, x2{}; // ub, ub2: midpoint states of consecutive iterations
   double *fields_mem = nullptr;
   Scratch sc{};
@@ -242,8 +242,6 @@ extern "C" int dsw_init_grid(const dsw_grid_desc *desc, const dsw_material *mat,
   g.pole_lo = pole_lo; g.pole_hi = pole_hi;
   g.dr = dr; g.dt = dt; g.dp = dp;
   g.idr = 1.0 / dr; g.idt = 1.0 / dt; g.idp = 1.0 / dp;
-  g.mr = G->tables;
-  g.mt = G->tables + 8 * (size_t)nr;
   double *t = G->tables + o_rc;
   const long o_rf = nr, o_sc = o_rf + nr1, o_cc = o_sc + nt, o_sf = o_cc + nt, o_cf = o_sf + nt1,
              o_irc = o_cf + nt1, o_irf = o_irc + nr, o_isc = o_irf + nr1, o_ctc = o_isc + nt,
@@ -381,6 +379,8 @@ static PassArgs base_args(const dsw_grid *G) {
   a.scb = G->sc.blk;
   a.scs = G->sc.sca;
   a.status = G->status;
+  a.mr = G->tables;  // dsw_init_grid's layout
+  a.mt = G->tables + 8 * (size_t)G->geo.nr;
   return a;
 }
 

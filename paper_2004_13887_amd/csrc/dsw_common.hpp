@@ -28,11 +28,6 @@ struct Geo {
   const double *isc, *ctc; // 1/sin, cot at centres
   const double *isf, *ctf; // 1/sin, cot at faces (0 at a pole face: never used there)
   const double *scx;       // sin of theta at centres j = -1 .. nt (ghosts included), at scx[j + 1]
-  // what a block row takes from its r index (theta index), 8 doubles per row,
-  // 16-byte aligned: the divergence factors dp, dm of the faces after and
-  // before the cell, the viscous factors wp, w0, wm of the face after it, then
-  // 1/r (cot theta, 1/sin theta).  The theta factors lack the powers of 1/r.
-  const double *mr, *mt;
 };
 
 struct Mat {

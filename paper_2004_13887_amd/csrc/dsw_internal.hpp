@@ -56,6 +56,15 @@ struct Scratch {
 // not use are left zero.
 struct PassArgs {
   Geo g;
+  // r and theta sweeps: what a block row takes from its r index (theta index),
+  // 8 doubles per row, 16-byte aligned: the divergence factors dp, dm of the
+  // faces after and before the cell, the viscous factors wp, w0, wm of the face
+  // after it, then 1/r (cot theta, 1/sin theta).  The theta factors lack the
+  // powers of 1/r.  Here and not among the metric tables of Geo, which every
+  // kernel takes: as two more pointers of Geo they cost the public residual of
+  // a small grid 1 us (32 x 32 x 16 cells 18.4, 19.7 us; 324 more moves of
+  // scalars through vector lanes).
+  const double *mr, *mt;
   Mat m;
   SrcOne u;          // midpoint state: residual operand / sweep coefficients
   Diff d;            // residual: -(Uk - Un)

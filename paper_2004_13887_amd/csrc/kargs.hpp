@@ -44,7 +44,7 @@ __device__ __forceinline__ Geo kgeo(KPtr p, unsigned at) {
   DSW_KI(nr); DSW_KI(nt); DSW_KI(np); DSW_KI(npf); DSW_KI(periodic); DSW_KI(pole_lo); DSW_KI(pole_hi);
   DSW_KD(dr); DSW_KD(dt); DSW_KD(dp); DSW_KD(idr); DSW_KD(idt); DSW_KD(idp);
   DSW_KT(rc); DSW_KT(rf); DSW_KT(sc); DSW_KT(cc); DSW_KT(sf); DSW_KT(cf); DSW_KT(irc); DSW_KT(irf);
-  DSW_KT(isc); DSW_KT(ctc); DSW_KT(isf); DSW_KT(ctf); DSW_KT(scx); DSW_KT(mr); DSW_KT(mt);
+  DSW_KT(isc); DSW_KT(ctc); DSW_KT(isf); DSW_KT(ctf); DSW_KT(scx);
 #undef DSW_KI
 #undef DSW_KD
 #undef DSW_KT

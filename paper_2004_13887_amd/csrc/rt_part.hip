@@ -76,7 +76,7 @@ __device__ __forceinline__ void rt_block_lines(const PassArgs &a, unsigned line0
   const unsigned oF = 8u * (unsigned)(D == 0 ? pa * g.npf + k : pa * g.nt * g.npf + k);
   const int dF = 8 * (g.periodic && k == g.np - 1 ? 1 - g.np : 1);
   const double *u_r = a.u.a[F_UR], *u_t = a.u.a[F_UT], *u_f = a.u.a[F_UF];
-  const double *mt = D == 0 ? g.mr : g.mt;
+  const double *mt = D == 0 ? a.mr : a.mt;
   // per row what its coefficients need, P and T one cell further: held from
   // here to the row's elimination (row q at index q + X)
   constexpr int X = TR ? 1 : 0, NQ = PM + 2 * X;
@@ -347,7 +347,7 @@ __device__ __forceinline__ void rt_scalar_lines(const PassArgs &a, int fam, unsi
     sX = 8u * (D == 0 ? (unsigned)g.nt * g.npf : (unsigned)g.npf);
     X = a.o.x.uf; Rh = a.rhs.uf;
   }
-  const double *V = a.u.a[D == 0 ? F_UR : F_UT], *mt = D == 0 ? g.mr : g.mt;
+  const double *V = a.u.a[D == 0 ? F_UR : F_UT], *mt = D == 0 ? a.mr : a.mt;
   const double irr = D == 0 ? 1.0 : (fam == 0 ? g.irf[pa] : g.irc[pa]);
   const double hh = D == 0 ? g.idr : irr * g.idt, hv = 0.125 * hs * hh, hn = hs * m.mu * 2.0 * m.Rg * hh * irr;
   double sglo = -1.0, sghi = -1.0;
