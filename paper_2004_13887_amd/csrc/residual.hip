@@ -1005,28 +1005,71 @@ void launch_residual_in_pass(bool periodic, const PassArgs &a, const Batch &b, u
 // grid.  Non-negative doubles order as their bit patterns, so the maxima are
 // unsigned 64-bit atomic maxima (vector atomics) into out[0], out[1].
 //
-// A workgroup walks the (r, theta) rows in turn, its lanes the phi cells, so
-// that the spacings are formed once per row and no flat index is taken apart;
-// the acoustic number of a row is that of its largest T, with one square root
-// and the spacings' reciprocals at the row's end; and a workgroup issues one
-// pair of atomics.  Bound by the reads of u_r, u_theta, u_phi and T.  A flat
-// index per cell taken apart by 64-bit divisions, a square root and six
-// divisions per cell and a pair of atomics per wave took 386 us on the
-// 200 x 200 x 100 sector, this about 60 us.
-__global__ void __launch_bounds__(256) k_courant(Geo g, Mat m, Fields U, double tau, unsigned long long *out) {
+// A wave takes a piece of an (r, theta) row at a time, its lanes the phi cells,
+// so that the spacings are formed once per piece and no flat index is taken
+// apart; the acoustic number of a lane's cells is that of their largest T, with
+// one square root and the spacings' reciprocals at the piece's end; and a
+// workgroup issues one pair of atomics.  Bound by the reads of u_r, u_theta,
+// u_phi and T.  A flat index per cell taken apart by 64-bit divisions, a square
+// root and six divisions per cell and a pair of atomics per wave took 386 us on
+// the 200 x 200 x 100 sector, this about 60 us (30 of them the call's launches and
+// copy).  Few long rows are cut into pieces of about 256 cells, up to COUR_CUT of
+// them: 3 x 3 x 60000 cells as 9 waves 476 us, flat 221, cut 36; but cut into 8192
+// pieces, 40 x 40 x 1000 cells take 54 us for their atomics, whole rows 43.
+// PACK: rows of up to half a wave, several to a wave, w lanes (a power of two)
+// to a row: 64 x 128 rows of 3 cells, a wave each 53 us, flat 38, packed 31; of
+// 32 cells 52, 122, 41.
+struct CourShape {
+  int w, seg, len, items;  // lanes per row; pieces per row, cells per piece; pieces of work of a wave
+};
+constexpr int COUR_WAVES = 8192;  // 8 workgroups per CU
+constexpr int COUR_CUT = 2048;    // pieces that rows are cut into
+static CourShape cour_shape(const Geo &g) {
+  const int rows = g.nr * g.nt;
+  CourShape c{64, 1, g.np, rows};
+  if (g.np <= 32) {
+    c.w = 4;
+    while (c.w < g.np) c.w *= 2;
+    c.items = (rows + 64 / c.w - 1) / (64 / c.w);
+  } else if (rows <= COUR_CUT / 2) {
+    const int seg = std::min((g.np + 255) / 256, COUR_CUT / rows);
+    c.len = ((g.np + seg - 1) / seg + 63) / 64 * 64;
+    c.seg = (g.np + c.len - 1) / c.len;
+    c.items = rows * c.seg;
+  }
+  return c;
+}
+
+template <bool PACK>
+__global__ void __launch_bounds__(256) k_courant(Geo g, Mat m, Fields U, double tau, CourShape s,
+                                                 unsigned long long *out) {
   __shared__ double red[8];
   const int rows = g.nr * g.nt, np = g.np;
-  // waves take rows: a row of np cells per wave at a time
   const int wave = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
   double ca = 0.0, cs = 0.0;
-  for (int row = (int)blockIdx.x * 4 + wave; row < rows; row += (int)gridDim.x * 4) {
-    const int rw = __builtin_amdgcn_readfirstlane(row), i = rw / g.nt, j = rw - i * g.nt;
+  for (int item = (int)blockIdx.x * 4 + wave; item < s.items; item += (int)gridDim.x * 4) {
+    int row, k, ke, dk;
+    if (PACK) {
+      row = item * (64 / s.w) + lane / s.w;
+      k = lane & (s.w - 1);
+      ke = row < rows ? np : 0;
+      dk = s.w;
+      row = min(row, rows - 1);
+    } else {
+      const int it = __builtin_amdgcn_readfirstlane(item);
+      row = it / s.seg;
+      const int k0 = (it - row * s.seg) * s.len;
+      k = k0 + lane;
+      ke = min(np, k0 + s.len);
+      dk = 64;
+    }
+    const int i = row / g.nt, j = row - i * g.nt;
     const double hr = g.dr, ht = g.rc[i] * g.dt, hf = g.rc[i] * g.sc[j] * g.dp;
     const double *r0 = U.ur + idx_r(g, i, j, 0), *r1 = U.ur + idx_r(g, i + 1, j, 0);
     const double *t0 = U.ut + idx_t(g, i, j, 0), *t1 = U.ut + idx_t(g, i, j + 1, 0);
     const double *f0 = U.uf + idx_f(g, i, j, 0), *T = U.T + idx_c(g, i, j, 0);
     double a = 0.0, tm = 0.0;
-    for (int k = lane; k < np; k += 64) {
+    for (; k < ke; k += dk) {
       const int k1 = g.periodic && k + 1 == np ? 0 : k + 1;
       const double ur = 0.5 * (r0[k] + r1[k]), ut = 0.5 * (t0[k] + t1[k]), uf = 0.5 * (f0[k] + f0[k1]);
       const double v = fabs(ur) / hr + fabs(ut) / ht + fabs(uf) / hf;
@@ -1059,8 +1102,10 @@ __global__ void k_zero_u64(unsigned long long *p, int n) {
 void launch_courant(const Geo &g, const Mat &m, const Fields &U, double tau, unsigned long long *out,
                     hipStream_t st) {
   hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, st, out, 2);
-  const unsigned blocks = (unsigned)std::min<long>(((long)g.nr * g.nt + 3) / 4, 2048);  // 8 workgroups per CU
-  hipLaunchKernelGGL(k_courant, dim3(blocks), dim3(256), 0, st, g, m, U, tau, out);
+  const CourShape s = cour_shape(g);
+  const dim3 gr((unsigned)std::min((s.items + 3) / 4, COUR_WAVES / 4)), bl(256);
+  if (s.w < 64) hipLaunchKernelGGL(k_courant<true>, gr, bl, 0, st, g, m, U, tau, s, out);
+  else hipLaunchKernelGGL(k_courant<false>, gr, bl, 0, st, g, m, U, tau, s, out);
 }
 
 } // namespace dsw
