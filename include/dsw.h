@@ -349,10 +349,14 @@ int dsw_adjoint_trajectory(dsw_grid *grid, const dsw_fields *ckpts, int32_t nste
  *                         apart, by the partitioned solver); -1 = by line
  *                         length: partitioned where a line has at most 256
  *                         rows (64 chunks), else two-ended (in an ensemble,
- *                         member by member).  Lines of more than
+ *                         member by member); with a sweep_block below 256,
+ *                         30000 r lines of more than 128 rows and more
+ *                         two-ended too.  Lines of more than
  *                         4 x sweep_block rows take the two-ended solver.
  *                         The transposed r and theta solves of the adjoint
- *                         take the same solvers.  Measured: partitioned r
+ *                         take the same solvers, except that -1 takes the
+ *                         two-ended one for many short transposed theta
+ *                         lines (up to 24 rows) as well.  Measured: partitioned r
  *                         0.11 ms, theta 0.13 ms against 0.20 / 0.30 ms
  *                         two-ended on the 256 x 128 x 64 sector; on the
  *                         512 x 256 x 128 sphere r 0.98 / 1.37 ms and theta

@@ -392,7 +392,7 @@ struct Pass {
 
 // the kind of an r (d = 0) or theta (d = 1) pass under a configuration
 static int rt_kind(const Geo &g, const Cfg &c, int d) {
-  const int pm = c.rt_pm[d] < 0 ? rt_default_pm(g, d) : c.rt_pm[d];  // -1: by line length
+  const int pm = c.rt_pm[d] < 0 ? rt_default_pm(g, d, (unsigned)c.sweep_bs[d]) : c.rt_pm[d];  // -1: by line length
   if (pm > 0 && rt_part_supported(g, d, (unsigned)c.sweep_bs[d], pm)) return d == 0 ? PK_SW0P : PK_SW1P;
   const bool tw = families(g, d).nb < TWIST_LINES;
   return d == 0 ? (tw ? PK_SW0T : PK_SW0) : (tw ? PK_SW1T : PK_SW1);
@@ -1003,7 +1003,8 @@ static void launch_T(const dsw_grid *G, int d, const Pass &p, hipStream_t st) {
     const int pm = phi_part_supported(G->geo, 2) ? 2 : G->cfg.phi_pm;
     launch_phi_T(pm, p.a, (unsigned)G->geo.nr * (unsigned)G->geo.nt, phi_part_threads(G->geo, pm),
                  phi_part_lds(G->geo, pm), st);
-  } else if (p.kind == PK_SW0P || p.kind == PK_SW1P) {
+  } else if (p.kind == PK_SW0P || (p.kind == PK_SW1P && !(G->cfg.rt_pm[1] < 0 && families(G->geo, 1).nb < TWIST_LINES &&
+                                                          rt_T_two_ended(G->geo, (unsigned)G->cfg.sweep_bs[1])))) {
     launch_rt_T(d, p.a, (unsigned)G->cfg.sweep_bs[d], st);
   } else if (d < 2 && families(G->geo, d).nb < TWIST_LINES) {
     const unsigned bs = (unsigned)G->cfg.sweep_bs[d];

@@ -181,6 +181,7 @@ void launch_phi_forced(int pm, const PassArgs &a, hipStream_t st);
 void launch_rt_forced(int d, int pm, const PassArgs &a, unsigned threads, hipStream_t st);
 // transposed r and theta systems (adjoint) by the partitioned solver
 void launch_rt_T(int d, const PassArgs &a, unsigned threads, hipStream_t st);
+bool rt_T_two_ended(const Geo &g, unsigned bs);  // theta, chosen by line length
 // the scalar lines of an r or theta sweep alone, partitioned (one grid or a
 // batch; workgroups numbered from 0 per grid)
 bool rt_scalar_supported(const Geo &g, int d, unsigned bs);
@@ -190,7 +191,7 @@ unsigned rt_scalar_threads(const Geo &g, int d, unsigned bs);  // of a launch of
 void launch_rt_scalar_pass(int d, const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads,
                            hipStream_t st);
 // the r / theta solver a grid takes by default (4 partitioned, 0 two-ended)
-int rt_default_pm(const Geo &g, int d);
+int rt_default_pm(const Geo &g, int d, unsigned bs);
 
 // r and theta sweeps take two threads per line (two-ended elimination) on
 // grids with fewer block lines than this; measured faster than one thread

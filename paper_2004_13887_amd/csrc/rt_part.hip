@@ -30,6 +30,7 @@
 // block lines stay at two waves per SIMD (256 registers: 63 doubles of
 // intermediates and the reduction's 30) and are bound by their FP64 work and
 // the reduction's barriers; the scalar lines by their reads.
+#include <algorithm>
 #include <type_traits>
 
 #include "rows_fast.hpp"
@@ -558,6 +559,10 @@ __global__ void __launch_bounds__(PART == 1 ? 512 : 256) DSW_OCC(PART == 1 ? 0 :
 // same from 256 to 1024.
 constexpr unsigned RT_SPLIT_WGS = 1024;
 
+// Lines from which on narrow workgroups (sweep_block below 256) leave long lines
+// to the two-ended solver.
+constexpr long RT_NARROW_LINES = 30000;
+
 // Threads per workgroup of a launch of scalar lines: lines of more than 16
 // chunks (128 rows) take 512 where the blocks take 256, so that a row's loads
 // cover 16 neighbouring lines (128 bytes) up to 256 rows.  Measured, theta
@@ -611,11 +616,46 @@ void launch_rt_pass(int d, int pm, const PassArgs &a, const Batch &b, unsigned b
   else launch_rt_d<1, 4>(a, b, blocks, threads, st);
 }
 
+// The transposed theta block and scalar lines share a launch while all its
+// workgroups are resident at once, two of 256 threads per CU (in workgroups of
+// 256).  Measured, one launch / two, at 100 phi cells: 468 workgroups (400 x 3)
+// 17.5 / 18.7 us, 499 (160 x 16) 21.7 / 23.4, 547 (200 x 9) 29.6 / 23.2, 585
+// (500 x 3) 24.8 / 19.9, 800 (256 x 16) 37.4 / 31.1.  (The r lines as the forward
+// ones: 12 x 256 x 100 22.9 / 24.6.)
+constexpr unsigned RT_T_ONE_WGS = 512;
+static unsigned wgs256(unsigned wgs, unsigned bs) { return (unsigned)(((unsigned long)wgs * bs + 255) / 256); }
+
+// Whether transposed theta lines take the two-ended solver where the solver is
+// chosen by line length.  Short lines are a short chain for its two threads per
+// line, which fill the chip from some 30000 lines on, while the partitioned
+// solver's workgroups run in several rounds by then.  Estimates of both times in
+// units of 10 ns at 256 threads, from the measured grid of 3 to 40 rows by 8000
+// to 130000 lines.  Measured, two-ended / partitioned (us): 3 rows, 25600 lines
+// 10.4 / 15.1, 64000 21.5 / 20.4; 5 rows, 40000 19.9 / 26.7, 130000 54.6 / 47.8; 9
+// rows, 8000 16.3 / 13.7, 25600 21.0 / 29.0, 64000 46.7 / 45.6; 16 rows, 16000
+// 29.6 / 21.7; 17 rows, 32000 40.6 / 46.0, 50000 66.5 / 59.8; 24 rows and more,
+// partitioned at every count.  And many lines of more than 128 rows in
+// workgroups of 128 threads, which hold two or three of them: 192 rows, 32768
+// lines 614 / 702, 256 rows 817 / 868, 200 rows, 25600 lines 565 / 567.
+bool rt_T_two_ended(const Geo &g, unsigned bs) {
+  const long n = g.nt, lines = families(g, 1).nb;
+  if (n > 128) return bs == 128u && lines >= RT_NARROW_LINES;
+  if (n > 24) return false;
+  const unsigned nbw = wgs256(rt_block_wgs(g, 1, bs, 4), bs), all = nbw + wgs256(rt_scalar_wgs(g, 1, bs), bs);
+  const long two = std::max(1000L, (12 + 7 * n) * std::max(25000L, lines) / 1000);
+  long part;
+  if (all <= 256u) part = 1150;
+  else if (all <= RT_T_ONE_WGS) part = 1750;
+  else if (nbw <= 256u) part = 2400;
+  else part = 300 + 1100L * ((nbw + 255) / 256) + 200L * rt_block_chunks((int)n, 4);
+  return two <= part;
+}
+
 template <int D, int PM>
 static void launch_rt_T_d(const PassArgs &a, unsigned threads, hipStream_t st) {
   const size_t lds = rt_part_lds(threads);
   const unsigned nbw = rt_block_wgs(a.g, D, threads, PM), nsw = rt_scalar_wgs(a.g, D, threads);
-  if (nbw + nsw < RT_SPLIT_WGS) {
+  if (D == 0 ? nbw + nsw < RT_SPLIT_WGS : wgs256(nbw, threads) + wgs256(nsw, threads) <= RT_T_ONE_WGS) {
     hipLaunchKernelGGL((k_rt_partT<D, PM, 2>), dim3(nbw + nsw), dim3(threads), lds, st, a);
     return;
   }
@@ -699,8 +739,17 @@ void launch_rt_scalar_pass(int d, const PassArgs &a, const Batch &b, unsigned bl
 // solves: theta on the 512 x 256 x 128 sphere (256 rows) 1.01 / 1.37 ms, theta
 // and r on 200 x 200 x 200 cells 0.56 / 0.81 and 0.67 / 0.74 ms, theta on the
 // 1024 x 512 x 64 sector (512 rows, 128 chunks) 3.2 / 3.0 ms.
-int rt_default_pm(const Geo &g, int d) {
-  return rt_part_supported(g, d, 256, 4) && rt_block_chunks(families(g, d).n, 4) <= 64 ? 4 : 0;
+// r lines of more than 128 rows in narrower workgroups, one to three lines each,
+// load memory in pieces of as many values: partitioned while there are few
+// lines.  Measured, r, 192 rows, two-ended / partitioned: 64 threads, 25600 lines
+// 799 / 583 us, 32768 888 / 942, 65536 1703 / 2724, transposed 745 / 627, 853 / 1015,
+// 1679 / 3154; 128 threads 520 / 422, 580 / 606, 1166 / 1458, transposed 499 / 455,
+// 585 / 657, 1196 / 1563.  (theta, neighbouring rows next to each other: 64
+// threads, 65536 lines 1749 / 1502.)
+int rt_default_pm(const Geo &g, int d, unsigned bs) {
+  const Families F = families(g, d);
+  if (d == 0 && bs < 256u && F.n > 128 && F.nb >= RT_NARROW_LINES) return 0;
+  return rt_part_supported(g, d, 256, 4) && rt_block_chunks(F.n, 4) <= 64 ? 4 : 0;
 }
 
 void launch_rt_forced(int d, int pm, const PassArgs &a, unsigned threads, hipStream_t st) {

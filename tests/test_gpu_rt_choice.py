@@ -1,0 +1,50 @@
+"""Which solver r and theta lines take by themselves, on both sides of each
+rule: short transposed theta lines (two-ended where many lines fill the chip
+with it; partitioned in one launch and in two), and lines of more than 128 rows
+in narrow workgroups.  The result is bitwise that of the solver named
+explicitly, the other one differs in rounding, and the pair of solves meets the
+adjoint tests' 1e-10 on <M^-T y, b> = <y, M^-1 b>."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2004_13887_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+# direction, grid, sphere, threads, rows per thread of the solve and of the transposed one
+CASES = [(1, 256, 3, 100, False, 256, 4, 0), (1, 1000, 3, 100, True, 256, 4, 4), (1, 80, 9, 100, False, 256, 4, 4),
+         (1, 256, 9, 100, True, 256, 4, 0), (1, 640, 9, 100, False, 256, 4, 4), (1, 160, 16, 100, True, 256, 4, 4),
+         (1, 200, 20, 100, False, 256, 4, 4), (1, 32, 25, 1000, False, 256, 4, 4), (1, 256, 9, 100, False, 128, 4, 0),
+         (0, 132, 150, 200, False, 64, 0, 0), (0, 132, 149, 201, True, 128, 4, 4), (0, 129, 10, 20, False, 64, 4, 4),
+         (1, 150, 132, 200, True, 128, 4, 0), (1, 149, 132, 201, False, 128, 4, 4), (1, 150, 132, 200, False, 64, 4, 4)]
+
+
+@pytest.mark.parametrize("d,nr,nt,np_,sphere,bs,pm,pm_T", CASES)
+def test_solver_chosen(d, nr, nt, np_, sphere, bs, pm, pm_T):
+    from paper_2004_13887_amd import dsw
+    spec = I.full_sphere(nr, nt, np_) if sphere else I.sector(nr, nt, np_, 4e-4, 5e-4)
+    w = I.Workload("choice", spec, mach=1e-2, amplitude=0.5, steps=1, K=1, seed=830 + nr + nt)
+    print(f"[rt choice] d={d} {nr}x{nt}x{np_} sphere={sphere} threads={bs}", flush=True)
+    U0, tau = I.initial_state(w)
+    gg = dsw.Grid.from_spec(spec, w.material)
+    dU0 = dsw.to_device(U0)
+    b, y = dsw.to_device(I.random_fields(spec, 41 + d)), dsw.to_device(I.random_fields(spec, 51 + d))
+    out = {}
+    for rows in (-1, 0, 4):
+        gg.set_config(sweep_block_r=bs, sweep_block_theta=bs, rows_per_thread_r=rows, rows_per_thread_theta=rows)
+        x, z = gg.empty(), gg.empty()
+        gg.line_solve(d, dU0, tau, b, x)
+        gg.line_solve_T(d, dU0, tau, y, z)
+        torch.cuda.synchronize()
+        gg.get_status()
+        out[rows] = (x, z)
+    for q, chosen in ((0, pm), (1, pm_T)):
+        same = {rows: all(torch.equal(out[-1][q][k], out[rows][q][k]) for k in out[-1][q]) for rows in (0, 4)}
+        assert same == {0: chosen == 0, 4: chosen == 4}, ("transposed" if q else "plain", same)
+    for x, z in out.values():
+        hx, hz, hb, hy = (dsw.to_host(v) for v in (x, z, b, y))
+        lhs = sum(float(np.vdot(hz[k], hb[k])) for k in hx)
+        both = sum(float(np.vdot(hy[k], hx[k])) for k in hx)
+        size = sum(float(np.linalg.norm(hy[k]) * np.linalg.norm(hx[k])) for k in hx)
+        assert abs(lhs - both) <= 1e-10 * size
