@@ -509,7 +509,6 @@ static unsigned kind_threads(int kind, const Geo &g, const Cfg &c) {
   case PK_SW1B:
   case PK_SW1P: return (unsigned)c.sweep_bs[1];
   case PK_SW1S: return rt_scalar_threads(g, 1, (unsigned)c.sweep_bs[1]);
-  case PK_SW2_PART: return phi_part_threads(g, c.phi_pm);
   case PK_SW2_CP:
   case PK_SW2_CN: return phi_fast_threads(g, c.phi_pm);
   default: return 128u; // boundary copy, thread-per-line phi
@@ -539,7 +538,7 @@ static unsigned kind_blocks(int kind, const Geo &g, const Cfg &c, unsigned threa
   case PK_SW2_LINE: return cdiv(sweep_lines(g, 2), threads);
   case PK_SW2_CP:
   case PK_SW2_CN: return phi_fast_blocks(g, c.phi_pm, threads);
-  default: return (unsigned)g.nr * (unsigned)g.nt; // PK_SW2_PART
+  default: return 0;
   }
 }
 
@@ -547,7 +546,7 @@ static size_t kind_lds(int kind, const Geo &g, const Cfg &c) {
   if (kind == PK_SW0P || kind == PK_SW1P) return rt_part_lds(kind_threads(kind, g, c));
   if (kind == PK_SW0S || kind == PK_SW1S) return rt_scalar_lds(kind_threads(kind, g, c));
   if (kind == PK_SW2_CP || kind == PK_SW2_CN) return phi_fast_lds(kind_threads(kind, g, c));
-  return kind == PK_SW2_PART ? phi_part_lds(g, c.phi_pm) : 0;
+  return 0;
 }
 
 static void launch_kind(int kind, const Cfg &c, const PassArgs &a, const Batch &b, unsigned blocks,
@@ -572,7 +571,7 @@ static void launch_kind(int kind, const Cfg &c, const PassArgs &a, const Batch &
   case PK_SW2_LINE: launch_sweep_pass(2, a, b, blocks, threads, st); break;
   case PK_SW2_CP: launch_phi_pass_c(c.phi_pm, true, a, b, blocks, threads, lds, st); break;
   case PK_SW2_CN: launch_phi_pass_c(c.phi_pm, false, a, b, blocks, threads, lds, st); break;
-  default: launch_phi_pass(c.phi_pm, a, b, blocks, threads, lds, st); break;
+  default: break;
   }
 }
 
@@ -704,13 +703,9 @@ extern "C" int dsw_split_step_pert(dsw_grid *G, const dsw_fields *Un, dsw_fields
       case PK_SW0B: launch_sweep2_pert(0, a, sweep2_blocks(g, 0, th), th, st); break;
       case PK_SW1T:
       case PK_SW1B: launch_sweep2_pert(1, a, sweep2_blocks(g, 1, th), th, st); break;
-      case PK_SW2_CP:
-      case PK_SW2_CN:
+      default:  // PK_SW2_CP, PK_SW2_CN
         launch_phi_pert_c(G->cfg.phi_pm, p.kind == PK_SW2_CP, a, kind_blocks(p.kind, g, G->cfg, th), th,
                           kind_lds(p.kind, g, G->cfg), st);
-        break;
-      default:  // PK_SW2_PART
-        launch_phi_pert(G->cfg.phi_pm, a, kind_blocks(p.kind, g, G->cfg, th), th, kind_lds(p.kind, g, G->cfg), st);
       }
     });
   }
@@ -996,13 +991,6 @@ extern "C" int dsw_get_status(dsw_grid *G, void *stream) {
 static void launch_T(const dsw_grid *G, int d, const Pass &p, hipStream_t st) {
   if (d == 2 && (p.kind == PK_SW2_CP || p.kind == PK_SW2_CN)) {
     launch_phi_T_c(G->cfg.phi_pm, p.a, st);
-  } else if (d == 2 && p.kind == PK_SW2_PART) {
-    // two rows per chunk where the line allows it: twice the chunks in
-    // flight for the same line (measured faster than four on the transposed
-    // systems, whose row windows hold more registers)
-    const int pm = phi_part_supported(G->geo, 2) ? 2 : G->cfg.phi_pm;
-    launch_phi_T(pm, p.a, (unsigned)G->geo.nr * (unsigned)G->geo.nt, phi_part_threads(G->geo, pm),
-                 phi_part_lds(G->geo, pm), st);
   } else if (p.kind == PK_SW0P || (p.kind == PK_SW1P && !(G->cfg.rt_pm[1] < 0 && families(G->geo, 1).nb < TWIST_LINES &&
                                                           rt_T_two_ended(G->geo, (unsigned)G->cfg.sweep_bs[1])))) {
     launch_rt_T(d, p.a, (unsigned)G->cfg.sweep_bs[d], st);
@@ -1466,6 +1454,7 @@ struct dsw_ensemble {
   struct Group {
     int kind, tk;
     unsigned blocks, threads;
+    bool big;  // a member's byte offsets need 64 bits
     size_t lds;
     size_t tab_off, woff_off; // byte offsets into the plan's device buffer
     int n;
@@ -1634,6 +1623,7 @@ static int build_plan(dsw_ensemble *E, const Cfg &cfg, const dsw_fields *Un, dsw
       if (total == 0) continue;  // nothing to launch (e.g. no interior workgroups)
       gr.blocks = (unsigned)total;
       gr.threads = th;
+      gr.big = std::any_of(who.begin(), who.end(), [&](int m) { return !off32_ok(mem[m]->geo); });
       gr.lds = lds;
       gr.n = (int)who.size();
       gr.tab_off = append(tab.data(), tab.size() * sizeof(PassArgs));
@@ -1660,7 +1650,7 @@ static void enqueue_plan(const dsw_ensemble::Plan &plan, const Cfg &cfg, hipStre
   for (size_t q = g0; q < end; q++) {
     const auto &gr = plan.groups[q];
     const Batch b{(CPassArgs *)(plan.dev + gr.tab_off), (const unsigned *)(plan.dev + gr.woff_off),
-                  gr.n};
+                  gr.n, gr.big};
     if (ev) (void)hipEventRecord((*ev)[q].first, st);
     launch_kind(gr.kind, cfg, dummy, b, gr.blocks, gr.threads, gr.lds, st);
     if (ev) (void)hipEventRecord((*ev)[q].second, st);

@@ -69,8 +69,6 @@ struct SrcOneT {
   __device__ __forceinline__ double ldk(int f, int row, int k) const { return a[f][row + k]; }
 };
 using SrcOne = SrcOneT<false>;
-using SrcInN = SrcOneT<true, false>; // interior, phi bounded by walls
-using SrcInP = SrcOneT<true, true>;  // interior, phi periodic
 struct SrcMid {
   const double *n[5], *k[5];
   static constexpr bool INTERIOR = false;

@@ -16,9 +16,6 @@ namespace dsw {
 #ifndef DSW_WAVES_SWEEP
 #define DSW_WAVES_SWEEP 0
 #endif
-#ifndef DSW_WAVES_PHI
-#define DSW_WAVES_PHI 0
-#endif
 #define DSW_OCC(w) __attribute__((amdgpu_waves_per_eu((w) > 0 ? (w) : 1)))
 
 // device status words, each set by plain stores of 1 (no atomics)
@@ -128,6 +125,7 @@ struct Batch {
   CPassArgs *tab;
   const unsigned *woff;
   int n;
+  bool big = false;  // a member's byte offsets need 64 bits (host side; one grid: off32_ok of its own)
 };
 
 // member m's arguments, as a reference the pass bodies take
@@ -150,15 +148,14 @@ struct Cfg {
 // block lines two-ended (PK_SW0B / PK_SW1B) and then the scalar lines
 // partitioned (PK_SW0S / PK_SW1S).  PK_NONE: a pass that launches nothing
 // (it keeps the passes of different grids' steps aligned).
-enum PassKind { PK_BND = 0, PK_RES = 1, PK_SW0 = 2, PK_SW1 = 3, PK_SW2_LINE = 4, PK_SW2_PART = 5,
+enum PassKind { PK_BND = 0, PK_RES = 1, PK_SW0 = 2, PK_SW1 = 3, PK_SW2_LINE = 4,
                 PK_RES_IN = 6, PK_SW0T = 7, PK_SW1T = 8, PK_RES_INP = 9, PK_SW0P = 10, PK_SW1P = 11,
                 PK_SW0B = 12, PK_SW1B = 13, PK_SW0S = 14, PK_SW1S = 15, PK_NONE = 16,
                 PK_SW2_CP = 17, PK_SW2_CN = 18, PK_RES_MN = 19, PK_RES_MP = 20 };
 // PK_RES_IN / PK_RES_INP: the interior of the residual (bounded / periodic
 // phi; one grid: the shell as well, and PK_RES launches nothing); PK_RES_MN /
 // PK_RES_MP: the same by the kernel for large grids.
-// PK_SW2_CP / PK_SW2_CN: the partitioned phi pass with 32-bit byte offsets
-// (periodic / bounded phi); PK_SW2_PART: the same on grids beyond them.
+// PK_SW2_CP / PK_SW2_CN: the partitioned phi pass (periodic / bounded phi).
 
 // forced split step (source term, wall velocities, Dirichlet data at the new
 // time level): one grid; the same solvers as the plain step, their theta block
@@ -221,8 +218,6 @@ inline bool is_res_in(int kind) {
 unsigned residual_general_blocks(const Geo &g, int bs);
 void launch_sweep_pass(int d, const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads,
                        hipStream_t st);
-void launch_phi_pass(int pm, const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads,
-                     size_t lds, hipStream_t st);
 void launch_bnd_pass(const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads,
                      hipStream_t st);
 unsigned sweep_lines(const Geo &g, int d);   // lines of all families of sweep d
@@ -241,8 +236,6 @@ size_t rt_part_lds(unsigned bs);
 void launch_rt_pass(int d, int pm, const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads,
                     hipStream_t st);
 unsigned bnd_points(const Geo &g);           // boundary-normal faces
-unsigned phi_part_threads(const Geo &g, int pm);
-size_t phi_part_lds(const Geo &g, int pm);
 
 // adjoint pieces: transposed line solves (one thread per line), the
 // transposed Jacobians of the residual and of the line operators (both
@@ -250,8 +243,6 @@ size_t phi_part_lds(const Geo &g, int pm);
 void launch_sweep_T(int d, const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st);
 void launch_sweep2_T(int d, const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st);
 void launch_phi_T_c(int pm, const PassArgs &a, hipStream_t st);
-void launch_phi_T(int pm, const PassArgs &a, unsigned blocks, unsigned threads, size_t lds,
-                  hipStream_t st);
 void launch_residual_vjp(const Geo &g, const Mat &m, const Fields &Ub, double tau, const Fields &mu,
                          const Fields &acc, hipStream_t st);
 void launch_line_vjp(int d, const Geo &g, const Mat &m, const Fields &Ub, double tau, const Fields &X,
@@ -272,7 +263,6 @@ void launch_adj_mix(const Geo &g, const long *cnt, const Fields &L, const Fields
 void launch_residual_pert(const PassArgs &a, unsigned threads, hipStream_t st);
 void launch_rt_pert(int d, const PassArgs &a, unsigned threads, hipStream_t st);
 void launch_sweep2_pert(int d, const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st);
-void launch_phi_pert(int pm, const PassArgs &a, unsigned blocks, unsigned threads, size_t lds, hipStream_t st);
 
 // Courant numbers (advective, acoustic) of a state for the step tau into
 // out[0], out[1] (device, as the bit patterns of non-negative doubles)
@@ -296,8 +286,8 @@ void sweep_scratch_size(const Geo &g, long *blk, long *sca);
 __host__ __device__ inline bool off32_ok(const Geo &g) {
   return (long)(g.nr + 1) * (g.nt + 1) * (g.np + 1) < (1L << 29);
 }
-// the phi pass of such a grid, or of a batch of them: shape, workgroups
-// (block lines, then as many for the scalar lines), launch
+// the phi pass of a grid or of a batch: shape, workgroups (block lines, then as
+// many for the scalar lines), launch
 unsigned phi_fast_threads(const Geo &g, int pm);
 unsigned phi_fast_blocks(const Geo &g, int pm, unsigned threads);
 size_t phi_fast_lds(unsigned threads);
@@ -308,8 +298,7 @@ void launch_phi_pert_c(int pm, bool periodic, const PassArgs &a, unsigned blocks
 // the kind of the phi pass of a grid under a configuration
 inline int phi_kind(const Geo &g, const Cfg &c) {
   if (!(c.phi_pm > 0 && phi_part_supported(g, c.phi_pm))) return PK_SW2_LINE;
-  if (off32_ok(g)) return g.periodic ? PK_SW2_CP : PK_SW2_CN;
-  return PK_SW2_PART;
+  return g.periodic ? PK_SW2_CP : PK_SW2_CN;
 }
 
 // Workgroups go to the chip's 8 XCDs in turn (w mod 8), and each XCD has an

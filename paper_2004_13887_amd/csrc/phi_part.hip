@@ -1,9 +1,9 @@
 // phi_part.hip -- partitioned line solver for the phi sweep (paper eq. (spl3),
 // operator D_phi of Appendix B eq. (dphi)).
 //
-// One workgroup per line slot (i, j).  It solves the 3x3-block line in
-// (p, T, u_phi) and the two scalar lines (u_r on r-face i, u_theta on
-// theta-face j) that share that slot.  Thread t owns a chunk of up to 4 rows:
+// A slot (i, j) holds a 3x3-block line in (p, T, u_phi) and two scalar lines,
+// u_r on r face i and u_theta on theta face j.  A workgroup takes as many
+// neighbouring slots as its lanes hold; a thread owns a chunk of up to 4 rows:
 //   1. it assembles its rows (consecutive threads read consecutive phi cells:
 //      contiguous loads) and eliminates its interior rows with the block
 //      Thomas recurrence, carrying the dependence on the previous chunk's last
@@ -15,18 +15,20 @@
 //   3. interior rows are filled in from the separators.
 // All intermediates stay in registers and LDS: no scratch traffic.
 //
-// Grids whose byte offsets fit 32 bits take the *_fast bodies: a workgroup on as
-// many neighbouring slots as its lanes hold, every input of a chunk loaded before its first row is eliminated, ghosts by clamped 32-bit
-// offsets and signs instead of branches (so no slot needs a launch or a
-// source of its own).  Line solves, one row at a time against this: 512 x 256
-// x 128 sphere 1.24 -> 0.98 ms, 200 x 200 x 200 cells 0.66 -> 0.51, 150 x 101
-// x 37 84 -> 55 us, 32 x 32 x 16 28 -> 14 us; transposed, on the sphere 2.00 ->
-// 0.97 ms, on the 256 x 128 x 64 sector 0.262 -> 0.144 (2 rows per chunk, the
-// better choice a row at a time, 0.167).  The block lines are bound by
-// their FP64 work at two waves per SIMD (a third of it the cyclic reduction)
-// and its barriers, the scalar lines by their reads; the scalar reductions
-// keep each quantity contiguous over the lanes (a record per lane, as the
-// block reductions have, put 16 lanes on one bank: 0.55 against 0.45 ms).
+// Every input of a chunk is loaded before its first row is eliminated, with
+// ghosts by clamped offsets and signs instead of branches (so no slot needs a
+// launch or a source of its own); byte offsets take 32 bits, or 64 on grids
+// whose arrays reach 4 GiB (BIG: 1024 x 1024 x 513 cells 47 ms, transposed 54, a
+// row at a time 68 and 128).  Line solves, one row at a time, a workgroup
+// per slot, against this: 512 x 256 x 128 sphere 1.24 -> 0.98 ms, 200 x 200 x
+// 200 cells 0.66 -> 0.51, 150 x 101 x 37 84 -> 55 us, 32 x 32 x 16 28 -> 14 us;
+// transposed, on the sphere 2.00 -> 0.97 ms, on the 256 x 128 x 64 sector 0.262
+// -> 0.144 (2 rows per chunk, the better choice a row at a time, 0.167).  The
+// block lines are bound by their FP64 work at two waves per SIMD (a third of it
+// the cyclic reduction) and its barriers, the scalar lines by their reads; the
+// scalar reductions keep each quantity contiguous over the lanes (a record per
+// lane, as the block reductions have, put 16 lanes on one bank: 0.55 against
+// 0.45 ms).
 #include <algorithm>
 #include <type_traits>
 
@@ -51,392 +53,6 @@ __host__ __device__ inline int phi_chunks(int n, int cyc, int pm) {
   return T;
 }
 
-// rows [a0, a0 + len) of chunk t (len 0 past the last chunk)
-template <int PM>
-__device__ __forceinline__ void phi_chunk(int n, int cyc, int T, int t, int &a0, int &len) {
-  if (cyc) {
-    const int lg = 31 - __builtin_clz((unsigned)T), base = n >> lg, rem = n & (T - 1);
-    a0 = t * base + min(t, rem);
-    len = t < T ? base + (t < rem ? 1 : 0) : 0;
-  } else {
-    a0 = t * PM;
-    len = t < T ? min(PM, n - a0) : 0;
-  }
-}
-
-// ---------------------------------------------------------- 3x3 helpers --
-__device__ __forceinline__ void mm3s(const double *A, const double *B, double *C, double s) {
-  mm3(A, B, C);
-#pragma unroll
-  for (int q = 0; q < 9; q++) C[q] *= s;
-}
-
-// ------------------------------------------------------- block: PCR step --
-// Solve the T separator rows A x_{t-1} + B x_t + C x_{t+1} = r (t < T) held
-// in registers of threads t < T; returns x_t.  Each step, every row
-// publishes B^{-1} A, B^{-1} C and B^{-1} r (LDS: 21 T doubles) and
-// eliminates its neighbours h rows away from them.
-__device__ __forceinline__ void pcr_block(int t, int T, int cyc, double *A, double *B, double *C, double *r,
-                          double *lds, double *x, int *status) {
-  double *sPA = lds, *sPC = lds + 9 * T, *sPr = lds + 18 * T;
-  const bool act = t < T;
-  for (int h = 1; h < T; h *= 2) {
-    if (act) {
-      double Bi[9];
-      inv3(B, Bi, status);
-      mm3(Bi, A, &sPA[t * 9]);
-      mm3(Bi, C, &sPC[t * 9]);
-      mv3(Bi, r, &sPr[t * 3]);
-    }
-    __syncthreads();
-    if (act) {
-      int lo = t - h, hi = t + h;
-      bool has_lo = lo >= 0, has_hi = hi < T;
-      if (cyc) { lo &= T - 1; hi &= T - 1; has_lo = has_hi = true; }  // cyclic: T a power of two
-      // B' = B - A P_C(lo) - C P_A(hi), r' alike, A' = -A P_A(lo),
-      // C' = -C P_C(hi) (P = B^{-1} times the published row)
-      if (has_lo) { mm3_sub(A, &sPC[lo * 9], B); mv3_sub(A, &sPr[lo * 3], r); }
-      if (has_hi) { mm3_sub(C, &sPA[hi * 9], B); mv3_sub(C, &sPr[hi * 3], r); }
-      if (has_lo) mm3_neg_inplace(A, &sPA[lo * 9]);
-      else {
-#pragma unroll
-        for (int q = 0; q < 9; q++) A[q] = 0.0;
-      }
-      if (has_hi) mm3_neg_inplace(C, &sPC[hi * 9]);
-      else {
-#pragma unroll
-        for (int q = 0; q < 9; q++) C[q] = 0.0;
-      }
-    }
-    __syncthreads();
-  }
-  if (act) {
-    // every remaining coupling points at x_t itself (cyclic) or is zero
-    double S[9], Si[9];
-#pragma unroll
-    for (int q = 0; q < 9; q++) S[q] = A[q] + B[q] + C[q];
-    inv3(S, Si, status);
-    mv3(Si, r, x);
-  }
-}
-
-__device__ __forceinline__ void pcr_scalar(int t, int T, int cyc, double &A, double &B, double &C, double &r,
-                           double *lds, double &x, int *status) {
-  double *sA = lds, *sC = lds + T, *sR = lds + 2 * T, *sB = lds + 3 * T;
-  const bool act = t < T;
-  for (int h = 1; h < T; h *= 2) {
-    if (act) { sA[t] = A; sC[t] = C; sR[t] = r; sB[t] = B; }
-    __syncthreads();
-    if (act) {
-      int lo = t - h, hi = t + h;
-      bool has_lo = lo >= 0, has_hi = hi < T;
-      if (cyc) { lo &= T - 1; hi &= T - 1; has_lo = has_hi = true; }  // cyclic: T a power of two
-      double nA = 0.0, nC = 0.0, nB = B, nr = r;
-      if (has_lo) {
-        const double al = -A * rcp_nr(sB[lo]);
-        nA = al * sA[lo];
-        nB += al * sC[lo];
-        nr += al * sR[lo];
-      }
-      if (has_hi) {
-        const double be = -C * rcp_nr(sB[hi]);
-        nC = be * sC[hi];
-        nB += be * sA[hi];
-        nr += be * sR[hi];
-      }
-      A = nA; B = nB; C = nC; r = nr;
-    }
-    __syncthreads();
-  }
-  if (act) {
-    const double S = A + B + C;
-    if (!(S != 0.0)) status[ST_SINGULAR] = 1;
-    x = r * rcp_nr(S);
-  }
-}
-
-// ------------------------------------------------------------ block line --
-template <int PM, bool TR, class US>
-__device__ __forceinline__ void part_block_line(const Geo &g, const Mat &m, const US &u, const Fields &rhs,
-                                const Out &o, int i, int j, double hs, double *lds, int *status) {
-  const int N = g.np, cyc = g.periodic, T = phi_chunks(N, cyc, PM);
-  const int t = threadIdx.x;
-  const bool act = t < T;
-  int a0, len;
-  phi_chunk<PM>(N, cyc, T, t, a0, len);
-  double Cm[PM - 1][9], Em[PM - 1][9], Ym[PM - 1][3];
-  // structural non-zeros of the row blocks (transposed rows: L = U^T, U = L^T)
-  constexpr unsigned mL = TR ? nz_tr(NZ_U) : NZ_L, mU = TR ? nz_tr(NZ_L) : NZ_U;
-  BRow R;
-  TrWalk<2> tw; // transposed rows: each row of the line assembled once
-  if constexpr (TR) {
-    if (act) tw.init(g, m, u, rhs, i, j, a0, N, cyc, hs);
-  }
-  // a zero pivot is recorded after the loop: a store inside it would hold
-  // the next row's loads back
-  bool sing = false;
-  // 1. forward elimination over interior rows with the left spike
-#pragma unroll
-  for (int q = 0; q < PM - 1; q++) {
-    if (q < len - 1) {
-      if constexpr (TR) tw.next(g, m, u, rhs, i, j, N, cyc, hs, R);
-      else block_row<2>(g, m, u, rhs, i, j, a0 + q, N, cyc, hs, R);
-      double Dp[9], rr[3], Lx[9], Ai[9];
-      if (q == 0) {
-#pragma unroll
-        for (int z = 0; z < 9; z++) Dp[z] = R.D[z];
-#pragma unroll
-        for (int z = 0; z < 3; z++) rr[z] = R.b[z];
-      } else {
-        double t9[9], t3[3];
-        mm3m<mL, NZ_ALL>(R.L, Cm[q - 1], t9);
-#pragma unroll
-        for (int z = 0; z < 9; z++) Dp[z] = R.D[z] - t9[z];
-        mv3m<mL>(R.L, Ym[q - 1], t3);
-#pragma unroll
-        for (int z = 0; z < 3; z++) rr[z] = R.b[z] - t3[z];
-        mm3m<mL, NZ_ALL>(R.L, Em[q - 1], Lx);
-#pragma unroll
-        for (int z = 0; z < 9; z++) Lx[z] *= -1.0;
-      }
-      sing |= inv3q(Dp, Ai);
-      mm3m<NZ_ALL, mU>(Ai, R.U, Cm[q]);
-      mv3(Ai, rr, Ym[q]);
-      if (q == 0) mm3m<NZ_ALL, mL>(Ai, R.L, Em[q]);
-      else mm3(Ai, Lx, Em[q]);
-    }
-  }
-  if (sing) status[ST_SINGULAR] = 1;
-  // separator row (last row of the chunk)
-  BRow S;
-  if (act) {
-    if constexpr (TR) tw.next(g, m, u, rhs, i, j, N, cyc, hs, S);
-    else block_row<2>(g, m, u, rhs, i, j, a0 + len - 1, N, cyc, hs, S);
-  }
-  // backward sweep: (Y, E, C) -> (g, V, W), x_q = g_q + V_q x_left + W_q x_sep
-#pragma unroll
-  for (int q = PM - 2; q >= 0; q--) {
-    if (q == len - 2) {
-#pragma unroll
-      for (int z = 0; z < 9; z++) { Em[q][z] = -Em[q][z]; Cm[q][z] = -Cm[q][z]; }
-    } else if (q < len - 2) {
-      double t9[9], t3[3];
-      mv3(Cm[q], Ym[q + 1], t3);
-#pragma unroll
-      for (int z = 0; z < 3; z++) Ym[q][z] -= t3[z];
-      mm3(Cm[q], Em[q + 1], t9);
-#pragma unroll
-      for (int z = 0; z < 9; z++) Em[q][z] = -Em[q][z] - t9[z];
-      mm3s(Cm[q], Cm[q + 1], t9, -1.0);
-#pragma unroll
-      for (int z = 0; z < 9; z++) Cm[q][z] = t9[z];
-    }
-  }
-  // 2. exchange the first interior row of each chunk with its left neighbour
-  double *sG = lds, *sV = lds + 3 * T, *sW = lds + 12 * T, *sL = lds + 21 * T;
-  if (act) {
-    sL[t] = (double)len;
-    if (len >= 2) {
-#pragma unroll
-      for (int z = 0; z < 3; z++) sG[t * 3 + z] = Ym[0][z];
-#pragma unroll
-      for (int z = 0; z < 9; z++) { sV[t * 9 + z] = Em[0][z]; sW[t * 9 + z] = Cm[0][z]; }
-    }
-  }
-  __syncthreads();
-  double A[9], B[9], Cc[9], r[3];
-  if (act) {
-    int nt_ = t + 1;
-    bool has_next = nt_ < T;
-    if (cyc) { nt_ &= T - 1; has_next = true; }
-    const int nlen = has_next ? (int)sL[nt_] : 0;
-    // last interior row of this chunk
-    double Gl[3] = {0, 0, 0}, Vl[9], Wl[9];
-#pragma unroll
-    for (int z = 0; z < 9; z++) { Vl[z] = 0.0; Wl[z] = 0.0; }
-#pragma unroll
-    for (int q = 0; q < PM - 1; q++)
-      if (q == len - 2) {
-#pragma unroll
-        for (int z = 0; z < 3; z++) Gl[z] = Ym[q][z];
-#pragma unroll
-        for (int z = 0; z < 9; z++) { Vl[z] = Em[q][z]; Wl[z] = Cm[q][z]; }
-      }
-    double t9[9], t3[3];
-#pragma unroll
-    for (int z = 0; z < 9; z++) B[z] = S.D[z];
-#pragma unroll
-    for (int z = 0; z < 3; z++) r[z] = S.b[z];
-    if (len >= 2) {
-      mm3m<mL, NZ_ALL>(S.L, Vl, A);
-      mm3m<mL, NZ_ALL>(S.L, Wl, t9);
-#pragma unroll
-      for (int z = 0; z < 9; z++) B[z] += t9[z];
-      mv3m<mL>(S.L, Gl, t3);
-#pragma unroll
-      for (int z = 0; z < 3; z++) r[z] -= t3[z];
-    } else {
-#pragma unroll
-      for (int z = 0; z < 9; z++) A[z] = S.L[z];
-    }
-    if (nlen >= 2) {
-      mm3m<mU, NZ_ALL>(S.U, &sV[nt_ * 9], t9);
-#pragma unroll
-      for (int z = 0; z < 9; z++) B[z] += t9[z];
-      mm3m<mU, NZ_ALL>(S.U, &sW[nt_ * 9], Cc);
-      mv3m<mU>(S.U, &sG[nt_ * 3], t3);
-#pragma unroll
-      for (int z = 0; z < 3; z++) r[z] -= t3[z];
-    } else {
-#pragma unroll
-      for (int z = 0; z < 9; z++) Cc[z] = S.U[z];
-    }
-  }
-  __syncthreads(); // exchange area is reused by the reduction
-  double xs[3] = {0, 0, 0};
-  pcr_block(t, T, cyc, A, B, Cc, r, lds, xs, status);
-  // 3. fill in the interior rows
-  double *sX = lds + 21 * T;
-  if (act) {
-#pragma unroll
-    for (int z = 0; z < 3; z++) sX[t * 3 + z] = xs[z];
-  }
-  __syncthreads();
-  double val[PM][3];
-  if (act) {
-    double xl[3] = {0, 0, 0};
-    if (t > 0 || cyc) {
-      const int lt = t > 0 ? t - 1 : T - 1;
-#pragma unroll
-      for (int z = 0; z < 3; z++) xl[z] = sX[lt * 3 + z];
-    }
-#pragma unroll
-    for (int q = 0; q < PM - 1; q++) {
-      if (q < len - 1) {
-        double t3[3];
-        mv3(Em[q], xl, val[q]);
-        mv3(Cm[q], xs, t3);
-#pragma unroll
-        for (int z = 0; z < 3; z++) val[q][z] += Ym[q][z] + t3[z];
-      }
-    }
-  }
-  __syncthreads(); // every thread has read the separators: the LDS is free
-  // stage the solution in LDS and store it row-contiguously (whole lines
-  // per store instruction instead of a 4-row stride across lanes)
-  double *sP = lds, *sT_ = lds + N, *sWv = lds + 2 * N;
-  if (act) {
-#pragma unroll
-    for (int q = 0; q < PM - 1; q++)
-      if (q < len - 1) { sP[a0 + q] = val[q][0]; sT_[a0 + q] = val[q][1]; sWv[a0 + q] = val[q][2]; }
-    sP[a0 + len - 1] = xs[0]; sT_[a0 + len - 1] = xs[1]; sWv[a0 + len - 1] = xs[2];
-  }
-  __syncthreads();
-  for (int r = t; r < N; r += blockDim.x) {
-    const double v[3] = {sP[r], sT_[r], sWv[r]};
-    block_store<2>(g, o, i, j, r, v);
-  }
-  __syncthreads();
-}
-
-// ----------------------------------------------------------- scalar line --
-template <int PM, int FAM, bool TR, class US>
-__device__ __forceinline__ void part_scalar_line(const Geo &g, const Mat &m, const US &u, const Fields &rhs,
-                                 const Out &o, int a, int b, double hs, double *lds, int *status) {
-  const int N = g.np, cyc = g.periodic, T = phi_chunks(N, cyc, PM);
-  const int t = threadIdx.x;
-  const bool act = t < T;
-  int a0, len;
-  phi_chunk<PM>(N, cyc, T, t, a0, len);
-  const int ofid = FAM == 0 ? F_UR : F_UT;
-  double Cm[PM - 1], Em[PM - 1], Ym[PM - 1];
-  SRow R;
-  long xi;
-  double *arr;
-  TrWalkS<2, FAM> tw; // transposed rows: each row of the line assembled once
-  if constexpr (TR) {
-    if (act) tw.init(g, m, u, rhs, a, b, a0, N, cyc, hs);
-  }
-  SRow S{0, 1, 0, 0};
-  if constexpr (TR) {
-#pragma unroll
-    for (int q = 0; q < PM - 1; q++) {
-      if (q < len - 1) {
-        tw.next(g, m, u, rhs, a, b, N, cyc, hs, R);
-        double dp = R.b, rr = R.r, lx = R.a;
-        if (q > 0) { dp -= R.a * Cm[q - 1]; rr -= R.a * Ym[q - 1]; lx = -R.a * Em[q - 1]; }
-        if (!(dp != 0.0)) status[ST_SINGULAR] = 1;
-        const double id = rcp_nr(dp);
-        Cm[q] = R.c * id;
-        Ym[q] = rr * id;
-        Em[q] = lx * id;
-      }
-    }
-    if (act) tw.next(g, m, u, rhs, a, b, N, cyc, hs, S);
-  } else {
-    const auto row = [&](int s, SRow &Q) { scalar_row<2, FAM>(g, m, u, rhs, a, b, s, N, cyc, hs, Q, xi, arr); };
-    if (scalar_chunk_fwd<PM>(row, a0, len, N, Cm, Em, Ym, S)) status[ST_SINGULAR] = 1;
-  }
-#pragma unroll
-  for (int q = PM - 2; q >= 0; q--) {
-    if (q == len - 2) { Em[q] = -Em[q]; Cm[q] = -Cm[q]; }
-    else if (q < len - 2) {
-      Ym[q] -= Cm[q] * Ym[q + 1];
-      Em[q] = -Em[q] - Cm[q] * Em[q + 1];
-      Cm[q] = -Cm[q] * Cm[q + 1];
-    }
-  }
-  double *sG = lds, *sV = lds + T, *sW = lds + 2 * T, *sL = lds + 3 * T;
-  if (act) {
-    sL[t] = (double)len;
-    if (len >= 2) { sG[t] = Ym[0]; sV[t] = Em[0]; sW[t] = Cm[0]; }
-  }
-  __syncthreads();
-  double A = 0.0, B = 1.0, C = 0.0, r = 0.0;
-  if (act) {
-    int nt_ = t + 1;
-    bool has_next = nt_ < T;
-    if (cyc) { nt_ &= T - 1; has_next = true; }
-    const int nlen = has_next ? (int)sL[nt_] : 0;
-    double Gl = 0.0, Vl = 0.0, Wl = 0.0;
-#pragma unroll
-    for (int q = 0; q < PM - 1; q++)
-      if (q == len - 2) { Gl = Ym[q]; Vl = Em[q]; Wl = Cm[q]; }
-    B = S.b;
-    r = S.r;
-    if (len >= 2) { A = S.a * Vl; B += S.a * Wl; r -= S.a * Gl; }
-    else A = S.a;
-    if (nlen >= 2) { B += S.c * sV[nt_]; C = S.c * sW[nt_]; r -= S.c * sG[nt_]; }
-    else C = S.c;
-  }
-  __syncthreads();
-  double xs = 0.0;
-  pcr_scalar(t, T, cyc, A, B, C, r, lds, xs, status);
-  double *sX = lds + 4 * T;
-  if (act) sX[t] = xs;
-  __syncthreads();
-  double val[PM];
-  if (act) {
-    double xl = 0.0;
-    if (t > 0 || cyc) xl = sX[t > 0 ? t - 1 : T - 1];
-#pragma unroll
-    for (int q = 0; q < PM - 1; q++)
-      if (q < len - 1) val[q] = Ym[q] + Em[q] * xl + Cm[q] * xs;
-  }
-  __syncthreads(); // the LDS is free: stage the line, store it contiguously
-  if (act) {
-#pragma unroll
-    for (int q = 0; q < PM - 1; q++)
-      if (q < len - 1) lds[a0 + q] = val[q];
-    lds[a0 + len - 1] = xs;
-  }
-  __syncthreads();
-  for (int r = t; r < N; r += blockDim.x)
-    put(o, ofid, FAM == 0 ? idx_r(g, a, b, r) : idx_t(g, a, b, r), lds[r]);
-  __syncthreads();
-}
-
-// ------------------------------------------------- 32-bit byte offsets --
 // A workgroup takes L = blockDim / T neighbouring slots; thread t = l T + c
 // holds chunk c of slot l's lines.  Ghosts across r and theta are a clamped
 // index and a sign per lane, across phi the wrap (CYC) or the same.
@@ -484,15 +100,16 @@ __device__ __forceinline__ unsigned phi_pos(const Geo &g, int s) {
 // (adjoint), whose rows take blocks of the rows on either side, so a chunk
 // loads one more row at each end; W: a forced pass, whose ghosts across a wall
 // are 2 g - u (the scalar lines read none); PT: perturbation-pressure form.
-// LDS SEP_REC doubles per thread.
-template <int PM, bool CYC, bool TR, bool W, bool PT>
+// BIG: 64-bit byte offsets.  LDS SEP_REC doubles per thread.
+template <int PM, bool CYC, bool TR, bool W, bool PT, bool BIG>
 __device__ __forceinline__ void phi_block_fast(const PassArgs &a, unsigned w, double *lds) {
+  using O = Off<BIG>;
   const Geo &g = a.g;
   const Mat &m = a.m;
   const double hs = a.tau;
   const PhiChunk pc = phi_lane<PM, CYC>(g, w);
   const int T = pc.T, t = threadIdx.x, c = pc.c, s0 = pc.s0, np = g.np;
-  const unsigned N8 = 8u * (unsigned)np, F8 = 8u * (unsigned)g.npf;
+  const O N8 = 8u * (O)np, F8 = 8u * (O)g.npf;
   const int i = (int)(pc.line / (unsigned)g.nt), j = (int)pc.line - i * g.nt;
   const double ir = g.irc[i], is = g.isc[j], ct = g.ctc[j], irs = ir * is;
   const double h = irs * g.idp;  // 1 / spacing; dp = h, dm = -h
@@ -509,13 +126,13 @@ __device__ __forceinline__ void phi_block_fast(const PassArgs &a, unsigned w, do
 #pragma unroll
     for (int q = 0; q <= NQ; q++) fpos[q] = CYC ? pos[q + 1] : 8u * (unsigned)min(max(s0 + q - X, 0), np);
     const double *u_r = a.u.a[F_UR], *u_t = a.u.a[F_UT], *u_f = a.u.a[F_UF];
-    const unsigned oC = pc.line * N8, pl = (unsigned)g.nt * N8;
-    const unsigned oT = (unsigned)(i * (g.nt + 1) + j) * N8, oF = pc.line * F8, pF = (unsigned)g.nt * F8;
+    const O oC = pc.line * N8, pl = (unsigned)g.nt * N8;
+    const O oT = (unsigned)(i * (g.nt + 1) + j) * N8, oF = pc.line * F8, pF = (unsigned)g.nt * F8;
     // u_phi on the four neighbouring lines: a wall or pole negates it
     const double sim = i == 0 ? -1.0 : 1.0, sip = i == g.nr - 1 ? -1.0 : 1.0;
     const double sjm = j == 0 ? -1.0 : 1.0, sjp = j == g.nt - 1 ? -1.0 : 1.0;
-    const unsigned oim = i == 0 ? oF : oF - pF, oip = i == g.nr - 1 ? oF : oF + pF;
-    const unsigned ojm = j == 0 ? oF : oF - F8, ojp = j == g.nt - 1 ? oF : oF + F8;
+    const O oim = i == 0 ? oF : oF - pF, oip = i == g.nr - 1 ? oF : oF + pF;
+    const O ojm = j == 0 ? oF : oF - F8, ojp = j == g.nt - 1 ? oF : oF + F8;
     const double kr = 0.5 * g.idr, kt = 0.5 * ir * g.idt * ct;
     const double kip = kr * sip, kim = kr * sim, kjp = kt * sjp, kjm = kt * sjm;
 #pragma unroll
@@ -530,8 +147,8 @@ __device__ __forceinline__ void phi_block_fast(const PassArgs &a, unsigned w, do
     for (int q = 0; q <= NQ; q++) wf[q] = fma_(-kjm, ldo(u_f, ojm + fpos[q]), wf[q]);
     if constexpr (W) {
       const Wall &wl = a.wall;
-      const unsigned fj = (unsigned)j * F8, fi = (unsigned)i * F8;
-      auto add = [&](const double *w_, unsigned o, double sc) {
+      const O fj = (unsigned)j * F8, fi = (unsigned)i * F8;
+      auto add = [&](const double *w_, O o, double sc) {
         if (!w_) return;
 #pragma unroll
         for (int q = 0; q <= NQ; q++) wf[q] = fma_(sc, ldo(w_, o + fpos[q]), wf[q]);
@@ -733,14 +350,15 @@ __device__ __forceinline__ void phi_block_fast(const PassArgs &a, unsigned w, do
 // its theta face (j >= 1).  The two lines share the slot's own cell and u_phi
 // loads and one set of barriers.  TR: the transposed systems, row s (c_{s-1},
 // b_s, a_{s+1}).  LDS 8 doubles per thread.
-template <int PM, bool CYC, bool TR, bool PT>
+template <int PM, bool CYC, bool TR, bool PT, bool BIG>
 __device__ __forceinline__ void phi_scalar_fast(const PassArgs &a, unsigned w, double *lds) {
+  using O = Off<BIG>;
   const Geo &g = a.g;
   const Mat &m = a.m;
   const double hs = a.tau;
   const PhiChunk pc = phi_lane<PM, CYC>(g, w);
   const int T = pc.T, t = threadIdx.x, c = pc.c, s0 = pc.s0, np = g.np;
-  const unsigned N8 = 8u * (unsigned)np, F8 = 8u * (unsigned)g.npf;
+  const O N8 = 8u * (O)np, F8 = 8u * (O)g.npf;
   const int i = (int)(pc.line / (unsigned)g.nt), j = (int)pc.line - i * g.nt;
   const int im = max(i - 1, 0), jm = max(j - 1, 0);
   double ra[2][PM], rb[2][PM], rc[2][PM], rr[2][PM];
@@ -764,13 +382,13 @@ __device__ __forceinline__ void phi_scalar_fast(const PassArgs &a, unsigned w, d
     double P[3][NQ], Te[3][NQ];
 #pragma unroll
     for (int z = 0; z < 3; z++) {
-      const unsigned o = (z == 0 ? l0 : z == 1 ? li : lj) * N8;
+      const O o = (z == 0 ? l0 : z == 1 ? li : lj) * N8;
 #pragma unroll
       for (int q = 0; q < NQ; q++) P[z][q] = ldo(Pp, o + pos[q]);
 #pragma unroll
       for (int q = 0; q < NQ; q++) Te[z][q] = ldo(Tp, o + pos[q]);
     }
-    const unsigned oT = (unsigned)(i * (g.nt + 1) + j) * N8;
+    const O oT = (unsigned)(i * (g.nt + 1) + j) * N8;
 #pragma unroll
     for (int q = 0; q < PM; q++) rr[0][q] = ldo(a.rhs.ur, l0 * N8 + pos[q + X]);
 #pragma unroll
@@ -947,7 +565,7 @@ __host__ __device__ inline unsigned phi_fast_wgs(const Geo &g, int pm, unsigned 
 // PART 0: the block lines; 1: the scalar lines; 2: both, the block lines in the
 // first half of the workgroups.  COMB: workgroups numbered as for PART 2
 // whatever the part (a batched launch's member table counts both halves).
-template <int PM, int PART, bool CYC, bool TR, bool W, bool PT, bool COMB>
+template <int PM, int PART, bool CYC, bool TR, bool W, bool PT, bool COMB, bool BIG>
 __device__ __forceinline__ void phi_fast_body(const PassArgs &a, unsigned w, double *lds) {
   const Geo &g = a.g;
   const unsigned nbw = PART == 2 || COMB ? phi_fast_wgs(g, PM, blockDim.x) : 0u;
@@ -969,114 +587,33 @@ __device__ __forceinline__ void phi_fast_body(const PassArgs &a, unsigned w, dou
           if (!CYC && pc.c == 0) x.uf[idx_f(g, i, j, 0)] = 0.0;
         }
       }
-      phi_block_fast<PM, CYC, TR, W, PT>(a, w, lds);
+      phi_block_fast<PM, CYC, TR, W, PT, BIG>(a, w, lds);
       return;
     }
   }
   if constexpr (PART != 0) {
     if (COMB && w < nbw) return;
-    phi_scalar_fast<PM, CYC, TR, PT>(a, PART == 2 || COMB ? w - nbw : w, lds);
+    phi_scalar_fast<PM, CYC, TR, PT, BIG>(a, PART == 2 || COMB ? w - nbw : w, lds);
   }
 }
 
-template <int PM, int PART, bool CYC, bool W, bool PT>
+template <int PM, int PART, bool CYC, bool W, bool PT, bool BIG>
 __global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_phi_fast(PassArgs a) {
   extern __shared__ double lds[];
-  phi_fast_body<PM, PART, CYC, false, W, PT, false>(a, PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x, lds);
+  phi_fast_body<PM, PART, CYC, false, W, PT, false, BIG>(a, PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x, lds);
 }
 // transposed systems (adjoint), one grid
-template <int PM, int PART, bool CYC>
+template <int PM, int PART, bool CYC, bool BIG>
 __global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_phi_fastT(PassArgs a) {
   extern __shared__ double lds[];
-  phi_fast_body<PM, PART, CYC, true, false, false, false>(
+  phi_fast_body<PM, PART, CYC, true, false, false, false, BIG>(
       a, PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x, lds);
 }
-template <int PM, int PART, bool CYC>
+template <int PM, int PART, bool CYC, bool BIG>
 __global__ void __launch_bounds__(256) DSW_OCC(PART == 1 ? 0 : 2) k_phi_fastB(PassArgs a, Batch bt) {
   extern __shared__ double lds[];
   const int mb = batch_member(bt, blockIdx.x);
-  phi_fast_body<PM, PART, CYC, false, false, false, true>(batch_args(bt, mb), blockIdx.x - bt.woff[mb], lds);
-}
-
-// one workgroup per (i, j): block line (i, j), u_r line on r-face i (i >= 1),
-// u_theta line on theta-face j (j >= 1).  Flat grid of nr * nt workgroups per
-// grid; one grid or a batch of grids.  The workgroup may be wider than the
-// chunk count: threads past it only join the barriers.  PART 0: the block
-// line; 1: the two scalar lines (which need far fewer registers).
-// W: forced pass (wall velocities); PT: perturbation-pressure form.
-template <int PM, bool TR, int PART, bool W = false, bool PT = false>
-__device__ __forceinline__ void phi_body(const PassArgs &a, unsigned w, double *lds) {
-  const Geo &g = a.g;
-  const int j = (int)(w % g.nt), i = (int)(w / g.nt);
-  const int t = threadIdx.x;
-  const Out &o = a.o;
-  if (PART != 1 && o.mode == 0) { // boundary-normal faces of x that no phi line owns
-    const Fields &x = o.x;
-    for (int k = t; k < g.np; k += blockDim.x) {
-      if (i == 0) x.ur[idx_r(g, 0, j, k)] = 0.0;
-      if (i == g.nr - 1) x.ur[idx_r(g, g.nr, j, k)] = 0.0;
-      if (j == 0) x.ut[idx_t(g, i, 0, k)] = 0.0;
-      if (j == g.nt - 1) x.ut[idx_t(g, i, g.nt, k)] = 0.0;
-    }
-    if (!g.periodic && t == 0) x.uf[idx_f(g, i, j, 0)] = 0.0;
-  }
-  decltype(auto) u = SrcSel<W, PT>::get(a);
-  if (PART != 1) part_block_line<PM, TR>(g, a.m, u, a.rhs, o, i, j, a.tau, lds, a.status);
-  if (PART != 0) {
-    if (i >= 1) part_scalar_line<PM, 0, TR>(g, a.m, u, a.rhs, o, i, j, a.tau, lds, a.status);
-    if (j >= 1) part_scalar_line<PM, 1, TR>(g, a.m, u, a.rhs, o, i, j, a.tau, lds, a.status);
-  }
-}
-
-// Grids whose byte offsets outgrow 32 bits (one grid or a batch; PT:
-// perturbation-pressure form, one grid).  The scalar lines of slot (i, j) read
-// the cells of slots (i - 1, j) and (i, j - 1) too: the scalar launch numbers
-// its slots XCD-contiguously.
-template <int PM, bool B, int PART>
-__global__ void __launch_bounds__(256) DSW_OCC(DSW_WAVES_PHI) k_phi_part(PassArgs a, Batch bt) {
-  extern __shared__ double lds[];
-  const unsigned w = PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;
-  if constexpr (B) {
-    const int mb = batch_member(bt, w);
-    phi_body<PM, false, PART>(batch_args(bt, mb), w - bt.woff[mb], lds);
-  } else {
-    phi_body<PM, false, PART>(a, w, lds);
-  }
-}
-template <int PM, int PART>
-__global__ void __launch_bounds__(256) DSW_OCC(DSW_WAVES_PHI) k_phi_partP(PassArgs a) {
-  extern __shared__ double lds[];
-  phi_body<PM, false, PART, false, true>(a, PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x, lds);
-}
-
-// forced split step, one grid
-template <int PM, int PART>
-__global__ void __launch_bounds__(256) DSW_OCC(DSW_WAVES_PHI) k_phi_partF(PassArgs a) {
-  extern __shared__ double lds[];
-  phi_body<PM, false, PART, true>(a, blockIdx.x, lds);
-}
-
-// transposed systems (adjoint), one grid: each chunk walks the rows of the
-// line once and forms the transposed rows from them (TrWalk, TrWalkS)
-template <int PM, int PART>
-__global__ void __launch_bounds__(256) k_phi_part_T(PassArgs a) {
-  extern __shared__ double lds[];
-  // the scalar launch numbered XCD-contiguously, as in the forward sweep
-  phi_body<PM, true, PART>(a, PART == 1 ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x, lds);
-}
-
-// block lines, then scalar lines, as two launches: the scalar launch holds a
-// fraction of the block launch's registers and runs at higher occupancy
-void launch_phi_T(int pm, const PassArgs &a, unsigned blocks, unsigned threads, size_t lds,
-                  hipStream_t st) {
-  const size_t lds_s = sizeof(double) * (size_t)(pm > 5 ? pm : 5) * threads;
-  if (pm == 2) {
-    hipLaunchKernelGGL((k_phi_part_T<2, 0>), dim3(blocks), dim3(threads), lds, st, a);
-    hipLaunchKernelGGL((k_phi_part_T<2, 1>), dim3(blocks), dim3(threads), lds_s, st, a);
-  } else {
-    hipLaunchKernelGGL((k_phi_part_T<4, 0>), dim3(blocks), dim3(threads), lds, st, a);
-    hipLaunchKernelGGL((k_phi_part_T<4, 1>), dim3(blocks), dim3(threads), lds_s, st, a);
-  }
+  phi_fast_body<PM, PART, CYC, false, false, false, true, BIG>(batch_args(bt, mb), blockIdx.x - bt.woff[mb], lds);
 }
 
 bool phi_part_supported(const Geo &g, int pm) {
@@ -1087,16 +624,6 @@ bool phi_part_supported(const Geo &g, int pm) {
 bool phi_part_equal(const Geo &g, int pm) {
   if (!phi_part_supported(g, pm)) return false;
   return !g.periodic || g.np == pm * phi_chunks(g.np, 1, pm);
-}
-
-unsigned phi_part_threads(const Geo &g, int pm) {
-  const int T = phi_chunks(g.np, g.periodic, pm);
-  return (unsigned)(((T + 63) / 64) * 64);
-}
-
-size_t phi_part_lds(const Geo &g, int pm) {
-  const int T = phi_chunks(g.np, g.periodic, pm);
-  return sizeof(double) * 24 * (size_t)T;
 }
 
 // Workgroup width of the fast kernels: the narrowest whose lanes the slots'
@@ -1115,27 +642,6 @@ unsigned phi_fast_blocks(const Geo &g, int pm, unsigned threads) { return 2 * ph
 
 size_t phi_fast_lds(unsigned threads) { return sizeof(double) * SEP_REC * (size_t)threads; }
 
-// the block lines, then the scalar lines (their LDS: the exchange and
-// reduction arrays, 5 doubles per chunk, or the staged line, PM per chunk)
-template <int PM>
-static void launch_phi_part(const PassArgs &a, const Batch &b, const dim3 &gr, const dim3 &bl, size_t lds,
-                            hipStream_t st) {
-  const size_t lds_s = sizeof(double) * 5 * (size_t)bl.x;
-  if (b.tab) {
-    hipLaunchKernelGGL((k_phi_part<PM, true, 0>), gr, bl, lds, st, a, b);
-    hipLaunchKernelGGL((k_phi_part<PM, true, 1>), gr, bl, lds_s, st, a, b);
-  } else {
-    hipLaunchKernelGGL((k_phi_part<PM, false, 0>), gr, bl, lds, st, a, b);
-    hipLaunchKernelGGL((k_phi_part<PM, false, 1>), gr, bl, lds_s, st, a, b);
-  }
-}
-
-void launch_phi_pass(int pm, const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads,
-                     size_t lds, hipStream_t st) {
-  if (pm == 2) launch_phi_part<2>(a, b, dim3(blocks), dim3(threads), lds, st);
-  else launch_phi_part<4>(a, b, dim3(blocks), dim3(threads), lds, st);
-}
-
 // From this many lanes on, the block and the scalar lines run as two launches
 // (the scalar lines need half of the block lines' registers and a third of
 // their LDS); below it one launch runs both side by side.  Measured, one launch
@@ -1144,37 +650,44 @@ void launch_phi_pass(int pm, const PassArgs &a, const Batch &b, unsigned blocks,
 // (2^20) 101 / 102; transposed 18.2 / 23.0, 38.2 / 41.6, 73.6 / 72.2, 131 / 126.
 constexpr unsigned PHI_SPLIT_LANES = 1u << 19;
 
-template <int PM, bool CYC, bool W, bool PT>
+template <int PM, bool CYC, bool W, bool PT, bool BIG>
 static void launch_phi_fast(const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads, size_t lds,
                             hipStream_t st) {
   const size_t lds_s = sizeof(double) * 8 * (size_t)threads;
   const dim3 gr(blocks), half(blocks / 2), bl(threads);
   if (b.tab) {
     if constexpr (!W && !PT) {
-      if ((unsigned long)blocks * threads < PHI_SPLIT_LANES) {
-        hipLaunchKernelGGL((k_phi_fastB<PM, 2, CYC>), gr, bl, lds, st, a, b);
+      if (!BIG && (unsigned long)blocks * threads < PHI_SPLIT_LANES) {
+        hipLaunchKernelGGL((k_phi_fastB<PM, 2, CYC, false>), gr, bl, lds, st, a, b);
       } else {
-        hipLaunchKernelGGL((k_phi_fastB<PM, 0, CYC>), gr, bl, lds, st, a, b);
-        hipLaunchKernelGGL((k_phi_fastB<PM, 1, CYC>), gr, bl, lds_s, st, a, b);
+        hipLaunchKernelGGL((k_phi_fastB<PM, 0, CYC, BIG>), gr, bl, lds, st, a, b);
+        hipLaunchKernelGGL((k_phi_fastB<PM, 1, CYC, BIG>), gr, bl, lds_s, st, a, b);
       }
     }
-  } else if ((unsigned long)blocks * threads < PHI_SPLIT_LANES) {
-    hipLaunchKernelGGL((k_phi_fast<PM, 2, CYC, W, PT>), gr, bl, lds, st, a);
+  } else if (!BIG && (unsigned long)blocks * threads < PHI_SPLIT_LANES) {
+    hipLaunchKernelGGL((k_phi_fast<PM, 2, CYC, W, PT, false>), gr, bl, lds, st, a);
   } else {
-    hipLaunchKernelGGL((k_phi_fast<PM, 0, CYC, W, PT>), half, bl, lds, st, a);
-    hipLaunchKernelGGL((k_phi_fast<PM, 1, CYC, false, PT>), half, bl, lds_s, st, a);
+    hipLaunchKernelGGL((k_phi_fast<PM, 0, CYC, W, PT, BIG>), half, bl, lds, st, a);
+    hipLaunchKernelGGL((k_phi_fast<PM, 1, CYC, false, PT, BIG>), half, bl, lds_s, st, a);
   }
+}
+
+template <int PM, bool CYC, bool W, bool PT>
+static void launch_phi_fast_o(const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads, size_t lds,
+                              hipStream_t st) {
+  if (b.tab ? b.big : !off32_ok(a.g)) launch_phi_fast<PM, CYC, W, PT, true>(a, b, blocks, threads, lds, st);
+  else launch_phi_fast<PM, CYC, W, PT, false>(a, b, blocks, threads, lds, st);
 }
 
 template <bool W, bool PT>
 static void launch_phi_fast_pm(int pm, bool periodic, const PassArgs &a, const Batch &b, unsigned blocks,
                                unsigned threads, size_t lds, hipStream_t st) {
   if (pm == 2) {
-    if (periodic) launch_phi_fast<2, true, W, PT>(a, b, blocks, threads, lds, st);
-    else launch_phi_fast<2, false, W, PT>(a, b, blocks, threads, lds, st);
+    if (periodic) launch_phi_fast_o<2, true, W, PT>(a, b, blocks, threads, lds, st);
+    else launch_phi_fast_o<2, false, W, PT>(a, b, blocks, threads, lds, st);
   } else {
-    if (periodic) launch_phi_fast<4, true, W, PT>(a, b, blocks, threads, lds, st);
-    else launch_phi_fast<4, false, W, PT>(a, b, blocks, threads, lds, st);
+    if (periodic) launch_phi_fast_o<4, true, W, PT>(a, b, blocks, threads, lds, st);
+    else launch_phi_fast_o<4, false, W, PT>(a, b, blocks, threads, lds, st);
   }
 }
 
@@ -1188,61 +701,41 @@ void launch_phi_pert_c(int pm, bool periodic, const PassArgs &a, unsigned blocks
   launch_phi_fast_pm<false, true>(pm, periodic, a, Batch{nullptr, nullptr, 0}, blocks, threads, lds, st);
 }
 
-void launch_phi_pert(int pm, const PassArgs &a, unsigned blocks, unsigned threads, size_t lds,
-                     hipStream_t st) {
-  const dim3 gr(blocks), bl(threads);
-  const size_t lds_s = sizeof(double) * 5 * (size_t)threads;
-  if (pm == 2) {
-    hipLaunchKernelGGL((k_phi_partP<2, 0>), gr, bl, lds, st, a);
-    hipLaunchKernelGGL((k_phi_partP<2, 1>), gr, bl, lds_s, st, a);
-  } else {
-    hipLaunchKernelGGL((k_phi_partP<4, 0>), gr, bl, lds, st, a);
-    hipLaunchKernelGGL((k_phi_partP<4, 1>), gr, bl, lds_s, st, a);
-  }
-}
-
 // transposed: as the plain pass
-template <int PM, bool CYC>
+template <int PM, bool CYC, bool BIG>
 static void launch_phi_fast_T(const PassArgs &a, unsigned blocks, unsigned threads, hipStream_t st) {
   const size_t lds = phi_fast_lds(threads), lds_s = sizeof(double) * 8 * (size_t)threads;
-  if ((unsigned long)blocks * threads < PHI_SPLIT_LANES) {
-    hipLaunchKernelGGL((k_phi_fastT<PM, 2, CYC>), dim3(blocks), dim3(threads), lds, st, a);
+  if (!BIG && (unsigned long)blocks * threads < PHI_SPLIT_LANES) {
+    hipLaunchKernelGGL((k_phi_fastT<PM, 2, CYC, false>), dim3(blocks), dim3(threads), lds, st, a);
     return;
   }
-  hipLaunchKernelGGL((k_phi_fastT<PM, 0, CYC>), dim3(blocks / 2), dim3(threads), lds, st, a);
-  hipLaunchKernelGGL((k_phi_fastT<PM, 1, CYC>), dim3(blocks / 2), dim3(threads), lds_s, st, a);
+  hipLaunchKernelGGL((k_phi_fastT<PM, 0, CYC, BIG>), dim3(blocks / 2), dim3(threads), lds, st, a);
+  hipLaunchKernelGGL((k_phi_fastT<PM, 1, CYC, BIG>), dim3(blocks / 2), dim3(threads), lds_s, st, a);
 }
 
-void launch_phi_T_c(int pm, const PassArgs &a, hipStream_t st) {
-  const unsigned th = phi_fast_threads(a.g, pm), nb = phi_fast_blocks(a.g, pm, th);
-  if (pm == 2) {
-    if (a.g.periodic) launch_phi_fast_T<2, true>(a, nb, th, st);
-    else launch_phi_fast_T<2, false>(a, nb, th, st);
+template <int PM>
+static void launch_phi_T_pm(const PassArgs &a, hipStream_t st) {
+  const unsigned th = phi_fast_threads(a.g, PM), nb = phi_fast_blocks(a.g, PM, th);
+  const bool big = !off32_ok(a.g);
+  if (a.g.periodic) {
+    if (big) launch_phi_fast_T<PM, true, true>(a, nb, th, st);
+    else launch_phi_fast_T<PM, true, false>(a, nb, th, st);
   } else {
-    if (a.g.periodic) launch_phi_fast_T<4, true>(a, nb, th, st);
-    else launch_phi_fast_T<4, false>(a, nb, th, st);
+    if (big) launch_phi_fast_T<PM, false, true>(a, nb, th, st);
+    else launch_phi_fast_T<PM, false, false>(a, nb, th, st);
   }
 }
+void launch_phi_T_c(int pm, const PassArgs &a, hipStream_t st) {
+  if (pm == 2) launch_phi_T_pm<2>(a, st);
+  else launch_phi_T_pm<4>(a, st);
+}
 
-// forced: as the plain pass; one slot per workgroup through the general source
-// where byte offsets outgrow 32 bits
+// forced: as the plain pass
 void launch_phi_forced(int pm, const PassArgs &a, hipStream_t st) {
   const Geo &g = a.g;
-  if (off32_ok(g)) {
-    const unsigned th = phi_fast_threads(g, pm);
-    launch_phi_fast_pm<true, false>(pm, g.periodic != 0, a, Batch{nullptr, nullptr, 0}, phi_fast_blocks(g, pm, th), th,
-                                    phi_fast_lds(th), st);
-    return;
-  }
-  const dim3 gr((unsigned)g.nr * (unsigned)g.nt), bl(phi_part_threads(g, pm));
-  const size_t lds = phi_part_lds(g, pm), lds_s = sizeof(double) * (size_t)(pm > 5 ? pm : 5) * bl.x;
-  if (pm == 2) {
-    hipLaunchKernelGGL((k_phi_partF<2, 0>), gr, bl, lds, st, a);
-    hipLaunchKernelGGL((k_phi_partF<2, 1>), gr, bl, lds_s, st, a);
-  } else {
-    hipLaunchKernelGGL((k_phi_partF<4, 0>), gr, bl, lds, st, a);
-    hipLaunchKernelGGL((k_phi_partF<4, 1>), gr, bl, lds_s, st, a);
-  }
+  const unsigned th = phi_fast_threads(g, pm);
+  launch_phi_fast_pm<true, false>(pm, g.periodic != 0, a, Batch{nullptr, nullptr, 0}, phi_fast_blocks(g, pm, th), th,
+                                  phi_fast_lds(th), st);
 }
 
 } // namespace dsw

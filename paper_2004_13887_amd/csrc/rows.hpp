@@ -60,30 +60,6 @@ __device__ __forceinline__ void mv3(const double *A, const double *x, double *y)
   for (int r = 0; r < 3; r++) y[r] = A[r * 3] * x[0] + A[r * 3 + 1] * x[1] + A[r * 3 + 2] * x[2];
 }
 
-// B -= A * P and y -= A * x, each product rounded as mm3 / mv3 round it;
-// A <- -(A * P) in place, a row at a time.  The reductions use these to keep
-// few registers live beside the rows they carry.
-__device__ __forceinline__ void mm3_sub(const double *A, const double *P, double *B) {
-#pragma unroll
-  for (int r = 0; r < 3; r++)
-#pragma unroll
-    for (int c = 0; c < 3; c++) B[r * 3 + c] -= A[r * 3] * P[c] + A[r * 3 + 1] * P[3 + c] + A[r * 3 + 2] * P[6 + c];
-}
-__device__ __forceinline__ void mv3_sub(const double *A, const double *x, double *y) {
-#pragma unroll
-  for (int r = 0; r < 3; r++) y[r] -= A[r * 3] * x[0] + A[r * 3 + 1] * x[1] + A[r * 3 + 2] * x[2];
-}
-__device__ __forceinline__ void mm3_neg_inplace(double *A, const double *P) {
-#pragma unroll
-  for (int r = 0; r < 3; r++) {
-    double t[3];
-#pragma unroll
-    for (int c = 0; c < 3; c++) t[c] = A[r * 3] * P[c] + A[r * 3 + 1] * P[3 + c] + A[r * 3 + 2] * P[6 + c];
-#pragma unroll
-    for (int c = 0; c < 3; c++) A[r * 3 + c] = -t[c];
-  }
-}
-
 // Structural non-zeros of the blocks that block_row assembles: bit 3r + c is
 // set where entry (r, c) can be non-zero (unknowns p, T, w).  The lower block
 // couples the p and T rows to p, T and w of the row before, the w row to w
@@ -93,15 +69,6 @@ __device__ __forceinline__ void mm3_neg_inplace(double *A, const double *P) {
 constexpr unsigned NZ_ALL = 0x1FFu;
 constexpr unsigned NZ_L = 0x137u;  // (0,0) (0,1) (0,2) (1,1) (1,2) (2,2)
 constexpr unsigned NZ_U = 0x153u;  // (0,0) (0,1) (1,1) (2,0) (2,2)
-// mask of the transposed block
-__host__ __device__ constexpr unsigned nz_tr(unsigned m) {
-  unsigned t = 0;
-  for (int r = 0; r < 3; r++)
-    for (int c = 0; c < 3; c++)
-      if ((m >> (r * 3 + c)) & 1u) t |= 1u << (c * 3 + r);
-  return t;
-}
-
 // a0 b0 + a1 b1 + a2 b2 over the terms present (p0, p1, p2), rounded as
 // mm3 and mv3 round the full sum under FMA contraction,
 // fma(a2, b2, fma(a0, b0, a1 b1)): dropping a term whose factor is zero
@@ -378,40 +345,6 @@ __device__ __forceinline__ void scalar_row(const Geo &g, const Mat &m, const S &
   R.r = arr[xi];
 }
 
-
-// Forward elimination of one chunk of a scalar line (partitioned solvers):
-// rows a0 .. a0 + len - 2 with the left spike, x_q = Y_q - C_q x_{q+1} -
-// E_q x_left, and the chunk's last row (the separator) into S.  Every row of
-// the chunk is assembled first, without a branch (rows past the chunk's end
-// repeat its last row, clamped into the line; their results are not used),
-// so that the loads of all its rows are in flight together: a row assembled
-// under a branch on the chunk length waits for the previous row's
-// elimination before its loads issue.  row(s, R) assembles row s.  Returns
-// whether an eliminated row had a zero pivot.
-template <int PM, class RowFn>
-__device__ __forceinline__ bool scalar_chunk_fwd(const RowFn &row, int a0, int len, int n, double *Cm,
-                                                 double *Em, double *Ym, SRow &S) {
-  const int rl = min(a0 + max(len - 1, 0), n - 1);
-  SRow R[PM];
-#pragma unroll
-  for (int q = 0; q < PM; q++) row(min(a0 + q, rl), R[q]);
-  bool sing = false;
-#pragma unroll
-  for (int q = 0; q < PM - 1; q++) {
-    double dp = R[q].b, rr = R[q].r, lx = R[q].a;
-    if (q > 0) { dp -= R[q].a * Cm[q - 1]; rr -= R[q].a * Ym[q - 1]; lx = -R[q].a * Em[q - 1]; }
-    sing |= q < len - 1 && !(dp != 0.0);
-    const double id = rcp_nr(dp);
-    Cm[q] = R[q].c * id;
-    Ym[q] = rr * id;
-    Em[q] = lx * id;
-  }
-#pragma unroll
-  for (int q = 0; q < PM; q++)
-    if (q == len - 1) S = R[q];
-  return sing;
-}
-
 // Row s of the line system, or of its transpose (TR): the transposed row s
 // has lower block U_{s-1}^T, diagonal D_s^T and upper block L_{s+1}^T, and
 // the right-hand side read at row s's unknowns.
@@ -450,57 +383,6 @@ __device__ __forceinline__ void get_brow(const Geo &g, const Mat &m, const SrcOn
   }
 }
 
-// The rows of the transposed line in increasing order s0, s0 + 1, ...,
-// assembling each row of the line once: the walker keeps U_{s-1}, D_s, U_s
-// and b_s, and next() assembles row s + 1 for L_{s+1}.
-template <int D>
-struct TrWalk {
-  double Up[9], Dc[9], Uc[9], bc[3];
-  int s;
-  __device__ __forceinline__ void init(const Geo &g, const Mat &m, const SrcOne &u, const Fields &rhs,
-                                       int a, int b, int s0, int n, int cyc, double hs) {
-    BRow R;
-    if (cyc || s0 > 0) {
-      block_row<D>(g, m, u, rhs, a, b, s0 > 0 ? s0 - 1 : n - 1, n, cyc, hs, R);
-#pragma unroll
-      for (int q = 0; q < 9; q++) Up[q] = R.U[q];
-    } else {
-#pragma unroll
-      for (int q = 0; q < 9; q++) Up[q] = 0.0;
-    }
-    block_row<D>(g, m, u, rhs, a, b, s0, n, cyc, hs, R);
-#pragma unroll
-    for (int q = 0; q < 9; q++) { Dc[q] = R.D[q]; Uc[q] = R.U[q]; }
-#pragma unroll
-    for (int q = 0; q < 3; q++) bc[q] = R.b[q];
-    s = s0;
-  }
-  // transposed row s into T, then advance to s + 1
-  __device__ __forceinline__ void next(const Geo &g, const Mat &m, const SrcOne &u, const Fields &rhs,
-                                       int a, int b, int n, int cyc, double hs, BRow &T) {
-    BRow R;
-    const bool has_p = cyc || s < n - 1;
-    if (has_p) {
-      block_row<D>(g, m, u, rhs, a, b, s < n - 1 ? s + 1 : 0, n, cyc, hs, R);
-    } else {
-#pragma unroll
-      for (int q = 0; q < 9; q++) { R.L[q] = 0.0; R.D[q] = 0.0; R.U[q] = 0.0; }
-#pragma unroll
-      for (int q = 0; q < 3; q++) R.b[q] = 0.0;
-    }
-    tr3(Up, T.L);
-    tr3(Dc, T.D);
-    tr3(R.L, T.U);
-#pragma unroll
-    for (int q = 0; q < 3; q++) T.b[q] = bc[q];
-#pragma unroll
-    for (int q = 0; q < 9; q++) { Up[q] = Uc[q]; Dc[q] = R.D[q]; Uc[q] = R.U[q]; }
-#pragma unroll
-    for (int q = 0; q < 3; q++) bc[q] = R.b[q];
-    s++;
-  }
-};
-
 template <int D, int FAM, bool TR>
 __device__ __forceinline__ void get_srow(const Geo &g, const Mat &m, const SrcOne &u,
                                          const Fields &rhs, int a, int b, int s, int n, int cyc,
@@ -522,38 +404,6 @@ __device__ __forceinline__ void get_srow(const Geo &g, const Mat &m, const SrcOn
   R.a = lo;
   R.c = up;
 }
-
-// The scalar counterpart of TrWalk: transposed row s is (c_{s-1}, b_s,
-// a_{s+1}) with the right-hand side r_s.
-template <int D, int FAM>
-struct TrWalkS {
-  double cp, bc, cc, rc;
-  int s;
-  __device__ __forceinline__ void init(const Geo &g, const Mat &m, const SrcOne &u, const Fields &rhs,
-                                       int a, int b, int s0, int n, int cyc, double hs) {
-    SRow Q;
-    long xq;
-    double *aq;
-    cp = 0.0;
-    if (cyc || s0 > 0) {
-      scalar_row<D, FAM>(g, m, u, rhs, a, b, s0 > 0 ? s0 - 1 : n - 1, n, cyc, hs, Q, xq, aq);
-      cp = Q.c;
-    }
-    scalar_row<D, FAM>(g, m, u, rhs, a, b, s0, n, cyc, hs, Q, xq, aq);
-    bc = Q.b; cc = Q.c; rc = Q.r;
-    s = s0;
-  }
-  __device__ __forceinline__ void next(const Geo &g, const Mat &m, const SrcOne &u, const Fields &rhs,
-                                       int a, int b, int n, int cyc, double hs, SRow &T) {
-    SRow Q{0.0, 0.0, 0.0, 0.0};
-    long xq;
-    double *aq;
-    if (cyc || s < n - 1) scalar_row<D, FAM>(g, m, u, rhs, a, b, s < n - 1 ? s + 1 : 0, n, cyc, hs, Q, xq, aq);
-    T.a = cp; T.b = bc; T.c = Q.a; T.r = rc;
-    cp = cc; bc = Q.b; cc = Q.c; rc = Q.r;
-    s++;
-  }
-};
 
 __device__ __forceinline__ double *fsel(const Fields &f, int fid) {
   return fid == F_P ? f.p : fid == F_UR ? f.ur : fid == F_UT ? f.ut : fid == F_UF ? f.uf : f.T;

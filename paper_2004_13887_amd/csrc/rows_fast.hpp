@@ -12,21 +12,28 @@
 // separator whatever its length.
 #pragma once
 
+#include <type_traits>
+
 #include "rows.hpp"
 
 namespace dsw {
 
 // a load at a byte offset from a uniform base: base in scalar registers, one
-// 32-bit offset register for any number of arrays of the same layout
-__device__ __forceinline__ double ldo(const double *base, unsigned off) {
+// 32-bit offset register for any number of arrays of the same layout (O:
+// unsigned), or a 64-bit offset on grids whose arrays reach 4 GiB (size_t)
+template <class O>
+__device__ __forceinline__ double ldo(const double *base, O off) {
   return *(const double *)((const char *)base + off);
 }
 __device__ __forceinline__ double2 ldo2(const double *base, unsigned off) {
   return *(const double2 *)((const char *)base + off);
 }
-__device__ __forceinline__ void sto(double *base, unsigned off, double v) {
+template <class O>
+__device__ __forceinline__ void sto(double *base, O off, double v) {
   *(double *)((char *)base + off) = v;
 }
+template <bool BIG>
+using Off = std::conditional_t<BIG, size_t, unsigned>;
 
 __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 

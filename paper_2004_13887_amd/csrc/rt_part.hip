@@ -18,8 +18,9 @@
 // pass moves one read of its inputs and one write of its result.
 //
 // Every input of a chunk is loaded before its first row is eliminated, byte
-// offsets are 32-bit from uniform bases, metric factors come from per-row
-// tables, and no row stands under a branch.  Assembling a row at a time under
+// offsets are 32-bit from uniform bases (64-bit on grids whose arrays reach 4 GiB,
+// BIG: 128 x 4100 x 1024 cells r 30.7 ms, two-ended 39.8), metric factors come
+// from per-row tables, and no row stands under a branch.  Assembling a row at a time under
 // a branch on the chunk's length spent half of the instructions on addresses,
 // ghost cases and register moves, and one memory latency per row.  Line
 // solves, a row at a time against this form: 512 x 256 x 128
@@ -49,9 +50,11 @@ __host__ __device__ inline int rt_chunks(int n) { return (n + PM - 1) / PM; }
 // TR: the transposed systems (adjoint), whose rows take blocks of the rows on
 // either side, so a chunk loads one more row at each end; W: a forced pass,
 // whose ghosts across a wall are 2 g - u (the r lines read none); PT:
-// perturbation-pressure form.  Byte offsets in 32 bits (off32_ok).
-template <int D, int PM, bool TR, bool W, bool PT>
+// perturbation-pressure form.  Byte offsets in 32 bits (off32_ok), or in
+// 64 (BIG).
+template <int D, int PM, bool TR, bool W, bool PT, bool BIG>
 __device__ __forceinline__ void rt_block_lines(const PassArgs &a, unsigned line0, double *lds) {
+  using O = Off<BIG>;
   const Geo &g = a.g;
   const Mat &m = a.m;
   const double hs = a.tau;
@@ -69,12 +72,12 @@ __device__ __forceinline__ void rt_block_lines(const PassArgs &a, unsigned line0
     else a.o.x.ut[idx_t(g, pa, 0, k)] = 0.0;
   }
   // byte offsets of row 0 and row strides; the phi face after the cell
-  const unsigned sC = 8u * (unsigned)(D == 0 ? g.nt * g.np : g.np);
-  const unsigned sT = 8u * (unsigned)(D == 0 ? (g.nt + 1) * g.np : g.np);
-  const unsigned sF = 8u * (unsigned)(D == 0 ? g.nt * g.npf : g.npf);
-  const unsigned oC = 8u * (unsigned)(D == 0 ? pa * g.np + k : pa * g.nt * g.np + k);
-  const unsigned oT = 8u * (unsigned)(D == 0 ? pa * g.np + k : pa * (g.nt + 1) * g.np + k);
-  const unsigned oF = 8u * (unsigned)(D == 0 ? pa * g.npf + k : pa * g.nt * g.npf + k);
+  const O sC = 8u * (D == 0 ? (O)g.nt * g.np : (O)g.np);
+  const O sT = 8u * (D == 0 ? (O)(g.nt + 1) * g.np : (O)g.np);
+  const O sF = 8u * (D == 0 ? (O)g.nt * g.npf : (O)g.npf);
+  const O oC = 8u * ((D == 0 ? (O)pa * g.np : (O)(pa * g.nt) * g.np) + k);
+  const O oT = 8u * ((D == 0 ? (O)pa * g.np : (O)(pa * (g.nt + 1)) * g.np) + k);
+  const O oF = 8u * ((D == 0 ? (O)pa * g.npf : (O)(pa * g.nt) * g.npf) + k);
   const int dF = 8 * (g.periodic && k == g.np - 1 ? 1 - g.np : 1);
   const double *u_r = a.u.a[F_UR], *u_t = a.u.a[F_UT], *u_f = a.u.a[F_UF];
   const double *mt = D == 0 ? a.mr : a.mt;
@@ -97,7 +100,7 @@ __device__ __forceinline__ void rt_block_lines(const PassArgs &a, unsigned line0
 #pragma unroll
       for (int q = 0; q <= NQ; q++) uw[q] = ldo(u_t, oT + face(q - X) * sT);
     }
-    const unsigned up = 8u * (unsigned)(g.nt * g.np);  // one r plane of u_r
+    const O up = 8u * (O)g.nt * g.np;  // one r plane of u_r
     double va[NQ + 2];  // D 1: the centre-averaged u_r of the rows and one more at each end
     double tim[NQ + 1], tip[NQ + 1];  // D 1: u_theta on the planes i - 1, i + 1
     if constexpr (D == 1) {
@@ -105,7 +108,7 @@ __device__ __forceinline__ void rt_block_lines(const PassArgs &a, unsigned line0
 #pragma unroll
       for (int q = 0; q < NQ + 2; q++) {
         const int s = s0 + q - 1 - X;
-        const unsigned o = oC + (unsigned)min(max(s, 0), n - 1) * sC;
+        const O o = oC + (unsigned)min(max(s, 0), n - 1) * sC;
         const double v = 0.5 * (ldo(u_r, o) + ldo(u_r, o + up));
         va[q] = s < 0 ? sgl * v : (s >= n ? sgh * v : v);
         if constexpr (W) {
@@ -113,12 +116,12 @@ __device__ __forceinline__ void rt_block_lines(const PassArgs &a, unsigned line0
           if (w) va[q] += w[(long)pa * g.np + k] + w[(long)(pa + 1) * g.np + k];
         }
       }
-      const unsigned pT = 8u * (unsigned)((g.nt + 1) * g.np);
+      const O pT = 8u * (O)(g.nt + 1) * g.np;
       const bool lo = pa == 0, hi = pa == g.nr - 1;
-      const unsigned om = lo ? oT : oT - pT, op = hi ? oT : oT + pT;
+      const O om = lo ? oT : oT - pT, op = hi ? oT : oT + pT;
 #pragma unroll
       for (int q = 0; q <= NQ; q++) {
-        const unsigned ro = face(q - X) * sT;
+        const O ro = face(q - X) * sT;
         const double x = ldo(u_t, om + ro), y = ldo(u_t, op + ro);
         tim[q] = lo ? -x : x;
         tip[q] = hi ? -y : y;
@@ -131,9 +134,9 @@ __device__ __forceinline__ void rt_block_lines(const PassArgs &a, unsigned line0
     }
 #pragma unroll
     for (int q = 0; q < NQ; q++) {
-      const unsigned s = row(q - X), o = oC + s * sC;
-      const unsigned of = oF + s * sF;
-      const double f0 = ldo(u_f, of), f1 = ldo(u_f, of + (unsigned)dF);
+      const unsigned s = row(q - X);
+      const O o = oC + s * sC, of = oF + s * sF;
+      const double f0 = ldo(u_f, of), f1 = ldo(u_f, of + (O)dF);
       P[q] = ldo(a.u.a[F_P], o);
       Te[q] = ldo(a.u.a[F_T], o);
       if (q >= X && q < PM + X) {
@@ -142,7 +145,7 @@ __device__ __forceinline__ void rt_block_lines(const PassArgs &a, unsigned line0
         b2[q - X] = D == 0 ? ldo(a.rhs.ur, o + sC) : ldo(a.rhs.ut, oT + s * sT + sT);
       }
       if constexpr (D == 0) {
-        const unsigned ot = oT + s * sT;
+        const O ot = oT + s * sT;
         const double t0 = ldo(u_t, ot), t1 = ldo(u_t, ot + 8u * (unsigned)g.np), ir = ldo(mt, 64u * s + 40u);
         const double ur = 0.5 * (uw[q] + uw[q + 1]), ut = 0.5 * (t0 + t1);
         const double gg = ((t1 - t0) * g.idt + 2.0 * ur + (f1 - f0) * (isk * g.idp) + ut * ctk) * ir;  // Gtt + Gff
@@ -167,7 +170,8 @@ __device__ __forceinline__ void rt_block_lines(const PassArgs &a, unsigned line0
       P[q] += m.pinf;
     }
     {
-      const unsigned s = (unsigned)min(s0 + PM + X, n - 1), o = oC + s * sC;
+      const unsigned s = (unsigned)min(s0 + PM + X, n - 1);
+      const O o = oC + s * sC;
       P[NQ] = ldo(a.u.a[F_P], o);
       Te[NQ] = ldo(a.u.a[F_T], o);
       if constexpr (PT) P[NQ] += a.pref[D == 0 ? (int)s : pa];
@@ -284,7 +288,7 @@ __device__ __forceinline__ void rt_block_lines(const PassArgs &a, unsigned line0
     double v[3];
     if (q < PM - 1) ch.fill(q, xl, xs, v);
     else { v[0] = xs[0]; v[1] = xs[1]; v[2] = xs[2]; }
-    const unsigned o = oC + (unsigned)s * sC;
+    const O o = oC + (unsigned)s * sC;
     sto(a.o.x.p, o, v[0]);
     sto(a.o.x.T, o, v[1]);
     if (D == 0) sto(a.o.x.ur, o + sC, v[2]);
@@ -301,8 +305,9 @@ __device__ __forceinline__ void rt_block_lines(const PassArgs &a, unsigned line0
 // their ends (fillers: a = -1, b = 1, c = 0, r = 0), as on the block lines.
 // TR: the transposed systems, row s (c_{s-1}, b_s, a_{s+1}).  LDS 4 doubles per
 // thread; mode 0.
-template <int D, int PM, bool TR, bool PT>
+template <int D, int PM, bool TR, bool PT, bool BIG>
 __device__ __forceinline__ void rt_scalar_lines(const PassArgs &a, int fam, unsigned line0, double *lds) {
+  using O = Off<BIG>;
   const Geo &g = a.g;
   const Mat &m = a.m;
   const double hs = a.tau;
@@ -315,37 +320,37 @@ __device__ __forceinline__ void rt_scalar_lines(const PassArgs &a, int fam, unsi
   const int cc = min(c, T - 1), s0 = cc * PM - pad;
   const int k = (int)(line - q0 * wid) + (fam == 0 || g.periodic ? 0 : 1), pa = (int)q0 + (fam == 0 ? 1 : 0);
   // cells A and B (before and after the face), velocity columns A and B, output
-  const unsigned N = (unsigned)g.np;
-  unsigned oA, oB, vA, vB, oX;
-  const unsigned sC = 8u * (D == 0 ? (unsigned)g.nt * N : N);
-  const unsigned sV = 8u * (D == 0 ? (unsigned)g.nt * N : N);
-  unsigned sX;
+  const O N = (O)g.np;
+  O oA, oB, vA, vB, oX;
+  const O sC = 8u * (D == 0 ? (O)g.nt * N : N);
+  const O sV = 8u * (D == 0 ? (O)g.nt * N : N);
+  O sX;
   double *X;
   const double *Rh;
   if (fam == 0) {
     if (D == 0) {  // u_theta on theta face pa: cells (., pa - 1, k), (., pa, k)
-      oB = 8u * ((unsigned)pa * N + k);
+      oB = 8u * ((O)pa * N + k);
       oA = oB - 8u * N;
       vA = oA; vB = oB; oX = oB;
-      sX = 8u * (unsigned)(g.nt + 1) * N;
+      sX = 8u * (O)(g.nt + 1) * N;
       X = a.o.x.ut; Rh = a.rhs.ut;
     } else {  // u_r on r face pa: cells (pa - 1, ., k), (pa, ., k)
-      oB = 8u * ((unsigned)(pa * g.nt) * N + k);
-      oA = oB - 8u * (unsigned)g.nt * N;
-      vB = 8u * ((unsigned)(pa * (g.nt + 1)) * N + k);
-      vA = vB - 8u * (unsigned)(g.nt + 1) * N;
+      oB = 8u * ((O)(pa * g.nt) * N + k);
+      oA = oB - 8u * (O)g.nt * N;
+      vB = 8u * ((O)(pa * (g.nt + 1)) * N + k);
+      vA = vB - 8u * (O)(g.nt + 1) * N;
       oX = oB;
       sX = sC;
       X = a.o.x.ur; Rh = a.rhs.ur;
     }
   } else {  // u_phi on phi face k: cells (., k - 1), (., k)
     const int k1 = g.periodic && k == 0 ? g.np - 1 : k - 1;
-    const unsigned ro = D == 0 ? (unsigned)pa * N : (unsigned)(pa * g.nt) * N;
+    const O ro = D == 0 ? (O)pa * N : (O)(pa * g.nt) * N;
     oA = 8u * (ro + k1); oB = 8u * (ro + k);
-    const unsigned vo = D == 0 ? ro : (unsigned)(pa * (g.nt + 1)) * N;
+    const O vo = D == 0 ? ro : (O)(pa * (g.nt + 1)) * N;
     vA = 8u * (vo + k1); vB = 8u * (vo + k);
-    oX = 8u * ((D == 0 ? (unsigned)pa * g.npf : (unsigned)(pa * g.nt) * g.npf) + k);
-    sX = 8u * (D == 0 ? (unsigned)g.nt * g.npf : (unsigned)g.npf);
+    oX = 8u * ((D == 0 ? (O)pa * g.npf : (O)(pa * g.nt) * g.npf) + k);
+    sX = 8u * (D == 0 ? (O)g.nt * g.npf : (O)g.npf);
     X = a.o.x.uf; Rh = a.rhs.uf;
   }
   const double *V = a.u.a[D == 0 ? F_UR : F_UT], *mt = D == 0 ? a.mr : a.mt;
@@ -360,13 +365,14 @@ __device__ __forceinline__ void rt_scalar_lines(const PassArgs &a, int fam, unsi
 #pragma unroll
     for (int q = 0; q <= NQ; q++) {
       const int f = s0 + q - X;
-      const unsigned o = (unsigned)(TR ? min(max(f, 0), n) : max(f, 0)) * sV;
+      const O o = (unsigned)(TR ? min(max(f, 0), n) : max(f, 0)) * sV;
       vs[q] = ldo(V, vA + o) + ldo(V, vB + o);
     }
 #pragma unroll
     for (int z = 0; z < NQ; z++) {
       const int q = z - X, s = s0 + q;
-      const unsigned sc = (unsigned)(TR ? min(max(s, 0), n - 1) : max(s, 0)), o = sc * sC;
+      const unsigned sc = (unsigned)(TR ? min(max(s, 0), n - 1) : max(s, 0));
+      const O o = sc * sC;
       double Pa = ldo(a.u.a[F_P], oA + o), Pb = ldo(a.u.a[F_P], oB + o);
       const double Ta = ldo(a.u.a[F_T], oA + o), Tb = ldo(a.u.a[F_T], oB + o);
       if constexpr (PT) {
@@ -494,7 +500,7 @@ __host__ __device__ inline unsigned rt_scalar_wgs(const Geo &g, int d, unsigned 
 // for PART 2 whatever the part (a batched launch's member table counts both
 // kinds), those of the other part leaving at once; else PART 1 numbers the
 // scalar workgroups from 0.
-template <int D, int PM, int PART, bool W = false, bool TR = false, bool PT = false, bool COMB = false>
+template <int D, int PM, int PART, bool W = false, bool TR = false, bool PT = false, bool COMB = false, bool BIG = false>
 __device__ __forceinline__ void rt_body(const PassArgs &a, unsigned w, double *lds) {
   const Geo &g = a.g;
   const unsigned bs = blockDim.x;
@@ -502,7 +508,7 @@ __device__ __forceinline__ void rt_body(const PassArgs &a, unsigned w, double *l
   if (w < nbw) {
     if constexpr (PART != 1) {
       const unsigned L = bs / (unsigned)rt_chunks<PM>(families(g, D).n);
-      rt_block_lines<D, PM, TR, W, PT>(a, (COMB ? xcd_contiguous(w, nbw) : w) * L, lds);
+      rt_block_lines<D, PM, TR, W, PT, BIG>(a, (COMB ? xcd_contiguous(w, nbw) : w) * L, lds);
     }
     return;
   }
@@ -510,7 +516,7 @@ __device__ __forceinline__ void rt_body(const PassArgs &a, unsigned w, double *l
     const unsigned w2 = COMB ? xcd_contiguous(w - nbw, rt_scalar_wgs(g, D, bs)) : w - nbw;
     const unsigned L = bs / (unsigned)rt_chunks<RT_PMS>(families(g, D).n);
     const unsigned nwa = rt_scalar_wgs_a(g, D, bs);
-    rt_scalar_lines<D, RT_PMS, TR, PT>(a, w2 < nwa ? 0 : 1, (w2 < nwa ? w2 : w2 - nwa) * L, lds);
+    rt_scalar_lines<D, RT_PMS, TR, PT, BIG>(a, w2 < nwa ? 0 : 1, (w2 < nwa ? w2 : w2 - nwa) * L, lds);
   }
 }
 
@@ -519,37 +525,37 @@ __device__ __forceinline__ void rt_body(const PassArgs &a, unsigned w, double *l
 // neighbour cells) meet in one L2; in a batch within each member's block lines
 // and within its scalar lines (over the whole launch the XCDs would get unequal
 // shares of the two).
-template <int D, int PM, int PART, bool B>
+template <int D, int PM, int PART, bool B, bool BIG>
 __global__ void __launch_bounds__(PART == 1 ? 512 : 256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_part(PassArgs a, Batch bt) {
   extern __shared__ double lds[];
   if constexpr (B) {
     const int mb = batch_member(bt, blockIdx.x);
-    rt_body<D, PM, PART, false, false, false, true>(batch_args(bt, mb), blockIdx.x - bt.woff[mb], lds);
+    rt_body<D, PM, PART, false, false, false, true, BIG>(batch_args(bt, mb), blockIdx.x - bt.woff[mb], lds);
   } else {
-    rt_body<D, PM, PART>(a, xcd_contiguous(blockIdx.x, gridDim.x), lds);
+    rt_body<D, PM, PART, false, false, false, false, BIG>(a, xcd_contiguous(blockIdx.x, gridDim.x), lds);
   }
 }
 
 // forced theta sweep, one grid: the block lines (PART 0), or with the scalar
 // lines (2; those see no wall data, nor do the r lines)
-template <int PM, int PART>
+template <int PM, int PART, bool BIG>
 __global__ void __launch_bounds__(256) DSW_OCC(2) k_rt_partF(PassArgs a) {
   extern __shared__ double lds[];
-  rt_body<1, PM, PART, true>(a, xcd_contiguous(blockIdx.x, gridDim.x), lds);
+  rt_body<1, PM, PART, true, false, false, false, BIG>(a, xcd_contiguous(blockIdx.x, gridDim.x), lds);
 }
 
 // perturbation-pressure form, one grid
-template <int D, int PM, int PART>
+template <int D, int PM, int PART, bool BIG>
 __global__ void __launch_bounds__(PART == 1 ? 512 : 256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_partP(PassArgs a) {
   extern __shared__ double lds[];
-  rt_body<D, PM, PART, false, false, true>(a, xcd_contiguous(blockIdx.x, gridDim.x), lds);
+  rt_body<D, PM, PART, false, false, true, false, BIG>(a, xcd_contiguous(blockIdx.x, gridDim.x), lds);
 }
 
 // transposed systems (adjoint), one grid
-template <int D, int PM, int PART>
+template <int D, int PM, int PART, bool BIG>
 __global__ void __launch_bounds__(PART == 1 ? 512 : 256) DSW_OCC(PART == 1 ? 0 : 2) k_rt_partT(PassArgs a) {
   extern __shared__ double lds[];
-  rt_body<D, PM, PART, false, true>(a, xcd_contiguous(blockIdx.x, gridDim.x), lds);
+  rt_body<D, PM, PART, false, true, false, false, BIG>(a, xcd_contiguous(blockIdx.x, gridDim.x), lds);
 }
 
 // From this many workgroups on, one grid's block and scalar lines run as two
@@ -575,7 +581,7 @@ unsigned rt_scalar_threads(const Geo &g, int d, unsigned bs) {
 
 bool rt_part_supported(const Geo &g, int d, unsigned bs, int pm) {
   const Families F = families(g, d);
-  return d < 2 && pm == 4 && bs <= 256 && off32_ok(g) && rt_block_chunks(F.n, pm) <= (int)bs &&
+  return d < 2 && pm == 4 && bs <= 256 && rt_block_chunks(F.n, pm) <= (int)bs &&
          rt_chunks<RT_PMS>(F.n) <= (int)bs;
 }
 
@@ -585,35 +591,41 @@ unsigned rt_part_blocks(const Geo &g, int d, unsigned bs, int pm) {
 
 size_t rt_part_lds(unsigned bs) { return sizeof(double) * 24 * (size_t)bs; }
 
-template <int D, int PM>
+template <int D, int PM, bool BIG>
 static void launch_rt_d(const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads, hipStream_t st) {
   const size_t lds = rt_part_lds(threads), lds_s = sizeof(double) * 4 * (size_t)threads;
   if (b.tab) {
     // a batch: the members' block and scalar workgroups as two launches over
     // the same table (each leaves the other kind's workgroups at once)
-    if (blocks < RT_SPLIT_WGS) {
-      hipLaunchKernelGGL((k_rt_part<D, PM, 2, true>), dim3(blocks), dim3(threads), lds, st, a, b);
+    if (!BIG && blocks < RT_SPLIT_WGS) {
+      hipLaunchKernelGGL((k_rt_part<D, PM, 2, true, false>), dim3(blocks), dim3(threads), lds, st, a, b);
     } else {
-      hipLaunchKernelGGL((k_rt_part<D, PM, 0, true>), dim3(blocks), dim3(threads), lds, st, a, b);
-      hipLaunchKernelGGL((k_rt_part<D, PM, 1, true>), dim3(blocks), dim3(threads), lds_s, st, a, b);
+      hipLaunchKernelGGL((k_rt_part<D, PM, 0, true, BIG>), dim3(blocks), dim3(threads), lds, st, a, b);
+      hipLaunchKernelGGL((k_rt_part<D, PM, 1, true, BIG>), dim3(blocks), dim3(threads), lds_s, st, a, b);
     }
     return;
   }
-  if (blocks < RT_SPLIT_WGS) {
-    hipLaunchKernelGGL((k_rt_part<D, PM, 2, false>), dim3(blocks), dim3(threads), lds, st, a, b);
+  if (!BIG && blocks < RT_SPLIT_WGS) {
+    hipLaunchKernelGGL((k_rt_part<D, PM, 2, false, false>), dim3(blocks), dim3(threads), lds, st, a, b);
     return;
   }
   const unsigned ts = rt_scalar_threads(a.g, D, threads);
-  hipLaunchKernelGGL((k_rt_part<D, PM, 0, false>), dim3(rt_block_wgs(a.g, D, threads, PM)), dim3(threads), lds, st, a, b);
-  hipLaunchKernelGGL((k_rt_part<D, PM, 1, false>), dim3(rt_scalar_wgs(a.g, D, ts)), dim3(ts), rt_scalar_lds(ts), st, a,
+  hipLaunchKernelGGL((k_rt_part<D, PM, 0, false, BIG>), dim3(rt_block_wgs(a.g, D, threads, PM)), dim3(threads), lds, st, a, b);
+  hipLaunchKernelGGL((k_rt_part<D, PM, 1, false, BIG>), dim3(rt_scalar_wgs(a.g, D, ts)), dim3(ts), rt_scalar_lds(ts), st, a,
                      b);
 }
 
 void launch_rt_pass(int d, int pm, const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads,
                     hipStream_t st) {
   (void)pm;  // 4: the only chunk size built (8 measured slower: one wave per SIMD)
-  if (d == 0) launch_rt_d<0, 4>(a, b, blocks, threads, st);
-  else launch_rt_d<1, 4>(a, b, blocks, threads, st);
+  const bool big = b.tab ? b.big : !off32_ok(a.g);
+  if (d == 0) {
+    if (big) launch_rt_d<0, 4, true>(a, b, blocks, threads, st);
+    else launch_rt_d<0, 4, false>(a, b, blocks, threads, st);
+  } else {
+    if (big) launch_rt_d<1, 4, true>(a, b, blocks, threads, st);
+    else launch_rt_d<1, 4, false>(a, b, blocks, threads, st);
+  }
 }
 
 // The transposed theta block and scalar lines share a launch while all its
@@ -651,40 +663,52 @@ bool rt_T_two_ended(const Geo &g, unsigned bs) {
   return two <= part;
 }
 
-template <int D, int PM>
+template <int D, int PM, bool BIG>
 static void launch_rt_T_d(const PassArgs &a, unsigned threads, hipStream_t st) {
   const size_t lds = rt_part_lds(threads);
   const unsigned nbw = rt_block_wgs(a.g, D, threads, PM), nsw = rt_scalar_wgs(a.g, D, threads);
-  if (D == 0 ? nbw + nsw < RT_SPLIT_WGS : wgs256(nbw, threads) + wgs256(nsw, threads) <= RT_T_ONE_WGS) {
-    hipLaunchKernelGGL((k_rt_partT<D, PM, 2>), dim3(nbw + nsw), dim3(threads), lds, st, a);
+  if (!BIG && (D == 0 ? nbw + nsw < RT_SPLIT_WGS : wgs256(nbw, threads) + wgs256(nsw, threads) <= RT_T_ONE_WGS)) {
+    hipLaunchKernelGGL((k_rt_partT<D, PM, 2, false>), dim3(nbw + nsw), dim3(threads), lds, st, a);
     return;
   }
-  hipLaunchKernelGGL((k_rt_partT<D, PM, 0>), dim3(nbw), dim3(threads), lds, st, a);
+  hipLaunchKernelGGL((k_rt_partT<D, PM, 0, BIG>), dim3(nbw), dim3(threads), lds, st, a);
   const unsigned ts = rt_scalar_threads(a.g, D, threads);
-  hipLaunchKernelGGL((k_rt_partT<D, PM, 1>), dim3(rt_scalar_wgs(a.g, D, ts)), dim3(ts), rt_scalar_lds(ts), st, a);
+  hipLaunchKernelGGL((k_rt_partT<D, PM, 1, BIG>), dim3(rt_scalar_wgs(a.g, D, ts)), dim3(ts), rt_scalar_lds(ts), st, a);
 }
 
-template <int D, int PM>
+template <int D, int PM, bool BIG>
 static void launch_rt_pert_d(const PassArgs &a, unsigned threads, hipStream_t st) {
   const size_t lds = rt_part_lds(threads);
   const unsigned nbw = rt_block_wgs(a.g, D, threads, PM), nsw = rt_scalar_wgs(a.g, D, threads);
-  if (nbw + nsw < RT_SPLIT_WGS) {
-    hipLaunchKernelGGL((k_rt_partP<D, PM, 2>), dim3(nbw + nsw), dim3(threads), lds, st, a);
+  if (!BIG && nbw + nsw < RT_SPLIT_WGS) {
+    hipLaunchKernelGGL((k_rt_partP<D, PM, 2, false>), dim3(nbw + nsw), dim3(threads), lds, st, a);
     return;
   }
-  hipLaunchKernelGGL((k_rt_partP<D, PM, 0>), dim3(nbw), dim3(threads), lds, st, a);
+  hipLaunchKernelGGL((k_rt_partP<D, PM, 0, BIG>), dim3(nbw), dim3(threads), lds, st, a);
   const unsigned ts = rt_scalar_threads(a.g, D, threads);
-  hipLaunchKernelGGL((k_rt_partP<D, PM, 1>), dim3(rt_scalar_wgs(a.g, D, ts)), dim3(ts), rt_scalar_lds(ts), st, a);
+  hipLaunchKernelGGL((k_rt_partP<D, PM, 1, BIG>), dim3(rt_scalar_wgs(a.g, D, ts)), dim3(ts), rt_scalar_lds(ts), st, a);
 }
 
 void launch_rt_pert(int d, const PassArgs &a, unsigned threads, hipStream_t st) {
-  if (d == 0) launch_rt_pert_d<0, 4>(a, threads, st);
-  else launch_rt_pert_d<1, 4>(a, threads, st);
+  const bool big = !off32_ok(a.g);
+  if (d == 0) {
+    if (big) launch_rt_pert_d<0, 4, true>(a, threads, st);
+    else launch_rt_pert_d<0, 4, false>(a, threads, st);
+  } else {
+    if (big) launch_rt_pert_d<1, 4, true>(a, threads, st);
+    else launch_rt_pert_d<1, 4, false>(a, threads, st);
+  }
 }
 
 void launch_rt_T(int d, const PassArgs &a, unsigned threads, hipStream_t st) {
-  if (d == 0) launch_rt_T_d<0, 4>(a, threads, st);
-  else launch_rt_T_d<1, 4>(a, threads, st);
+  const bool big = !off32_ok(a.g);
+  if (d == 0) {
+    if (big) launch_rt_T_d<0, 4, true>(a, threads, st);
+    else launch_rt_T_d<0, 4, false>(a, threads, st);
+  } else {
+    if (big) launch_rt_T_d<1, 4, true>(a, threads, st);
+    else launch_rt_T_d<1, 4, false>(a, threads, st);
+  }
 }
 
 // Where the scalar lines of a two-ended sweep run apart, by the partitioned
@@ -693,6 +717,8 @@ void launch_rt_T(int d, const PassArgs &a, unsigned threads, hipStream_t st) {
 // Measured: theta on the 512 x 256 x 128 sphere (256 rows) 1.53 -> 1.43 ms;
 // on 64 uneven sectors (lines of 64 to 256 rows) the ragged chunks and idle
 // lanes made the two passes slower than the one two-ended launch.
+// Not on grids whose byte offsets outgrow 32 bits: 1024 x 1024 x 513 cells, apart
+// r 49.1, theta 51.4 ms, in the two-ended launch 42.7 and 47.1.
 bool rt_scalar_supported(const Geo &g, int d, unsigned bs) {
   if (d > 1 || bs > 256 || !off32_ok(g)) return false;
   const int n = families(g, d).n, T = rt_chunks<RT_PMS>(n);
@@ -757,12 +783,17 @@ void launch_rt_forced(int d, int pm, const PassArgs &a, unsigned threads, hipStr
   const unsigned nbw = rt_block_wgs(a.g, d, threads, pm), nsw = rt_scalar_wgs(a.g, d, threads);
   if (d == 0) {
     launch_rt_pass(0, pm, a, none, nbw + nsw, threads, st);
-  } else if (nbw + nsw < RT_SPLIT_WGS) {
-    hipLaunchKernelGGL((k_rt_partF<4, 2>), dim3(nbw + nsw), dim3(threads), rt_part_lds(threads), st, a);
+  } else if (off32_ok(a.g) && nbw + nsw < RT_SPLIT_WGS) {
+    hipLaunchKernelGGL((k_rt_partF<4, 2, false>), dim3(nbw + nsw), dim3(threads), rt_part_lds(threads), st, a);
   } else {
-    hipLaunchKernelGGL((k_rt_partF<4, 0>), dim3(nbw), dim3(threads), rt_part_lds(threads), st, a);
-    const unsigned ts = rt_scalar_threads(a.g, 1, threads);
-    launch_rt_scalar_pass(1, a, none, rt_scalar_wgs(a.g, 1, ts), ts, st);
+    const unsigned ts = rt_scalar_threads(a.g, 1, threads), nts = rt_scalar_wgs(a.g, 1, ts);
+    if (off32_ok(a.g)) {
+      hipLaunchKernelGGL((k_rt_partF<4, 0, false>), dim3(nbw), dim3(threads), rt_part_lds(threads), st, a);
+      launch_rt_scalar_pass(1, a, none, nts, ts, st);
+    } else {
+      hipLaunchKernelGGL((k_rt_partF<4, 0, true>), dim3(nbw), dim3(threads), rt_part_lds(threads), st, a);
+      hipLaunchKernelGGL((k_rt_part<1, 4, 1, false, true>), dim3(nts), dim3(ts), rt_scalar_lds(ts), st, a, none);
+    }
   }
 }
 
