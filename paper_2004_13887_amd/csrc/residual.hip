@@ -18,13 +18,19 @@
 // keep the component form (the edge vorticity on the polar axis is one value
 // for the whole ring).
 //
-// One thread per point of the extended index space (nr+1) x (nt+1) x npf; a
-// thread owns the centre (i,j,k) and the three faces with the same indices.
-// Two variants:
-//   * inside a split step the midpoint is already resident (written by the
-//     previous iteration's last sweep, or U^n itself at the first iteration),
-//     so every neighbour read is a single load;
-//   * the C-ABI call forms the midpoint from Un and Uk and writes it.
+// A thread owns the centre (i,j,k) and the three faces with the same indices of
+// the extended index space (nr+1) x (nt+1) x npf.  Inside a step the midpoint is
+// resident (written by the previous iteration's phi sweep, or U^n itself at the
+// first); the C-ABI call forms it from Un and Uk and writes it.  The launches,
+// by size:
+//   * large grids: the interior's r planes walked through a window in LDS, the
+//     shell in the same launch or one of its own (k_residual_march, _march_mid
+//     with k_residual_mid_shell for the C-ABI call, _marchB for a batch);
+//   * smaller ones: interior and shell in one launch (k_residual_one; a batch
+//     k_residual_in and k_residual; the C-ABI call k_residual_mid, or k_midpoint
+//     and then k_residual_one);
+//   * what these launches' dimensions or 32-bit indices do not hold: every point
+//     by the general rules (k_residual).
 #include <algorithm>
 #include <cstring>
 #include <type_traits>
@@ -838,7 +844,7 @@ static dim3 march_grid(const Geo &g, int seg) {
 
 // Where it is taken: from 450 workgroups of two planes.  Below that the window
 // is a latency more than it saves: one launch with every load up front against
-// the window 6.3 against 10.1 us on 32 x 32 x 16 cells (112 workgroups), but
+// the window 6.3 against 10.1 us on 32 x 32 x 16 cells (56 workgroups), but
 // 17.4 against 14.5 on 128 x 64 x 32 (480), 40 against 34 on 150 x 101 x 37,
 // 162 against 102 on 360 x 180 x 40, 262 against 161 on 200 x 200 x 100, 900
 // against 506 on 512 x 256 x 128 (the perturbation form of 100 m columns on
@@ -921,10 +927,11 @@ static void set5(const double **dst, const Fields &f) {
 // The public residual of a grid whose interior is walked forms the midpoint as
 // the planes are loaded: 1024 x 512 x 64 sector 1.79 ms, against 1.97 with a
 // pass that writes the midpoint first and 5.83 with it formed at every load.
-// Else (small grids, and those beyond the walk's 32-bit offsets), from this
-// many interior workgroups of 64 points on, it writes the midpoint first and
-// reads it back: 256 x 128 x 64 sector 0.364 -> 0.198 ms; on 32 x 32 x 16 the
-// one launch wins (15 against 23 us).
+// Of other grids, those of at least this many interior workgroups of 64 points
+// (the largest below the walk, and those beyond its 32-bit offsets) write the
+// midpoint first and read it back: 256 x 128 x 64 sector 0.364 -> 0.198 ms; on
+// 32 x 32 x 16 the one launch wins (15 against 23 us).  A grid whose interior
+// outgrows 32-bit indices has no such workgroups and forms it at every load.
 constexpr unsigned RES_MID_SPLIT = 3000;
 
 void launch_residual(const Geo &g, const Mat &m, const Fields &Un, const Fields &Uk, double tau,
@@ -972,8 +979,7 @@ void launch_residual(const Geo &g, const Mat &m, const Fields &Un, const Fields 
   }
   hipLaunchKernelGGL(k_midpoint, dim3((unsigned)((w.pairs[5] + 255) / 256)), dim3(256), 0, st, w);
   const Batch none{nullptr, nullptr, 0};
-  if (res_interior_blocks(g, (int)th)) launch_residual_in_pass(g.periodic != 0, a, none, 0, th, st);
-  else launch_residual_pass(a, none, res_general_blocks(g, (int)th, false), th, st);
+  launch_residual_in_pass(g.periodic != 0, a, none, 0, th, st);
 }
 
 void launch_residual_pass(const PassArgs &a, const Batch &b, unsigned blocks, unsigned threads,
