@@ -648,10 +648,13 @@ static unsigned wgs256(unsigned wgs, unsigned bs) { return (unsigned)(((unsigned
 // 29.6 / 21.7; 17 rows, 32000 40.6 / 46.0, 50000 66.5 / 59.8; 24 rows and more,
 // partitioned at every count.  And many lines of more than 128 rows in
 // workgroups of 128 threads, which hold two or three of them: 192 rows, 32768
-// lines 614 / 702, 256 rows 817 / 868, 200 rows, 25600 lines 565 / 567.
+// lines 614 / 702, 256 rows 817 / 868, 200 rows, 25600 lines 565 / 567.  In
+// workgroups of 64 threads the two-ended solver is the slower one throughout (6
+// rows, 40000 lines 33.9 / 23.8).
 bool rt_T_two_ended(const Geo &g, unsigned bs) {
   const long n = g.nt, lines = families(g, 1).nb;
-  if (n > 128) return bs == 128u && lines >= RT_NARROW_LINES;
+  if (bs < 128u) return false;
+  if (n > 128) return bs < 256u && lines >= RT_NARROW_LINES;
   if (n > 24) return false;
   const unsigned nbw = wgs256(rt_block_wgs(g, 1, bs, 4), bs), all = nbw + wgs256(rt_scalar_wgs(g, 1, bs), bs);
   const long two = std::max(1000L, (12 + 7 * n) * std::max(25000L, lines) / 1000);

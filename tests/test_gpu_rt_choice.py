@@ -15,9 +15,10 @@ pytestmark = pytest.mark.gpu
 # direction, grid, sphere, threads, rows per thread of the solve and of the transposed one
 CASES = [(1, 256, 3, 100, False, 256, 4, 0), (1, 1000, 3, 100, True, 256, 4, 4), (1, 80, 9, 100, False, 256, 4, 4),
          (1, 256, 9, 100, True, 256, 4, 0), (1, 640, 9, 100, False, 256, 4, 4), (1, 160, 16, 100, True, 256, 4, 4),
-         (1, 200, 20, 100, False, 256, 4, 4), (1, 32, 25, 1000, False, 256, 4, 4), (1, 256, 9, 100, False, 128, 4, 0),
-         (0, 132, 150, 200, False, 64, 0, 0), (0, 132, 149, 201, True, 128, 4, 4), (0, 129, 10, 20, False, 64, 4, 4),
-         (1, 150, 132, 200, True, 128, 4, 0), (1, 149, 132, 201, False, 128, 4, 4), (1, 150, 132, 200, False, 64, 4, 4)]
+         (1, 200, 20, 100, False, 256, 4, 4), (1, 32, 25, 1000, False, 256, 4, 4),
+         (1, 256, 9, 100, False, 128, 4, 0), (1, 256, 9, 100, True, 64, 4, 4), (0, 132, 150, 200, False, 64, 0, 0),
+         (0, 132, 149, 201, True, 128, 4, 4), (0, 129, 10, 20, False, 64, 4, 4), (1, 150, 132, 200, True, 128, 4, 0),
+         (1, 149, 132, 201, False, 128, 4, 4), (1, 150, 132, 200, False, 64, 4, 4)]
 
 
 @pytest.mark.parametrize("d,nr,nt,np_,sphere,bs,pm,pm_T", CASES)
