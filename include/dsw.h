@@ -180,7 +180,7 @@ typedef struct {
  * midpoint their mean with Un's, and its ghost values the mean wall velocity.
  * The rest as dsw_split_step.  Runs the residual over every point and needs
  * phi lines that the partitioned solver takes (any sector of up to 1024 phi
- * cells; on a full sphere a power-of-two chunk count), else DSW_EINVAL.  The
+ * cells; on a full sphere a power of two of full chunks), else DSW_EINVAL.  The
  * first call on a handle allocates a small workspace for the wall data. */
 int dsw_split_step_forced(dsw_grid *grid, const dsw_fields *Un, dsw_fields *Unp1, double tau,
                           int32_t K, const dsw_fields *src, const dsw_wall *wall0,
@@ -326,6 +326,10 @@ int dsw_adjoint_trajectory(dsw_grid *grid, const dsw_fields *ckpts, int32_t nste
 /* Launch shapes of a grid's kernels (the tunable parameters; they change
  * speed and the order of rounding, never the method):
  *   residual_block        threads per workgroup of the residual (64, 128, 256)
+ *                         on the smaller grids; from 450 tiles of 64 phi x 4
+ *                         theta x 2 r points on (some 10^5 cells) the residual
+ *                         walks r planes in workgroups of its own, 256
+ *                         threads, and this has no effect
  *   sweep_block_r/_theta  threads per workgroup of the r / theta sweeps
  *                         (64, 128, 256)
  *   phi_rows_per_thread   phi sweep: 2 or 4 = partitioned solver, one
@@ -345,7 +349,7 @@ int dsw_adjoint_trajectory(dsw_grid *grid, const dsw_fields *ckpts, int32_t nste
  *                         reduction in LDS; no scratch memory); 0 = two
  *                         threads per line, eliminating from both ends,
  *                         intermediates in a scratch array (the scalar
- *                         lines of lines with 64, 128 or 256 rows run
+ *                         lines of lines of 8 times a power of two rows run
  *                         apart, by the partitioned solver); -1 = by line
  *                         length: partitioned where a line has at most 256
  *                         rows (64 chunks), else two-ended (in an ensemble,

@@ -304,10 +304,11 @@ inline int phi_kind(const Geo &g, const Cfg &c) {
 // Workgroups go to the chip's 8 XCDs in turn (w mod 8), and each XCD has an
 // L2 of its own.  Renumbered by this bijection of [0, n), every XCD takes one
 // contiguous range of n work items, so that items next to each other, which
-// read each other's neighbour data, share an L2.  Used where that pays: the
-// scalar lines of the three sweeps (bandwidth-bound); the block lines and the
-// residual keep the round-robin order, which spreads every moment's accesses
-// over the whole grid and measured faster for them.
+// read each other's neighbour data, share an L2.  Used where that pays: the r
+// and theta lines of one grid (in a batch within each member's block lines and
+// within its scalar lines) and the scalar phi lines of one grid; the phi block
+// lines and the residual keep the round-robin order, which spreads every
+// moment's accesses over the whole grid and measured faster for them.
 __device__ __forceinline__ unsigned xcd_contiguous(unsigned w, unsigned n) {
   const unsigned x = w & 7u, i = w >> 3, q = n >> 3, r = n & 7u;
   return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + i;

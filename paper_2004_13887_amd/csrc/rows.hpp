@@ -1,7 +1,8 @@
 // rows.hpp -- assembly of one row of the line systems (I + tau/2 D_d(Ubar))
 // of the three split sweeps (paper eqs. (spl1)-(spl3); direction operators
-// of Appendix B, eqs. (dr), (dtheta), (dphi)), and 3x3 helpers.  Shared by the
-// thread-per-line and the partitioned line solvers.
+// of Appendix B, eqs. (dr), (dtheta), (dphi)), and 3x3 helpers: the rows of the
+// thread-per-line and two-ended solvers and of the forced step's lifts (the
+// partitioned solvers form theirs from a chunk's inputs, rows_fast.hpp).
 #pragma once
 
 #include "dsw_common.hpp"
